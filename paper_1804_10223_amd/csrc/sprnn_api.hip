@@ -12,6 +12,7 @@
 #include "sprnn.h"
 #include "sprnn_device.h"
 #include "sprnn_pack.h"
+#include "sprnn_wgrad.h"
 
 using namespace sprnn;
 
@@ -32,8 +33,10 @@ struct sprnn_handle_s {
   uint32_t* d_fill_src = nullptr;    // column compaction only
   int32_t* d_wg_plane = nullptr;
   int32_t* d_lane_sum = nullptr;     // lane-pool layout only
-  int32_t* d_word_src = nullptr;     // vanilla cells without compaction: packed word -> CSR position (weight gradient)
-  const void* kernel_wgrad = nullptr;
+  int32_t* d_word_src = nullptr;     // without compaction: packed word -> CSR position (backward pass with the weight gradient fused in)
+  bool has_wgrad = false;            // the weight gradient is offered on this handle
+  WGradTile wgrad_tile;              // ... the shape of its tiles
+  int32_t* d_wgrad_starts = nullptr; // ... where each row's nonzeros enter each column of tiles
   uint32_t* d_ring = nullptr;
   uint32_t* d_ctrl = nullptr;
   unsigned long long* d_timeline = nullptr;   // [grid][16], only with options.timeline
@@ -115,6 +118,7 @@ void release(sprnn_handle_s* h) {
   if (!h) return;
   (void)hipFree(h->d_words); (void)hipFree(h->d_lane_row); (void)hipFree(h->d_wave_words); (void)hipFree(h->d_wave_early);
   (void)hipFree(h->d_fill_src); (void)hipFree(h->d_wg_plane); (void)hipFree(h->d_word_src); (void)hipFree(h->d_lane_sum);
+  (void)hipFree(h->d_wgrad_starts);
   (void)hipFree(h->d_ring); (void)hipFree(h->d_ctrl); (void)hipFree(h->d_timeline);
   (void)hipFree(h->d_row_ptr); (void)hipFree(h->d_col); (void)hipFree(h->d_val);
   delete h;
@@ -387,14 +391,8 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
     }
   }
   if (ok && (m.cell <= SPRNN_ACT_IDENTITY || m.cell == SPRNN_CELL_LSTM || m.cell == SPRNN_CELL_GRU) && !m.compact && !m.half) {
-    // the weight gradient re-uses the forward mapping: one accumulator per packed word, left through this map
-    // (built for the word counts of the one-group-per-row layout; a lane-pool mapping with another count has none:
-    // sprnn_weight_gradient is then unsupported on this handle, the fused backward pass is the way)
-    h->kernel_wgrad = weight_grad_kernel_for(m.batch, m.template_words);
-    ok = SPRNN_HIP(upload(&h->d_word_src, P.word_src.data(), P.word_src.size())) &&
-         (!h->kernel_wgrad || SPRNN_HIP(hipFuncSetAttribute(h->kernel_wgrad, hipFuncAttributeMaxDynamicSharedMemorySize, lds_cu)));
-    hipFuncAttributes wfa;   // (the instantiations with many words per lane are built for fewer threads than a lane-pool workgroup may have)
-    if (ok && h->kernel_wgrad && (!SPRNN_HIP(hipFuncGetAttributes(&wfa, h->kernel_wgrad)) || wfa.maxThreadsPerBlock < m.block)) h->kernel_wgrad = nullptr;
+    h->has_wgrad = true;
+    ok = SPRNN_HIP(upload(&h->d_word_src, P.word_src.data(), P.word_src.size()));
     if (ok && h->kernel_bwd && !m.timeline && m.cell <= SPRNN_ACT_IDENTITY) {
       // backward pass with the weight gradient fused in: same co-residency requirement as the plain one
       const void* k = pool ? pool_kernel_for(m.batch, m.template_words, kCellBackwardGrad) : persistent_kernel_for(m.batch, m.template_words, kCellBackwardGrad, false);
@@ -450,6 +448,17 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   return SPRNN_OK;
 }
 
+// The tables of the weight gradient, made once for the handle that is kept.
+static int prepare_weight_gradient_tables(sprnn_handle_s* h) {
+  if (!h->has_wgrad || h->map.nnz == 0) return SPRNN_OK;
+  const int rows = h->map.rows, cols = h->map.cols;
+  h->wgrad_tile = choose_weight_gradient_tile(rows, cols, h->num_cus);
+  const size_t entries = (size_t)rows * ((cols + h->wgrad_tile.cols - 1) / h->wgrad_tile.cols + 1);
+  return SPRNN_HIP(hipMalloc((void**)&h->d_wgrad_starts, entries * 4)) &&
+         SPRNN_HIP(launch_tile_starts(h->d_row_ptr, h->d_col, rows, cols, h->wgrad_tile.cols, h->d_wgrad_starts, nullptr)) &&
+         SPRNN_HIP(prepare_weight_gradient(h->wgrad_tile)) && SPRNN_HIP(hipStreamSynchronize(nullptr)) ? SPRNN_OK : SPRNN_ERR_HIP;
+}
+
 int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
                     const int32_t* col_idx, const uint16_t* val_fp16_bits, int device_id,
                     const sprnn_options_t* opt) {
@@ -476,7 +485,6 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
   const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, opt, prop,
                             free_choice, free_choice, &alt);
   if (rc != SPRNN_OK) return rc;
-  if (!free_choice || first->calibrated_us <= 0.0f) { *out = first; return SPRNN_OK; }
   sprnn_options_t base = opt ? *opt : sprnn_options_t();
   if (!opt) std::memset(&base, 0, sizeof(base));
   // builds the mapping `other` asks for, measures it like the first, and keeps the faster of the two in `first`
@@ -497,8 +505,9 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
       release(second);
     }
   };
+  const bool compare = free_choice && first->calibrated_us > 0.0f;
   // (1) fewer, larger workgroups on one XCD, or a wavefront count that copies h with fewer loads (see create_one)
-  if (alt.grid > 0 || alt.fill_waves > 0) {
+  if (compare && (alt.grid > 0 || alt.fill_waves > 0)) {
     sprnn_options_t other = base;
     other.grid = alt.grid;
     other.fill_waves = alt.fill_waves;
@@ -508,13 +517,15 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
   // for every shape; twice and half as many lanes are measured too, each with the mapping the packer picks for it.
   const int own_lanes = first->map.lanes_per_row;
   const bool gated_rows = first->map.cell == SPRNN_CELL_LSTM || first->map.cell == SPRNN_CELL_GRU;
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; compare && pass < 2; ++pass) {
     const int lanes = pass == 0 ? own_lanes * 2 : own_lanes / 2;
     if (lanes < batch || lanes < 1 || lanes > (gated_rows ? 16 : kWave)) continue;
     sprnn_options_t other = base;
     other.lanes_per_row = lanes;
     contend(other);
   }
+  const int planned = prepare_weight_gradient_tables(first);
+  if (planned != SPRNN_OK) { release(first); return planned; }
   *out = first;
   return SPRNN_OK;
 }
@@ -893,7 +904,8 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
 int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const float* h_fwd, const float* h0, float* dU,
                           void* stream) {
   if (!h || T < 0) return SPRNN_ERR_INVALID;
-  if (!h->kernel_wgrad || !h->d_word_src) return SPRNN_ERR_UNSUPPORTED;   // gated cell, or column compaction in use
+  // (not on a gated cell's backward handle, nor with column compaction or binary16 activations)
+  if (!h->has_wgrad) return SPRNN_ERR_UNSUPPORTED;
   if (!dU && h->map.nnz > 0) return SPRNN_ERR_INVALID;
   if (T > 0 && (!d_bprime || !h_fwd)) return SPRNN_ERR_INVALID;
   if (h->map.nnz == 0) return SPRNN_OK;
@@ -901,13 +913,11 @@ int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const 
   if (!guard.ok) return SPRNN_ERR_HIP;
   const Mapping& m = h->map;
   WGradArgs a;
-  a.words = h->d_words; a.lane_row = h->d_lane_row; a.wave_words = h->d_wave_words; a.word_src = h->d_word_src;
-  a.delta = d_bprime; a.h_fwd = h_fwd; a.h0 = h0; a.dU = dU;
-  a.hidden = m.hidden; a.T = T; a.index_shift = m.index_shift; a.rows = m.rows;
-  void* args[] = {&a};
-  // workgroups are independent here: an ordinary launch, one workgroup per CU by the same LDS request
-  const hipError_t e = hipLaunchKernel(h->kernel_wgrad, dim3(m.grid), dim3(m.block), args, (unsigned)h->launch_lds, (hipStream_t)stream);
-  return hip_ok(e, "hipLaunchKernel(weight gradient)") ? SPRNN_OK : SPRNN_ERR_HIP;
+  a.col = h->d_col; a.starts = h->d_wgrad_starts;
+  a.a.x = d_bprime; a.a.ld = m.rows;
+  a.b.x = h_fwd; a.b.first = h0; a.b.ld = m.cols; a.b.shift = m.batch;   // delta_t pairs with h_{t-1}
+  a.dU = dU; a.vectors = T * m.batch; a.nnz = (int)m.nnz;
+  return SPRNN_HIP(launch_weight_gradient(a, h->wgrad_tile, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
 }
 
 int sprnn_transpose_csr(int rows, int cols, const int32_t* row_ptr, const int32_t* col_idx, const uint16_t* val_fp16_bits,

@@ -1,0 +1,50 @@
+"""The weight gradient at the edges of its tiles (64 or 128 rows and columns, slabs of 32 vectors), against a binary64
+product sampled at the nonzeros.
+
+Bound per entry: the kernel's products are exact to 2^-26 of |a b| and its sums binary32, so with n = T * B terms
+    |got - want| <= (n + 8) 2^-24 sum_m |a[m][row] b[m][col]|.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_1804_10223_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("cell,H,B,T,dens,rownnz,with_h0", [
+    ("identity", 1, 1, 1, 1.0, "fixed", True),            # one row, one column, one vector
+    ("relu", 63, 1, 31, 0.3, "poisson", True),            # just short of a tile and of a slab
+    ("relu", 64, 4, 8, 0.3, "fixed", True),               # exactly one tile, exactly one slab
+    ("tanh", 65, 1, 33, 0.3, "poisson", False),           # one beyond both
+    ("relu", 129, 8, 13, 1.0, "fixed", True),             # dense, three tiles of 64 with one row left
+    ("tanh", 700, 2, 49, 0.05, "poisson", True),          # no multiple of anything, three slabs and two vectors
+    ("lstm", 200, 8, 9, 0.2, "fixed", True),              # more rows than columns
+    ("gru", 171, 2, 17, 0.15, "poisson", False),
+    ("relu", 2304, 4, 9, 0.3, "fixed", True),             # tiles of 128 x 192
+    ("relu", 1800, 1, 70, 0.02, "poisson", True),         # tiles of 128 x 128 with empty rows in them
+])
+def test_weight_gradient_at_tile_edges(cell, H, B, T, dens, rownnz, with_h0):
+    w = wl.make_workload("wg-edge", cell, H, B, T, dens, seed=H + T, row_nnz=rownnz)
+    rng = np.random.default_rng(H * 31 + T)
+    R = w.rows
+    delta = (rng.standard_normal((T, B, R)) * 10.0 ** rng.uniform(-6, 2, size=(1, 1, R))).astype(np.float32)   # rows of very different size
+    h = rng.standard_normal((T, B, H)).astype(np.float32)
+    h0 = rng.standard_normal((B, H)).astype(np.float32) if with_h0 else None
+    print("case", cell, H, "B", B, "T", T, dens, flush=True)
+    with binding.SparseRNN(H, B, cell, w.row_ptr, w.col_idx, w.val_bits, poll_delay=-1) as rnn:
+        dU = torch.full((w.nnz + 3,), 77.0, device="cuda")
+        got = rnn.weight_gradient(_dev(delta), _dev(h), _dev(h0), dU).cpu().numpy()
+        assert rnn.check() == binding.SPRNN_OK
+        assert (dU[w.nnz:] == 77.0).all()                 # nothing beyond the last nonzero is written
+    before = np.concatenate([np.zeros((1, B, H), np.float32) if h0 is None else h0[None], h[:-1]]).reshape(T * B, H).astype(np.float64)
+    d64 = delta.reshape(T * B, R).astype(np.float64)
+    rows = np.repeat(np.arange(R), np.diff(w.row_ptr))
+    want = (d64.T @ before)[rows, w.col_idx]
+    size = (np.abs(d64).T @ np.abs(before))[rows, w.col_idx]
+    assert np.all(np.abs(got - want) <= (T * B + 8) * 2.0 ** -24 * size)
