@@ -18,7 +18,9 @@
 // s is multiplied out of one, slab s + 1 is converted and written into the other between the MFMAs, and slabs
 // s + 2 and s + 3 are in flight from memory in two register sets; one workgroup barrier per slab.  LDS rows are
 // padded by 16 bytes so that the eight lanes served in one LDS pass touch all banks.  Consecutive tiles of one n
-// block (the same rows of W) are dealt to workgroups that share an XCD, hence an L2.
+// block (the same rows of W) are dealt to workgroups that share an XCD, hence an L2.  Rows of x and W are fetched 16 bytes
+// at a time whatever their alignment (element by element, an input size that is no multiple of eight cost two to three
+// times as much: 400 x 1152 x 771 42 -> 16 us, 2048 x 700 x 701 45 -> 18).
 #include <cstdlib>
 
 #include "sprnn_device.h"
@@ -52,16 +54,24 @@ struct Staging {
   uint32_t b_off[NJ];       // byte offset from W + n0 * K + k0 (row clamped to N - 1)
 };
 
-// Full slab, rows 16-byte aligned: plain vector loads at precomputed offsets.
+// 16 bytes from an address of any alignment (one load instruction: the memory pipeline takes unaligned addresses).
+template <typename T>
+__device__ __forceinline__ T load_unaligned(const void* at) {
+  T v;
+  __builtin_memcpy(&v, at, sizeof(T));
+  return v;
+}
+
+// Full slab: vector loads at precomputed offsets, whatever the alignment of the rows.
 template <int NJ>
 __device__ __forceinline__ void load_slab_fast(SlabRegs<NJ>& r, const Staging<NJ>& st, const char* xs, const char* ws) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) r.a[i] = *reinterpret_cast<const float4*>(xs + st.a_off[i]);
+  for (int i = 0; i < 2; ++i) r.a[i] = load_unaligned<float4>(xs + st.a_off[i]);
 #pragma unroll
-  for (int i = 0; i < NJ; ++i) r.b[i] = *reinterpret_cast<const uint4*>(ws + st.b_off[i]);
+  for (int i = 0; i < NJ; ++i) r.b[i] = load_unaligned<uint4>(ws + st.b_off[i]);
 }
 
-// Any slab: element-wise loads with zeros beyond K.
+// The ragged slab: element-wise loads with zeros beyond K.
 template <int NJ>
 __device__ __forceinline__ void load_slab_any(SlabRegs<NJ>& r, const float* __restrict__ X, const uint16_t* __restrict__ W,
                                               int tid, int m0, int n0, int k0, int M, int N, int K) {
@@ -117,7 +127,7 @@ __device__ __forceinline__ void store_b_chunk(const SlabRegs<NJ>& r, int i, char
 template <int NJ>
 __global__ __launch_bounds__(kThreads) void project_kernel(const float* __restrict__ X, const uint16_t* __restrict__ W,
                                                            const float* __restrict__ bias, float* __restrict__ out,
-                                                           int M, int N, int K, int tiles_m, int vec) {
+                                                           int M, int N, int K, int tiles_m) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   constexpr int kBN = 64 * NJ;
   constexpr int kStage = stage_bytes(NJ);
@@ -173,8 +183,8 @@ __global__ __launch_bounds__(kThreads) void project_kernel(const float* __restri
     mfmas(f);
   };
 
-  // Pipelined part: the full slabs of a problem whose rows are 16-byte aligned.
-  const int nfast = vec ? K / kBK : 0;
+  // Pipelined part: the full slabs.
+  const int nfast = K / kBK;
   auto load = [&](SlabRegs<NJ>& regs, int s) {
     load_slab_fast<NJ>(regs, st, x_tile + (size_t)s * kBK * 4, w_tile + (size_t)s * kBK * 2);
   };
@@ -214,9 +224,9 @@ __global__ __launch_bounds__(kThreads) void project_kernel(const float* __restri
     if (s < nfast) step(lds, lds + kStage, r1, s);
   }
 
-  // The rest (a ragged last slab, or every slab of an unaligned problem): one slab at a time, guarded loads.
-  const int slabs = (K + kBK - 1) / kBK;
-  for (int s = nfast; s < slabs; ++s) {
+  // The rest, a ragged last slab: guarded loads.
+  if (K % kBK != 0) {
+    const int s = nfast;
     SlabRegs<NJ> regs;
     load_slab_any<NJ>(regs, X, W, tid, m0, n0, s * kBK, M, N, K);
     __syncthreads();
@@ -255,13 +265,101 @@ __global__ __launch_bounds__(kThreads) void project_kernel(const float* __restri
   }
 }
 
+// The same product for small outputs, where the kernel above leaves most of the chip idle and a workgroup walks K slab by
+// slab, a barrier and the rest of a trip to memory each.  A workgroup owns 32 x 32 of b' and its eight wavefronts share
+// out K instead: each fetches its own fragments straight from memory (eight consecutive k of one row of x or W per lane;
+// an element is used by few workgroups, so nothing is gained by staging it), four steps of 16 k in flight, and the eight
+// sets of sums meet in LDS.  Bound by the latency of its loads; the larger the output, the more often x and W are
+// fetched again.  Measured (64 x 128 tiles of the kernel above / this one, M x N x K): 50 x 2048 x 512 10.7 / 5.6 us,
+// 50 x 2048 x 2048 21.5 / 13.6, 256 x 1024 x 1024 14.8 / 8.8, 64 x 1024 x 80 9.3 / 3.2.
+__global__ __launch_bounds__(kThreads) void project_small_kernel(const float* __restrict__ X, const uint16_t* __restrict__ W,
+                                                                 const float* __restrict__ bias, float* __restrict__ out,
+                                                                 int M, int N, int K, int tiles_m) {
+  __shared__ float sums[8][16][64];
+  const int m0 = ((int)blockIdx.x % tiles_m) * 32, n0 = ((int)blockIdx.x / tiles_m) * 32;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+  const int r = lane & 31, kh = lane >> 5;
+  const float* const x_row = X + (size_t)min(m0 + r, M - 1) * K + kh * 8;
+  const uint16_t* const w_row = W + (size_t)min(n0 + r, N - 1) * K + kh * 8;
+  floatx16 acc_hi, acc_lo;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) { acc_hi[v] = 0.0f; acc_lo[v] = 0.0f; }
+
+  struct Step { float4 a[2]; uint4 b; };
+  auto fetch = [&](Step& f, int k) {          // 16 k from k on, all of them inside the row
+    f.b = load_unaligned<uint4>(w_row + k);
+    f.a[0] = load_unaligned<float4>(x_row + k);
+    f.a[1] = load_unaligned<float4>(x_row + k + 4);
+  };
+  auto multiply = [&](const Step& f) {
+    const half8 b = __builtin_bit_cast(half8, f.b);
+    uint4 hi, lo;
+    split2(f.a[0].x, f.a[0].y, hi.x, lo.x);
+    split2(f.a[0].z, f.a[0].w, hi.y, lo.y);
+    split2(f.a[1].x, f.a[1].y, hi.z, lo.z);
+    split2(f.a[1].z, f.a[1].w, hi.w, lo.w);
+    acc_hi = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, hi), b, acc_hi, 0, 0, 0);
+    acc_lo = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, lo), b, acc_lo, 0, 0, 0);
+  };
+  const int full = K / 16, first = wave * full / 8, last = (wave + 1) * full / 8;
+  int s = first;
+  for (; s + 4 <= last; s += 4) {
+    Step f[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) fetch(f[q], (s + q) * 16);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) multiply(f[q]);
+  }
+  if (s < last) {                             // one to three more (the last one fetched again where there are fewer)
+    Step f[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) fetch(f[q], min(s + q, last - 1) * 16);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f[0]);
+    if (s + 1 < last) multiply(f[1]);
+    if (s + 2 < last) multiply(f[2]);
+  }
+  if (wave == 7 && K % 16 != 0) {             // what is left of the rows, element by element
+    const int k = full * 16;
+    Step f;
+    float a[8];
+    uint32_t h[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool in = k + kh * 8 + e < K;
+      h[e] = in ? (uint32_t)w_row[k + e] : 0u;
+      a[e] = in ? x_row[k + e] : 0.0f;
+    }
+    f.b = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+    f.a[0] = make_float4(a[0], a[1], a[2], a[3]);
+    f.a[1] = make_float4(a[4], a[5], a[6], a[7]);
+    multiply(f);
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) sums[wave][v][lane] = acc_hi[v] + acc_lo[v] * (1.0f / kLoScale);
+  __syncthreads();
+  // wavefront w finishes elements w and w + 8: element v of lane (r, kh) is row 8 (v / 4) + 4 kh + v % 4, column r
+  const int n = n0 + r;
+  const float bn = bias && n < N ? bias[n] : 0.0f;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int v = wave + 8 * q;
+    float t = sums[0][v][lane];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) t += sums[w][v][lane];
+    const int m = m0 + (v >> 2) * 8 + kh * 4 + (v & 3);
+    if (m < M && n < N) out[(size_t)m * N + n] = t + bn;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_project(const float* x, const uint16_t* w, const float* bias, float* out, int M, int N, int K,
                           hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
   if (K > (1 << 23)) return hipErrorInvalidValue;   // 32-bit byte offsets inside a tile
-  const int vec = (K % 8 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0) && (reinterpret_cast<uintptr_t>(w) % 16 == 0);
   const int tiles_m = (M + kBM - 1) / kBM;
   // Tile width 64 NJ (SPRNN_PROJECT_TILE=64|128|192 overrides the choice for experiments).
   static const int force = std::getenv("SPRNN_PROJECT_TILE") ? std::atoi(std::getenv("SPRNN_PROJECT_TILE")) : 0;
@@ -278,15 +376,27 @@ hipError_t launch_project(const float* x, const uint16_t* w, const float* bias, 
     }
     cus = cu_count[dev];
   }
+  // Up to one 32 x 32 tile per CU: the kernel that shares out K inside a workgroup (512 x 768 x 256, 384 tiles, 7.2 us
+  // against 6.6 with 64 x 64 tiles, 200 x 4096 x 1024, 896 tiles, 27 against 13).
+  int tiles_small = (M + 31) / 32;
+  const long long small = (long long)tiles_small * ((N + 31) / 32);
+  if (!force && small <= cus) {
+    void* args[] = {(void*)&x, (void*)&w, (void*)&bias, (void*)&out, (void*)&M, (void*)&N, (void*)&K, (void*)&tiles_small};
+    e = hipLaunchKernel((const void*)project_small_kernel, dim3((unsigned)small), dim3(kThreads), args, 0, stream);
+    return e == hipSuccess ? hipGetLastError() : e;
+  }
   int nj = 2;
   if (force) {
     nj = force / 64;
   } else {
     // Measured on four layer shapes: 128-wide tiles are the best all-rounder; 192-wide ones win when the 128-wide
     // tiles are a little more than one per CU (every CU would otherwise wait for the few that carry two) and the
-    // wider ones fit one per CU; 64-wide ones only serve outputs that are no wider.
+    // wider ones fit one per CU.  64-wide ones serve outputs that give about one of them to a CU or less (two or three
+    // share a CU): 400 x 1152 x 771 15.7 -> 11.4 us, 128 x 4096 x 2560 26.5 -> 20.6, 400 x 2313 x 333 (259 tiles) 13.0
+    // -> 11.4, but 1024 x 1152 x 1152 (288 tiles) 17.6 -> 18.5.
+    const long long t1 = (long long)tiles_m * ((N + 63) / 64);
     const long long t2 = (long long)tiles_m * ((N + 127) / 128), t3 = (long long)tiles_m * ((N + 191) / 192);
-    if (N <= 64) nj = 1;
+    if (N <= 64 || t1 * 16 <= cus * 17LL) nj = 1;
     else if (t2 > cus && 2 * t2 <= 3LL * cus && t3 <= cus) nj = 3;
   }
   if (nj < 1 || nj > 3) return hipErrorInvalidValue;
@@ -301,7 +411,7 @@ hipError_t launch_project(const float* x, const uint16_t* w, const float* bias, 
     if (e != hipSuccess) return e;
     raised[dev][nj] = true;
   }
-  void* args[] = {(void*)&x, (void*)&w, (void*)&bias, (void*)&out, (void*)&M, (void*)&N, (void*)&K, (void*)&tiles_m, (void*)&vec};
+  void* args[] = {(void*)&x, (void*)&w, (void*)&bias, (void*)&out, (void*)&M, (void*)&N, (void*)&K, (void*)&tiles_m};
   e = hipLaunchKernel(kernels[nj], dim3((unsigned)tiles), dim3(kThreads), args, (size_t)lds, stream);
   if (e != hipSuccess) return e;
   return hipGetLastError();
