@@ -312,10 +312,10 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
                                : (m.seg_rounds ? persistent_overlap_kernel_for(m.batch, m.template_words, m.timeline != 0)
                                   : (m.half ? persistent_half_kernel_for(m.batch, m.template_words)
                                             : persistent_kernel_for(m.batch, m.template_words, m.cell, m.timeline != 0))));
-  // a short h (at most three rounds of the copy): the forward instantiation that issues exactly that many loads
-  const int copy_rounds = (m.h_bytes / 16 + m.block - 1) / m.block;
-  if (!pool && !m.narrow && !m.seg_rounds && !m.half && !m.timeline && !m.compact && m.grid > 1 && copy_rounds <= 3 &&
-      m.cell <= SPRNN_CELL_GRU) {
+  // a short h (at most three rounds of the copy): the instantiation that issues exactly that many loads
+  const bool short_copy = !pool && !m.compact && m.grid > 1 && (m.h_bytes / 16 + m.block - 1) / m.block <= 3;
+  const bool gated_backward = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;
+  if (short_copy && !m.narrow && !m.seg_rounds && !m.half && !m.timeline && (m.cell <= SPRNN_CELL_GRU || gated_backward)) {
     const void* k = persistent_short_kernel_for(m.batch, m.template_words, m.cell);
     if (k) h->kernel = k;
   }
@@ -332,7 +332,9 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   if (!SPRNN_HIP(hipFuncSetAttribute(h->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_cu))) { release(h); return SPRNN_ERR_HIP; }
   if (m.cell <= SPRNN_ACT_IDENTITY && !m.timeline && !m.narrow && !m.half) {
     // the backward pass of a vanilla cell runs on a handle that holds the transposed matrix: same shape, same LDS
-    h->kernel_bwd = pool ? pool_kernel_for(m.batch, m.template_words, kCellBackward) : persistent_kernel_for(m.batch, m.template_words, kCellBackward, false);
+    h->kernel_bwd = pool ? pool_kernel_for(m.batch, m.template_words, kCellBackward)
+                         : (short_copy ? persistent_short_kernel_for(m.batch, m.template_words, kCellBackward)
+                                       : persistent_kernel_for(m.batch, m.template_words, kCellBackward, false));
     if (h->kernel_bwd && !SPRNN_HIP(hipFuncSetAttribute(h->kernel_bwd, hipFuncAttributeMaxDynamicSharedMemorySize, lds_cu))) { release(h); return SPRNN_ERR_HIP; }
     // it spins on its neighbours like the forward kernel: usable only if the same grid is co-resident with it
     int per_cu_bwd = 0;
@@ -430,7 +432,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
       const int n4 = m.h_bytes / 16;
       auto issued = [&](int waves) {
         const int rounds = (n4 + waves * kWave - 1) / (waves * kWave);
-        const int loads = rounds <= 3 && m.cell <= SPRNN_CELL_GRU ? rounds : (rounds <= 4 ? 4 : (rounds + 7) / 8 * 8);
+        const int loads = rounds <= 3 ? rounds : (rounds <= 4 ? 4 : (rounds + 7) / 8 * 8);
         return (int64_t)loads * waves;
       };
       int best_waves = m.waves;

@@ -526,14 +526,18 @@ __device__ __forceinline__ bool copy_two_parts(__amdgpu_buffer_rsrc_t ring, int 
 // 11 = the vanilla cell's forward pass with h exchanged and kept in LDS as binary16 (batch 4; options.activations;
 // Section 6 names lower-precision activations as future work): one 8-byte gather per nonzero, products and sums in
 // binary32, every h_t rounded to nearest once before it is published (h_out keeps the unrounded value),
-// 12, 13, 14 = the forward passes 0, 1, 2 for a layer whose h takes at most three rounds of the copy (one 16-byte piece
+// 12 .. 17 = the passes 0, 1, 2, 3, 5, 7 for a layer whose h takes at most three rounds of the copy (one 16-byte piece
 // per lane and round): the copy issues exactly that many loads.  The general code always issues four (rounds past the
 // end re-fetch the clamped last piece), which costs a small layer 0.1 us per surplus round; choosing between the two
-// inside one kernel cost the four-round layers 3 %, hence separate instantiations.
+// inside one kernel cost the four-round layers 3 %, hence separate instantiations (backward pass, 701 units, batch 2, one
+// round: 1.48 -> 1.25 us per step).  Copies of more than four rounds gain nothing that way: with exactly the rounds that
+// are left in the last batch, or with all rounds in flight at once, 5120 x batch 4 (seven rounds) took 3 % longer and 2560 x
+// batch 8 (ten) 5 to 12 %: the loads past the end all ask for one line, and while the first batch of eight is on its way
+// the slower workgroups publish what the second asks for.
 template <int B, int NW, int CELLX, bool TL>
 __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELLX == 8) && NW >= 24 ? 512 : 768)) void persistent_kernel(const KernelArgs p) {
-  constexpr bool kShort = CELLX >= 12 && CELLX <= 14;        // forward pass of cell CELLX - 12 for a short h (see the list above)
-  constexpr int CELL = kShort ? CELLX - 12 : CELLX;
+  constexpr bool kShort = CELLX >= 12 && CELLX <= 17;        // a pass for a short h (see the list above)
+  constexpr int CELL = kShort ? (CELLX <= 15 ? CELLX - 12 : 2 * CELLX - 27) : CELLX;
   constexpr bool LSTM = CELL == 1 || CELL == 2;   // gated cell: four row groups per unit, cell lanes
   constexpr bool LBWD = CELL >= 5 && CELL <= 8;                // backward pass of a gated cell
   constexpr bool GBWD = CELL == 7 || CELL == 8;                // ... of the GRU
