@@ -262,10 +262,11 @@ int sprnn_backward(sprnn_handle_t h_transposed, int T, const float* dh_ext, cons
                    float* dh0, void* stream);
 
 /*
- * sprnn_backward with the gradient of the recurrent weights fused in.  The column of delta_{t+1} that a lane gathers
- * for a nonzero (j, i) of the transposed matrix is exactly the factor that dL/dU[i][j] pairs with the forward output
- * h_t[.][j] of the lane's own row, so every gather of the recurrence also feeds one accumulator per nonzero that
- * stays in a register for the whole sequence; the sums cost no extra pass over h.
+ * sprnn_backward and the gradient of the recurrent weights in one call.  Short calls sum it inside the recurrence: the
+ * column of delta_{t+1} that a lane gathers for a nonzero (j, i) of the transposed matrix is exactly the factor that
+ * dL/dU[i][j] pairs with the forward output h_t[.][j] of the lane's own row, so every gather also feeds one accumulator
+ * per nonzero that stays in a register for the whole sequence.  Where it is faster, as for most longer ones, the product
+ * of sprnn_weight_gradient follows the recurrence on the same stream.
  *   h0             device, float32 [B][H] or NULL (zeros): h_0 of the forward pass (pairs with delta_1).
  *   dU_transposed  device, float32 [nnz]: dL/dU in the order of the TRANSPOSED matrix's CSR arrays (entry p belongs to
  *                  the forward nonzero t_source[p] of sprnn_transpose_csr); overwritten.
@@ -344,12 +345,12 @@ int sprnn_backward_gru(sprnn_handle_t h_transposed, int T, const float* dh_ext, 
                        const float* h0, float* d_bprime, float* d_recurrent, float* dh0, void* stream);
 
 /*
- * sprnn_backward_gru with the gradient of the recurrent weights fused in, as in sprnn_backward_with_weights: the column
- * of v_{t+1} that a lane gathers for a nonzero (j, r) of the transposed matrix is the factor that dL/dU[r][j] pairs with
- * the forward output h_t[.][j] of the lane's own row.
+ * sprnn_backward_gru and the gradient of the recurrent weights in one call, as in sprnn_backward_with_weights (with
+ * v_{t+1} in delta's place).  Without d_recurrent a longer call keeps v in an array of its own while it runs (allocated
+ * and given back in stream order).
  *   dU_transposed  device, float32 [nnz]: dL/dU in the order of the TRANSPOSED matrix's CSR arrays (entry p belongs to
  *                  the forward nonzero t_source[p] of sprnn_transpose_csr); overwritten.
- * Other arguments as sprnn_backward_gru.  Always runs T + 1 steps.  Not available with column compaction or where the
+ * Other arguments as sprnn_backward_gru.  Not available with column compaction or where the
  * mapping needs more threads than the instantiation is built for (SPRNN_ERR_UNSUPPORTED: use the two separate calls).
  */
 int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const float* dh_ext, const float* gates,
@@ -357,9 +358,8 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
                                     float* dU_transposed, void* stream);
 
 /*
- * sprnn_backward_lstm with the gradient of the recurrent weights fused in, as in sprnn_backward_with_weights: the
- * column of dp_{t+1} that a lane gathers for a nonzero (j, r) of the transposed matrix is the factor that dL/dU[r][j]
- * pairs with the forward output h_t[.][j] of the lane's own row.
+ * sprnn_backward_lstm and the gradient of the recurrent weights in one call, as in sprnn_backward_with_weights (with
+ * dp_{t+1} in delta's place).
  *   h_fwd          device, float32 [T][B][H]: forward outputs h_1..h_T;  h0: [B][H] or NULL (zeros).
  *   dU_transposed  device, float32 [nnz]: dL/dU in the order of the TRANSPOSED matrix's CSR arrays (entry p belongs to
  *                  the forward nonzero t_source[p] of sprnn_transpose_csr); overwritten.

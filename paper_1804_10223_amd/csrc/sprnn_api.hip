@@ -214,6 +214,19 @@ static hipError_t launch_in_order(int device, const void* kernel, int grid, int 
 
 static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_runs);
 
+// The weight gradient asked of a backward call: summed inside the recurrence (one more gather-fed accumulator per nonzero
+// and step), or as one product on the matrix cores behind it.  The former costs every step 0.1 us and 0.006 us per word of
+// a lane and sample, the latter a launch and 13.4 ps per element of the dense matrix and vector, but no less than a slab
+// of 32 vectors takes a workgroup.  Whole calls measured, inside / behind: 2304 at 30 %, batch 4, T 256 620 / 541 us;
+// 1152 at 10 %, batch 4, T 64 146 / 110; LSTM 1024 at 20 %, batch 8, T 128 810 / 767 (step with its forward pass); but
+// 4096 at 8 %, batch 4, T 64 173 / 208, 5000 at 2 %, batch 1, T 128 267 / 311, LSTM 2000 at 5 %, batch 1, T 64 241 / 260.
+static bool product_is_faster(const sprnn_handle_s* h, int T) {
+  const Mapping& m = h->map;
+  const double vectors = (double)T * m.batch;
+  const double behind = 5.0 + std::max(vectors * m.rows * m.cols * 13.4e-9, vectors / 32.0 * 0.35);
+  return behind < (T + 1) * (0.1 + 0.006 * m.words_max * m.batch);
+}
+
 extern "C" {
 
 const char* sprnn_status_string(int code) {
@@ -452,7 +465,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
 
 // The tables of the weight gradient, made once for the handle that is kept.
 static int prepare_weight_gradient_tables(sprnn_handle_s* h) {
-  if (!h->has_wgrad || h->map.nnz == 0) return SPRNN_OK;
+  if ((!h->has_wgrad && !h->kernel_bwd_grad) || h->map.nnz == 0) return SPRNN_OK;
   const int rows = h->map.rows, cols = h->map.cols;
   h->wgrad_tile = choose_weight_gradient_tile(rows, cols, h->num_cus);
   const size_t entries = (size_t)rows * ((cols + h->wgrad_tile.cols - 1) / h->wgrad_tile.cols + 1);
@@ -688,9 +701,9 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
     }
     best_ms_kept = best_ms;
     // A gated cell's backward handle serves two kernels, the plain pass and the one with the weight gradient fused in,
-    // and a mapping that suits one may not suit the other: handles are compared by the sum of both.
+    // and a mapping that suits one may not suit the other: handles are compared by the sum of both (where the latter is used).
     const bool gated_bwd_cell = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;
-    if (ok && rc == SPRNN_OK && gated_bwd_cell && h->kernel_bwd_grad && best_ms > 0.0f) {
+    if (ok && rc == SPRNN_OK && gated_bwd_cell && h->kernel_bwd_grad && !product_is_faster(h, T) && best_ms > 0.0f) {
       float* d_dU = nullptr;
       h->map.poll_delay = best;
       h->one_xcd = best_one_xcd;
@@ -720,6 +733,22 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
   if (rc == SPRNN_OK && sprnn_check(h) != SPRNN_OK) rc = SPRNN_ERR_STATE;
   return rc;   // allocation or timing trouble is not fatal: the fallback value is used
 }
+
+// dL/dU on the handle of the transposed matrix, in its CSR order: rows pair with h_{t-1}, columns with the gradient of
+// the recurrent sums (`delta`, [T][B][cols]).
+static int transposed_weight_gradient(sprnn_handle_t h, int T, const float* delta, const float* h_fwd, const float* h0, float* dU, void* stream) {
+  if (h->map.nnz == 0) return SPRNN_OK;
+  DeviceGuard guard(h->device);
+  if (!guard.ok) return SPRNN_ERR_HIP;
+  const Mapping& m = h->map;
+  WGradArgs a;
+  a.col = h->d_col; a.starts = h->d_wgrad_starts;
+  a.a.x = h_fwd; a.a.first = h0; a.a.ld = m.rows; a.a.shift = m.batch;
+  a.b.x = delta; a.b.ld = m.cols;
+  a.dU = dU; a.vectors = T * m.batch; a.nnz = (int)m.nnz;
+  return SPRNN_HIP(launch_weight_gradient(a, h->wgrad_tile, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
+}
+
 
 int sprnn_forward(sprnn_handle_t h, int T, const float* x, const float* h0, float* h_out, void* stream) {
   if (!h || T < 0) return SPRNN_ERR_INVALID;
@@ -800,6 +829,10 @@ int sprnn_backward_lstm_with_weights(sprnn_handle_t h_transposed, int T, const f
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
+  if (product_is_faster(h, T)) {
+    const int rc = sprnn_backward_lstm(h, T, dh_ext, gates, c_fwd, c0, d_bprime, dh0, dc0, stream);
+    return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
+  }
   LaunchExtras ex;
   ex.backward = true; ex.saved = gates; ex.dh0 = dh0; ex.dc0 = dc0;
   ex.wgrad_h_fwd = h_fwd; ex.wgrad_h0 = h0; ex.dU = dU_transposed;
@@ -860,6 +893,23 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
+  if (product_is_faster(h, T)) {
+    // (the product's factor has to be in memory: without d_recurrent it goes to an array of the call's own, in stream order)
+    DeviceGuard guard(h->device);
+    if (!guard.ok) return SPRNN_ERR_HIP;
+    void* own = nullptr;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;   // (a captured call is refused below, and allocates nothing)
+    if (!d_recurrent && hipStreamIsCapturing((hipStream_t)stream, &capturing) != hipSuccess) (void)hipGetLastError();
+    if (!d_recurrent && capturing == hipStreamCaptureStatusNone &&
+        !SPRNN_HIP(hipMallocAsync(&own, (size_t)T * h->map.batch * h->map.cols * 4, (hipStream_t)stream))) own = nullptr;
+    float* const factor = d_recurrent ? d_recurrent : static_cast<float*>(own);
+    if (factor) {
+      int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, factor, dh0, stream);
+      if (rc == SPRNN_OK) rc = transposed_weight_gradient(h, T, factor, h_fwd, h0, dU_transposed, stream);
+      if (own && !SPRNN_HIP(hipFreeAsync(own, (hipStream_t)stream)) && rc == SPRNN_OK) rc = SPRNN_ERR_HIP;
+      return rc;
+    }
+  }
   LaunchExtras ex;
   ex.backward = true; ex.saved = gates; ex.dh0 = dh0; ex.gates_out = d_recurrent;
   ex.wgrad_h_fwd = h_fwd; ex.wgrad_h0 = h0; ex.dU = dU_transposed;
@@ -896,6 +946,10 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
     if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.batch * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     if (h->map.nnz == 0) return SPRNN_OK;
     return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
+  }
+  if (product_is_faster(h, T)) {
+    const int rc = sprnn_backward(h, T, dh_ext, h_fwd, d_bprime, dh0, stream);
+    return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
   LaunchExtras ex;
   ex.backward = true; ex.saved = h_fwd; ex.dh0 = dh0;   // (vanilla cells: g' and the weight gradient both use h_t)

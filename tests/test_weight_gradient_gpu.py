@@ -48,3 +48,46 @@ def test_weight_gradient_at_tile_edges(cell, H, B, T, dens, rownnz, with_h0):
     want = (d64.T @ before)[rows, w.col_idx]
     size = (np.abs(d64).T @ np.abs(before))[rows, w.col_idx]
     assert np.all(np.abs(got - want) <= (T * B + 8) * 2.0 ** -24 * size)
+
+
+@pytest.mark.parametrize("cell,H,B,T,dens,with_h0", [
+    # long enough for the product behind the recurrence to be the chosen way ...
+    ("relu", 130, 8, 80, 0.3, True), ("tanh", 65, 4, 150, 0.5, False), ("lstm", 100, 8, 70, 0.3, True),
+    ("lstm", 257, 2, 90, 0.2, False), ("gru", 129, 4, 90, 0.25, True),
+    # ... and too short for it: summed inside the recurrence
+    ("relu", 130, 8, 3, 0.3, True), ("lstm", 100, 8, 2, 0.3, True), ("gru", 129, 4, 2, 0.25, False),
+])
+def test_weight_gradient_asked_of_the_backward_call(cell, H, B, T, dens, with_h0):
+    """dL/dU of the call's own delta, within the bound above; the product leaves the plain backward call's outputs as they are."""
+    w = wl.make_workload("wg-asked", cell, H, B, T, dens, seed=H + T, row_nnz="poisson")
+    rng = np.random.default_rng(H + B)
+    normal = lambda *shape: _dev(rng.standard_normal(shape).astype(np.float32))
+    h0 = normal(B, H) if with_h0 else None
+    t_row_ptr, t_col, t_val, source = binding.transpose_csr(w.rows, H, w.row_ptr, w.col_idx, w.val_bits, with_source=True)
+    gated = cell in ("lstm", "gru")
+    dh, h = normal(T, B, H), normal(T, B, H).tanh_()
+    print("case", cell, H, "B", B, "T", T, dens, flush=True)
+    with binding.SparseRNN(H, B, cell + "_backward" if gated else cell, t_row_ptr, t_col, t_val) as bwd:
+        if gated:
+            saved = normal(T, B, 4 * H).sigmoid_()
+            c = normal(T, B, H)
+        if cell == "lstm":
+            plain = bwd.backward_lstm(dh, saved, c)
+            asked = bwd.backward_lstm_with_weights(dh, saved, c, h, None, h0)
+        elif cell == "gru":
+            plain = bwd.backward_gru(dh, saved, h, h0)
+            asked = bwd.backward_gru_with_weights(dh, saved, h, h0)
+        else:
+            plain = bwd.backward(dh, h)
+            asked = bwd.backward_with_weights(dh, h, h0)
+        torch.cuda.synchronize()
+        assert bwd.check() == binding.SPRNN_OK
+    if T >= 70:
+        for a, b in zip(plain, asked):
+            assert torch.equal(a, b)
+    delta = asked[1 if cell == "gru" else 0].reshape(T * B, w.rows).double().cpu().numpy()
+    before = torch.cat([torch.zeros(1, B, H) if h0 is None else h0[None].cpu(), h[:-1].cpu()]).reshape(T * B, H).double().numpy()
+    rows, cols = np.repeat(np.arange(w.rows), np.diff(w.row_ptr)), w.col_idx
+    want, size = (delta.T @ before)[rows, cols], (np.abs(delta).T @ np.abs(before))[rows, cols]
+    got = asked[-1].cpu().numpy()
+    assert np.all(np.abs(got - want[source]) <= (T * B + 8) * 2.0 ** -24 * size[source])
