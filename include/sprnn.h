@@ -363,7 +363,7 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
  *   h_fwd          device, float32 [T][B][H]: forward outputs h_1..h_T;  h0: [B][H] or NULL (zeros).
  *   dU_transposed  device, float32 [nnz]: dL/dU in the order of the TRANSPOSED matrix's CSR arrays (entry p belongs to
  *                  the forward nonzero t_source[p] of sprnn_transpose_csr); overwritten.
- * Other arguments as sprnn_backward_lstm.  Always runs T + 1 steps.  Not available with column compaction or where
+ * Other arguments as sprnn_backward_lstm.  Not available with column compaction or where
  * the mapping needs more threads than the instantiation is built for (SPRNN_ERR_UNSUPPORTED: use the two separate calls).
  */
 int sprnn_backward_lstm_with_weights(sprnn_handle_t h_transposed, int T, const float* dh_ext, const float* gates,
