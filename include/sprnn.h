@@ -284,8 +284,9 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
  *             d_recurrent from sprnn_backward_gru (R = 3H).
  *   h_fwd     device, float32 [T][B][H]: forward outputs h_1..h_T;  h0: device [B][H] or NULL (zeros).
  *   dU        device, float32 [nnz]: overwritten (T = 0 writes zeros).
- * Operands keep their 24 bits (three bfloat16 parts each), sums are binary32 in an order that is the same from call to
- * call.  Only enqueues work; allocates nothing.
+ * Operands keep their 24 bits over the whole range of binary32 (three bfloat16 parts each), sums are binary32 in an order
+ * that is the same from call to call, infinities and NaN come out as binary32 multiply-adds give them.  Only enqueues work;
+ * allocates nothing.
  */
 int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const float* h_fwd, const float* h0, float* dU,
                           void* stream);

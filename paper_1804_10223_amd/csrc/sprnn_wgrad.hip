@@ -4,7 +4,9 @@
 // On this chip the dense product on the matrix cores is the faster way to it at every density: the multiply-adds of the
 // nonzeros alone on the vector units, with h and delta in LDS, took 1.6 times as long at 30 % and no less at 2 % (there
 // the fetch of the operands bounds both).  Both operands are binary32 and stay so: each is split, while it is staged, into
-// three bfloat16 numbers (round to nearest) whose sum is the number exactly, 3 x 8 bits; six of the nine products go through
+// three bfloat16 numbers (round to nearest) whose sum is the number exactly, 3 x 8 bits (times a power of two that keeps the
+// parts of the smallest numbers normal, 1-4 % of the call; what is too large for that, and infinities, are added up again at
+// the end of the kernel); six of the nine products go through
 // v_mfma_f32_16x16x32_bf16 with binary32 sums, the three that are left out are below 2^-26 of the product of the two
 // numbers, a quarter of the rounding of one binary32 product (measured against binary64: 4.8e-7 of the gradient's norm over
 // 1024 vectors, a chain of binary32 multiply-adds 5.7e-7).
@@ -34,6 +36,8 @@ constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kSlab = 32;                      // m per slab
 constexpr int kPitch = kSlab * 2;              // bytes of one row of one part in LDS: four 16-byte pieces
+constexpr float kOperandScale = 0x1p24f;       // both operands, so sums carry its square: with it every binary32 number,
+constexpr float kSumScale = 0x1p-48f;          // the smallest included, is three normal bfloat16 numbers
 constexpr int plane_bytes(int tm, int tn) { return (tm + tn) * kPitch; }
 constexpr int stage_bytes(int tm, int tn) { return 3 * plane_bytes(tm, tn); }
 constexpr int lds_bytes(int tm, int tn) { return std::max(2 * stage_bytes(tm, tn), tm * (tn + 4) * 4); }
@@ -58,6 +62,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_buffer(const void* bas
   const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
   return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(lo | hi << 32), 0, __builtin_amdgcn_readfirstlane(bytes), kBufWord3);
 }
+__device__ __forceinline__ bool is_finite(float v) { return (__builtin_bit_cast(uint32_t, v) & 0x7f800000u) != 0x7f800000u; }
 __device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t buf, uint32_t byte) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(buf, (int)byte, 0, 0));
 }
@@ -72,6 +77,12 @@ __device__ __forceinline__ uint32_t take_bf16(float& x0, float& x1) {
   x0 -= __builtin_bit_cast(float, bits << 16);
   x1 -= __builtin_bit_cast(float, bits & 0xffff0000u);
   return bits;
+}
+
+// Vector m's element of one row or column.
+__device__ __forceinline__ float element(const WGradOperand& o, int m, int at) {
+  if (m >= o.shift) return o.x[(size_t)(m - o.shift) * o.ld + at];
+  return o.first ? o.first[(size_t)m * o.ld + at] : 0.0f;
 }
 
 template <int TM, int TN>
@@ -146,6 +157,8 @@ __global__ __launch_bounds__(kThreads) void weight_grad_kernel(const WGradArgs p
   auto store = [&](float (&v)[kMine][8], int i, int stage) {
     if (kUnits % kWaves != 0 && unit_of(i) >= kUnits) return;
 #pragma unroll
+    for (int e = 0; e < 8; ++e) v[i][e] *= kOperandScale;
+#pragma unroll
     for (int part = 0; part < 3; ++part) {
       i32x4 q;
 #pragma unroll
@@ -195,7 +208,7 @@ __global__ __launch_bounds__(kThreads) void weight_grad_kernel(const WGradArgs p
 #pragma unroll
     for (int q = 0; q < 6 * MI * NI; ++q) {
       __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
+      __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
     }
     lds_barrier();
   };
@@ -234,6 +247,7 @@ __global__ __launch_bounds__(kThreads) void weight_grad_kernel(const WGradArgs p
       col[i][q] = __builtin_amdgcn_raw_buffer_load_b32(colbuf, k < last[i] ? k * 4 : kOutOfRange, 0, 0);
     }
   lds_barrier();
+  bool odd = false;
 #pragma unroll
   for (int i = 0; i < kTurns; ++i)
 #pragma unroll
@@ -241,8 +255,27 @@ __global__ __launch_bounds__(kThreads) void weight_grad_kernel(const WGradArgs p
       const int k = first[i] + q * 32 + (lane & 31);
       const bool mine = k < last[i];
       const float v = tile[(i * 32 + wave * 2 + (lane >> 5)) * (TN + 4) + (mine ? col[i][q] - c0 : 0)];
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), out, mine ? k * 4 : kOutOfRange, 0, 0);
+      const bool good = is_finite(v);
+      odd |= mine && !good;
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v * kSumScale), out, mine && good ? k * 4 : kOutOfRange, 0, 0);
     }
+
+  // ---- sums that left the range of the split (an infinite or NaN operand, one of 2^104 or more, a sum of 2^80 or more):
+  // the same lanes add them up again, one multiply-add per vector, which is what the numbers themselves give
+  if (!__any(odd)) return;
+#pragma unroll 1
+  for (int i = 0; i < kTurns; ++i) {
+    const int r = r0 + i * 32 + wave * 2 + (lane >> 5);
+    if (r >= rows) continue;
+    const int end = p.starts[(size_t)(tile_c + 1) * rows + r];
+    for (int k = p.starts[(size_t)tile_c * rows + r] + (lane & 31); k < end; k += 32) {
+      const int c = p.col[k];
+      if (is_finite(tile[(r - r0) * (TN + 4) + c - c0])) continue;
+      float sum = 0.0f;
+      for (int m = 0; m < p.vectors && sum == sum; ++m) sum = fmaf(element(p.a, m, r), element(p.b, m, c), sum);
+      p.dU[k] = sum;
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void tile_starts_kernel(const int32_t* row_ptr, const int32_t* col, int rows, int tile_cols, int entries, int32_t* starts) {

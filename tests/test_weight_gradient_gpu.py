@@ -91,3 +91,38 @@ def test_weight_gradient_asked_of_the_backward_call(cell, H, B, T, dens, with_h0
     want, size = (delta.T @ before)[rows, cols], (np.abs(delta).T @ np.abs(before))[rows, cols]
     got = asked[-1].cpu().numpy()
     assert np.all(np.abs(got - want[source]) <= (T * B + 8) * 2.0 ** -24 * size[source])
+
+
+@pytest.mark.parametrize("H,B,T", [(70, 4, 9), (300, 8, 12), (1152, 1, 40), (1800, 2, 17), (2304, 4, 9)])   # each shape of tile
+def test_weight_gradient_over_the_whole_range_of_binary32(H, B, T):
+    """Rows and columns of every size binary32 has, and some with an infinity, a NaN or a number next to the largest.
+
+    Bound per finite entry: the one above, and what numbers below the normal range lose, 2^-149 a term.  Entries whose terms
+    hold an infinity or a NaN are what binary64 makes of them.  Left out: entries whose finite terms leave binary32's range."""
+    w = wl.make_workload("wg-range", "relu", H, B, T, 0.1, seed=H, row_nnz="poisson")
+    rng = np.random.default_rng(H)
+    delta, h = rng.standard_normal((T, B, H)).astype(np.float32), rng.standard_normal((T, B, H)).astype(np.float32)
+    size = np.zeros(H)
+    size[1::3] = rng.uniform(-45, -28, size=size[1::3].shape)        # down to the smallest number there is
+    size[2::3] = rng.uniform(0, 30, size=size[2::3].shape)
+    delta *= np.float64(10.0) ** size
+    h[:, :, 5::7] *= np.float32(1e-36)
+    h[:, :, 6::7] *= np.float32(1e5)
+    h[h < -1.0] = 0.0                                                # exact zeros, as after a ReLU
+    top = np.finfo(np.float32).max
+    delta[2, 0, 4::50], delta[3, 0, 10::50], delta[4, 0, 16::50], delta[5, 0, 22::50] = np.inf, -np.inf, top, np.nan
+    h[1, 0, 3::60], h[6, 0, 9::60] = np.inf, -top                    # (delta_t pairs with h_{t-1}: the first meets delta[2])
+    print("case", H, B, T, flush=True)
+    with binding.SparseRNN(H, B, "relu", w.row_ptr, w.col_idx, w.val_bits, poll_delay=-1) as rnn:
+        got = rnn.weight_gradient(_dev(delta), _dev(h)).cpu().numpy().astype(np.float64)
+    before = np.concatenate([np.zeros((1, B, H), np.float32), h[:-1]]).reshape(T * B, H)
+    rows = np.repeat(np.arange(H), np.diff(w.row_ptr))
+    with np.errstate(invalid="ignore"):
+        terms = delta.reshape(T * B, H)[:, rows].astype(np.float64) * before[:, w.col_idx].astype(np.float64)
+        want = terms.sum(axis=0)
+    magnitude = np.abs(np.where(np.isfinite(terms), terms, 0.0)).sum(axis=0)
+    in_range = magnitude < top / 2                                    # (beyond that binary32 sums may overflow)
+    special, fine = in_range & ~np.isfinite(want), in_range & np.isfinite(want)
+    assert np.isnan(want[special]).any() and np.isinf(want[special]).any() and fine.sum() > len(rows) // 2
+    np.testing.assert_array_equal(got[special], want[special])
+    assert np.all(np.abs(got[fine] - want[fine]) <= (T * B + 8) * (2.0 ** -24 * magnitude[fine] + 2.0 ** -149))
