@@ -279,14 +279,15 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
  * Gradient of the recurrent weights on their sparsity pattern, the non-recurrent half of the backward pass:
  *   dU[k] = sum_t sum_b delta_t[b][row(k)] * h_{t-1}[b][col(k)]      for every stored nonzero k, in CSR order.
  * Runs on the FORWARD handle (vanilla cells, the LSTM and the GRU, where h fits in LDS whole: no column compaction), as
- * one product over all T * B vectors on the matrix cores, sampled at the nonzeros.
+ * one product over all T * B vectors on the matrix cores, sampled at the nonzeros; for wide, sparse layers and very short
+ * calls, where the product's dense elements cost more, as one sum per nonzero in the lane that holds it in the forward pass.
  *   d_bprime  device, float32 [T][B][R]: delta_t from sprnn_backward (R = H), dp_t from sprnn_backward_lstm (R = 4H),
  *             d_recurrent from sprnn_backward_gru (R = 3H).
  *   h_fwd     device, float32 [T][B][H]: forward outputs h_1..h_T;  h0: device [B][H] or NULL (zeros).
  *   dU        device, float32 [nnz]: overwritten (T = 0 writes zeros).
- * Operands keep their 24 bits over the whole range of binary32 (three bfloat16 parts each), sums are binary32 in an order
- * that is the same from call to call, infinities and NaN come out as binary32 multiply-adds give them.  Only enqueues work;
- * allocates nothing.
+ * Operands keep their 24 bits over the whole range of binary32 (in the product as three bfloat16 parts each), sums are
+ * binary32 in an order that is the same for every call of one length on one handle, infinities and NaN come out as binary32
+ * multiply-adds give them.  Only enqueues work; allocates nothing.
  */
 int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const float* h_fwd, const float* h0, float* dU,
                           void* stream);

@@ -33,9 +33,10 @@ struct sprnn_handle_s {
   uint32_t* d_fill_src = nullptr;    // column compaction only
   int32_t* d_wg_plane = nullptr;
   int32_t* d_lane_sum = nullptr;     // lane-pool layout only
-  int32_t* d_word_src = nullptr;     // without compaction: packed word -> CSR position (backward pass with the weight gradient fused in)
+  int32_t* d_word_src = nullptr;     // without compaction: packed word -> CSR position (sums kept by the lanes that hold the nonzeros)
   bool has_wgrad = false;            // the weight gradient is offered on this handle
-  WGradTile wgrad_tile;              // ... the shape of its tiles
+  const void* kernel_lane_sums = nullptr;   // ... one sum per lane and nonzero on the forward mapping, null where it is not built
+  WGradTile wgrad_tile;              // ... as a product: the shape of its tiles
   int32_t* d_wgrad_starts = nullptr; // ... where each row's nonzeros enter each column of tiles
   uint32_t* d_ring = nullptr;
   uint32_t* d_ctrl = nullptr;
@@ -227,6 +228,14 @@ static bool product_is_faster(const sprnn_handle_s* h, int T) {
   return behind < (T + 1) * (0.1 + 0.006 * m.words_max * m.batch);
 }
 
+static WGradCall weight_gradient_call(const sprnn_handle_s* h, int T) {
+  const Mapping& m = h->map;
+  WGradCall c;
+  c.rows = m.rows; c.cols = m.cols; c.num_cus = h->num_cus; c.tile = h->wgrad_tile;
+  c.batch = m.batch; c.block = m.block; c.h_bytes = m.h_bytes; c.steps = T;
+  return c;
+}
+
 extern "C" {
 
 const char* sprnn_status_string(int code) {
@@ -407,6 +416,12 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   }
   if (ok && (m.cell <= SPRNN_ACT_IDENTITY || m.cell == SPRNN_CELL_LSTM || m.cell == SPRNN_CELL_GRU) && !m.compact && !m.half) {
     h->has_wgrad = true;
+    // (built for the word counts of the one-group-per-row layout, with many words per lane for fewer threads than a lane-pool
+    // workgroup may have)
+    h->kernel_lane_sums = lane_sums_kernel_for(m.batch, m.template_words);
+    hipFuncAttributes lfa;
+    if (h->kernel_lane_sums && (!SPRNN_HIP(hipFuncGetAttributes(&lfa, h->kernel_lane_sums)) || lfa.maxThreadsPerBlock < m.block ||
+                                !SPRNN_HIP(hipFuncSetAttribute(h->kernel_lane_sums, hipFuncAttributeMaxDynamicSharedMemorySize, lds_cu)))) h->kernel_lane_sums = nullptr;
     ok = SPRNN_HIP(upload(&h->d_word_src, P.word_src.data(), P.word_src.size()));
     if (ok && h->kernel_bwd && !m.timeline && m.cell <= SPRNN_ACT_IDENTITY) {
       // backward pass with the weight gradient fused in: same co-residency requirement as the plain one
@@ -968,6 +983,16 @@ int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const 
   DeviceGuard guard(h->device);
   if (!guard.ok) return SPRNN_ERR_HIP;
   const Mapping& m = h->map;
+  const WGradCall call = weight_gradient_call(h, T);
+  if (h->kernel_lane_sums && lane_sums_are_faster(call)) {
+    LaneSumsArgs s;
+    s.words = h->d_words; s.lane_row = h->d_lane_row; s.wave_words = h->d_wave_words; s.word_src = h->d_word_src;
+    s.delta = d_bprime; s.h_fwd = h_fwd; s.h0 = h0; s.dU = dU;
+    s.hidden = m.hidden; s.T = T; s.index_shift = m.index_shift; s.rows = m.rows;
+    void* args[] = {&s};
+    // workgroups are independent here: an ordinary launch, one workgroup per CU by the same LDS request
+    return SPRNN_HIP(hipLaunchKernel(h->kernel_lane_sums, dim3(m.grid), dim3(m.block), args, (unsigned)h->launch_lds, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
+  }
   WGradArgs a;
   a.col = h->d_col; a.starts = h->d_wgrad_starts;
   a.a.x = d_bprime; a.a.ld = m.rows;

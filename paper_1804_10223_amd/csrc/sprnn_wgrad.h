@@ -1,4 +1,5 @@
-// Weight gradient on the sparsity pattern: tables made once per handle and the launch (see sprnn_wgrad.hip).
+// Weight gradient on the sparsity pattern: the product's tables, made once per handle, and its launch (sprnn_wgrad.hip), and
+// the kernel that keeps one sum per lane and nonzero (sprnn_wgrad_lanes.hip).  sprnn_wgrad_rule.h says which is taken when.
 #ifndef SPRNN_WGRAD_H_
 #define SPRNN_WGRAD_H_
 
@@ -6,13 +7,9 @@
 
 #include <cstdint>
 
-namespace sprnn {
+#include "sprnn_wgrad_rule.h"
 
-struct WGradTile {
-  int rows = 0, cols = 0;            // shape of one workgroup's part of the dense product
-};
-// The tile shape for a matrix of this size on a device with this many CUs.
-WGradTile choose_weight_gradient_tile(int rows, int cols, int num_cus);
+namespace sprnn {
 
 // starts[t * rows + r] = CSR position of row r's first nonzero at or beyond column t * tile_cols, t = 0 .. column tiles.
 hipError_t launch_tile_starts(const int32_t* row_ptr, const int32_t* col, int rows, int cols, int tile_cols, int32_t* starts,
@@ -34,6 +31,21 @@ struct WGradArgs {
 };
 hipError_t launch_weight_gradient(const WGradArgs& args, WGradTile tile, hipStream_t stream);
 hipError_t prepare_weight_gradient(WGradTile tile);   // once per device before the first launch
+
+// The lane sums: same sums, in time order, on the forward mapping.
+struct LaneSumsArgs {
+  const uint32_t* words;             // the handle's packed words (only the column offsets are used)
+  const int32_t* lane_row;           // [grid][block]
+  const int32_t* wave_words;         // [grid][waves]
+  const int32_t* word_src;           // [grid][NW][block] CSR position of each packed word, -1 for padding
+  const float* delta;                // [T][B][rows]
+  const float* h_fwd;                // [T][B][H] forward outputs h_1..h_T
+  const float* h0;                   // [B][H] or null (zeros)
+  float* dU;                         // [nnz] CSR order
+  int hidden, T, index_shift;
+  int rows;                          // rows of the matrix: hidden, or 3 or 4 times as many for the gated cells
+};
+const void* lane_sums_kernel_for(int batch, int template_words);
 
 }  // namespace sprnn
 #endif

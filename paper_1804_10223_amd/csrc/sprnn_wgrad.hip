@@ -1,15 +1,17 @@
 // Weight gradient on the sparsity pattern, dU[p] = sum_m a[m][row(p)] * b[m][col(p)] over m = (timestep, sample): the
 // non-recurrent half of the backward pass, a dense product of two tall matrices sampled at the nonzeros.
 //
-// On this chip the dense product on the matrix cores is the faster way to it at every density: the multiply-adds of the
-// nonzeros alone on the vector units, with h and delta in LDS, took 1.6 times as long at 30 % and no less at 2 % (there
-// the fetch of the operands bounds both).  Both operands are binary32 and stay so: each is split, while it is staged, into
-// three bfloat16 numbers (round to nearest) whose sum is the number exactly, 3 x 8 bits (times a power of two that keeps the
-// parts of the smallest numbers normal, 1-4 % of the call; what is too large for that, and infinities, are added up again at
-// the end of the kernel); six of the nine products go through
-// v_mfma_f32_16x16x32_bf16 with binary32 sums, the three that are left out are below 2^-26 of the product of the two
-// numbers, a quarter of the rounding of one binary32 product (measured against binary64: 4.8e-7 of the gradient's norm over
-// 1024 vectors, a chain of binary32 multiply-adds 5.7e-7).
+// On this chip the dense product on the matrix cores is the faster way to it for matrices up to about 4000 x 4000 whatever
+// their density: the multiply-adds of the nonzeros alone on the vector units, with h and delta in LDS, took 1.6 times as
+// long at 30 % and no less at 2 % (there the fetch of the operands bounds both).  Wider matrices, whose dense elements
+// outgrow what a step costs otherwise, and very short calls go to sprnn_wgrad_lanes.hip (see sprnn_wgrad_rule.h).
+//
+// Both operands are binary32 and stay so: each is split, while it is staged, into three bfloat16 numbers (round to nearest)
+// whose sum is the number exactly, 3 x 8 bits (times a power of two that keeps the parts of the smallest numbers normal, 1-4 %
+// of the call; what is too large for that, and infinities, are added up again at the end of the kernel); six of the nine
+// products go through v_mfma_f32_16x16x32_bf16 with binary32 sums, the three that are left out are below 2^-26 of the product
+// of the two numbers, a quarter of the rounding of one binary32 product (measured against binary64: 4.8e-7 of the gradient's
+// norm over 1024 vectors, a chain of binary32 multiply-adds 5.7e-7).
 //
 // A workgroup of sixteen wavefronts (4 x 4 over the tile) owns a tile of TM rows x TN columns of dU and walks m in slabs
 // of 32.  The operands are [m][row] and [m][column]: a lane fetches eight consecutive m of one column (128 consecutive
@@ -41,11 +43,6 @@ constexpr float kSumScale = 0x1p-48f;          // the smallest included, is thre
 constexpr int plane_bytes(int tm, int tn) { return (tm + tn) * kPitch; }
 constexpr int stage_bytes(int tm, int tn) { return 3 * plane_bytes(tm, tn); }
 constexpr int lds_bytes(int tm, int tn) { return std::max(2 * stage_bytes(tm, tn), tm * (tn + 4) * 4); }
-
-// The grid of tiles and how the eight XCDs share it: parts_m x (8 / parts_m) rectangles.
-struct TileGrid {
-  int tiles_m, tiles_n, parts_m;
-};
 
 // Where piece q (eight m) of a row sits in the row.  Rows of 64 bytes repeat their banks every four rows, so the pieces
 // change places with bits 1 to 3 of the row: the sixteen lanes that one LDS cycle serves when a matrix instruction's
@@ -301,37 +298,7 @@ const void* kernel_of(WGradTile t) {
   }
 }
 
-// The division among the XCDs whose largest rectangle has the fewest tiles, then the fewest rows and columns to fetch.
-TileGrid grid_of(int rows, int cols, WGradTile tile, int* most) {
-  TileGrid best = {(rows + tile.rows - 1) / tile.rows, (cols + tile.cols - 1) / tile.cols, 1};
-  long long least = 0;
-  for (int parts = 1; parts <= 8; parts *= 2) {
-    const int m = (best.tiles_m + parts - 1) / parts, n = (best.tiles_n + 8 / parts - 1) / (8 / parts);
-    const long long cost = (long long)m * n * 100000 + (long long)m * tile.rows + (long long)n * tile.cols;
-    if (parts == 1 || cost < least) { least = cost; best.parts_m = parts; *most = m * n; }
-  }
-  return best;
-}
-
 }  // namespace
-
-// Clocks of a workgroup: 8000 to start and to store its nonzeros, and per slab 400 around the barrier and 0.1 per element
-// of the tile; an XCD works through its rectangle in turns of one tile per CU.  (Each of the four shapes is the fastest
-// somewhere: 64 x 64 where there are few tiles, 128 x 192 where the 128 x 128 tiles of a matrix just exceed the CUs: 2304
-// x 2304 93 against 73 us, 4096 x 1024 52 against 70.)
-WGradTile choose_weight_gradient_tile(int rows, int cols, int num_cus) {
-  constexpr WGradTile shapes[] = {{64, 64}, {64, 128}, {128, 128}, {128, 192}};
-  WGradTile best;
-  double least = 0.0;
-  for (const WGradTile& t : shapes) {
-    int most = 0;
-    (void)grid_of(rows, cols, t, &most);
-    const int per_xcd = std::max(num_cus / 8, 1);
-    const double cost = (double)((most + per_xcd - 1) / per_xcd) * (8000.0 + 16.0 * (400.0 + 0.1 * t.rows * t.cols));
-    if (best.rows == 0 || cost < least) { best = t; least = cost; }
-  }
-  return best;
-}
 
 hipError_t launch_tile_starts(const int32_t* row_ptr, const int32_t* col, int rows, int cols, int tile_cols, int32_t* starts,
                               hipStream_t stream) {
@@ -344,7 +311,7 @@ hipError_t launch_weight_gradient(const WGradArgs& args, WGradTile tile, hipStre
   const void* const kernel = kernel_of(tile);
   if (!kernel) return hipErrorInvalidValue;
   int most = 0;
-  TileGrid grid = grid_of(args.a.ld, args.b.ld, tile, &most);
+  TileGrid grid = tile_grid(args.a.ld, args.b.ld, tile, &most);
   void* a[] = {(void*)&args, (void*)&grid};
   const hipError_t e = hipLaunchKernel(kernel, dim3((unsigned)most * 8), dim3(kThreads), a, (size_t)lds_bytes(tile.rows, tile.cols), stream);
   return e == hipSuccess ? hipGetLastError() : e;

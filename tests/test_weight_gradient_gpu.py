@@ -50,6 +50,59 @@ def test_weight_gradient_at_tile_edges(cell, H, B, T, dens, rownnz, with_h0):
     assert np.all(np.abs(got - want) <= (T * B + 8) * 2.0 ** -24 * size)
 
 
+def _chain(delta, before, rows, cols, order):
+    """The sums as one binary32 multiply-add per vector gives them, vectors in `order`.  (Rounded through binary64: an entry in
+    some 2^29 differs from a true multiply-add.)"""
+    out = np.zeros(len(rows), np.float32)
+    for m in order:
+        out = (out + delta[m][rows].astype(np.float64) * before[m][cols]).astype(np.float32)
+    return out
+
+
+def _wide_csr(rows, cols, per_row, rng):
+    """A pattern for wide matrices, drawn without looking at every element: at most one nonzero in each of `per_row` equal parts
+    of a row, a quarter of them left out."""
+    col = np.arange(per_row) * (cols // per_row) + rng.integers(0, cols // per_row, (rows, per_row))
+    keep = rng.random((rows, per_row)) < 0.75
+    row_ptr = np.concatenate([[0], np.cumsum(keep.sum(axis=1))]).astype(np.int32)
+    return row_ptr, col[keep].astype(np.int32), np.full(row_ptr[-1], 0x2C00, np.uint16)
+
+
+@pytest.mark.parametrize("cell,H,B,T,per_row,with_h0,lanes", [
+    ("relu", 11520, 1, 21, 24, True, True),                # wide and sparse: one accumulator per lane and nonzero
+    ("tanh", 8190, 4, 5, 8, False, True),                  # ... four batches of copy rounds, a column a piece
+    ("relu", 20001, 2, 5, 12, True, True),                 # ... an odd size: the last piece of h is ragged
+    ("lstm", 4095, 1, 9, 8, True, True),                   # ... ragged, four rows a unit
+    ("gru", 4096, 2, 7, 8, False, True),
+    ("relu", 4096, 8, 2, 16, True, True),                  # ... both planes of batch 8
+    ("identity", 40000, 1, 9, 8, True, True),              # ... about the widest layer whose h the LDS holds
+    ("relu", 1152, 4, 1, 115, True, True),                 # one step: too little for the product's tiles
+    ("relu", 1152, 4, 16, 115, True, False),
+    ("lstm", 1024, 8, 6, 50, True, False),
+])
+def test_weight_gradient_takes_the_way_the_shape_asks_for(cell, H, B, T, per_row, with_h0, lanes):
+    """Right either way; and which way it took shows in the bits: the lanes add one vector after the other."""
+    rng = np.random.default_rng(H + B)
+    R = H * binding.GATES.get(cell, 1)
+    row_ptr, col, val = _wide_csr(R, H, per_row, rng)
+    nnz = len(col)
+    delta, h = rng.standard_normal((T, B, R)).astype(np.float32), rng.standard_normal((T, B, H)).astype(np.float32)
+    h0 = rng.standard_normal((B, H)).astype(np.float32) if with_h0 else None
+    print("case", cell, H, "B", B, "T", T, per_row, flush=True)
+    with binding.SparseRNN(H, B, cell, row_ptr, col, val, poll_delay=-1, compact=2) as rnn:
+        dU = torch.full((nnz + 3,), 77.0, device="cuda")
+        got = rnn.weight_gradient(_dev(delta), _dev(h), _dev(h0), dU).cpu().numpy()
+        assert rnn.check() == binding.SPRNN_OK
+        assert (dU[nnz:] == 77.0).all()
+    before = np.concatenate([np.zeros((1, B, H), np.float32) if h0 is None else h0[None], h[:-1]]).reshape(T * B, H)
+    delta = delta.reshape(T * B, R)
+    rows = np.repeat(np.arange(R), np.diff(row_ptr))
+    terms = delta[:, rows].astype(np.float64) * before[:, col]
+    assert np.all(np.abs(got - terms.sum(axis=0)) <= (T * B + 8) * 2.0 ** -24 * np.abs(terms).sum(axis=0))
+    same = np.mean(got == _chain(delta, before, rows, col, range(T * B)))
+    assert same > 0.999 if lanes else same < 0.9
+
+
 @pytest.mark.parametrize("cell,H,B,T,dens,with_h0", [
     # long enough for the product behind the recurrence to be the chosen way ...
     ("relu", 130, 8, 80, 0.3, True), ("tanh", 65, 4, 150, 0.5, False), ("lstm", 100, 8, 70, 0.3, True),
