@@ -993,6 +993,7 @@ int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const 
     // workgroups are independent here: an ordinary launch, one workgroup per CU by the same LDS request
     return SPRNN_HIP(hipLaunchKernel(h->kernel_lane_sums, dim3(m.grid), dim3(m.block), args, (unsigned)h->launch_lds, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
+  if (call.steps * call.batch > kMostProductVectors) return SPRNN_ERR_UNSUPPORTED;   // (a lane-pool mapping without the other kernel)
   WGradArgs a;
   a.col = h->d_col; a.starts = h->d_wgrad_starts;
   a.a.x = d_bprime; a.a.ld = m.rows;

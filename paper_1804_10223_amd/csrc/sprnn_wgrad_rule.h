@@ -85,8 +85,11 @@ inline double lane_sums_us(const WGradCall& c) {
 // sprnn_weight_gradient.  Both sides measured, lane sums / product in us: 2304 at 30 %, batch 4, T 16 28 / 14, T 256 285 / 74;
 // LSTM 1024 at 20 %, batch 8, T 256 323 / 110; but 5120 at 5 %, batch 4, T 16 37 / 52 (T 256 521 / 332); 8192 at 2 %, batch 1,
 // T 64 65 / 110; LSTM 4096 at 4 %, batch 2, T 64 114 / 157; 20000 at 0.5 %, batch 1, T 64 131 / 597; 40000 at 0.1 %, T 16
-// 63 / 1788.
-inline bool lane_sums_are_faster(const WGradCall& c) { return lane_sums_us(c) < product_us(c); }
+// 63 / 1788.  (The product counts vectors in 32 bits.)
+constexpr int64_t kMostProductVectors = 0x7fffffff - 256;
+inline bool lane_sums_are_faster(const WGradCall& c) {
+  return c.steps * c.batch > kMostProductVectors || lane_sums_us(c) < product_us(c);
+}
 
 }  // namespace sprnn
 #endif

@@ -53,3 +53,8 @@ def test_the_faster_way_is_taken(route):
     calls = [(shape + (T,), times) for shape, at in MEASURED.items() for T, times in at.items()]
     for (call, (lanes, product)), got in zip(calls, route([c for c, _ in calls])):
         assert got == ("lanes" if lanes < product else "product"), (call, lanes, product)
+
+
+def test_more_vectors_than_the_product_counts(route):
+    # (two billion vectors of a layer of one unit, which the product is otherwise the way for)
+    assert route([(1, 1, 8, 64, 2 ** 28 - 64), (1, 1, 8, 64, 2 ** 28), (1, 1, 1, 64, 2 ** 31 - 1)]) == ["product", "lanes", "lanes"]
