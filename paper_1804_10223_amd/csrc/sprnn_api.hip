@@ -51,6 +51,7 @@ struct sprnn_handle_s {
   bool poisoned = false;         // a watchdog trip was observed: the ring no longer holds a consistent state
   bool used_shared_exchange = false;   // sprnn_forward_noalloc ran on this handle: sprnn_check also reads its status word
   float calibrated_us = 0.0f;    // microseconds per step of the setting the calibration kept (0: not measured)
+  float calibrated_grad_us = 0.0f;   // ... of the pass with the weight gradient fused in (0: not measured, not part of a comparison)
 };
 
 // ---- storage of sprnn_forward_noalloc: one array per device, alive as long as the library is loaded.
@@ -213,7 +214,7 @@ static hipError_t launch_in_order(int device, const void* kernel, int grid, int 
   return hipSuccess;
 }
 
-static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_runs);
+static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_runs, const sprnn_handle_s* incumbent);
 
 // The weight gradient asked of a backward call: summed inside the recurrence (one more gather-fed accumulator per nonzero
 // and step), or as one product on the matrix cores behind it.  The former costs every step 0.1 us and 0.006 us per word of
@@ -290,11 +291,12 @@ struct Alternative {
 };
 
 // One handle for one set of options: mapping, packing, upload, kernel choice, calibration.  `long_runs` makes the
-// calibration time runs long enough to be compared between two handles of different launch size.
+// calibration time runs long enough to be compared between two handles of different launch size; `incumbent` is the
+// handle it is compared with, null for the first.
 static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
                       const int32_t* col_idx, const uint16_t* val_fp16_bits, int device_id,
                       const sprnn_options_t* opt, const hipDeviceProp_t& prop, bool free_choice, bool long_runs,
-                      Alternative* alternative) {
+                      const sprnn_handle_s* incumbent, Alternative* alternative) {
   Packed P;
   int rc;
   try {
@@ -470,7 +472,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
     }
   }
   if (calibrate) {
-    const int rc2 = calibrate_poll_delay(h, try_one_xcd, long_runs || alt.grid > 0 || alt.fill_waves > 0);
+    const int rc2 = calibrate_poll_delay(h, try_one_xcd, long_runs || alt.grid > 0 || alt.fill_waves > 0, incumbent);
     if (rc2 != SPRNN_OK) { release(h); return rc2; }
   }
   if (alternative) *alternative = alt;
@@ -513,7 +515,7 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
   sprnn_handle_t first = nullptr;
   Alternative alt;
   const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, opt, prop,
-                            free_choice, free_choice, &alt);
+                            free_choice, free_choice, nullptr, &alt);
   if (rc != SPRNN_OK) return rc;
   sprnn_options_t base = opt ? *opt : sprnn_options_t();
   if (!opt) std::memset(&base, 0, sizeof(base));
@@ -521,14 +523,18 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
   auto contend = [&](const sprnn_options_t& other) {
     sprnn_handle_t second = nullptr;
     const int rc2 = create_one(&second, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &other, prop,
-                               false, true, nullptr);
+                               false, true, first, nullptr);
+    // like with like: by the plain pass alone unless both were measured with the weight gradient as well
+    const bool both = rc2 == SPRNN_OK && first->calibrated_grad_us > 0.0f && second->calibrated_grad_us > 0.0f;
+    const float incumbent_us = first->calibrated_us + (both ? first->calibrated_grad_us : 0.0f);
+    const float contender_us = rc2 != SPRNN_OK || second->calibrated_us <= 0.0f ? 0.0f : second->calibrated_us + (both ? second->calibrated_grad_us : 0.0f);
     static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
     if (verbose)
-      std::fprintf(stderr, "sprnn_create: contender (lanes %d, grid %d, fill %d) -> %s, %d x %d, %.3f us per step against %.3f\n",
+      std::fprintf(stderr, "sprnn_create: contender (lanes %d, grid %d, fill %d) -> %s, %d x %d, %.3f us per step against %.3f%s\n",
                    other.lanes_per_row, other.grid, other.fill_waves, sprnn_status_string(rc2), rc2 == SPRNN_OK ? second->map.grid : 0,
-                   rc2 == SPRNN_OK ? second->map.block : 0, rc2 == SPRNN_OK ? second->calibrated_us : 0.0f, first->calibrated_us);
+                   rc2 == SPRNN_OK ? second->map.block : 0, contender_us, incumbent_us, both ? ", with and without weights" : "");
     if (rc2 != SPRNN_OK) return;
-    if (second->calibrated_us > 0.0f && second->calibrated_us < 0.98f * first->calibrated_us) {
+    if (contender_us > 0.0f && contender_us < 0.98f * incumbent_us) {
       release(first);
       first = second;
     } else {
@@ -656,7 +662,7 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
 // conflicts, cell type).  Polling too early is far more expensive than polling late, and the sweet spot moves
 // from 3 to 12 units between the measured shapes, so it is measured once per handle: a short run on zero input
 // for a handful of candidates, keeping the fastest.  Timing does not depend on the data.
-static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_runs) {
+static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_runs, const sprnn_handle_s* incumbent) {
   const Mapping& m = h->map;
   // (a launch of the one-XCD mode holds eight times the workgroups and costs a few microseconds more to start: the
   // comparison of the two placements runs long enough for the per-step time to decide, as it does at real lengths)
@@ -716,9 +722,10 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
     }
     best_ms_kept = best_ms;
     // A gated cell's backward handle serves two kernels, the plain pass and the one with the weight gradient fused in,
-    // and a mapping that suits one may not suit the other: handles are compared by the sum of both (where the latter is used).
+    // and a mapping that suits one may not suit the other: both are measured where the first handle uses the latter.
     const bool gated_bwd_cell = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;
-    if (ok && rc == SPRNN_OK && gated_bwd_cell && h->kernel_bwd_grad && !product_is_faster(h, T) && best_ms > 0.0f) {
+    const bool with_grad = incumbent ? incumbent->calibrated_grad_us > 0.0f : gated_bwd_cell && !product_is_faster(h, T);
+    if (ok && rc == SPRNN_OK && with_grad && h->kernel_bwd_grad && best_ms > 0.0f) {
       float* d_dU = nullptr;
       h->map.poll_delay = best;
       h->one_xcd = best_one_xcd;
@@ -734,7 +741,7 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
           if (!SPRNN_HIP(hipEventRecord(e1, nullptr)) || !SPRNN_HIP(hipEventSynchronize(e1)) || !SPRNN_HIP(hipEventElapsedTime(&ms, e0, e1))) { ok = false; break; }
           if (rep > 0 && (fused == 0.0f || ms < fused)) fused = ms;
         }
-        if (ok && rc == SPRNN_OK) best_ms_kept += fused;
+        if (ok && rc == SPRNN_OK) h->calibrated_grad_us = fused * 1000.0f / (float)T;
       }
       (void)hipFree(d_dU);
     }

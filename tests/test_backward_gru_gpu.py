@@ -4,6 +4,11 @@ handle) against the CPU oracle, through the C ABI.
 Both sides of a backward comparison get the same inputs: r, z, n, q and the outputs kept by the oracle's own binary32
 forward pass, and seeded e_t = dL/dh_t.  Bar, as everywhere: per timestep max|got - want| <= 1e-3 * max|want|.
 """
+import os
+import re
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -14,6 +19,7 @@ from paper_1804_10223_amd import binding, workloads as wl
 pytestmark = pytest.mark.gpu
 
 REL_TOL = 1e-3
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _dev(a):
@@ -232,3 +238,20 @@ def test_gru_backward_with_weights_matches_oracle(H, B, T, dens, rownnz, opts):
     dU = np.empty_like(dU_t)
     dU[t_src] = dU_t                       # back to the forward matrix's CSR order
     _close(dU, want_dU, "dU")
+
+
+# ------------------------------------------------------------------ mappings measured against each other
+def test_contending_mappings_of_a_backward_handle_are_measured_by_the_same_passes():
+    # 64 lanes a row hold 9 words each, 32 lanes 17: by themselves the first would be timed with the weight gradient fused in
+    # and the second without.  SPRNN_DEBUG is read once per process, so the handle is made in one of its own.
+    code = (
+        "import numpy as np\n"
+        "from paper_1804_10223_amd import binding, workloads as wl\n"
+        "w = wl.make_workload('passes', 'gru', 1500, 4, 1, 0.1, seed=3)\n"
+        "t = binding.transpose_csr(w.rows, 1500, w.row_ptr, w.col_idx, w.val_bits)\n"
+        "binding.SparseRNN(1500, 4, 'gru_backward', *t).close()\n")
+    run = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=dict(os.environ, SPRNN_DEBUG="1"), capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stderr
+    print(run.stderr, flush=True)
+    compared = re.findall(r"contender .* -> ok, .* us per step against [\d.]+(.*)", run.stderr)
+    assert compared and all(c == ", with and without weights" for c in compared)
