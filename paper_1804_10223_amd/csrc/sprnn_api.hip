@@ -915,22 +915,9 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  if (product_is_faster(h, T)) {
-    // (the product's factor has to be in memory: without d_recurrent it goes to an array of the call's own, in stream order)
-    DeviceGuard guard(h->device);
-    if (!guard.ok) return SPRNN_ERR_HIP;
-    void* own = nullptr;
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;   // (a captured call is refused below, and allocates nothing)
-    if (!d_recurrent && hipStreamIsCapturing((hipStream_t)stream, &capturing) != hipSuccess) (void)hipGetLastError();
-    if (!d_recurrent && capturing == hipStreamCaptureStatusNone &&
-        !SPRNN_HIP(hipMallocAsync(&own, (size_t)T * h->map.batch * h->map.cols * 4, (hipStream_t)stream))) own = nullptr;
-    float* const factor = d_recurrent ? d_recurrent : static_cast<float*>(own);
-    if (factor) {
-      int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, factor, dh0, stream);
-      if (rc == SPRNN_OK) rc = transposed_weight_gradient(h, T, factor, h_fwd, h0, dU_transposed, stream);
-      if (own && !SPRNN_HIP(hipFreeAsync(own, (hipStream_t)stream)) && rc == SPRNN_OK) rc = SPRNN_ERR_HIP;
-      return rc;
-    }
+  if (d_recurrent && product_is_faster(h, T)) {   // (the product's factor has to be in memory, and a call allocates none)
+    const int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, d_recurrent, dh0, stream);
+    return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_recurrent, h_fwd, h0, dU_transposed, stream) : rc;
   }
   LaunchExtras ex;
   ex.backward = true; ex.saved = gates; ex.dh0 = dh0; ex.gates_out = d_recurrent;
