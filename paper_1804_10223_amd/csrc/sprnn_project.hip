@@ -382,8 +382,7 @@ hipError_t launch_project(const float* x, const uint16_t* w, const float* bias, 
   const long long small = (long long)tiles_small * ((N + 31) / 32);
   if (!force && small <= cus) {
     void* args[] = {(void*)&x, (void*)&w, (void*)&bias, (void*)&out, (void*)&M, (void*)&N, (void*)&K, (void*)&tiles_small};
-    e = hipLaunchKernel((const void*)project_small_kernel, dim3((unsigned)small), dim3(kThreads), args, 0, stream);
-    return e == hipSuccess ? hipGetLastError() : e;
+    return hipLaunchKernel((const void*)project_small_kernel, dim3((unsigned)small), dim3(kThreads), args, 0, stream);
   }
   int nj = 2;
   if (force) {
@@ -412,9 +411,7 @@ hipError_t launch_project(const float* x, const uint16_t* w, const float* bias, 
     raised[dev][nj] = true;
   }
   void* args[] = {(void*)&x, (void*)&w, (void*)&bias, (void*)&out, (void*)&M, (void*)&N, (void*)&K, (void*)&tiles_m};
-  e = hipLaunchKernel(kernels[nj], dim3((unsigned)tiles), dim3(kThreads), args, (size_t)lds, stream);
-  if (e != hipSuccess) return e;
-  return hipGetLastError();
+  return hipLaunchKernel(kernels[nj], dim3((unsigned)tiles), dim3(kThreads), args, (size_t)lds, stream);
 }
 
 }  // namespace sprnn

@@ -302,9 +302,9 @@ const void* kernel_of(WGradTile t) {
 
 hipError_t launch_tile_starts(const int32_t* row_ptr, const int32_t* col, int rows, int cols, int tile_cols, int32_t* starts,
                               hipStream_t stream) {
-  const int entries = rows * ((cols + tile_cols - 1) / tile_cols + 1);
-  hipLaunchKernelGGL(tile_starts_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, row_ptr, col, rows, tile_cols, entries, starts);
-  return hipGetLastError();
+  int entries = rows * ((cols + tile_cols - 1) / tile_cols + 1);
+  void* a[] = {(void*)&row_ptr, (void*)&col, (void*)&rows, (void*)&tile_cols, (void*)&entries, (void*)&starts};
+  return hipLaunchKernel((const void*)tile_starts_kernel, dim3((entries + 255) / 256), dim3(256), a, 0, stream);
 }
 
 hipError_t launch_weight_gradient(const WGradArgs& args, WGradTile tile, hipStream_t stream) {
@@ -313,8 +313,7 @@ hipError_t launch_weight_gradient(const WGradArgs& args, WGradTile tile, hipStre
   int most = 0;
   TileGrid grid = tile_grid(args.a.ld, args.b.ld, tile, &most);
   void* a[] = {(void*)&args, (void*)&grid};
-  const hipError_t e = hipLaunchKernel(kernel, dim3((unsigned)most * 8), dim3(kThreads), a, (size_t)lds_bytes(tile.rows, tile.cols), stream);
-  return e == hipSuccess ? hipGetLastError() : e;
+  return hipLaunchKernel(kernel, dim3((unsigned)most * 8), dim3(kThreads), a, (size_t)lds_bytes(tile.rows, tile.cols), stream);
 }
 
 hipError_t prepare_weight_gradient(WGradTile tile) {   // two stages exceed the 64 KB of LDS a launch may ask for by default

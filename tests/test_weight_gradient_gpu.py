@@ -4,6 +4,8 @@ product sampled at the nonzeros.
 Bound per entry: the kernel's products are exact to 2^-26 of |a b| and its sums binary32, so with n = T * B terms
     |got - want| <= (n + 8) 2^-24 sum_m |a[m][row] b[m][col]|.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -179,3 +181,27 @@ def test_weight_gradient_over_the_whole_range_of_binary32(H, B, T):
     assert np.isnan(want[special]).any() and np.isinf(want[special]).any() and fine.sum() > len(rows) // 2
     np.testing.assert_array_equal(got[special], want[special])
     assert np.all(np.abs(got[fine] - want[fine]) <= (T * B + 8) * (2.0 ** -24 * magnitude[fine] + 2.0 ** -149))
+
+
+def test_an_error_the_caller_left_behind_is_not_taken_for_the_librarys():
+    H, B, T = 300, 4, 40
+    w = wl.make_workload("wg-error", "relu", H, B, T, 0.2, seed=2)
+    hip = ctypes.CDLL(sorted(binding.hip_runtimes_mapped())[0])
+    t_csr = binding.transpose_csr(H, H, w.row_ptr, w.col_idx, w.val_bits)
+    x, out = torch.randn((T, B, H), device="cuda"), torch.empty((T, B, H), device="cuda")
+    w_in, dU, dh0 = torch.randn((H, H), device="cuda").half(), torch.empty(w.nnz, device="cuda"), torch.empty((B, H), device="cuda")
+    long_x, long_out = torch.randn((700, B, H), device="cuda"), torch.empty((700, B, H), device="cuda")
+    torch.cuda.synchronize()
+
+    def leave_one():
+        assert hip.hipSetDevice(9999) != 0
+
+    try:
+        leave_one()
+        with binding.SparseRNN(H, B, "relu", *t_csr) as rnn:
+            for call in (lambda: rnn.weight_gradient(x, x, None, dU), lambda: rnn.backward_with_weights(x, x, None, out, dh0=dh0, dU=dU),
+                         lambda: rnn.project(x, w_in, None, out), lambda: rnn.project(long_x, w_in, None, long_out)):
+                leave_one()
+                call()
+    finally:
+        hip.hipGetLastError()
