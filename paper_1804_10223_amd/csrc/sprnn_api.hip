@@ -424,8 +424,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
     hipFuncAttributes lfa;
     if (h->kernel_lane_sums && (!SPRNN_HIP(hipFuncGetAttributes(&lfa, h->kernel_lane_sums)) || lfa.maxThreadsPerBlock < m.block ||
                                 !SPRNN_HIP(hipFuncSetAttribute(h->kernel_lane_sums, hipFuncAttributeMaxDynamicSharedMemorySize, lds_cu)))) h->kernel_lane_sums = nullptr;
-    ok = SPRNN_HIP(upload(&h->d_word_src, P.word_src.data(), P.word_src.size()));
-    if (ok && h->kernel_bwd && !m.timeline && m.cell <= SPRNN_ACT_IDENTITY) {
+    if (h->kernel_bwd && !m.timeline && m.cell <= SPRNN_ACT_IDENTITY) {
       // backward pass with the weight gradient fused in: same co-residency requirement as the plain one
       const void* k = pool ? pool_kernel_for(m.batch, m.template_words, kCellBackwardGrad) : persistent_kernel_for(m.batch, m.template_words, kCellBackwardGrad, false);
       int per_cu_g = 0;
@@ -436,6 +435,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
           m.grid <= per_cu_g * prop.multiProcessorCount)
         h->kernel_bwd_grad = k;
     }
+    if (h->kernel_lane_sums || h->kernel_bwd_grad) ok = SPRNN_HIP(upload(&h->d_word_src, P.word_src.data(), P.word_src.size()));
   }
   if (ok && m.timeline) {
     std::vector<unsigned long long> zeros((size_t)m.grid * kTimelineSlots, 0ull);
@@ -480,15 +480,21 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   return SPRNN_OK;
 }
 
-// The tables of the weight gradient, made once for the handle that is kept.
-static int prepare_weight_gradient_tables(sprnn_handle_s* h) {
-  if ((!h->has_wgrad && !h->kernel_bwd_grad) || h->map.nnz == 0) return SPRNN_OK;
+// The table of the product, made once for the handle that is kept, where some length of call takes the product (a wide layer's
+// table is larger than its packed weights).  Without it, for want of memory too, the calls go the other way.
+static void prepare_weight_gradient_product(sprnn_handle_s* h) {
   const int rows = h->map.rows, cols = h->map.cols;
   h->wgrad_tile = choose_weight_gradient_tile(rows, cols, h->num_cus);
+  bool used = false;
+  for (const int T : {1, 1 << 24})   // (both ways' times are linear in the length)
+    used |= (h->has_wgrad && !(h->kernel_lane_sums && lane_sums_are_faster(weight_gradient_call(h, T)))) || (h->kernel_bwd_grad && product_is_faster(h, T));
+  if (!used || h->map.nnz == 0) return;
   const size_t entries = (size_t)rows * ((cols + h->wgrad_tile.cols - 1) / h->wgrad_tile.cols + 1);
-  return SPRNN_HIP(hipMalloc((void**)&h->d_wgrad_starts, entries * 4)) &&
-         SPRNN_HIP(launch_tile_starts(h->d_row_ptr, h->d_col, rows, cols, h->wgrad_tile.cols, h->d_wgrad_starts, nullptr)) &&
-         SPRNN_HIP(prepare_weight_gradient(h->wgrad_tile)) && SPRNN_HIP(hipStreamSynchronize(nullptr)) ? SPRNN_OK : SPRNN_ERR_HIP;
+  if (SPRNN_HIP(hipMalloc((void**)&h->d_wgrad_starts, entries * 4)) &&
+      SPRNN_HIP(launch_tile_starts(h->d_row_ptr, h->d_col, rows, cols, h->wgrad_tile.cols, h->d_wgrad_starts, nullptr)) &&
+      SPRNN_HIP(prepare_weight_gradient(h->wgrad_tile)) && SPRNN_HIP(hipStreamSynchronize(nullptr))) return;
+  (void)hipFree(h->d_wgrad_starts);
+  h->d_wgrad_starts = nullptr;
 }
 
 int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
@@ -560,8 +566,7 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
     other.lanes_per_row = lanes;
     contend(other);
   }
-  const int planned = prepare_weight_gradient_tables(first);
-  if (planned != SPRNN_OK) { release(first); return planned; }
+  prepare_weight_gradient_product(first);
   *out = first;
   return SPRNN_OK;
 }
@@ -851,7 +856,7 @@ int sprnn_backward_lstm_with_weights(sprnn_handle_t h_transposed, int T, const f
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  if (product_is_faster(h, T)) {
+  if (h->d_wgrad_starts && product_is_faster(h, T)) {
     const int rc = sprnn_backward_lstm(h, T, dh_ext, gates, c_fwd, c0, d_bprime, dh0, dc0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
@@ -915,7 +920,7 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  if (d_recurrent && product_is_faster(h, T)) {   // (the product's factor has to be in memory, and a call allocates none)
+  if (d_recurrent && h->d_wgrad_starts && product_is_faster(h, T)) {   // (the product's factor has to be in memory, and a call allocates none)
     const int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, d_recurrent, dh0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_recurrent, h_fwd, h0, dU_transposed, stream) : rc;
   }
@@ -956,7 +961,7 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
     if (h->map.nnz == 0) return SPRNN_OK;
     return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
-  if (product_is_faster(h, T)) {
+  if (h->d_wgrad_starts && product_is_faster(h, T)) {
     const int rc = sprnn_backward(h, T, dh_ext, h_fwd, d_bprime, dh0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
@@ -978,7 +983,7 @@ int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const 
   if (!guard.ok) return SPRNN_ERR_HIP;
   const Mapping& m = h->map;
   const WGradCall call = weight_gradient_call(h, T);
-  if (h->kernel_lane_sums && lane_sums_are_faster(call)) {
+  if (h->kernel_lane_sums && (!h->d_wgrad_starts || lane_sums_are_faster(call))) {
     LaneSumsArgs s;
     s.words = h->d_words; s.lane_row = h->d_lane_row; s.wave_words = h->d_wave_words; s.word_src = h->d_word_src;
     s.delta = d_bprime; s.h_fwd = h_fwd; s.h0 = h0; s.dU = dU;
@@ -987,7 +992,7 @@ int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const 
     // workgroups are independent here: an ordinary launch, one workgroup per CU by the same LDS request
     return SPRNN_HIP(hipLaunchKernel(h->kernel_lane_sums, dim3(m.grid), dim3(m.block), args, (unsigned)h->launch_lds, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
-  if (call.steps * call.batch > kMostProductVectors) return SPRNN_ERR_UNSUPPORTED;   // (a lane-pool mapping without the other kernel)
+  if (!h->d_wgrad_starts || call.steps * call.batch > kMostProductVectors) return SPRNN_ERR_UNSUPPORTED;   // (a lane-pool mapping without the other kernel)
   WGradArgs a;
   a.col = h->d_col; a.starts = h->d_wgrad_starts;
   a.a.x = d_bprime; a.a.ld = m.rows;

@@ -205,3 +205,15 @@ def test_an_error_the_caller_left_behind_is_not_taken_for_the_librarys():
                 call()
     finally:
         hip.hipGetLastError()
+
+
+def test_a_layer_whose_calls_never_take_the_product_keeps_no_table_for_it():
+    H = 40000                                  # the table would be 34 MB, the packed weights 1.3
+    row_ptr, col, val = _wide_csr(H, H, 8, np.random.default_rng(1))
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with binding.SparseRNN(H, 1, "relu", row_ptr, col, val, poll_delay=-1, compact=2) as rnn:
+        used = free - torch.cuda.mem_get_info()[0]
+        assert rnn.check() == binding.SPRNN_OK
+    print("bytes of the handle", used, flush=True)
+    assert used < 24 << 20
