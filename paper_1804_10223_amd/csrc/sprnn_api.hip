@@ -218,7 +218,7 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
 
 // The weight gradient asked of a backward call: summed inside the recurrence (one more gather-fed accumulator per nonzero
 // and step), or as one product on the matrix cores behind it.  The former costs every step 0.1 us and 0.006 us per word of
-// a lane and sample, the latter a launch and 13.4 ps per element of the dense matrix and vector, but no less than a slab
+// a lane and sample, the latter a launch and 13.4 fs per element of the dense matrix and vector, but no less than a slab
 // of 32 vectors takes a workgroup.  Whole calls measured, inside / behind: 2304 at 30 %, batch 4, T 256 620 / 541 us;
 // 1152 at 10 %, batch 4, T 64 146 / 110; LSTM 1024 at 20 %, batch 8, T 128 810 / 767 (step with its forward pass); but
 // 4096 at 8 %, batch 4, T 64 173 / 208, 5000 at 2 %, batch 1, T 128 267 / 311, LSTM 2000 at 5 %, batch 1, T 64 241 / 260.

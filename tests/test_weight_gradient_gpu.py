@@ -146,6 +146,9 @@ def test_weight_gradient_asked_of_the_backward_call(cell, H, B, T, dens, with_h0
     want, size = (delta.T @ before)[rows, cols], (np.abs(delta).T @ np.abs(before))[rows, cols]
     got = asked[-1].cpu().numpy()
     assert np.all(np.abs(got - want[source]) <= (T * B + 8) * 2.0 ** -24 * size[source])
+    back = [t * B + b for t in range(T - 1, -1, -1) for b in range(B)]
+    inside = np.mean(got == _chain(delta.astype(np.float32), before.astype(np.float32), rows, cols, back)[source])
+    assert inside < 0.9 if T >= 70 else inside > 0.999
 
 
 @pytest.mark.parametrize("H,B,T", [(70, 4, 9), (300, 8, 12), (1152, 1, 40), (1800, 2, 17), (2304, 4, 9)])   # each shape of tile
@@ -217,3 +220,59 @@ def test_a_layer_whose_calls_never_take_the_product_keeps_no_table_for_it():
         assert rnn.check() == binding.SPRNN_OK
     print("bytes of the handle", used, flush=True)
     assert used < 24 << 20
+
+
+# Calls short or wide enough for the weight gradient to be summed inside the backward recurrence (the others of this file and of
+# the backward tests that are longer take the product): every kernel of that kind, with pauses in the hand-off.
+@pytest.mark.parametrize("cell,H,B,T,dens,opts", [
+    ("relu", 96, 4, 6, 0.3, {}),
+    ("tanh", 257, 1, 7, 0.2, {}),
+    ("identity", 130, 8, 5, 0.1, {}),
+    ("tanh", 64, 4, 4, 0.4, {"grid": 1}),
+    ("relu", 640, 1, 12, 0.5, {"lanes_per_row": 16, "jitter": 5}),        # 24 slots per lane in 512 threads
+    ("relu", 640, 4, 3, 0.5, {"lanes_per_row": 8, "jitter": 5}),          # 48 slots per lane in 256 threads
+    ("tanh", 2048, 4, 40, 0.02, {"lanes_per_row": 16, "jitter": 5}),      # wide and sparse: inside at any length
+    ("tanh", 2048, 4, 40, 0.02, {"lanes_per_row": 16, "jitter": 11, "sync": "barrier"}),
+    ("relu", 4096, 4, 24, 0.08, {}),
+    ("relu", 2304, 4, 8, 0.3, {"jitter": 5}),
+    ("relu", 1500, 8, 8, 0.05, {"lanes_per_row": 16, "jitter": 11}),
+    ("tanh", 1152, 4, 8, 0.1, {"layout": "lane_pool", "jitter": 5}),
+    ("relu", 333, 2, 6, 0.15, {"layout": "lane_pool"}),
+    ("lstm", 1024, 4, 20, 0.05, {"lanes_per_row": 32, "jitter": 5}),
+    ("lstm", 1024, 8, 4, 0.2, {"jitter": 11}),
+    ("lstm", 2000, 1, 24, 0.05, {}),
+    ("lstm", 300, 2, 6, 0.5, {"lanes_per_row": 16, "jitter": 5}),         # 32 slots
+    ("gru", 1200, 2, 30, 0.1, {"lanes_per_row": 32, "jitter": 11}),
+    ("gru", 1024, 8, 4, 0.2, {"jitter": 5}),
+])
+def test_weight_gradient_summed_inside_the_recurrence(cell, H, B, T, dens, opts):
+    """dL/dU bit for bit as multiply-adds from the last timestep to the first give it from the call's own delta, and delta bit
+    for bit that of the plain call without pauses."""
+    rng = np.random.default_rng(H + T)
+    R = H * binding.GATES.get(cell, 1)
+    per_row = int(round(dens * H))
+    row_ptr, col, val = _wide_csr(R, H, per_row, rng)
+    row_ptr_t, col_t, val_t, source = binding.transpose_csr(R, H, row_ptr, col, val, with_source=True)
+    normal = lambda *shape: _dev(rng.standard_normal(shape).astype(np.float32))
+    dh, h, h0 = normal(T, B, H), normal(T, B, H).tanh_(), normal(B, H)
+    gates, c, c0 = (normal(T, B, 4 * H).sigmoid_(), normal(T, B, H), normal(B, H)) if cell in binding.GATES else (None, None, None)
+    outs = {}
+    for name, options in (("plain", {k: v for k, v in opts.items() if k != "jitter"}), ("asked", opts)):
+        print("case", cell, H, "B", B, "T", T, dens, name, options, flush=True)
+        with binding.SparseRNN(H, B, cell + "_backward" if cell in binding.GATES else cell, row_ptr_t, col_t, val_t, poll_delay=6, compact=2, **options) as bwd:
+            if name == "plain":
+                out = (bwd.backward_lstm(dh, gates, c, c0) if cell == "lstm" else
+                       bwd.backward_gru(dh, gates, h, h0) if cell == "gru" else bwd.backward(dh, h))
+            else:
+                out = (bwd.backward_lstm_with_weights(dh, gates, c, h, c0, h0) if cell == "lstm" else
+                       bwd.backward_gru_with_weights(dh, gates, h, h0) if cell == "gru" else bwd.backward_with_weights(dh, h, h0))
+            assert bwd.check() == binding.SPRNN_OK
+            outs[name] = [o.cpu().numpy() for o in out]
+    for a, b in zip(outs["plain"], outs["asked"]):
+        assert np.array_equal(a, b)
+    delta = outs["asked"][1 if cell == "gru" else 0].reshape(T * B, R)
+    before = np.concatenate([h0[None].cpu(), h[:-1].cpu()]).reshape(T * B, H)
+    rows = np.repeat(np.arange(R), np.diff(row_ptr))
+    back = [t * B + b for t in range(T - 1, -1, -1) for b in range(B)]
+    same = outs["asked"][-1] == _chain(delta, before, rows, col, back)[source]
+    assert same.mean() > 0.999, same.mean()
