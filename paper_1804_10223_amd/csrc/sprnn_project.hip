@@ -390,12 +390,14 @@ hipError_t launch_project(const float* x, const uint16_t* w, const float* bias, 
   } else {
     // Measured on four layer shapes: 128-wide tiles are the best all-rounder; 192-wide ones win when the 128-wide
     // tiles are a little more than one per CU (every CU would otherwise wait for the few that carry two) and the
-    // wider ones fit one per CU.  64-wide ones serve outputs that give about one of them to a CU or less (two or three
-    // share a CU): 400 x 1152 x 771 15.7 -> 11.4 us, 128 x 4096 x 2560 26.5 -> 20.6, 400 x 2313 x 333 (259 tiles) 13.0
-    // -> 11.4, but 1024 x 1152 x 1152 (288 tiles) 17.6 -> 18.5.
+    // wider ones fit one per CU.  64-wide ones serve outputs that give at most one of them to a CU: 400 x 1152 x 771 15.7 ->
+    // 11.4 us, 128 x 4096 x 2560 26.5 -> 20.6, 1028 x 960 (255 tiles) at K 80 to 1500 0.71 to 0.86 of the time.  A few more
+    // (two or three share a CU) pay as long as K is short: 257 to 272 tiles of seven shapes took 0.80 to 0.82 of the time of
+    // 128-wide ones at K 80, 0.92 to 0.95 at 333, 0.87 to 1.05 at 771, 0.94 to 1.05 at 896, 0.95 to 1.11 at 1024 and 1.11 to
+    // 1.20 at 2048 and 2560.
     const long long t1 = (long long)tiles_m * ((N + 63) / 64);
     const long long t2 = (long long)tiles_m * ((N + 127) / 128), t3 = (long long)tiles_m * ((N + 191) / 192);
-    if (N <= 64 || t1 * 16 <= cus * 17LL) nj = 1;
+    if (N <= 64 || t1 <= cus || (t1 * 16 <= cus * 17LL && K <= 896)) nj = 1;
     else if (t2 > cus && 2 * t2 <= 3LL * cus && t3 <= cus) nj = 3;
   }
   if (nj < 1 || nj > 3) return hipErrorInvalidValue;

@@ -18,9 +18,9 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1, 1, 0), (33, 1, 33, 15, 1), (32, 4, 8, 16, 0), (65, 1, 31, 17, 1), (200, 2, 50, 129, 0),
     (90, 1, 3, 1037, 1), (40, 8, 9, 96, 0), (2000, 1, 50, 200, 0),
     # tiles of 64 x 64 (too many of the above, about one per CU)
-    (1111, 4, 100, 333, 0), (2304, 1, 400, 64, 1), (60, 8, 900, 70, 0),
+    (1111, 4, 100, 333, 0), (2304, 1, 400, 64, 1), (60, 8, 900, 70, 0), (1024, 1, 1024, 897, 0), (1024, 8, 136, 896, 0),
     # 64 x 128 and 64 x 192
-    (1100, 1, 1100, 77, 1), (1100, 4, 275, 128, 0), (1100, 4, 525, 70, 0), (1100, 1, 2100, 193, 1),
+    (1024, 8, 136, 897, 0), (1100, 1, 1100, 77, 1), (1100, 4, 275, 128, 0), (1100, 4, 525, 70, 0), (1100, 1, 2100, 193, 1),
 ])
 def test_projection_paths(rows, batch, T, K, offset):
     print("case", rows, batch, T, K, offset, flush=True)
