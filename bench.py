@@ -137,10 +137,10 @@ def measure_backward(w, steps, warmup, torch, options=None):
         dU_t = torch.empty((max(w.nnz, 1),), dtype=torch.float32, device="cuda")
         # (every output is allocated here, outside the timed region: the binding allocates nothing when given them)
         _, per_call = time_forward(lambda: rnn.backward(e, h_fwd, d, dh0=dh0), steps, warmup, torch)
-        fused_ms = None
-        try:   # the same pass with the weight gradient fused in (not built for every mapping)
-            _, per_fused = time_forward(lambda: rnn.backward_with_weights(e, h_fwd, None, d, dh0=dh0, dU=dU_t), steps, warmup, torch)
-            fused_ms = float(np.median(per_fused))
+        with_ms = None
+        try:   # both gradients from one call: inside the recurrence or, as here, as a product behind it (not for every mapping)
+            _, per_with = time_forward(lambda: rnn.backward_with_weights(e, h_fwd, None, d, dh0=dh0, dU=dU_t), steps, warmup, torch)
+            with_ms = float(np.median(per_with))
         except binding.SprnnError:
             pass
         if rnn.check() != 0:
@@ -154,12 +154,12 @@ def measure_backward(w, steps, warmup, torch, options=None):
     return {"kernel": "persistent_kernel<B=%d,NW=%d,backward>" % (w.batch, info["template_words"]), "ms_per_launch": ms,
             "us_per_timestep": ms * 1e3 / w.steps, "grid": info["grid"], "block": info["block"], "poll_delay": info["poll_delay"],
             "weight_gradient_ms_per_launch": wg_ms, "weight_gradient_us_per_timestep": wg_ms * 1e3 / w.steps,
-            "fused_with_weight_gradient_ms_per_launch": fused_ms,
-            "fused_with_weight_gradient_us_per_timestep": None if fused_ms is None else fused_ms * 1e3 / w.steps}
+            "with_weight_gradient_ms_per_call": with_ms,
+            "with_weight_gradient_us_per_timestep": None if with_ms is None else with_ms * 1e3 / w.steps}
 
 
 def measure_lstm_training(steps, warmup, torch):
-    """One training step of the LSTM layer of cfg5, all three launches: forward keeping the gate values, backward pass
+    """One training step of the LSTM layer of cfg5, all three calls: forward keeping the gate values, backward pass
     through time on the transposed matrix (sprnn_backward_lstm), weight gradient on the forward handle."""
     from paper_1804_10223_amd import binding, workloads
     w = workloads.make_config("cfg5")
@@ -177,11 +177,11 @@ def measure_lstm_training(steps, warmup, torch):
         _, per_f = time_forward(lambda: fwd.forward_lstm_train(x, None, None, h, c, g), steps, warmup, torch)
         _, per_b = time_forward(lambda: bwd.backward_lstm(e, g, c, d_bprime=d, dh0=dh0, dc0=dc0), steps, warmup, torch)
         _, per_w = time_forward(lambda: fwd.weight_gradient(d, h, None, dU), steps, warmup, torch)
-        fused_ms = None
-        try:   # backward and weight gradient in one kernel (not built for every mapping)
-            _, per_fused = time_forward(lambda: bwd.backward_lstm_with_weights(e, g, c, h, d_bprime=d, dh0=dh0, dc0=dc0, dU=dU_t),
+        with_ms = None
+        try:   # backward and weight gradient in one call (not for every mapping)
+            _, per_with = time_forward(lambda: bwd.backward_lstm_with_weights(e, g, c, h, d_bprime=d, dh0=dh0, dc0=dc0, dU=dU_t),
                                         steps, warmup, torch)
-            fused_ms = float(np.median(per_fused))
+            with_ms = float(np.median(per_with))
         except binding.SprnnError:
             pass
         if fwd.check() != 0 or bwd.check() != 0:
@@ -191,7 +191,7 @@ def measure_lstm_training(steps, warmup, torch):
     return {"workload": "cfg5: sparse LSTM, hidden %d, batch %d, T %d, density %.0f%%" % (H, B, T, 100 * w.meta["density"]),
             "forward_keeping_gates_us_per_timestep": f_ms * 1e3 / T, "backward_us_per_timestep": b_ms * 1e3 / T,
             "weight_gradient_us_per_timestep": w_ms * 1e3 / T,
-            "backward_fused_with_weight_gradient_us_per_timestep": None if fused_ms is None else fused_ms * 1e3 / T,
+            "backward_with_weight_gradient_us_per_timestep": None if with_ms is None else with_ms * 1e3 / T,
             "backward_grid": bi["grid"], "backward_block": bi["block"],
             "backward_exchange_bytes_per_timestep": 4 * H * B * 4}
 
@@ -355,13 +355,13 @@ def main():
     bwd = measure_backward(w, args.steps, args.warmup, torch, options=options)
     if bwd:
         log("  backward pass through time: %.3f us/timestep (%.3f ms per launch); weight gradient alone %.3f us/timestep (%.3f ms per launch); "
-            "both fused: %s us/timestep" % (bwd["us_per_timestep"], bwd["ms_per_launch"], bwd["weight_gradient_us_per_timestep"],
-                                           bwd["weight_gradient_ms_per_launch"], bwd["fused_with_weight_gradient_us_per_timestep"]))
+            "both in one call: %s us/timestep" % (bwd["us_per_timestep"], bwd["ms_per_launch"], bwd["weight_gradient_us_per_timestep"],
+                                           bwd["weight_gradient_ms_per_launch"], bwd["with_weight_gradient_us_per_timestep"]))
 
     lstm = measure_lstm_training(max(5, args.steps // 2), 2, torch)
-    log("  LSTM training step at cfg5: forward keeping gates %.3f, backward %.3f, weight gradient %.3f, both fused %s us/timestep" % (
+    log("  LSTM training step at cfg5: forward keeping gates %.3f, backward %.3f, weight gradient %.3f, the last two in one call %s us/timestep" % (
         lstm["forward_keeping_gates_us_per_timestep"], lstm["backward_us_per_timestep"], lstm["weight_gradient_us_per_timestep"],
-        lstm["backward_fused_with_weight_gradient_us_per_timestep"]))
+        lstm["backward_with_weight_gradient_us_per_timestep"]))
 
     table = []
     if args.all_configs:

@@ -76,7 +76,7 @@ struct StepArgs {
 };
 
 const void* persistent_kernel_for(int batch, int template_words, int cell, bool timeline);   // cell: SPRNN_ACT_* / SPRNN_CELL_*
-// (the instantiations live in four translation units; persistent_kernel_for forwards to these three)
+// (the instantiations live in translation units of their own; persistent_kernel_for forwards to some of these)
 const void* persistent_timeline_kernel_for(int batch, int template_words, bool lstm);        // forward pass with the phase timeline
 const void* persistent_overlap_kernel_for(int batch, int template_words, bool timeline);     // vanilla forward with the copy of h consumed in two parts (batch <= 4; timeline: batch 4)
 const void* persistent_short_kernel_for(int batch, int template_words, int cell);              // a layer whose h takes at most three copy rounds: forward passes, kCellBackward, SPRNN_CELL_*_BACKWARD

@@ -22,7 +22,8 @@
 //
 // Measured (one call, before: every workgroup brought all of h into LDS in every timestep): 2304 x 2304 at 30 %, 1024
 // vectors 288 -> 73 us; 4096 x 1024 at 20 %, 1024 vectors 177 -> 52; 1792 at 10 % 247 -> 50; 701 at 15 %, 154 vectors
-// 76 -> 13.  Matrix instructions are busy 43 % of the cycles and vector instructions (half of them the split) 33 %: a
+// 76 -> 13.  Matrix instructions are busy 45 % of the launch (2304 x 2304), with 135 other vector instructions (most of them
+// the split) to 36 of theirs per wavefront and slab: a
 // workgroup's wavefronts meet at a barrier per slab, and around it neither runs.
 #include <algorithm>
 

@@ -288,8 +288,8 @@ def cells(torch, wl, reps):
 
 def training(torch, wl, reps):
     from . import binding
-    print("## Training step: hidden 1024, density 20 %, T 256 (microseconds per timestep of each launch)\n")
-    print("| cell | batch | forward | backward through time | weight gradient | backward with weight gradient fused in | backward grid x block |")
+    print("## Training step: hidden 1024, density 20 %, T 256 (microseconds per timestep of each call)\n")
+    print("| cell | batch | forward | backward through time | weight gradient | backward with weight gradient in one call | backward grid x block |")
     print("|---|---|---|---|---|---|---|")
     dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
     for B in (4, 8):
@@ -299,7 +299,7 @@ def training(torch, wl, reps):
             x = dev(w.x)
             e = torch.randn((T, B, H), device="cuda")
             t_csr = binding.transpose_csr(w.rows, H, w.row_ptr, w.col_idx, w.val_bits)
-            fused = None
+            both = None
             with binding.SparseRNN(H, B, cell, w.row_ptr, w.col_idx, w.val_bits) as fwd, \
                     binding.SparseRNN(H, B, {"lstm": "lstm_backward", "gru": "gru_backward"}.get(cell, cell), *t_csr) as bwd:
                 if cell == "lstm":
@@ -308,7 +308,7 @@ def training(torch, wl, reps):
                     b_us = _time_us_per_step(torch, lambda: bwd.backward_lstm(e, g, c), T, reps)
                     d = bwd.backward_lstm(e, g, c)[0]
                     try:
-                        fused = _time_us_per_step(torch, lambda: bwd.backward_lstm_with_weights(e, g, c, h), T, reps)
+                        both = _time_us_per_step(torch, lambda: bwd.backward_lstm_with_weights(e, g, c, h), T, reps)
                     except binding.SprnnError:
                         pass
                 elif cell == "gru":
@@ -318,7 +318,7 @@ def training(torch, wl, reps):
                     b_us = _time_us_per_step(torch, lambda: bwd.backward_gru(e, g, h), T, reps)
                     d = bwd.backward_gru(e, g, h)[1]          # the recurrent sums' gradient feeds the weight gradient
                     try:
-                        fused = _time_us_per_step(torch, lambda: bwd.backward_gru_with_weights(e, g, h), T, reps)
+                        both = _time_us_per_step(torch, lambda: bwd.backward_gru_with_weights(e, g, h), T, reps)
                     except binding.SprnnError:
                         pass
                 else:
@@ -327,7 +327,7 @@ def training(torch, wl, reps):
                     b_us = _time_us_per_step(torch, lambda: bwd.backward(e, h), T, reps)
                     d = bwd.backward(e, h)[0]
                     try:
-                        fused = _time_us_per_step(torch, lambda: bwd.backward_with_weights(e, h), T, reps)
+                        both = _time_us_per_step(torch, lambda: bwd.backward_with_weights(e, h), T, reps)
                     except binding.SprnnError:
                         pass
                 w_us = _time_us_per_step(torch, lambda: fwd.weight_gradient(d, h), T, reps)
@@ -335,7 +335,7 @@ def training(torch, wl, reps):
                     raise RuntimeError("spin watchdog tripped")
                 bi = bwd.info()
             print("| %s | %d | %.2f | %.2f | %.2f | %s | %d x %d |" % (
-                cell, B, f_us, b_us, w_us, "-" if fused is None else "%.2f" % fused, bi["grid"], bi["block"]), flush=True)
+                cell, B, f_us, b_us, w_us, "-" if both is None else "%.2f" % both, bi["grid"], bi["block"]), flush=True)
     print()
 
 
