@@ -5,8 +5,10 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "sprnn.h"
@@ -761,6 +763,19 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
   return rc;   // allocation or timing trouble is not fatal: the fallback value is used
 }
 
+// The product behind the recurrence reads h_fwd and h0 once the recurrence has written its outputs, the sums inside it read
+// them a step ahead: a caller who lets an output take the place of either (delta over h, dL/dh_0 over h_0) gets the latter.
+static bool overwrites_states(const sprnn_handle_s* h, int T, const float* h_fwd, const float* h0, std::initializer_list<std::pair<const float*, size_t>> outputs) {
+  const size_t state = (size_t)h->map.batch * h->map.hidden;
+  auto overlap = [](const float* a, size_t na, const float* b, size_t nb) {
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a && b && a0 < b0 + nb * 4 && b0 < a0 + na * 4;
+  };
+  for (const auto& o : outputs)
+    if (overlap(o.first, o.second, h_fwd, T * state) || overlap(o.first, o.second, h0, state)) return true;
+  return false;
+}
+
 // dL/dU on the handle of the transposed matrix, in its CSR order: rows pair with h_{t-1}, columns with the gradient of
 // the recurrent sums (`delta`, [T][B][cols]).
 static int transposed_weight_gradient(sprnn_handle_t h, int T, const float* delta, const float* h_fwd, const float* h0, float* dU, void* stream) {
@@ -856,7 +871,9 @@ int sprnn_backward_lstm_with_weights(sprnn_handle_t h_transposed, int T, const f
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  if (h->d_wgrad_starts && product_is_faster(h, T)) {
+  const size_t state = (size_t)h->map.batch * h->map.hidden;
+  if (h->d_wgrad_starts && product_is_faster(h, T) &&
+      !overwrites_states(h, T, h_fwd, h0, {{d_bprime, 4 * T * state}, {dh0, state}, {dc0, state}})) {
     const int rc = sprnn_backward_lstm(h, T, dh_ext, gates, c_fwd, c0, d_bprime, dh0, dc0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
@@ -920,7 +937,9 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  if (d_recurrent && h->d_wgrad_starts && product_is_faster(h, T)) {   // (the product's factor has to be in memory, and a call allocates none)
+  const size_t state = (size_t)h->map.batch * h->map.hidden;
+  if (d_recurrent && h->d_wgrad_starts && product_is_faster(h, T) &&   // (the product's factor has to be in memory, and a call allocates none)
+      !overwrites_states(h, T, h_fwd, h0, {{d_bprime, 3 * T * state}, {d_recurrent, 3 * T * state}, {dh0, state}})) {
     const int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, d_recurrent, dh0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_recurrent, h_fwd, h0, dU_transposed, stream) : rc;
   }
@@ -961,7 +980,8 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
     if (h->map.nnz == 0) return SPRNN_OK;
     return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
-  if (h->d_wgrad_starts && product_is_faster(h, T)) {
+  const size_t state = (size_t)h->map.batch * h->map.hidden;
+  if (h->d_wgrad_starts && product_is_faster(h, T) && !overwrites_states(h, T, h_fwd, h0, {{d_bprime, T * state}, {dh0, state}})) {
     const int rc = sprnn_backward(h, T, dh_ext, h_fwd, d_bprime, dh0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }

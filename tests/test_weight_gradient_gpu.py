@@ -276,3 +276,36 @@ def test_weight_gradient_summed_inside_the_recurrence(cell, H, B, T, dens, opts)
     back = [t * B + b for t in range(T - 1, -1, -1) for b in range(B)]
     same = outs["asked"][-1] == _chain(delta, before, rows, col, back)[source]
     assert same.mean() > 0.999, same.mean()
+
+
+@pytest.mark.parametrize("cell,what", [("tanh", "delta over h"), ("tanh", "dh0 over h0"), ("lstm", "dh0 over h0"), ("gru", "dh0 over h0")])
+def test_backward_with_weights_where_an_output_takes_the_place_of_a_state(cell, what):
+    """The sums read h and h_0 before the recurrence writes there, also in calls long enough for the product behind it."""
+    H, B, T = 257, 4, 90
+    rng = np.random.default_rng(5)
+    R = H * binding.GATES.get(cell, 1)
+    row_ptr, col, val = _wide_csr(R, H, 60, rng)
+    csr_t = binding.transpose_csr(R, H, row_ptr, col, val)
+    normal = lambda *shape: _dev(rng.standard_normal(shape).astype(np.float32))
+    dh, h, h0 = normal(T, B, H), normal(T, B, H).tanh_(), normal(B, H)
+    gates, c, c0 = (normal(T, B, 4 * H).sigmoid_(), normal(T, B, H), normal(B, H)) if cell in binding.GATES else (None, None, None)
+    print("case", cell, what, flush=True)
+    with binding.SparseRNN(H, B, cell + "_backward" if cell in binding.GATES else cell, *csr_t) as bwd:
+        def call(h, h0, **outputs):
+            if cell == "lstm":
+                return bwd.backward_lstm_with_weights(dh, gates, c, h, c0, h0, **outputs)
+            if cell == "gru":
+                return bwd.backward_gru_with_weights(dh, gates, h, h0, **outputs)
+            return bwd.backward_with_weights(dh, h, h0, **outputs)
+        apart = call(h, h0)
+        in_h, in_h0 = h.clone(), h0.clone()
+        placed = call(in_h, in_h0, **({"d_bprime": in_h} if what == "delta over h" else {"dh0": in_h0}))
+        assert bwd.check() == binding.SPRNN_OK
+    for a, b in zip(apart[:-1], placed[:-1]):
+        assert torch.equal(a, b)
+    factor = apart[1 if cell == "gru" else 0].reshape(T * B, R).double().abs()
+    before = torch.cat([h0[None], h[:-1]]).reshape(T * B, H).double().abs()
+    rows = np.repeat(np.arange(R), np.diff(row_ptr))
+    bound = 2 * (T * B + 8) * 2.0 ** -24 * (factor.T @ before).cpu().numpy()[rows, col]   # each of the two within half of it
+    source = binding.transpose_csr(R, H, row_ptr, col, val, with_source=True)[3]
+    assert np.all(np.abs((apart[-1] - placed[-1]).cpu().numpy()) <= bound[source])
