@@ -348,7 +348,7 @@ int sprnn_backward_gru(sprnn_handle_t h_transposed, int T, const float* dh_ext, 
 
 /*
  * sprnn_backward_gru and the gradient of the recurrent weights in one call, as in sprnn_backward_with_weights (with
- * v_{t+1} in delta's place; without d_recurrent, which the product would read, always inside the recurrence).
+ * v_{t+1} in delta's place; d_recurrent may be NULL).
  *   dU_transposed  device, float32 [nnz]: dL/dU in the order of the TRANSPOSED matrix's CSR arrays (entry p belongs to
  *                  the forward nonzero t_source[p] of sprnn_transpose_csr); overwritten.
  * Other arguments as sprnn_backward_gru.  Not available with column compaction or where the

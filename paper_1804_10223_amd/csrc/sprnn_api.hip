@@ -494,7 +494,8 @@ static void prepare_weight_gradient_product(sprnn_handle_s* h) {
   const size_t entries = (size_t)rows * ((cols + h->wgrad_tile.cols - 1) / h->wgrad_tile.cols + 1);
   if (SPRNN_HIP(hipMalloc((void**)&h->d_wgrad_starts, entries * 4)) &&
       SPRNN_HIP(launch_tile_starts(h->d_row_ptr, h->d_col, rows, cols, h->wgrad_tile.cols, h->d_wgrad_starts, nullptr)) &&
-      SPRNN_HIP(prepare_weight_gradient(h->wgrad_tile)) && SPRNN_HIP(hipStreamSynchronize(nullptr))) return;
+      SPRNN_HIP(prepare_weight_gradient(h->wgrad_tile, false)) &&
+      (h->map.cell != SPRNN_CELL_GRU_BACKWARD || SPRNN_HIP(prepare_weight_gradient(h->wgrad_tile, true))) && SPRNN_HIP(hipStreamSynchronize(nullptr))) return;
   (void)hipFree(h->d_wgrad_starts);
   h->d_wgrad_starts = nullptr;
 }
@@ -763,22 +764,23 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
   return rc;   // allocation or timing trouble is not fatal: the fallback value is used
 }
 
-// The product behind the recurrence reads h_fwd and h0 once the recurrence has written its outputs, the sums inside it read
-// them a step ahead: a caller who lets an output take the place of either (delta over h, dL/dh_0 over h_0) gets the latter.
-static bool overwrites_states(const sprnn_handle_s* h, int T, const float* h_fwd, const float* h0, std::initializer_list<std::pair<const float*, size_t>> outputs) {
-  const size_t state = (size_t)h->map.batch * h->map.hidden;
-  auto overlap = [](const float* a, size_t na, const float* b, size_t nb) {
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
-    return a && b && a0 < b0 + nb * 4 && b0 < a0 + na * 4;
-  };
-  for (const auto& o : outputs)
-    if (overlap(o.first, o.second, h_fwd, T * state) || overlap(o.first, o.second, h0, state)) return true;
+// The product behind the recurrence reads its inputs (h_fwd, h0, the GRU's gates) once the recurrence has written its outputs;
+// the sums inside it read them a step ahead.  A caller who lets an output take an input's place (delta over h, dL/dh_0 over
+// h_0) gets the latter.
+struct Span { const float* at; size_t n; };
+static bool any_overlap(std::initializer_list<Span> inputs, std::initializer_list<Span> outputs) {
+  for (const Span& i : inputs)
+    for (const Span& o : outputs) {
+      const uintptr_t i0 = reinterpret_cast<uintptr_t>(i.at), o0 = reinterpret_cast<uintptr_t>(o.at);
+      if (i.at && o.at && i0 < o0 + o.n * 4 && o0 < i0 + i.n * 4) return true;
+    }
   return false;
 }
 
 // dL/dU on the handle of the transposed matrix, in its CSR order: rows pair with h_{t-1}, columns with the gradient of
 // the recurrent sums (`delta`, [T][B][cols]).
-static int transposed_weight_gradient(sprnn_handle_t h, int T, const float* delta, const float* h_fwd, const float* h0, float* dU, void* stream) {
+static int transposed_weight_gradient(sprnn_handle_t h, int T, const float* delta, const float* h_fwd, const float* h0, float* dU, void* stream,
+                                      const float* gru_gates = nullptr) {
   if (h->map.nnz == 0) return SPRNN_OK;
   DeviceGuard guard(h->device);
   if (!guard.ok) return SPRNN_ERR_HIP;
@@ -787,6 +789,7 @@ static int transposed_weight_gradient(sprnn_handle_t h, int T, const float* delt
   a.col = h->d_col; a.starts = h->d_wgrad_starts;
   a.a.x = h_fwd; a.a.first = h0; a.a.ld = m.rows; a.a.shift = m.batch;
   a.b.x = delta; a.b.ld = m.cols;
+  if (gru_gates) { a.gate = gru_gates; a.gate_from = 2 * m.hidden; a.gate_ld = 4 * m.hidden; }   // third block: times r
   a.dU = dU; a.vectors = T * m.batch; a.nnz = (int)m.nnz;
   return SPRNN_HIP(launch_weight_gradient(a, h->wgrad_tile, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
 }
@@ -873,7 +876,7 @@ int sprnn_backward_lstm_with_weights(sprnn_handle_t h_transposed, int T, const f
   }
   const size_t state = (size_t)h->map.batch * h->map.hidden;
   if (h->d_wgrad_starts && product_is_faster(h, T) &&
-      !overwrites_states(h, T, h_fwd, h0, {{d_bprime, 4 * T * state}, {dh0, state}, {dc0, state}})) {
+      !any_overlap({{h_fwd, T * state}, {h0, state}}, {{d_bprime, 4 * T * state}, {dh0, state}, {dc0, state}})) {
     const int rc = sprnn_backward_lstm(h, T, dh_ext, gates, c_fwd, c0, d_bprime, dh0, dc0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
@@ -938,10 +941,15 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
     return SPRNN_OK;
   }
   const size_t state = (size_t)h->map.batch * h->map.hidden;
-  if (d_recurrent && h->d_wgrad_starts && product_is_faster(h, T) &&   // (the product's factor has to be in memory, and a call allocates none)
-      !overwrites_states(h, T, h_fwd, h0, {{d_bprime, 3 * T * state}, {d_recurrent, 3 * T * state}, {dh0, state}})) {
+  if (h->d_wgrad_starts && product_is_faster(h, T) &&
+      !any_overlap({{h_fwd, T * state}, {h0, state}, {d_recurrent ? nullptr : gates, 4 * T * state}},
+                   {{d_bprime, 3 * T * state}, {d_recurrent, 3 * T * state}, {dh0, state}})) {
     const int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, d_recurrent, dh0, stream);
-    return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_recurrent, h_fwd, h0, dU_transposed, stream) : rc;
+    if (rc != SPRNN_OK) return rc;
+    // (without d_recurrent the product makes v of what is in memory: its blocks for r and z are those of d_bprime, the third
+    // is d_bprime's times the reset gate)
+    return d_recurrent ? transposed_weight_gradient(h, T, d_recurrent, h_fwd, h0, dU_transposed, stream)
+                       : transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream, gates);
   }
   LaunchExtras ex;
   ex.backward = true; ex.saved = gates; ex.dh0 = dh0; ex.gates_out = d_recurrent;
@@ -981,7 +989,7 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
     return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
   const size_t state = (size_t)h->map.batch * h->map.hidden;
-  if (h->d_wgrad_starts && product_is_faster(h, T) && !overwrites_states(h, T, h_fwd, h0, {{d_bprime, T * state}, {dh0, state}})) {
+  if (h->d_wgrad_starts && product_is_faster(h, T) && !any_overlap({{h_fwd, T * state}, {h0, state}}, {{d_bprime, T * state}, {dh0, state}})) {
     const int rc = sprnn_backward(h, T, dh_ext, h_fwd, d_bprime, dh0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }

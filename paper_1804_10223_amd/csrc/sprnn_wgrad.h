@@ -24,13 +24,15 @@ struct WGradOperand {
 };
 struct WGradArgs {
   WGradOperand a, b;                 // row side (ld = rows of the matrix), column side (ld = its columns)
+  const float* gate = nullptr;       // where set: columns from gate_from on are b[m][c] * gate[m][c - gate_from] (rounded once),
+  int gate_from = 0, gate_ld = 0;    // ... [vectors][gate_ld] (no shift on the column side then)
   const int32_t* col;                // CSR column indices
   const int32_t* starts;             // from launch_tile_starts
   float* dU;
   int vectors, nnz;
 };
 hipError_t launch_weight_gradient(const WGradArgs& args, WGradTile tile, hipStream_t stream);
-hipError_t prepare_weight_gradient(WGradTile tile);   // once per device before the first launch
+hipError_t prepare_weight_gradient(WGradTile tile, bool gated);   // once per device before the first launch (with gate set)
 
 // The lane sums: same sums, in time order, on the forward mapping.
 struct LaneSumsArgs {

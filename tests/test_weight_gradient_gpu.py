@@ -278,7 +278,8 @@ def test_weight_gradient_summed_inside_the_recurrence(cell, H, B, T, dens, opts)
     assert same.mean() > 0.999, same.mean()
 
 
-@pytest.mark.parametrize("cell,what", [("tanh", "delta over h"), ("tanh", "dh0 over h0"), ("lstm", "dh0 over h0"), ("gru", "dh0 over h0")])
+@pytest.mark.parametrize("cell,what", [("tanh", "delta over h"), ("tanh", "dh0 over h0"), ("lstm", "dh0 over h0"), ("gru", "dh0 over h0"),
+                                       ("gru", "dh0 over a gate")])
 def test_backward_with_weights_where_an_output_takes_the_place_of_a_state(cell, what):
     """The sums read h and h_0 before the recurrence writes there, also in calls long enough for the product behind it."""
     H, B, T = 257, 4, 90
@@ -299,7 +300,11 @@ def test_backward_with_weights_where_an_output_takes_the_place_of_a_state(cell, 
             return bwd.backward_with_weights(dh, h, h0, **outputs)
         apart = call(h, h0)
         in_h, in_h0 = h.clone(), h0.clone()
-        placed = call(in_h, in_h0, **({"d_bprime": in_h} if what == "delta over h" else {"dh0": in_h0}))
+        if what == "dh0 over a gate":           # (gates of the first timestep, read when dh0 is not yet written)
+            d, v, dh0, dU = call(h, h0, dh0=gates[0, :1].view(4, H)[:B], want_recurrent=False)
+            placed = d, apart[1], dh0.clone(), dU
+        else:
+            placed = call(in_h, in_h0, **({"d_bprime": in_h} if what == "delta over h" else {"dh0": in_h0}))
         assert bwd.check() == binding.SPRNN_OK
     for a, b in zip(apart[:-1], placed[:-1]):
         assert torch.equal(a, b)
