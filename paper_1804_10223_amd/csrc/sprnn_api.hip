@@ -235,7 +235,7 @@ static WGradCall weight_gradient_call(const sprnn_handle_s* h, int T) {
   const Mapping& m = h->map;
   WGradCall c;
   c.rows = m.rows; c.cols = m.cols; c.num_cus = h->num_cus; c.tile = h->wgrad_tile;
-  c.batch = m.batch; c.block = m.block; c.h_bytes = m.h_bytes; c.steps = T;
+  c.batch = m.batch; c.steps = T;
   return c;
 }
 

@@ -60,12 +60,11 @@ inline WGradTile choose_weight_gradient_tile(int rows, int cols, int num_cus) {
   return best;
 }
 
-// A layer's call, as far as its weight gradient's time depends on it.
+// A layer's call, as far as the choice of a way depends on it.
 struct WGradCall {
   int rows = 0, cols = 0, num_cus = 0;   // of the handle's matrix, of the device
   WGradTile tile;
-  int batch = 0, block = 0;
-  int64_t h_bytes = 0;                   // one copy of the exchanged vector
+  int batch = 0;
   int64_t steps = 0;
 };
 
@@ -75,9 +74,11 @@ inline double product_us(const WGradCall& c) {
 }
 
 // Microseconds of the lane sums: what a step takes is bringing h to the workgroup in rounds of one 16-byte piece per lane,
-// four of them at a time (one batch 0.85 to 1.4 us with everything else in a step, each further one 0.75).
+// four of them at a time (one batch 0.85 to 1.4 us with everything else in a step, each further one 0.75).  Of 512 lanes,
+// whatever the handle's mapping has (384 to 768): the two ways add in different orders, and handles of one matrix are to
+// give the same bits.
 inline double lane_sums_us(const WGradCall& c) {
-  const int64_t rounds = (c.h_bytes / 16 + c.block - 1) / c.block, batches = std::max<int64_t>((rounds + 3) / 4, 1);
+  const int64_t rounds = ((int64_t)c.cols * c.batch * 4 / 16 + 511) / 512, batches = std::max<int64_t>((rounds + 3) / 4, 1);
   const double first = c.batch == 1 ? 0.85 : (c.batch == 2 ? 1.4 : (c.batch == 4 ? 1.05 : 1.2));
   return 8.0 + (double)c.steps * (first + 0.75 * (double)(batches - 1));
 }

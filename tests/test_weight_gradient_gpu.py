@@ -314,3 +314,32 @@ def test_backward_with_weights_where_an_output_takes_the_place_of_a_state(cell, 
     bound = 2 * (T * B + 8) * 2.0 ** -24 * (factor.T @ before).cpu().numpy()[rows, col]   # each of the two within half of it
     source = binding.transpose_csr(R, H, row_ptr, col, val, with_source=True)[3]
     assert np.all(np.abs((apart[-1] - placed[-1]).cpu().numpy()) <= bound[source])
+
+
+def test_weight_gradient_has_the_same_bits_on_handles_of_different_mapping():
+    H, B, T = 8192, 4, 110                     # where both ways take about the same time
+    row_ptr, col, val = _wide_csr(H, H, 8, np.random.default_rng(3))
+    delta, h = torch.randn((T, B, H), device="cuda"), torch.randn((T, B, H), device="cuda")
+    outs = []
+    for waves in (8, 12):
+        with binding.SparseRNN(H, B, "relu", row_ptr, col, val, poll_delay=-1, compact=2, waves=waves, lanes_per_row=4) as rnn:
+            print("case", waves, rnn.info()["block"], flush=True)
+            outs.append(rnn.weight_gradient(delta, h))
+            assert rnn.check() == binding.SPRNN_OK
+    assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("H,B,T,per_row", [(300, 4, 40, 60), (8192, 1, 12, 16)])   # the product, the sums of the lanes
+def test_weight_gradient_captured_in_a_graph(H, B, T, per_row):
+    row_ptr, col, val = _wide_csr(H, H, per_row, np.random.default_rng(4))
+    delta, h, dU = torch.randn((T, B, H), device="cuda"), torch.randn((T, B, H), device="cuda"), torch.empty(len(col), device="cuda")
+    with binding.SparseRNN(H, B, "relu", row_ptr, col, val, poll_delay=-1, compact=2) as rnn:
+        rnn.weight_gradient(delta, h, None, dU)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            rnn.weight_gradient(delta, h, None, dU)
+        for i in range(4):
+            delta.normal_(), h.normal_(), dU.fill_(float(i))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(dU, rnn.weight_gradient(delta, h))
