@@ -58,13 +58,15 @@ enum {
   SPRNN_SYNC_BARRIER = 2 /* one grid-wide barrier per timestep                                     */
 };
 
+#define SPRNN_XCD_PARTS(n) ((n) << 8)   /* for sprnn_options_t.xcd */
+
 /*
  * Optional tuning knobs for sprnn_create_ex; zero in any field means "choose automatically".
  * They change only where operands live and in which order they are visited, never the result
  * (Section 4.1: re-ordering the nonzeros of a row does not affect the final result).
  */
 typedef struct sprnn_options_s {
-  int grid;          /* number of persistent workgroups (<= co-resident capacity)                  */
+  int grid;          /* number of persistent workgroups (<= co-resident capacity; of one part)     */
   int waves;         /* wavefronts (64 lanes) per workgroup, 1..12                                 */
   int lanes_per_row; /* lanes that share one weight row: batch,...,32,64 (<= 16 for the gated cells) */
   int sync;          /* SPRNN_SYNC_*                                                               */
@@ -104,11 +106,16 @@ typedef struct sprnn_options_s {
   int gather;        /* 0 auto, 1 = one wide LDS read per nonzero fetches all samples of its column (Section 4.1's wide
                         loads), 2 = one 4-byte read per sample (the rung below it in the ablation; batch 4, vanilla
                         cells, layout 1, forward pass only)                                            */
-  int xcd;           /* small layers (at most 32 workgroups; not the gated cells' backward passes): 0 auto = measured at
-                        create time together with the back-off, 1 = workgroups spread over all XCDs, 2 = one XCD:
-                        the launch holds eight times the workgroups, those that the dispatcher put on one XCD take
-                        the work and exchange h through that XCD's L2 alone (if it put too few there, the launch
-                        leaves without results and sprnn_check reports SPRNN_ERR_STATE)                       */
+  int xcd;           /* small layers (at most 32 workgroups a part; not the gated cells' backward passes): 0 auto = measured at
+                        create time together with the back-off, 1 = workgroups spread over all XCDs, 2 = one XCD (a part):
+                        the launch holds eight times the workgroups of a part, those that the dispatcher put on one XCD
+                        take the work (of a part) and exchange h through that XCD's L2 alone; where the dispatcher dealt
+                        them so that there are fewer such XCDs than parts, the exchange of that launch leaves the XCDs.
+                        Plus SPRNN_XCD_PARTS(n), n = 2, 4 or 8: n groups of workgroups ("parts") share out the samples
+                        (batch >= n; layout 1, tagged hand-off, no timeline, narrow gathers or overlap): each holds the
+                        whole matrix on its share of the CUs, advances batch / n samples and exchanges h with nobody
+                        else; grid, waves and lanes_per_row then describe one part.  Without it: measured at create time
+                        when nothing about the mapping is asked for, else all samples in one part               */
   int overlap;       /* copy of h into LDS overlapped with the gathers (vanilla cells, forward pass, batch <= 4, no column
                         compaction, 2..8 copy rounds): 0 auto, 1 off, 2 on = the columns of h are consumed in two
                         parts; a row's nonzeros of the first part sit in its lanes' leading slots and are worked
@@ -129,7 +136,7 @@ typedef struct sprnn_info_s {
   int words_per_lane_max;   /* largest number of packed nonzeros held by one lane                 */
   int template_words;       /* register slots per lane of the kernel instantiation in use         */
   int lds_bytes;            /* LDS bytes per workgroup for h (one copy; two when grid is 1; less
-                               with column compaction)                                               */
+                               with column compaction; of one workgroup of every part together)      */
   int resident_capacity;    /* co-resident workgroups the device can hold for this kernel         */
   int64_t nnz;              /* nonzeros in the CSR input                                           */
   int64_t padded_words;     /* packed words including zero padding                                 */
@@ -144,7 +151,7 @@ typedef struct sprnn_info_s {
                                the copy is overlapped with the gathers (see sprnn_options_t.overlap)     */
   int overlap_words;        /* leading slots per lane that read only that first part: least over the wavefronts */
   int activations;          /* 1 = h is exchanged as binary32, 2 = as binary16 (see sprnn_options_t.activations)   */
-  int reserved[1];
+  int parts;                /* groups of workgroups that share out the samples; grid and padded_words are one part's */
 } sprnn_info_t;
 
 /*
@@ -176,11 +183,12 @@ int sprnn_create(sprnn_handle_t* out, int hidden, int batch, int activation, con
  * layout, poll_delay, xcd, sync, timeline, gather, overlap, compact all 0), up to three more mappings are built and
  * measured the same way, and the fastest is kept (sprnn_get_info reports the one in use): fewer, larger workgroups when
  * the layer needs only a few more than one XCD has compute units, or another number of wavefronts per workgroup when
- * that copies a large h with at least a tenth fewer loads; and twice and half the lanes per row.  Creation then takes
- * 0.05 to 0.25 s depending on the size of the matrix (the packing runs on several host threads).
+ * that copies a large h with at least a tenth fewer loads; and twice and half the lanes per row.  With several samples the
+ * batch shared out to 2, 4 and 8 parts (SPRNN_XCD_PARTS) is measured as well, where the layer fits that share of the CUs.
+ * Creation then takes 0.1 to 0.3 s depending on the size of the matrix (the packing runs on several host threads).
  * Results are bit-for-bit the same from call to call on one handle, and between handles with the same lanes_per_row
- * (which fixes the order in which a row's products are added); a caller who needs that across handles passes the value
- * sprnn_get_info reported for the first. */
+ * (which fixes the order in which a row's products are added, however the samples are shared out); a caller who needs that
+ * across handles passes the value sprnn_get_info reported for the first. */
 int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
                     const int32_t* col_idx, const uint16_t* val_fp16_bits, int device_id,
                     const sprnn_options_t* opt);

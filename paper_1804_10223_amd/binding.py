@@ -57,10 +57,10 @@ class Info(ctypes.Structure):
                 ("nnz", ctypes.c_int64), ("padded_words", ctypes.c_int64), ("ring_bytes", ctypes.c_int64),
                 ("lds_pass_factor", ctypes.c_double), ("compact", ctypes.c_int), ("layout", ctypes.c_int),
                 ("gather_waves", ctypes.c_int), ("one_xcd", ctypes.c_int), ("overlap_rounds", ctypes.c_int),
-                ("overlap_words", ctypes.c_int), ("activations", ctypes.c_int), ("reserved", ctypes.c_int * 1)]
+                ("overlap_words", ctypes.c_int), ("activations", ctypes.c_int), ("parts", ctypes.c_int)]
 
     def as_dict(self) -> dict:
-        return {k: getattr(self, k) for k, _ in self._fields_ if k != "reserved"}
+        return {k: getattr(self, k) for k, _ in self._fields_}
 
 
 class SprnnError(RuntimeError):
@@ -190,9 +190,12 @@ def make_options(**kw) -> Options:
             v = ACTIVATIONS[v]
         if k == "launch" and isinstance(v, str):
             v = LAUNCH[v]
+        if k == "parts":
+            continue
         if not hasattr(o, k):
             raise TypeError("unknown option %r" % k)
         setattr(o, k, int(v))
+    o.xcd += int(kw.get("parts", 0)) << 8
     return o
 
 

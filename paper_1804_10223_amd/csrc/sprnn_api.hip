@@ -20,6 +20,8 @@ using namespace sprnn;
 
 struct sprnn_handle_s {
   Mapping map;
+  sprnn_handle_s* whole = nullptr;   // several parts: the same matrix with all samples in one part, for the calls that need that
+                                     // (weight gradients, the comparison path)
   int device = 0;
   int num_cus = 0;
   int capacity = 0;
@@ -92,13 +94,14 @@ struct DeviceGuard {
 
 void fill_info(const Mapping& m, int capacity, double pass_factor, sprnn_info_t* info) {
   std::memset(info, 0, sizeof(*info));
-  info->hidden = m.hidden; info->rows = m.rows; info->batch = m.batch; info->cell = m.cell;
+  info->hidden = m.hidden; info->rows = m.rows; info->batch = m.samples(); info->cell = m.cell;
   info->grid = m.grid; info->block = m.block; info->waves = m.waves; info->lanes_per_row = m.lanes_per_row;
   info->sync = m.sync; info->bank_aware = m.bank_aware; info->balance = m.balance; info->poll_delay = m.poll_delay;
-  info->words_per_lane_max = m.words_max; info->template_words = m.template_words; info->lds_bytes = m.lds_bytes;
+  info->words_per_lane_max = m.words_max; info->template_words = m.template_words; info->lds_bytes = m.lds_bytes * m.parts;
   info->resident_capacity = capacity;
   info->nnz = m.nnz; info->padded_words = m.padded_words;
-  info->ring_bytes = (int64_t)kRingSlots * m.h_bytes;
+  info->ring_bytes = (int64_t)kRingSlots * m.h_bytes * m.parts;
+  info->parts = m.parts;
   info->lds_pass_factor = pass_factor;
   info->compact = m.compact;
   info->layout = m.layout ? 2 : 1;
@@ -120,6 +123,7 @@ hipError_t upload(T** dst, const T* src, size_t n) {
 
 void release(sprnn_handle_s* h) {
   if (!h) return;
+  release(h->whole);
   (void)hipFree(h->d_words); (void)hipFree(h->d_lane_row); (void)hipFree(h->d_wave_words); (void)hipFree(h->d_wave_early);
   (void)hipFree(h->d_fill_src); (void)hipFree(h->d_wg_plane); (void)hipFree(h->d_word_src); (void)hipFree(h->d_lane_sum);
   (void)hipFree(h->d_wgrad_starts);
@@ -146,6 +150,8 @@ unsigned char* scratch_on_device(int device) {
 }
 
 }  // namespace
+
+static int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
 
 // What a launch of the persistent kernel takes beyond the forward pass's five buffers.
 struct LaunchExtras {
@@ -224,18 +230,22 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
 // of 32 vectors takes a workgroup.  Whole calls measured, inside / behind: 2304 at 30 %, batch 4, T 256 620 / 541 us;
 // 1152 at 10 %, batch 4, T 64 146 / 110; LSTM 1024 at 20 %, batch 8, T 128 810 / 767 (step with its forward pass); but
 // 4096 at 8 %, batch 4, T 64 173 / 208, 5000 at 2 %, batch 1, T 128 267 / 311, LSTM 2000 at 5 %, batch 1, T 64 241 / 260.
-static bool product_is_faster(const sprnn_handle_s* h, int T) {
+// The sums inside need all samples in one part; where the handle has several, the recurrence ahead of the product is faster
+// than that by what creation measured.
+static bool product_is_faster(const sprnn_handle_s* handle, int T) {
+  const sprnn_handle_s* const h = handle->whole ? handle->whole : handle;
   const Mapping& m = h->map;
-  const double vectors = (double)T * m.batch;
+  const double vectors = (double)T * m.samples();
+  const double saved = handle->whole ? std::max(0.0, (double)h->calibrated_us - handle->calibrated_us) : 0.0;
   const double behind = 5.0 + std::max(vectors * m.rows * m.cols * 13.4e-9, vectors / 32.0 * 0.35);
-  return behind < (T + 1) * (0.1 + 0.006 * m.words_max * m.batch);
+  return behind < (T + 1) * (0.1 + 0.006 * m.words_max * m.batch + saved);
 }
 
 static WGradCall weight_gradient_call(const sprnn_handle_s* h, int T) {
   const Mapping& m = h->map;
   WGradCall c;
   c.rows = m.rows; c.cols = m.cols; c.num_cus = h->num_cus; c.tile = h->wgrad_tile;
-  c.batch = m.batch; c.steps = T;
+  c.batch = m.samples(); c.steps = T;
   return c;
 }
 
@@ -298,11 +308,11 @@ struct Alternative {
 static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
                       const int32_t* col_idx, const uint16_t* val_fp16_bits, int device_id,
                       const sprnn_options_t* opt, const hipDeviceProp_t& prop, bool free_choice, bool long_runs,
-                      const sprnn_handle_s* incumbent, Alternative* alternative) {
+                      const sprnn_handle_s* incumbent, Alternative* alternative, OrderCache* cache) {
   Packed P;
   int rc;
   try {
-    rc = pack(hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, opt, prop.multiProcessorCount, &P);
+    rc = pack(hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, opt, prop.multiProcessorCount, &P, cache);
   } catch (const std::bad_alloc&) {
     return SPRNN_ERR_CAPACITY;
   }
@@ -365,14 +375,14 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
     // it spins on its neighbours like the forward kernel: usable only if the same grid is co-resident with it
     int per_cu_bwd = 0;
     if (h->kernel_bwd && (!SPRNN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_bwd, h->kernel_bwd, m.block, h->launch_lds)) ||
-                          m.grid > per_cu_bwd * prop.multiProcessorCount)) h->kernel_bwd = nullptr;
+                          m.grid * m.parts > per_cu_bwd * prop.multiProcessorCount)) h->kernel_bwd = nullptr;
   }
   int per_cu = 0;
   if (!SPRNN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, h->kernel, m.block, h->launch_lds))) { release(h); return SPRNN_ERR_HIP; }
   h->capacity = per_cu * h->num_cus;
-  if (m.grid > h->capacity) { release(h); return SPRNN_ERR_CAPACITY; }   // a spinning grid that is not co-resident would deadlock
-  // One-XCD mode: small layers whose workgroups fit the CUs of one XCD (8 x grid workgroups must be co-resident)
-  const int xcd_opt = opt ? opt->xcd : 0;
+  if (m.grid * m.parts > h->capacity) { release(h); return SPRNN_ERR_CAPACITY; }   // a spinning grid that is not co-resident would deadlock
+  // One-XCD mode: small layers whose workgroups (of one part) fit the CUs of one XCD (8 x grid workgroups must be co-resident)
+  const int xcd_opt = opt ? (parts_asked(opt) > 1 ? opt->xcd & 255 : opt->xcd) : 0;
   if (xcd_opt < 0 || xcd_opt > 2) { release(h); return SPRNN_ERR_INVALID; }
   const bool xcd_eligible = !pool && m.grid >= 2 && m.grid * 8 <= h->capacity && m.grid <= prop.multiProcessorCount / 8 &&
                             m.cell != SPRNN_CELL_LSTM_BACKWARD && m.cell != SPRNN_CELL_GRU_BACKWARD && !m.timeline;
@@ -380,13 +390,14 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   h->one_xcd = xcd_opt == 2;
   const bool try_one_xcd = xcd_opt == 0 && xcd_eligible && calibrate;
 
-  const size_t ring_words = (size_t)kRingSlots * m.h_bytes / 4;
+  const int ring_slots = kRingSlots * m.parts;
+  const size_t ring_words = (size_t)ring_slots * m.h_bytes / 4;
   // (binary16 activations: two elements per 32-bit word, each carrying the mark)
   std::vector<uint32_t> ring(ring_words, m.half ? (kSentinel >> 16 | kSentinel) : kSentinel);
   {
     // bytes of a slot beyond the last element of h are never written by a producer: mark them as present
     const size_t used = (size_t)m.cols * m.batch / (m.half ? 2 : 1);     // 32-bit words (both planes for batch 8)
-    for (int s = 0; s < kRingSlots; ++s)
+    for (int s = 0; s < ring_slots; ++s)
       for (size_t i = used; i < (size_t)m.h_bytes / 4; ++i) ring[(size_t)s * m.h_bytes / 4 + i] = 0u;
   }
   std::vector<uint32_t> ctrl(kCtrlWords, 0u);
@@ -400,10 +411,12 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
             (!m.seg_rounds || SPRNN_HIP(upload(&h->d_wave_early, P.wave_early.data(), P.wave_early.size()))) &&
             SPRNN_HIP(upload(&h->d_ring, ring.data(), ring.size())) &&
             SPRNN_HIP(upload(&h->d_ctrl, ctrl.data(), ctrl.size())) &&
-            SPRNN_HIP(upload(&h->d_row_ptr, row_ptr, (size_t)rows + 1)) &&
-            SPRNN_HIP(upload(&h->d_col, col_idx, (size_t)m.nnz)) &&
-            SPRNN_HIP(upload(&h->d_val, val_fp16_bits, (size_t)m.nnz));
-  if (ok && (m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD) && !m.compact) {
+            (m.parts > 1 || (SPRNN_HIP(upload(&h->d_row_ptr, row_ptr, (size_t)rows + 1)) &&
+                             SPRNN_HIP(upload(&h->d_col, col_idx, (size_t)m.nnz)) &&
+                             SPRNN_HIP(upload(&h->d_val, val_fp16_bits, (size_t)m.nnz))));
+  // (what serves the weight gradient needs all samples in one part: handles of several parts have another one for that)
+  const bool sums = m.parts == 1;
+  if (ok && sums && (m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD) && !m.compact) {
     // backward pass of a gated cell with the weight gradient fused in: needs the word -> CSR position map, co-residency
     // of the same grid with that kernel, and a kernel built for this many threads
     const void* k = persistent_kernel_for(m.batch, m.template_words,
@@ -418,7 +431,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
       if (ok) h->kernel_bwd_grad = k;
     }
   }
-  if (ok && (m.cell <= SPRNN_ACT_IDENTITY || m.cell == SPRNN_CELL_LSTM || m.cell == SPRNN_CELL_GRU) && !m.compact && !m.half) {
+  if (ok && sums && (m.cell <= SPRNN_ACT_IDENTITY || m.cell == SPRNN_CELL_LSTM || m.cell == SPRNN_CELL_GRU) && !m.compact && !m.half) {
     h->has_wgrad = true;
     // (built for the word counts of the one-group-per-row layout, with many words per lane for fewer threads than a lane-pool
     // workgroup may have)
@@ -482,14 +495,18 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   return SPRNN_OK;
 }
 
+// Does the ring of this mapping fit behind the control words of the device's static array (sprnn_forward_noalloc)?
+static bool fits_scratch(const Mapping& m) { return (size_t)kRingSlots * m.h_bytes * m.parts + kScratchCtrlBytes <= kScratchBytes; }
+
 // The table of the product, made once for the handle that is kept, where some length of call takes the product (a wide layer's
 // table is larger than its packed weights).  Without it, for want of memory too, the calls go the other way.
-static void prepare_weight_gradient_product(sprnn_handle_s* h) {
+// `caller` is the handle the user holds: `h` itself, or the one of several parts in front of it.
+static void prepare_weight_gradient_product(sprnn_handle_s* h, const sprnn_handle_s* caller) {
   const int rows = h->map.rows, cols = h->map.cols;
   h->wgrad_tile = choose_weight_gradient_tile(rows, cols, h->num_cus);
   bool used = false;
   for (const int T : {1, 1 << 24})   // (both ways' times are linear in the length)
-    used |= (h->has_wgrad && !(h->kernel_lane_sums && lane_sums_are_faster(weight_gradient_call(h, T)))) || (h->kernel_bwd_grad && product_is_faster(h, T));
+    used |= (h->has_wgrad && !(h->kernel_lane_sums && lane_sums_are_faster(weight_gradient_call(h, T)))) || (h->kernel_bwd_grad && product_is_faster(caller, T));
   if (!used || h->map.nnz == 0) return;
   const size_t entries = (size_t)rows * ((cols + h->wgrad_tile.cols - 1) / h->wgrad_tile.cols + 1);
   if (SPRNN_HIP(hipMalloc((void**)&h->d_wgrad_starts, entries * 4)) &&
@@ -521,55 +538,114 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
   const bool free_choice = !opt || (opt->grid == 0 && opt->waves == 0 && opt->fill_waves == 0 && opt->lanes_per_row == 0 &&
                                     opt->layout == 0 && opt->poll_delay == 0 && opt->xcd == 0 && opt->sync == 0 &&
                                     opt->timeline == 0 && opt->gather == 0 && opt->overlap == 0 && opt->compact == 0);
-  sprnn_handle_t first = nullptr;
-  Alternative alt;
-  const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, opt, prop,
-                            free_choice, free_choice, nullptr, &alt);
-  if (rc != SPRNN_OK) return rc;
   sprnn_options_t base = opt ? *opt : sprnn_options_t();
   if (!opt) std::memset(&base, 0, sizeof(base));
-  // builds the mapping `other` asks for, measures it like the first, and keeps the faster of the two in `first`
-  auto contend = [&](const sprnn_options_t& other) {
+  OrderCache orders;
+  sprnn_handle_t first = nullptr;
+  if (parts_asked(opt) > 1) {   // asked for: the handle of several parts, and behind it one with all samples for the other calls
+    const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &base, prop,
+                              false, true, nullptr, nullptr, &orders);
+    if (rc != SPRNN_OK) return rc;
+    sprnn_options_t one = with_parts(base, 1);
+    one.grid = one.waves = one.fill_waves = one.xcd = 0;
+    one.lanes_per_row = first->map.lanes_per_row;   // (the same sums, bit for bit)
+    const int rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
+                               false, true, nullptr, nullptr, &orders);
+    if (rc2 != SPRNN_OK) { release(first); return rc2; }
+    prepare_weight_gradient_product(first->whole, first);
+    *out = first;
+    return SPRNN_OK;
+  }
+  Alternative alt;
+  const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, opt, prop,
+                            free_choice, free_choice, nullptr, &alt, &orders);
+  if (rc != SPRNN_OK) return rc;
+  int compacts[7] = {-1, -1, -1, -1, -1, -1, -1};   // with 2^i lanes per row and all samples in one part: column compaction (-1: not seen)
+  compacts[ilog2(first->map.lanes_per_row)] = first->map.compact;
+  // Builds the mapping `other` asks for, measures it like the one in `best`, and keeps the faster of the two there; with
+  // nothing in `best` it is compared with `reference` and kept if it is faster than that.
+  auto contend = [&](const sprnn_options_t& other, sprnn_handle_t* best, const sprnn_handle_s* reference, Alternative* alternative) {
+    const sprnn_handle_s* const incumbent = *best ? *best : reference;
     sprnn_handle_t second = nullptr;
     const int rc2 = create_one(&second, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &other, prop,
-                               false, true, first, nullptr);
+                               alternative != nullptr, true, incumbent, alternative, &orders);
     // like with like: by the plain pass alone unless both were measured with the weight gradient as well
-    const bool both = rc2 == SPRNN_OK && first->calibrated_grad_us > 0.0f && second->calibrated_grad_us > 0.0f;
-    const float incumbent_us = first->calibrated_us + (both ? first->calibrated_grad_us : 0.0f);
+    const bool both = rc2 == SPRNN_OK && incumbent->calibrated_grad_us > 0.0f && second->calibrated_grad_us > 0.0f;
+    const float incumbent_us = incumbent->calibrated_us + (both ? incumbent->calibrated_grad_us : 0.0f);
     const float contender_us = rc2 != SPRNN_OK || second->calibrated_us <= 0.0f ? 0.0f : second->calibrated_us + (both ? second->calibrated_grad_us : 0.0f);
     static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
     if (verbose)
-      std::fprintf(stderr, "sprnn_create: contender (lanes %d, grid %d, fill %d) -> %s, %d x %d, %.3f us per step against %.3f%s\n",
-                   other.lanes_per_row, other.grid, other.fill_waves, sprnn_status_string(rc2), rc2 == SPRNN_OK ? second->map.grid : 0,
-                   rc2 == SPRNN_OK ? second->map.block : 0, contender_us, incumbent_us, both ? ", with and without weights" : "");
-    if (rc2 != SPRNN_OK) return;
-    if (contender_us > 0.0f && contender_us < 0.98f * incumbent_us) {
-      release(first);
-      first = second;
-    } else {
-      release(second);
+      std::fprintf(stderr, "sprnn_create: %s (parts %d, lanes %d, grid %d, fill %d) -> %s, %d x %d, %d lanes, %.3f us per step against %.3f%s\n",
+                   parts_asked(&other) > 1 ? "shared out" : "contender", parts_asked(&other), other.lanes_per_row, other.grid, other.fill_waves, sprnn_status_string(rc2), rc2 == SPRNN_OK ? second->map.grid : 0,
+                   rc2 == SPRNN_OK ? second->map.block : 0, rc2 == SPRNN_OK ? second->map.lanes_per_row : 0, contender_us, incumbent_us, both ? ", with and without weights" : "");
+    if (rc2 != SPRNN_OK) return false;
+    if (second->map.parts == 1) compacts[ilog2(second->map.lanes_per_row)] = second->map.compact;
+    // (what the incumbent can do must stay possible: the vanilla backward pass, the call on the device's static ring)
+    const bool able = (second->map.parts == 1 || compacts[ilog2(second->map.lanes_per_row)] == 0) && (second->kernel_bwd || !first->kernel_bwd) && (fits_scratch(second->map) || !fits_scratch(first->map));
+    if (able && contender_us > 0.0f && contender_us < 0.98f * incumbent_us) {
+      release(*best);
+      *best = second;
+      return true;
     }
+    release(second);
+    return false;
   };
   const bool compare = free_choice && first->calibrated_us > 0.0f;
   // (1) fewer, larger workgroups on one XCD, or a wavefront count that copies h with fewer loads (see create_one)
-  if (compare && (alt.grid > 0 || alt.fill_waves > 0)) {
-    sprnn_options_t other = base;
-    other.grid = alt.grid;
-    other.fill_waves = alt.fill_waves;
-    contend(other);
-  }
+  auto contend_alternative = [&](const Alternative& a, int parts, sprnn_handle_t* best, const sprnn_handle_s* reference) {
+    if (a.grid == 0 && a.fill_waves == 0) return;
+    sprnn_options_t other = with_parts(base, parts);
+    other.grid = a.grid;
+    other.fill_waves = a.fill_waves;
+    if (parts > 1) other.compact = 2;
+    contend(other, best, reference, nullptr);
+  };
+  if (compare) contend_alternative(alt, 1, &first, nullptr);
   // (2) The lanes a row is spread over: the packer's rule of thumb (at least eight nonzeros per lane) is not the best
   // for every shape; twice and half as many lanes are measured too, each with the mapping the packer picks for it.
-  const int own_lanes = first->map.lanes_per_row;
   const bool gated_rows = first->map.cell == SPRNN_CELL_LSTM || first->map.cell == SPRNN_CELL_GRU;
-  for (int pass = 0; compare && pass < 2; ++pass) {
-    const int lanes = pass == 0 ? own_lanes * 2 : own_lanes / 2;
-    if (lanes < batch || lanes < 1 || lanes > (gated_rows ? 16 : kWave)) continue;
-    sprnn_options_t other = base;
-    other.lanes_per_row = lanes;
-    contend(other);
+  auto contend_lanes = [&](int parts, sprnn_handle_t* best) {
+    const int own_lanes = (*best)->map.lanes_per_row;
+    for (int pass = 0; pass < 2; ++pass) {
+      const int lanes = pass == 0 ? own_lanes * 2 : own_lanes / 2;
+      if (lanes < batch || lanes < 1 || lanes > (gated_rows ? 16 : kWave)) continue;
+      sprnn_options_t other = with_parts(base, parts);
+      other.lanes_per_row = lanes;
+      if (parts > 1) other.compact = 2;
+      contend(other, best, nullptr, nullptr);
+    }
+  };
+  if (compare) contend_lanes(1, &first);
+  // (3) The samples shared out to several groups of workgroups (see persistent_kernel): every one that the batch can be
+  // divided into, each with the packer's mapping and its alternative; then the lanes of the best.  The order of a row's sums
+  // is the one that all samples in one part would have with these lanes, unless that mapping copies only the columns its
+  // rows read (the order follows their places): such lanes are left to it.
+  sprnn_handle_t split = nullptr;
+  for (int parts = 2; compare && parts <= batch; parts *= 2) {
+    sprnn_options_t other = with_parts(base, parts);
+    other.compact = 2;
+    Alternative alt_split;
+    contend(other, &split, first, &alt_split);
+    contend_alternative(alt_split, parts, &split, first);
   }
-  prepare_weight_gradient_product(first);
+  if (split) {
+    contend_lanes(split->map.parts, &split);
+    if (first->map.lanes_per_row != split->map.lanes_per_row) {   // (all the handle's calls add a row's products in one order)
+      sprnn_options_t other = base;
+      other.lanes_per_row = split->map.lanes_per_row;
+      sprnn_handle_t same = nullptr;
+      const int rc2 = create_one(&same, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &other, prop,
+                                 false, true, nullptr, nullptr, &orders);
+      if (rc2 != SPRNN_OK) { release(split); release(first); return rc2; }
+      release(first);
+      first = same;
+    }
+    split->whole = first;
+    prepare_weight_gradient_product(first, split);
+    *out = split;
+    return SPRNN_OK;
+  }
+  prepare_weight_gradient_product(first, first);
   *out = first;
   return SPRNN_OK;
 }
@@ -596,9 +672,9 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
   const Mapping& m = h->map;
   // The kernel addresses x and the outputs with 32-bit byte offsets from the start of the call, so a very
   // long sequence is run as several launches, each continuing from the last state of the one before.
-  const size_t step_bytes = (size_t)m.batch * std::max(std::max(m.rows, m.cols), m.cell > SPRNN_ACT_IDENTITY ? 4 * m.hidden : 0) * 4;
+  const size_t step_bytes = (size_t)m.samples() * std::max(std::max(m.rows, m.cols), m.cell > SPRNN_ACT_IDENTITY ? 4 * m.hidden : 0) * 4;
   const int t_max = (int)std::max<size_t>(1, ((size_t)1 << 30) / step_bytes);
-  const size_t hb = (size_t)m.batch * m.hidden;
+  const size_t hb = (size_t)m.samples() * m.hidden;
   if (ex.backward && T > t_max) return SPRNN_ERR_UNSUPPORTED;   // time runs backwards: one launch only
   uint32_t* ring = h->d_ring;
   uint32_t* ctrl = h->d_ctrl;
@@ -614,7 +690,7 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
     if (ex.shared_exchange) {
       // the array keeps whatever the last call on this device left: every launch starts from a freshly marked ring and
       // cleared control words, as a new handle would (a fill kernel, so that the call can be captured in a graph)
-      if (!SPRNN_HIP(launch_exchange_reset(ring, (size_t)m.h_bytes / 4, (size_t)m.cols * m.batch, kRingSlots, ctrl, kCtrlWords,
+      if (!SPRNN_HIP(launch_exchange_reset(ring, (size_t)m.h_bytes / 4, (size_t)m.cols * m.batch, kRingSlots * m.parts, ctrl, kCtrlWords,
                                            (hipStream_t)stream))) return SPRNN_ERR_HIP;
     }
     KernelArgs a;
@@ -627,12 +703,13 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
     a.launch_epoch = ex.shared_exchange ? 0u : h->launch_epoch;
     a.lds_h_bytes = m.grid == 1 ? m.lds_bytes / 2 : m.lds_bytes;
     a.ring = ring; a.ctrl = ctrl;
-    a.x = x + (size_t)t0 * m.batch * m.rows;
+    a.batch = m.samples(); a.parts = m.parts; a.part_grid = m.grid;
+    a.x = x + (size_t)t0 * m.samples() * m.rows;
     a.h0 = t0 ? h_out + (size_t)(t0 - 1) * hb : h0;
     a.c0 = t0 ? (c_out ? c_out + (size_t)(t0 - 1) * hb : nullptr) : c0;
     a.h_out = h_out + (size_t)t0 * hb;
     a.c_out = c_out ? c_out + (size_t)t0 * hb : nullptr;
-    a.gates_out = ex.gates_out ? ex.gates_out + (size_t)t0 * m.batch * 4 * m.hidden : nullptr;   // [T][B][4H] for both gated cells
+    a.gates_out = ex.gates_out ? ex.gates_out + (size_t)t0 * m.samples() * 4 * m.hidden : nullptr;   // [T][B][4H] for both gated cells
     a.dc0 = ex.dc0;
     a.b_hn = ex.b_hn;
     a.aux = ex.saved; a.dh0 = ex.dh0; a.bwd_h0 = ex.wgrad_h0; a.word_src = h->d_word_src; a.dU = ex.dU;
@@ -646,7 +723,8 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
     void* args[] = {&a};
     const bool lstm_bwd = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;   // the handle's own kernel is the backward pass
     const void* kernel = ex.backward ? (ex.dU ? h->kernel_bwd_grad : (lstm_bwd ? h->kernel : h->kernel_bwd)) : h->kernel;
-    const int launch_grid = m.grid * (h->one_xcd ? 8 : 1);
+    // (several parts take consecutive XCDs each: whole rounds of the dispatcher over the eight of them)
+    const int launch_grid = h->one_xcd ? m.grid * 8 : (m.parts == 1 ? m.grid : (m.grid * m.parts + 7) / 8 * 8);
     hipError_t e;
     if (m.cooperative && m.grid > 1) {
       e = hipLaunchCooperativeKernel(kernel, dim3(launch_grid), dim3(m.block), args, (unsigned)h->launch_lds, (hipStream_t)stream);
@@ -676,7 +754,7 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
   // comparison of the two placements runs long enough for the per-step time to decide, as it does at real lengths)
   const int T = (try_one_xcd || long_runs) ? 160 : 48;
   // (the gated cells' backward passes read [T][B][4H] kept gate values from the zero buffer)
-  const size_t xn = (size_t)T * m.batch * std::max(std::max(m.rows, m.cols), 4 * m.hidden), hn = (size_t)T * m.batch * m.cols;
+  const size_t xn = (size_t)T * m.samples() * std::max(std::max(m.rows, m.cols), 4 * m.hidden), hn = (size_t)T * m.samples() * m.cols;
   float *d_x = nullptr, *d_h = nullptr, *d_c = nullptr, *d_v = nullptr;
   const bool gru_bwd = m.cell == SPRNN_CELL_GRU_BACKWARD;   // (its second output costs stores in every step: measured with it)
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -726,6 +804,8 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
           }
         }
         if (best_ms == 0.0f || ms < best_ms) { best_ms = ms; best = h->map.poll_delay; best_one_xcd = mode == 1; }
+        // (a contender that is a fifth behind after half of a placement's back-offs will not win with another one)
+        if (incumbent && incumbent->calibrated_us > 0.0f && ci * 2 >= ncand && best_ms * 1000.0f > 1.2f * incumbent->calibrated_us * (float)T) break;
       }
     }
     best_ms_kept = best_ms;
@@ -777,20 +857,25 @@ static bool any_overlap(std::initializer_list<Span> inputs, std::initializer_lis
   return false;
 }
 
+// The handle whose mapping has all samples in one part: what the weight gradients are made with.
+static sprnn_handle_s* with_all_samples(sprnn_handle_s* h) { return h->whole ? h->whole : h; }
+static bool has_backward_with_weights(sprnn_handle_s* h) { return with_all_samples(h)->kernel_bwd_grad && with_all_samples(h)->d_word_src; }
+
 // dL/dU on the handle of the transposed matrix, in its CSR order: rows pair with h_{t-1}, columns with the gradient of
 // the recurrent sums (`delta`, [T][B][cols]).
 static int transposed_weight_gradient(sprnn_handle_t h, int T, const float* delta, const float* h_fwd, const float* h0, float* dU, void* stream,
                                       const float* gru_gates = nullptr) {
   if (h->map.nnz == 0) return SPRNN_OK;
+  h = with_all_samples(h);
   DeviceGuard guard(h->device);
   if (!guard.ok) return SPRNN_ERR_HIP;
   const Mapping& m = h->map;
   WGradArgs a;
   a.col = h->d_col; a.starts = h->d_wgrad_starts;
-  a.a.x = h_fwd; a.a.first = h0; a.a.ld = m.rows; a.a.shift = m.batch;
+  a.a.x = h_fwd; a.a.first = h0; a.a.ld = m.rows; a.a.shift = m.samples();
   a.b.x = delta; a.b.ld = m.cols;
   if (gru_gates) { a.gate = gru_gates; a.gate_from = 2 * m.hidden; a.gate_ld = 4 * m.hidden; }   // third block: times r
-  a.dU = dU; a.vectors = T * m.batch; a.nnz = (int)m.nnz;
+  a.dU = dU; a.vectors = T * m.samples(); a.nnz = (int)m.nnz;
   return SPRNN_HIP(launch_weight_gradient(a, h->wgrad_tile, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
 }
 
@@ -808,10 +893,10 @@ int sprnn_forward_noalloc(sprnn_handle_t h, int T, const float* x, const float* 
   if (h->map.half) return SPRNN_ERR_UNSUPPORTED;   // (the per-launch reset marks binary32 elements)
   if (T > 0 && (!x || !h_out)) return SPRNN_ERR_INVALID;
   // the ring of this layer must fit behind the control words of the static array
-  if ((size_t)kRingSlots * (size_t)h->map.h_bytes + kScratchCtrlBytes > kScratchBytes) {
+  if (!fits_scratch(h->map)) {
     static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
     if (verbose) std::fprintf(stderr, "sprnn_forward_noalloc: exchange ring of %zu bytes exceeds the static limit of %zu bytes\n",
-                              (size_t)kRingSlots * (size_t)h->map.h_bytes, kScratchBytes - kScratchCtrlBytes);
+                              (size_t)kRingSlots * h->map.h_bytes * h->map.parts, kScratchBytes - kScratchCtrlBytes);
     return SPRNN_ERR_CAPACITY;
   }
   LaunchExtras ex;
@@ -846,7 +931,7 @@ int sprnn_backward_lstm(sprnn_handle_t h_transposed, int T, const float* dh_ext,
   if (T == 0) {   // nothing flows back: both initial-state gradients are zero
     DeviceGuard guard(h->device);
     if (!guard.ok) return SPRNN_ERR_HIP;
-    const size_t n = (size_t)h->map.batch * h->map.hidden;
+    const size_t n = (size_t)h->map.samples() * h->map.hidden;
     for (float* out : {dh0, dc0})
       if (out && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(out), 0u, n, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
@@ -862,24 +947,25 @@ int sprnn_backward_lstm_with_weights(sprnn_handle_t h_transposed, int T, const f
                                      float* dh0, float* dc0, float* dU_transposed, void* stream) {
   sprnn_handle_t h = h_transposed;
   if (!h || T < 0) return SPRNN_ERR_INVALID;
-  if (h->map.cell != SPRNN_CELL_LSTM_BACKWARD || !h->kernel_bwd_grad || !h->d_word_src) return SPRNN_ERR_UNSUPPORTED;
+  if (h->map.cell != SPRNN_CELL_LSTM_BACKWARD || !has_backward_with_weights(h)) return SPRNN_ERR_UNSUPPORTED;
   if (!dU_transposed && h->map.nnz > 0) return SPRNN_ERR_INVALID;
   if (T > 0 && (!dh_ext || !gates || !c_fwd || !h_fwd || !d_bprime)) return SPRNN_ERR_INVALID;
   if (T == 0) {   // nothing to sum, nothing flows back
     DeviceGuard guard(h->device);
     if (!guard.ok) return SPRNN_ERR_HIP;
-    const size_t n = (size_t)h->map.batch * h->map.hidden;
+    const size_t n = (size_t)h->map.samples() * h->map.hidden;
     for (float* out : {dh0, dc0})
       if (out && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(out), 0u, n, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  const size_t state = (size_t)h->map.batch * h->map.hidden;
-  if (h->d_wgrad_starts && product_is_faster(h, T) &&
+  const size_t state = (size_t)h->map.samples() * h->map.hidden;
+  if (with_all_samples(h)->d_wgrad_starts && product_is_faster(h, T) &&
       !any_overlap({{h_fwd, T * state}, {h0, state}}, {{d_bprime, 4 * T * state}, {dh0, state}, {dc0, state}})) {
     const int rc = sprnn_backward_lstm(h, T, dh_ext, gates, c_fwd, c0, d_bprime, dh0, dc0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
+  h = with_all_samples(h);
   LaunchExtras ex;
   ex.backward = true; ex.saved = gates; ex.dh0 = dh0; ex.dc0 = dc0;
   ex.wgrad_h_fwd = h_fwd; ex.wgrad_h0 = h0; ex.dU = dU_transposed;
@@ -915,7 +1001,7 @@ int sprnn_backward_gru(sprnn_handle_t h_transposed, int T, const float* dh_ext, 
   if (T == 0) {   // nothing flows back
     DeviceGuard guard(h->device);
     if (!guard.ok) return SPRNN_ERR_HIP;
-    if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.batch * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
+    if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.samples() * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
   // (h_{t-1} travels where the LSTM's backward pass has its cell states, the second output where the forward pass
@@ -930,18 +1016,18 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
                                     float* dU_transposed, void* stream) {
   sprnn_handle_t h = h_transposed;
   if (!h || T < 0) return SPRNN_ERR_INVALID;
-  if (h->map.cell != SPRNN_CELL_GRU_BACKWARD || !h->kernel_bwd_grad || !h->d_word_src) return SPRNN_ERR_UNSUPPORTED;
+  if (h->map.cell != SPRNN_CELL_GRU_BACKWARD || !has_backward_with_weights(h)) return SPRNN_ERR_UNSUPPORTED;
   if (!dU_transposed && h->map.nnz > 0) return SPRNN_ERR_INVALID;
   if (T > 0 && (!dh_ext || !gates || !h_fwd || !d_bprime)) return SPRNN_ERR_INVALID;
   if (T == 0) {   // nothing to sum, nothing flows back
     DeviceGuard guard(h->device);
     if (!guard.ok) return SPRNN_ERR_HIP;
-    if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.batch * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
+    if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.samples() * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     if (h->map.nnz > 0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     return SPRNN_OK;
   }
-  const size_t state = (size_t)h->map.batch * h->map.hidden;
-  if (h->d_wgrad_starts && product_is_faster(h, T) &&
+  const size_t state = (size_t)h->map.samples() * h->map.hidden;
+  if (with_all_samples(h)->d_wgrad_starts && product_is_faster(h, T) &&
       !any_overlap({{h_fwd, T * state}, {h0, state}, {d_recurrent ? nullptr : gates, 4 * T * state}},
                    {{d_bprime, 3 * T * state}, {d_recurrent, 3 * T * state}, {dh0, state}})) {
     const int rc = sprnn_backward_gru(h, T, dh_ext, gates, h_fwd, h0, d_bprime, d_recurrent, dh0, stream);
@@ -951,6 +1037,7 @@ int sprnn_backward_gru_with_weights(sprnn_handle_t h_transposed, int T, const fl
     return d_recurrent ? transposed_weight_gradient(h, T, d_recurrent, h_fwd, h0, dU_transposed, stream)
                        : transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream, gates);
   }
+  h = with_all_samples(h);
   LaunchExtras ex;
   ex.backward = true; ex.saved = gates; ex.dh0 = dh0; ex.gates_out = d_recurrent;
   ex.wgrad_h_fwd = h_fwd; ex.wgrad_h0 = h0; ex.dU = dU_transposed;
@@ -967,7 +1054,7 @@ int sprnn_backward(sprnn_handle_t h_transposed, int T, const float* dh_ext, cons
     if (!dh0) return SPRNN_OK;
     DeviceGuard guard(h->device);
     if (!guard.ok) return SPRNN_ERR_HIP;
-    return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.batch * h->map.hidden, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
+    return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.samples() * h->map.hidden, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
   LaunchExtras ex;
   ex.backward = true; ex.saved = h_fwd; ex.dh0 = dh0;
@@ -978,21 +1065,22 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
                                 float* d_bprime, float* dh0, float* dU_transposed, void* stream) {
   sprnn_handle_t h = h_transposed;
   if (!h || T < 0) return SPRNN_ERR_INVALID;
-  if (h->map.cell > SPRNN_ACT_IDENTITY || !h->kernel_bwd_grad || !h->d_word_src) return SPRNN_ERR_UNSUPPORTED;
+  if (h->map.cell > SPRNN_ACT_IDENTITY || !has_backward_with_weights(h)) return SPRNN_ERR_UNSUPPORTED;
   if (!dU_transposed && h->map.nnz > 0) return SPRNN_ERR_INVALID;
   if (T > 0 && (!dh_ext || !h_fwd || !d_bprime)) return SPRNN_ERR_INVALID;
   if (T == 0) {   // nothing to sum, nothing flows back
     DeviceGuard guard(h->device);
     if (!guard.ok) return SPRNN_ERR_HIP;
-    if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.batch * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
+    if (dh0 && !SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dh0), 0u, (size_t)h->map.samples() * h->map.hidden, (hipStream_t)stream))) return SPRNN_ERR_HIP;
     if (h->map.nnz == 0) return SPRNN_OK;
     return SPRNN_HIP(launch_fill(reinterpret_cast<uint32_t*>(dU_transposed), 0u, (size_t)h->map.nnz, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
   }
-  const size_t state = (size_t)h->map.batch * h->map.hidden;
-  if (h->d_wgrad_starts && product_is_faster(h, T) && !any_overlap({{h_fwd, T * state}, {h0, state}}, {{d_bprime, T * state}, {dh0, state}})) {
+  const size_t state = (size_t)h->map.samples() * h->map.hidden;
+  if (with_all_samples(h)->d_wgrad_starts && product_is_faster(h, T) && !any_overlap({{h_fwd, T * state}, {h0, state}}, {{d_bprime, T * state}, {dh0, state}})) {
     const int rc = sprnn_backward(h, T, dh_ext, h_fwd, d_bprime, dh0, stream);
     return rc == SPRNN_OK ? transposed_weight_gradient(h, T, d_bprime, h_fwd, h0, dU_transposed, stream) : rc;
   }
+  h = with_all_samples(h);
   LaunchExtras ex;
   ex.backward = true; ex.saved = h_fwd; ex.dh0 = dh0;   // (vanilla cells: g' and the weight gradient both use h_t)
   ex.wgrad_h_fwd = h_fwd; ex.wgrad_h0 = h0; ex.dU = dU_transposed;
@@ -1002,6 +1090,7 @@ int sprnn_backward_with_weights(sprnn_handle_t h_transposed, int T, const float*
 int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const float* h_fwd, const float* h0, float* dU,
                           void* stream) {
   if (!h || T < 0) return SPRNN_ERR_INVALID;
+  h = with_all_samples(h);
   // (not on a gated cell's backward handle, nor with column compaction or binary16 activations)
   if (!h->has_wgrad) return SPRNN_ERR_UNSUPPORTED;
   if (!dU && h->map.nnz > 0) return SPRNN_ERR_INVALID;
@@ -1024,8 +1113,8 @@ int sprnn_weight_gradient(sprnn_handle_t h, int T, const float* d_bprime, const 
   WGradArgs a;
   a.col = h->d_col; a.starts = h->d_wgrad_starts;
   a.a.x = d_bprime; a.a.ld = m.rows;
-  a.b.x = h_fwd; a.b.first = h0; a.b.ld = m.cols; a.b.shift = m.batch;   // delta_t pairs with h_{t-1}
-  a.dU = dU; a.vectors = T * m.batch; a.nnz = (int)m.nnz;
+  a.b.x = h_fwd; a.b.first = h0; a.b.ld = m.cols; a.b.shift = m.samples();   // delta_t pairs with h_{t-1}
+  a.dU = dU; a.vectors = T * m.samples(); a.nnz = (int)m.nnz;
   return SPRNN_HIP(launch_weight_gradient(a, h->wgrad_tile, (hipStream_t)stream)) ? SPRNN_OK : SPRNN_ERR_HIP;
 }
 
@@ -1055,12 +1144,13 @@ int sprnn_forward_stepwise(sprnn_handle_t h, int T, const float* x, const float*
                            float* h_out, float* c_out, void* stream) {
   if (!h || T < 0) return SPRNN_ERR_INVALID;
   if (h->map.cell == SPRNN_CELL_GRU || h->map.cell >= SPRNN_CELL_LSTM_BACKWARD) return SPRNN_ERR_UNSUPPORTED;
+  if (h->whole) h = h->whole;   // (it has the CSR arrays)
   const Mapping& m = h->map;
   const bool lstm = m.cell == SPRNN_CELL_LSTM;
   if (T > 0 && (!x || !h_out || (lstm && !c_out))) return SPRNN_ERR_INVALID;
   DeviceGuard guard(h->device);
   if (!guard.ok) return SPRNN_ERR_HIP;
-  const size_t hb = (size_t)m.batch * m.hidden, xb = (size_t)m.batch * m.rows;
+  const size_t hb = (size_t)m.samples() * m.hidden, xb = (size_t)m.samples() * m.rows;
   for (int t = 0; t < T; ++t) {
     StepArgs a;
     a.row_ptr = h->d_row_ptr; a.col = h->d_col; a.val = h->d_val;
@@ -1070,7 +1160,7 @@ int sprnn_forward_stepwise(sprnn_handle_t h, int T, const float* x, const float*
     a.h_cur = h_out + (size_t)t * hb;
     a.c_cur = lstm ? c_out + (size_t)t * hb : nullptr;
     a.hidden = m.hidden; a.act = m.cell;
-    if (launch_stepwise(m.batch, lstm, a, (hipStream_t)stream) != hipSuccess) return SPRNN_ERR_HIP;
+    if (launch_stepwise(m.samples(), lstm, a, (hipStream_t)stream) != hipSuccess) return SPRNN_ERR_HIP;
   }
   return SPRNN_OK;
 }
@@ -1079,12 +1169,12 @@ int sprnn_project(sprnn_handle_t h, int T, int input_size, const float* x_in, co
                   const float* bias, float* b_prime, void* stream) {
   if (!h || T < 0 || input_size <= 0) return SPRNN_ERR_INVALID;
   if (T > 0 && (!x_in || !w_in_fp16_bits || !b_prime)) return SPRNN_ERR_INVALID;
-  if ((long long)T * h->map.batch > 0x7fffffffLL) return SPRNN_ERR_INVALID;
+  if ((long long)T * h->map.samples() > 0x7fffffffLL) return SPRNN_ERR_INVALID;
   if (h->map.cell >= SPRNN_CELL_LSTM_BACKWARD) return SPRNN_ERR_UNSUPPORTED;
   if (T == 0) return SPRNN_OK;
   DeviceGuard guard(h->device);
   if (!guard.ok) return SPRNN_ERR_HIP;
-  const hipError_t e = launch_project(x_in, w_in_fp16_bits, bias, b_prime, T * h->map.batch, h->map.rows, input_size,
+  const hipError_t e = launch_project(x_in, w_in_fp16_bits, bias, b_prime, T * h->map.samples(), h->map.rows, input_size,
                                       static_cast<hipStream_t>(stream));
   if (e == hipErrorInvalidValue) return SPRNN_ERR_INVALID;
   return SPRNN_HIP(e) ? SPRNN_OK : SPRNN_ERR_HIP;
@@ -1127,8 +1217,14 @@ int sprnn_check(sprnn_handle_t h) {
     unsigned char* const base = scratch_on_device(h->device);
     if (!base || hipMemcpy(&status, reinterpret_cast<uint32_t*>(base) + kCtrlStatus, 4, hipMemcpyDeviceToHost) != hipSuccess) return SPRNN_ERR_HIP;
   }
-  if (status) h->poisoned = true;
-  return status ? SPRNN_ERR_STATE : SPRNN_OK;
+  int rc = status ? SPRNN_ERR_STATE : SPRNN_OK;
+  if (h->whole) {
+    const int rc2 = sprnn_check(h->whole);
+    if (rc == SPRNN_OK) rc = rc2;
+    if (rc == SPRNN_ERR_STATE) h->whole->poisoned = true;
+  }
+  if (rc == SPRNN_ERR_STATE) h->poisoned = true;
+  return rc;
 }
 
 int sprnn_destroy(sprnn_handle_t h) {

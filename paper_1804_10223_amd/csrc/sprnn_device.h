@@ -32,7 +32,7 @@ struct KernelArgs {
   const int32_t* wg_plane;    // column compaction: [grid] bytes of one plane of the workgroup's LDS copy
   const int32_t* wave_early;  // two-part copy: [grid][waves] leading slots of a wavefront's lanes that read only the first part, or null
   const int32_t* lane_sum;    // lane-pool layout: [grid][block] for an output lane: first group of its row | groups << 16
-  uint32_t* ring;             // [4][h_bytes / 4]
+  uint32_t* ring;             // [parts][4][h_bytes / 4]
   uint32_t* ctrl;             // [kCtrlWords]
   const float* x;             // [T][B][R]
   const float* h0;            // [B][H] or null
@@ -54,7 +54,10 @@ struct KernelArgs {
   int lds_h_bytes;            // bytes of one LDS copy of h (= h_bytes without column compaction)
   int jitter;                 // test aid: seed of pseudo-random pauses (0 = none)
   int tl_wave;                // phase timeline: the wavefront of every workgroup that records it
-  int one_xcd;                // 1: the launch has 8 x the workgroups, those of one XCD take the work (see persistent_kernel)
+  int one_xcd;                // 1: the launch has 8 x part_grid workgroups, those of one XCD per part take the work (see persistent_kernel)
+  int batch;                  // samples of the call: the layout's batch x parts (x, h_out, ... hold this many per timestep)
+  int parts;                  // groups of workgroups that each advance their share of the samples: 1, 2, 4 or 8
+  int part_grid;              // workgroups of a part
   uint32_t launch_epoch;      // launches of this handle so far (parity selects the placement counters)
   int seg_rounds;             // > 0: the copy of h is consumed in two parts, its first seg_rounds rounds first (see persistent_kernel)
   int gather_waves;           // lane-pool layout: wavefronts of a workgroup that hold weights (the others own the outputs)

@@ -82,7 +82,7 @@ static PassModel make_pass_model(int batch) {
   return pm;
 }
 
-static int choose_mapping(int hidden, int batch, int cell, const std::vector<int>& row_nnz, const sprnn_options_t* opt,
+static int choose_mapping(int hidden, int batch, int order_batch, int cell, const std::vector<int>& row_nnz, const sprnn_options_t* opt,
                           int num_cus, Mapping* m) {
   const bool lstm = gated(cell);                 // four row groups per unit
   const int rows = hidden * (lstm ? 4 : 1);      // rows of the layout (row_nnz has this many entries)
@@ -98,8 +98,9 @@ static int choose_mapping(int hidden, int batch, int cell, const std::vector<int
     return ceil_div(hidden, units_per_wave);   // a unit is one row (vanilla) or one hidden unit's 4 gate rows
   };
 
-  // The reduction leaves one sample per lane, so a row needs at least `batch` lanes.
-  const int lmin = batch;
+  // The reduction leaves one sample per lane, so a row needs at least as many lanes as there are samples (in all parts: the
+  // same lanes have to serve them all in one).
+  const int lmin = order_batch;
   int L = opt ? opt->lanes_per_row : 0;
   if (L != 0) {
     if (!is_pow2(L) || L > lmax || L < lmin) return SPRNN_ERR_INVALID;
@@ -247,65 +248,103 @@ static int64_t segs_cycles(const std::vector<Seg>& segs, int trip, const PassMod
   return total;
 }
 
-static void order_segments(std::vector<Seg>& segs, int trip, const PassModel& pm, bool bank_aware) {
+// The geometries that one order has to serve, finest passes first: a batch that may be shared out to several parts is
+// gathered with 16-, 8- or 4-byte columns depending on how many, and the results of a handle must not depend on that,
+// so one order is made for all of them.  (A pass of the wider reads is half a pass of the narrower ones.)
+static std::vector<PassModel> make_pass_models(int batch, int least) {
+  std::vector<PassModel> all;
+  for (int b = std::min(batch, 4); b >= std::max(std::min(least, 4), 1); b /= 2) all.push_back(make_pass_model(b));
+  return all;
+}
+
+static int64_t all_cycles(const std::vector<Seg>& segs, int trip, const std::vector<PassModel>& models) {
+  int64_t total = 0;
+  for (const PassModel& pm : models) total += segs_cycles(segs, trip, pm);
+  return total;
+}
+
+static void order_segments(std::vector<Seg>& segs, int trip, const std::vector<PassModel>& models, bool bank_aware) {
   for (auto& q : segs) {
     q.pos.assign((size_t)trip * q.n, -1);
     for (int i = 0; i < (int)q.items.size(); ++i) q.pos[i] = i;   // CSR order: item i -> lane i % n, slot i / n
   }
   if (!bank_aware || trip == 0) return;
-  const int64_t csr_cycles = segs_cycles(segs, trip, pm);
+  const int64_t csr_cycles = all_cycles(segs, trip, models);
   std::vector<std::vector<int>> csr_pos(segs.size());
   for (size_t q = 0; q < segs.size(); ++q) { csr_pos[q] = segs[q].pos; segs[q].pos.assign((size_t)trip * segs[q].n, -1); }
-  const int classes = pm.classes, np = pm.npass;
-  const int P = trip * np;                         // passes of this wavefront: index k * np + p
-  std::vector<int> pass_cycles(P, 0), pass_load(P, 0), mult((size_t)P * classes, 0);
-  std::vector<int64_t> class_total(classes, 0);
-  std::vector<std::vector<std::vector<int>>> bucket(segs.size(), std::vector<std::vector<int>>(classes));
+  const int nm = (int)models.size(), np = models[0].npass;
+  const int P = trip * np;                         // passes of this wavefront under the finest model: index k * np + p
+  const int fine = models[nm - 1].classes, coarse = models[0].classes;   // (every model's classes divide the last one's)
+  std::vector<int> pass_load(P, 0);
+  std::vector<std::vector<int>> cycles(nm), mult(nm);
+  std::vector<int> shift(nm, 0);                   // finest passes per pass of a model: 1 << shift
+  for (int i = 0; i < nm; ++i) {
+    while ((models[i].npass << shift[i]) < np) ++shift[i];
+    cycles[i].assign(P >> shift[i], 1);             // (every pass takes a cycle, however empty)
+    mult[i].assign((size_t)(P >> shift[i]) * models[i].classes, 0);
+  }
+  std::vector<int64_t> coarse_total(coarse, 0), fine_total(fine, 0);
+  std::vector<std::vector<std::vector<int>>> bucket(segs.size(), std::vector<std::vector<int>>(fine));
   std::vector<std::vector<int>> taken(segs.size());
   std::vector<std::vector<std::vector<int>>> mine(segs.size(), std::vector<std::vector<int>>(np));   // lanes of a segment (as offsets into it) per pass
   for (size_t q = 0; q < segs.size(); ++q) {
     taken[q].assign((size_t)trip * np, 0);
-    for (int j = 0; j < segs[q].n; ++j) mine[q][pm.pass_of[segs[q].lane0 + j]].push_back(j);
+    for (int j = 0; j < segs[q].n; ++j) mine[q][models[0].pass_of[segs[q].lane0 + j]].push_back(j);
     for (int i = (int)segs[q].items.size() - 1; i >= 0; --i) {
-      bucket[q][segs[q].items[i].col % classes].push_back(i);
-      class_total[segs[q].items[i].col % classes] += 1;
+      bucket[q][segs[q].items[i].col % fine].push_back(i);
+      fine_total[segs[q].items[i].col % fine] += 1;
+      coarse_total[segs[q].items[i].col % coarse] += 1;
     }
   }
-  std::vector<int> order(classes);
+  std::vector<int> order(fine);
   std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return class_total[a] > class_total[b]; });
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+    const int ca = a % coarse, cb = b % coarse;
+    if (coarse_total[ca] != coarse_total[cb]) return coarse_total[ca] > coarse_total[cb];
+    if (ca != cb) return ca < cb;
+    return fine_total[a] > fine_total[b];
+  });
+  std::vector<int> cost_of(P);
   for (int g : order)
     for (size_t q = 0; q < segs.size(); ++q) {
       const Seg& sg = segs[q];
+      if (bucket[q][g].empty()) continue;
+      auto price = [&](int at) {                   // cycles that a nonzero of class g would add to this pass, over the models
+        int cost = 0;
+        for (int i = 0; i < nm; ++i) {
+          const int a = at >> shift[i];
+          cost += mult[i][(size_t)a * models[i].classes + g % models[i].classes] + 1 > cycles[i][a] ? 1 : 0;
+        }
+        return cost;
+      };
+      for (int at = 0; at < P; ++at) cost_of[at] = price(at);
       while (!bucket[q][g].empty()) {
-        int best_k = -1, best_p = 0, best_cost = 0, best_load = 0;
-        for (int k = 0; k < trip; ++k)
-          for (int p = 0; p < np; ++p) {
-            if (taken[q][(size_t)k * np + p] >= (int)mine[q][p].size()) continue;
-            const int at = k * np + p;
-            const int cost = (mult[(size_t)at * classes + g] + 1 > pass_cycles[at]) ? 1 : 0;
-            if (best_k < 0 || cost < best_cost || (cost == best_cost && pass_load[at] < best_load)) {
-              best_k = k; best_p = p; best_cost = cost; best_load = pass_load[at];
-            }
-          }
-        const int i = bucket[q][g].back();   // (a segment never holds more than trip * n nonzeros: a free lane exists)
+        int best = -1;
+        for (int at = 0; at < P; ++at) {
+          if (taken[q][at] >= (int)mine[q][at % np].size()) continue;
+          if (best < 0 || cost_of[at] < cost_of[best] || (cost_of[at] == cost_of[best] && pass_load[at] < pass_load[best])) best = at;
+        }
+        const int item = bucket[q][g].back();   // (a segment never holds more than trip * n nonzeros: a free lane exists)
         bucket[q][g].pop_back();
-        const int at = best_k * np + best_p;
-        int& used = taken[q][(size_t)best_k * np + best_p];
-        segs[q].pos[(size_t)best_k * sg.n + mine[q][best_p][used]] = i;
-        used += 1;
-        pass_load[at] += 1;
-        const int mcount = ++mult[(size_t)at * classes + g];
-        pass_cycles[at] = std::max(pass_cycles[at], mcount);
+        segs[q].pos[(size_t)(best / np) * sg.n + mine[q][best % np][taken[q][best]]] = item;
+        taken[q][best] += 1;
+        pass_load[best] += 1;
+        for (int i = 0; i < nm; ++i) {
+          const int a = best >> shift[i];
+          const int count = ++mult[i][(size_t)a * models[i].classes + g % models[i].classes];
+          cycles[i][a] = std::max(cycles[i][a], count);
+        }
+        const int widest = 1 << shift[nm - 1], from = best / widest * widest;   // passes whose price this changed
+        for (int at = from; at < from + widest; ++at) cost_of[at] = price(at);
       }
     }
   // the greedy deal is not optimal when many short rows share a pass: never do worse than CSR order
-  if (segs_cycles(segs, trip, pm) > csr_cycles)
+  if (all_cycles(segs, trip, models) > csr_cycles)
     for (size_t q = 0; q < segs.size(); ++q) segs[q].pos = csr_pos[q];
 }
 
 // Place the nonzeros of all rows of one wavefront of the one-group-per-row layout: every row group is one segment.
-static void order_wave(std::vector<RowGroup>& rg, int L, int trip, const PassModel& pm, bool bank_aware) {
+static void order_wave(std::vector<RowGroup>& rg, int L, int trip, const std::vector<PassModel>& pm, bool bank_aware) {
   std::vector<Seg> segs(rg.size());
   for (size_t q = 0; q < rg.size(); ++q) { segs[q].lane0 = rg[q].lane0; segs[q].n = L; segs[q].row = rg[q].row; segs[q].items = rg[q].items; }
   order_segments(segs, trip, pm, bank_aware);
@@ -329,7 +368,7 @@ static int phase_words(const std::vector<RowGroup>& rg, int L, int trip, int seg
   return k1;
 }
 
-static void order_wave_phased(std::vector<RowGroup>& rg, int L, int trip, int k1, int seg_col, const PassModel& pm, bool bank_aware) {
+static void order_wave_phased(std::vector<RowGroup>& rg, int L, int trip, int k1, int seg_col, const std::vector<PassModel>& pm, bool bank_aware) {
   std::vector<Seg> early(rg.size()), late(rg.size());
   std::vector<std::vector<int>> early_of(rg.size()), late_of(rg.size());   // index into the row's items
   for (size_t q = 0; q < rg.size(); ++q) {
@@ -356,19 +395,21 @@ static void order_wave_phased(std::vector<RowGroup>& rg, int L, int trip, int k1
 
 // Filler words should not add bank conflicts: give each one a column whose bank group is still free in
 // its pass (or, failing that, an address that another lane of the pass already reads: a broadcast).
-static void place_fillers(Packed& P, const std::vector<int>& wg_cols, const std::vector<char>& is_real_zero) {
+static void place_fillers(Packed& P, int wg_begin, int wg_end, const std::vector<int>& wg_cols, const std::vector<char>& is_real_zero) {
   const Mapping& m = P.map;
   const int NW = m.template_words;
   const PassModel pm = make_pass_model(m.layout_batch ? m.layout_batch : m.batch);
   const int classes = pm.classes;
-  for (int wg = 0; wg < m.grid; ++wg)
+  std::vector<char> used;
+  std::vector<int> fillers;
+  for (int wg = wg_begin; wg < wg_end; ++wg)
     for (int wave = 0; wave < m.waves; ++wave) {
       const int trip = P.wave_words[(size_t)wg * m.waves + wave];
       for (int k = 0; k < trip; ++k)
         for (int p = 0; p < pm.npass; ++p) {
-          std::vector<char> used(classes, 0);
+          used.assign(classes, 0);
+          fillers.clear();
           const size_t base = ((size_t)wg * NW + k) * m.block + (size_t)wave * kWave;
-          std::vector<int> fillers;
           uint32_t some_addr = 0; bool have_addr = false;
           for (int l : pm.lanes[p]) {
             const uint32_t w = P.words[base + l];
@@ -520,7 +561,7 @@ static int pack_pool(int hidden, int batch, int cell, const int32_t* row_ptr, co
   P.lane_sum.assign(lanes, 0);
   P.wave_words.assign((size_t)grid * m.waves, 0);
   std::vector<char> is_real_zero(P.words.size(), 0);
-  const PassModel pm = make_pass_model(batch);
+  const std::vector<PassModel> pm = make_pass_models(batch, batch);
   int64_t padded = 0;
   int used_words_max = 0;
   std::vector<std::vector<Seg>> wave_segs(W);
@@ -576,16 +617,33 @@ static int pack_pool(int hidden, int batch, int cell, const int32_t* row_ptr, co
     }
   }
   std::vector<int> wg_cols(grid, cols);
-  place_fillers(P, wg_cols, is_real_zero);
+  place_fillers(P, 0, grid, wg_cols, is_real_zero);
   P.map.words_max = used_words_max;
   P.map.padded_words = padded;
   return SPRNN_OK;
 }
 
+static int pack_part(int hidden, int batch, int order_batch, int cell, const int32_t* row_ptr, const int32_t* col_idx,
+                     const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out, OrderCache* cache);
+
 int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t* col_idx,
-         const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out) {
+         const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out, OrderCache* cache) {
   int rc = validate_csr(hidden, batch, cell, row_ptr, col_idx, val_bits);
   if (rc != SPRNN_OK) return rc;
+  // Several parts: every part is mapped like a layer of its own with its share of the samples and of the CUs.
+  const int parts = parts_asked(opt);
+  if (parts > 1) {
+    if (batch < parts || opt->layout == 2 || opt->sync == SPRNN_SYNC_BARRIER || opt->timeline || opt->gather == 2 || opt->overlap == 2) return SPRNN_ERR_UNSUPPORTED;
+  }
+  rc = pack_part(hidden, batch / parts, batch, cell, row_ptr, col_idx, val_bits, opt, num_cus / parts, out, cache);
+  if (rc == SPRNN_OK) out->map.parts = parts;
+  return rc;
+}
+
+// One part: a layer of its own, but for the order of a row's nonzeros, which is that of the whole batch.
+static int pack_part(int hidden, int batch, int order_batch, int cell, const int32_t* row_ptr, const int32_t* col_idx,
+                     const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out, OrderCache* cache) {
+  int rc = SPRNN_OK;
   const int layout = opt ? opt->layout : 0;
   if (layout < 0 || layout > 2) return SPRNN_ERR_INVALID;
   if (layout == 2 && cell > SPRNN_ACT_IDENTITY) return SPRNN_ERR_UNSUPPORTED;
@@ -606,7 +664,7 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
   std::vector<int> row_nnz(rows);
   for (int r = 0; r < rows; ++r) row_nnz[r] = row_ptr[r + 1] - row_ptr[r];
   Mapping m;
-  rc = choose_mapping(hidden, batch, cell, row_nnz, opt, num_cus, &m);
+  rc = choose_mapping(hidden, batch, order_batch, cell, row_nnz, opt, num_cus, &m);
   if (rc != SPRNN_OK) return rc;
 
   const int L = m.lanes_per_row;
@@ -625,6 +683,7 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
   // --- units -> (workgroup, wave, unit slot)
   const int total_waves = m.grid * m.waves;
   std::vector<int> wave_units((size_t)total_waves * upw, -1);   // unit id per (global wave, slot)
+  std::vector<int> wave_rows(total_waves, -1);                  // which of the wavefronts that own rows this is
   if (m.balance == 1) {
     // deal by nonzero count: similar rows share a wavefront (little padding inside it), and wavefronts are
     // dealt to workgroups in serpentine order of their trip count so every workgroup gets the same load
@@ -636,6 +695,7 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
       const int round = w / m.grid, idx = w % m.grid;
       const int wg = (round & 1) ? (m.grid - 1 - idx) : idx;
       const int gw = wg * m.waves + round;        // round < row_waves because grid * row_waves >= nw
+      wave_rows[gw] = w;
       for (int s = 0; s < upw; ++s) {
         const int i = w * upw + s;
         if (i < units) wave_units[(size_t)gw * upw + s] = order[i];
@@ -646,6 +706,7 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
       const int cw = u / upw;
       const int gw = (cw / m.row_waves) * m.waves + cw % m.row_waves;
       wave_units[(size_t)gw * upw + u % upw] = u;
+      wave_rows[gw] = cw;
     }
   }
 
@@ -749,6 +810,9 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
   if (m.seg_rounds) P.wave_early.assign(total_waves, 0);
 
   const PassModel pm = make_pass_model(lb);
+  // (narrow gathers and the two-part copy are never offered with several parts: one geometry)
+  const int whole_lb = m.half ? order_batch / 2 : order_batch;
+  const std::vector<PassModel> models = make_pass_models(whole_lb, m.narrow || m.seg_rounds ? whole_lb : (m.half ? 2 : 1));
   auto pad_word = [&](int lane_in_wave, int k, int ncols) -> uint32_t {
     // zero-valued filler (place_fillers gives it a bank class that is free in its pass afterwards)
     int col = (lane_in_wave + k * L) % pm.classes;
@@ -757,6 +821,19 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
   };
 
   std::vector<char> is_real_zero(P.words.size(), 0);   // positions holding a stored (explicit) zero weight
+  OrderCache::Entry* known = nullptr;                  // orders made before, or to be kept
+  bool make_known = false;
+  if (cache && !compact && !m.seg_rounds && !m.narrow) {   // (with compaction the order follows the places in LDS)
+    for (auto& e : cache->entries)
+      if (e.lanes == L && e.balance == m.balance && e.order_batch == order_batch && e.activations == m.half) known = &e;
+    if (!known) {
+      cache->entries.emplace_back();
+      known = &cache->entries.back();
+      known->balance = m.balance; known->order_batch = order_batch; known->activations = m.half;
+      known->pos.resize(ceil_div(units, upw));
+      make_known = true;
+    }
+  }
   int words_max = 0;
   int64_t padded = 0;
   std::vector<int> wg_cols(m.grid, cols);     // LDS column positions a workgroup may address
@@ -803,9 +880,13 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
           if (m.seg_rounds) {
             const int k1 = phase_words(rg, L, trip, seg_col);
             P.wave_early[gw] = k1;
-            order_wave_phased(rg, L, trip, k1, seg_col, pm, m.bank_aware == 1);
+            order_wave_phased(rg, L, trip, k1, seg_col, models, m.bank_aware == 1);
+          } else if (known && !make_known && wave_rows[gw] >= 0) {
+            for (size_t q = 0; q < rg.size(); ++q) rg[q].pos = known->pos[wave_rows[gw]][q];
           } else {
-            order_wave(rg, L, trip, pm, m.bank_aware == 1);
+            order_wave(rg, L, trip, models, m.bank_aware == 1);
+            if (make_known && wave_rows[gw] >= 0)
+              for (const RowGroup& q : rg) known->pos[wave_rows[gw]].push_back(q.pos);
           }
           for (const RowGroup& q : rg) {
             const size_t tid0 = (size_t)wg * m.block + (size_t)wave * kWave + q.lane0;
@@ -824,6 +905,7 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
           }
         }
       }
+      place_fillers(P, wg_begin, wg_end, wg_cols, is_real_zero);
       *words_max_out = local_max;
       *padded_out = local_padded;
     } catch (const std::bad_alloc&) {
@@ -849,9 +931,9 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
     pack_workgroups(0, (int)((int64_t)m.grid / nthreads), &part_max[0], &part_padded[0]);
     for (auto& w : workers) w.join();
     if (out_of_memory) throw std::bad_alloc();
+    if (make_known) known->lanes = L;   // (complete from here on; an entry without lanes is never found)
     for (int t = 0; t < nthreads; ++t) { words_max = std::max(words_max, part_max[t]); padded += part_padded[t]; }
   }
-  place_fillers(P, wg_cols, is_real_zero);
   P.map.words_max = words_max;
   P.map.padded_words = padded;
   if (m.seg_rounds) {

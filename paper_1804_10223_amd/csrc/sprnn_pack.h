@@ -27,7 +27,8 @@ constexpr int kNumTemplateWords = 6;
 struct Mapping {
   int hidden = 0, rows = 0, batch = 0, cell = 0;
   int cols = 0;              // columns of the matrix = length of the exchanged vector (4 * hidden for the LSTM's backward pass, else hidden)
-  int grid = 0, waves = 0, row_waves = 0, block = 0, lanes_per_row = 0;   // waves = all, row_waves = those owning rows
+  int parts = 1;             // groups of workgroups that each hold the whole matrix and advance `batch` of the call's samples
+  int grid = 0, waves = 0, row_waves = 0, block = 0, lanes_per_row = 0;   // grid = workgroups of a part; waves = all, row_waves = those owning rows
   int sync = SPRNN_SYNC_TAGGED, bank_aware = 1, balance = 2, poll_delay = 0, spin_limit = 0, timeline = 0;
   int cooperative = 0;       // 1: cooperative launch instead of an ordinary one
   int jitter = 0;            // test aid: seed of pseudo-random pauses in the hand-off (0 = none)
@@ -48,6 +49,8 @@ struct Mapping {
   int layout = 0;            // 0: one power-of-two lane group per row; 1: lane pool (see pack_pool): row_waves gather, the others own the outputs
   int group = 0;             // lane pool: lanes per group (= batch); a row takes whole groups
   int64_t nnz = 0, padded_words = 0;
+
+  int samples() const { return batch * parts; }   // sequences a call advances (`batch` above is a part's share, which the layout is made for)
 };
 
 struct Packed {
@@ -63,11 +66,33 @@ struct Packed {
   std::vector<int32_t> lane_sum;    // lane pool: [grid][block] for an output lane: first group of its row | groups of the row << 16
 };
 
-// Returns SPRNN_OK or an error code; on success `out` holds the mapping and the image.
+// Bank-aware orders of one matrix that were already made, for packing it again with another mapping: they depend on the
+// lanes per row and on how rows are dealt to wavefronts, not on where the wavefronts go.
+struct OrderCache {
+  struct Entry {
+    int lanes = 0, balance = 0, order_batch = 0, activations = 0;
+    std::vector<std::vector<std::vector<int>>> pos;   // [wavefront that owns rows][row group] RowGroup::pos
+  };
+  std::vector<Entry> entries;
+};
+
+// Returns SPRNN_OK or an error code; on success `out` holds the mapping and the image.  `cache`, if given, belongs to this
+// matrix and this value of opt->bank_aware.
 int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t* col_idx,
-         const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out);
+         const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out, OrderCache* cache = nullptr);
 
 double lds_pass_factor(const Packed& P);
+
+// Parts asked for in sprnn_options_t.xcd (1: none, or nothing that could be meant), and the options with that replaced.
+inline int parts_asked(const sprnn_options_t* opt) {
+  const int n = opt && opt->xcd > 0 && (opt->xcd & 255) <= 2 ? opt->xcd >> 8 : 0;
+  return n == 2 || n == 4 || n == 8 ? n : 1;
+}
+inline sprnn_options_t with_parts(const sprnn_options_t& opt, int parts) {
+  sprnn_options_t o = opt;
+  o.xcd = (opt.xcd & 255) + (parts > 1 ? SPRNN_XCD_PARTS(parts) : 0);
+  return o;
+}
 
 // CSR checks shared by create and pack_host: shape, monotone row_ptr, strictly increasing in-range
 // columns, finite binary16 values.

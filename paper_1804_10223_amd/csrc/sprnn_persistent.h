@@ -104,8 +104,10 @@ __device__ __forceinline__ float reduce_scatter(float (&v)[B], int lane) {
   if constexpr (SPLITS <= 0 && STAGES > 0) t += from_partner<0>(t);
   if constexpr (SPLITS <= 1 && STAGES > 1) t += from_partner<1>(t);
   if constexpr (SPLITS <= 2 && STAGES > 3) {
-    // both in-row stages are plain: two rotations sum the four lanes that share lane % 4
-    t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x124, 0xf, 0xf, false));   // row_ror:4
+    // both in-row stages are plain: two rotations sum the four lanes that share lane % 4.  (From the next quad first: the
+    // owners, in the first quad of a row, then add the same pairs as the halving stages of a larger B do, so that the bits of
+    // a result do not depend on how many samples the workgroup advances.)
+    t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x12C, 0xf, 0xf, false));   // row_ror:12
     t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x128, 0xf, 0xf, false));   // row_ror:8
   } else {
     if constexpr (SPLITS <= 2 && STAGES > 2) t += from_partner<2>(t);
@@ -550,15 +552,27 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
   // h and writes h_t straight into the other one; otherwise one copy is enough, because the workgroup barrier
   // before a step's first poll also separates the last gather of step t from the first write of h_t.
   extern __shared__ __align__(16) unsigned char lds[];
-  // One-XCD mode (small layers: at most 32 workgroups): the launch holds eight times the workgroups the mapping needs,
-  // dealt over the eight XCDs by the dispatcher.  Every workgroup reports the XCD it runs on, waits until all have
-  // reported, and the first XCD that received enough of them takes the work; its workgroups number themselves in the
-  // order they arrived, all others leave.  The exchange then stays inside one L2: results are published with plain
-  // stores (no write-through to the memory side) and read with loads that only miss the per-CU cache.  If no XCD got
-  // enough workgroups the launch gives up and flags it in the status word.
-  int grid_x = (int)gridDim.x, wg_index = (int)blockIdx.x;
+  // Samples never meet, so a batch may be dealt to p.parts groups of workgroups ("parts"), each of which holds the whole
+  // matrix, advances B of the p.batch samples and exchanges with nobody else: a part copies its own samples' share of
+  // h instead of all of it and waits for its own workgroups only.  The dispatcher deals workgroups to the eight XCDs in
+  // turn, so a part that takes consecutive XCDs has 1 / p.parts of the traffic of every L2 to itself; that only is a
+  // matter of speed, the exchange works wherever the workgroups run.
+  // One-XCD mode (at most 32 workgroups a part): the launch holds eight times the workgroups of a part.  Every workgroup
+  // reports the XCD it runs on, waits until all have reported, and the first p.parts XCDs that received enough of them
+  // take a part each; their workgroups number themselves in the order they arrived, all others leave.  The exchange then
+  // stays inside one L2: results are published with plain stores (no write-through to the memory side) and read with
+  // loads that only miss the per-CU cache.  One XCD always gets enough; should fewer than p.parts, every workgroup sees
+  // the same counts and takes its place by its index instead, and the exchange goes through the memory side.
+  constexpr bool kParts = !WGRAD && !TL && CELL != 9 && CELL != 10;   // (the passes that are offered with several parts)
+  const int parts = kParts ? p.parts : 1;
+  int grid_x = p.part_grid, wg_index = (int)blockIdx.x, part = 0;
+  bool local = false;
+  if (parts > 1) {
+    const int xcd = (int)blockIdx.x & 7, per_part = 8 / parts;   // XCDs of a part
+    part = xcd / per_part;
+    wg_index = ((int)blockIdx.x >> 3) * per_part + xcd % per_part;
+  }
   if (p.one_xcd) {
-    grid_x = (int)gridDim.x / 8;
     const uint32_t flags = lds_address(lds);          // two words at the start of LDS, before anything else uses it
     if (threadIdx.x == 0) {
       uint32_t* const cnt = p.ctrl + kCtrlPlacement + 16 * (p.launch_epoch & 1u);
@@ -570,24 +584,45 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       while (__hip_atomic_load(cnt + 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x) {
         if (++spins > p.spin_limit) { all_here = false; break; }
       }
-      int chosen = -1;
+      int mine = -1, found = 0;   // the part this XCD takes, XCDs with enough workgroups
       if (all_here) {
-        for (int x = 7; x >= 0; --x)
-          if (__hip_atomic_load(cnt + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)grid_x) chosen = x;
+        uint32_t enough[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) enough[x] = __hip_atomic_load(cnt + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int has = enough[x] >= (uint32_t)grid_x ? 1 : 0;
+          if (has && x == (int)xcc && found < parts) mine = found;
+          found += has;
+        }
       }
-      if (chosen == (int)xcc && order < (uint32_t)grid_x) rank = (int)order;
-      if (chosen < 0 && blockIdx.x == 0) __hip_atomic_fetch_or(p.ctrl + kCtrlStatus, kStatusPlacement, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (found >= parts) {
+        if (mine >= 0 && order < (uint32_t)grid_x) rank = (int)order;
+      } else if (all_here) {
+        mine = part;
+        if (wg_index < grid_x) rank = wg_index;
+      } else if (blockIdx.x == 0) {
+        __hip_atomic_fetch_or(p.ctrl + kCtrlStatus, kStatusPlacement, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       if (blockIdx.x == 0) {   // the other set of counters belongs to the launch before (done) and the one after (not begun)
         uint32_t* const other = p.ctrl + kCtrlPlacement + 16 * ((p.launch_epoch + 1u) & 1u);
         for (int i = 0; i < 9; ++i) __hip_atomic_store(other + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       lds_store_int(flags, rank);
+      lds_store_int(flags + 4, mine | (found >= parts ? 256 : 0));
     }
     __syncthreads();
-    wg_index = lds_load_int(flags);
-    __syncthreads();                                   // (LDS is initialised only after everyone has read the flag)
+    wg_index = __builtin_amdgcn_readfirstlane(lds_load_int(flags));
+    part = __builtin_amdgcn_readfirstlane(lds_load_int(flags + 4));
+    local = part >= 256;
+    part &= 255;
+    __syncthreads();                                   // (LDS is initialised only after everyone has read the flags)
     if (wg_index < 0) return;
+  } else if (wg_index >= grid_x) {
+    return;                                            // (launches of several parts are filled up to whole rounds of the XCDs)
   }
+  // samples of the call, first sample of this part (which the lanes' offsets carry)
+  const int Bt = kParts ? p.batch : B, b0 = kParts ? part * B : 0;
   const bool solo = grid_x == 1;   // no other workgroup to exchange with
   unsigned char* const lds_tail = lds + (solo ? 2 : 1) * p.lds_h_bytes;
   // abort flags, indexed by step parity so that a fast wave's next-step flag cannot be read one step early
@@ -636,7 +671,8 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
   const int row = p.lane_row[(size_t)wg * block + tid];
   const int sample = sample_of_lane<B>(lane);
   const bool owner = row >= 0 && (lane & (L - 1)) < B;
-  const int x_voff = (owner && row < Rx) ? (sample * Rx + row) * 4 : kOutOfRange;
+  const int x_step = Bt * Rx * 4, h_step = Bt * H * 4, unit_step = Bt * Hu * 4;   // bytes of a timestep of b', h and what has one element per unit
+  const int x_voff = (owner && row < Rx) ? ((b0 + sample) * Rx + row) * 4 : kOutOfRange;
   const int gate = LSTM ? (lane / L) & 3 : 0;
   const float bhn = (gru && owner && gate == 2 && p.b_hn) ? p.b_hn[row - 2 * H] : 0.0f;
   int out_voff, ring_voff;
@@ -648,26 +684,26 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       cell_unit = r >= 0 ? r % H : -1;
     }
     const int b = lane % B;
-    out_voff = cell_unit >= 0 ? (b * H + cell_unit) * 4 : kOutOfRange;
+    out_voff = cell_unit >= 0 ? ((b0 + b) * H + cell_unit) * 4 : kOutOfRange;
     ring_voff = cell_unit >= 0 ? lds_offset<B>(cell_unit, b, H) : kOutOfRange;
   } else {
-    out_voff = owner ? (sample * H + row) * 4 : kOutOfRange;
+    out_voff = owner ? ((b0 + sample) * H + row) * 4 : kOutOfRange;
     // (binary16 activations: the owner of sample 0 stores the row's four elements as one 8-byte piece)
     ring_voff = kHalf ? ((owner && sample == 0) ? row * (B * 2) : kOutOfRange) : (owner ? lds_offset<B>(row, sample, H) : kOutOfRange);
   }
-  const __amdgpu_buffer_rsrc_t ring = __builtin_amdgcn_make_buffer_rsrc(p.ring, 0, kRingSlotsDev * p.h_bytes, kBufWord3);
-  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.x), 0, p.T * B * Rx * 4, kBufWord3);
-  const __amdgpu_buffer_rsrc_t hbuf = __builtin_amdgcn_make_buffer_rsrc(p.h_out, 0, p.T * B * H * 4, kBufWord3);
+  const __amdgpu_buffer_rsrc_t ring = __builtin_amdgcn_make_buffer_rsrc(p.ring + (size_t)part * (kRingSlotsDev * p.h_bytes / 4), 0, kRingSlotsDev * p.h_bytes, kBufWord3);
+  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.x), 0, p.T * Bt * Rx * 4, kBufWord3);
+  const __amdgpu_buffer_rsrc_t hbuf = __builtin_amdgcn_make_buffer_rsrc(p.h_out, 0, p.T * Bt * H * 4, kBufWord3);
   const __amdgpu_buffer_rsrc_t abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>((BWD || LBWD) ? p.aux : p.x), 0,
-                                                                        p.T * B * (LBWD ? 4 * Hu : H) * 4, kBufWord3);
-  const int gates_voff = (LBWD && owner) ? (sample * 4 * Hu + row) * 4 : kOutOfRange;   // this lane's first kept gate value
-  const __amdgpu_buffer_rsrc_t dbuf = __builtin_amdgcn_make_buffer_rsrc((BWD || LBWD) && p.dh0 ? p.dh0 : p.h_out, 0, B * Hu * 4, kBufWord3);
+                                                                        p.T * Bt * (LBWD ? 4 * Hu : H) * 4, kBufWord3);
+  const int gates_voff = (LBWD && owner) ? ((b0 + sample) * 4 * Hu + row) * 4 : kOutOfRange;   // this lane's first kept gate value
+  const __amdgpu_buffer_rsrc_t dbuf = __builtin_amdgcn_make_buffer_rsrc((BWD || LBWD) && p.dh0 ? p.dh0 : p.h_out, 0, Bt * Hu * 4, kBufWord3);
   // LSTM backward: forward cell states [T][B][Hu], c_0 and dL/dc_0 [B][Hu] (an absent one is an empty buffer: loads
   // give zero, stores are dropped); this lane's element of them, and the distance of two gate blocks in the ring
-  const __amdgpu_buffer_rsrc_t cfbuf = __builtin_amdgcn_make_buffer_rsrc(LBWD ? p.c_out : p.h_out, 0, LBWD ? p.T * B * Hu * 4 : 0, kBufWord3);
-  const __amdgpu_buffer_rsrc_t c0buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(LBWD && p.c0 ? p.c0 : p.x), 0, (LBWD && p.c0) ? B * Hu * 4 : 0, kBufWord3);
-  const __amdgpu_buffer_rsrc_t dc0buf = __builtin_amdgcn_make_buffer_rsrc(LBWD && p.dc0 ? p.dc0 : p.h_out, 0, (LBWD && p.dc0) ? B * Hu * 4 : 0, kBufWord3);
-  const int unit_voff = (LBWD && owner) ? (sample * Hu + row) * 4 : kOutOfRange;
+  const __amdgpu_buffer_rsrc_t cfbuf = __builtin_amdgcn_make_buffer_rsrc(LBWD ? p.c_out : p.h_out, 0, LBWD ? p.T * Bt * Hu * 4 : 0, kBufWord3);
+  const __amdgpu_buffer_rsrc_t c0buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(LBWD && p.c0 ? p.c0 : p.x), 0, (LBWD && p.c0) ? Bt * Hu * 4 : 0, kBufWord3);
+  const __amdgpu_buffer_rsrc_t dc0buf = __builtin_amdgcn_make_buffer_rsrc(LBWD && p.dc0 ? p.dc0 : p.h_out, 0, (LBWD && p.dc0) ? Bt * Hu * 4 : 0, kBufWord3);
+  const int unit_voff = (LBWD && owner) ? ((b0 + sample) * Hu + row) * 4 : kOutOfRange;
   const int gate_ring_bytes = Hu * (B < 4 ? B : 4) * 4;
 
   // ---- the copy of h into LDS: 16-byte chunks.  In round c a lane copies the chunk at ring offset src to LDS
@@ -695,7 +731,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
   if (!compacted) {
     for (int e = tid; e < H * B; e += block) {
       const int j = e / B, b = e % B;
-      const float v = p.h0 ? p.h0[(size_t)b * H + j] : 0.0f;
+      const float v = p.h0 ? p.h0[(size_t)(b0 + b) * H + j] : 0.0f;
       if constexpr (kHalf) *reinterpret_cast<_Float16*>(lds + (j * B + b) * 2) = (_Float16)v;
       else *reinterpret_cast<float*>(lds + lds_offset<B>(j, b, H)) = v;
     }
@@ -709,7 +745,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int f = (src >> 1) + i, j = f / B, b = f % B;
-          v[i] = (_Float16)((p.h0 && j < H) ? p.h0[(size_t)b * H + j] : 0.0f);
+          v[i] = (_Float16)((p.h0 && j < H) ? p.h0[(size_t)(b0 + b) * H + j] : 0.0f);
         }
         *reinterpret_cast<halfx8*>(lds + dst) = v;
         continue;
@@ -720,13 +756,13 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
         const int f = (src >> 2) + i;             // element of the slot layout: [H][B], or [2][H][4] for batch 8
         const int j = B == 8 ? (f % (H * 4)) / 4 : f / B;
         const int b = B == 8 ? (f / (H * 4)) * 4 + (f & 3) : f % B;
-        v[i] = (p.h0 && j < H) ? p.h0[(size_t)b * H + j] : 0.0f;
+        v[i] = (p.h0 && j < H) ? p.h0[(size_t)(b0 + b) * H + j] : 0.0f;
       }
       *reinterpret_cast<f32x4*>(lds + dst) = v;
     }
   }
   const float* const state0 = gru ? p.h0 : p.c0;
-  float c_state = (LSTM && cell_unit >= 0 && state0) ? state0[(size_t)(lane % B) * H + cell_unit] : 0.0f;
+  float c_state = (LSTM && cell_unit >= 0 && state0) ? state0[(size_t)(b0 + lane % B) * H + cell_unit] : 0.0f;
   // hand-over area of this wavefront: [unit slot][sample][gate] floats, after the flags and the timeline sums
   float* const stage = reinterpret_cast<float*>(lds_tail + kLdsTailBytes) + (LSTM ? wave * (64 / (4 * L)) * B * 4 : 0);
   const int stage_write = ((lane / (4 * L)) * B + sample) * 4 + ((lane / L) & 3);   // [unit slot][sample][gate]
@@ -736,22 +772,22 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
   // whole timestep, so the load for step t+1 is issued before step t's wait for h_t.
   // (scalar offsets select the timestep and the sample; the host keeps one launch below 1 GiB of x, so an
   // out-of-range lane offset stays out of range whatever scalar offset is added to it)
-  float xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(0) * B * Rx * 4, 0));
+  float xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(0) * x_step, 0));
   float an = 0.0f;   // backward pass: forward output h_t of the same element
-  if constexpr (BWD) an = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time_of(0) * B * H * 4, 0));
+  if constexpr (BWD) an = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time_of(0) * h_step, 0));
   // LSTM backward: gate values i, f, g, o and the cell states c_t, c_{t-1} of this lane's (unit, sample), fetched one
   // step ahead like e_t; carry = dc_{t+1} f_{t+1}
   float gn[4] = {0.0f, 0.0f, 0.0f, 0.0f}, c_cur = 0.0f, c_prev = 0.0f, carry = 0.0f;
   auto load_saved = [&](int time) {   // c_cur of this time is the c_prev of the step before
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      gn[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, gates_voff, (time * B * 4 + q) * Hu * 4, 0));
-    c_prev = __builtin_bit_cast(float, time > 0 ? __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, (time - 1) * B * Hu * 4, 0)
+      gn[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, gates_voff, time * unit_step * 4 + q * Hu * 4, 0));
+    c_prev = __builtin_bit_cast(float, time > 0 ? __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, (time - 1) * unit_step, 0)
                                                 : __builtin_amdgcn_raw_buffer_load_b32(c0buf, unit_voff, 0, 0));
   };
   if constexpr (LBWD) {
     if (p.T > 0) {
-      if constexpr (!GBWD) c_cur = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, time_of(0) * B * Hu * 4, 0));
+      if constexpr (!GBWD) c_cur = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, time_of(0) * unit_step, 0));
       load_saved(time_of(0));
     }
   }
@@ -971,7 +1007,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
     // The re-arm stores issued one step ago must be performed before this step's data can be seen, hence the wait.
     const int slot_byte = (int)(g & (kRingSlotsDev - 1)) * p.h_bytes;
     const int rearm_byte = (int)((g + 2) & (kRingSlotsDev - 1)) * p.h_bytes;
-    const int out_soff = time_of(t) * B * H * 4;
+    const int out_soff = time_of(t) * h_step;
     float hval;
     float kept[4] = {0.0f, 0.0f, 0.0f, 0.0f}, c_new = 0.0f;   // gated cells: values stored after the publish
     if constexpr (LSTM) {
@@ -1045,7 +1081,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       }
       if (t < p.T) {
         if constexpr (GBWD) {   // the recurrent sums' gradient for the weight gradient, then dL/db' with da in the third block
-          const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc(p.gates_out, 0, p.gates_out ? p.T * B * H * 4 : 0, kBufWord3);
+          const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc(p.gates_out, 0, p.gates_out ? p.T * Bt * H * 4 : 0, kBufWord3);
 #pragma unroll
           for (int q = 0; q < NG; ++q)
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dp[q]), vbuf, out_voff, out_soff + q * Hu * 4, 0);
@@ -1059,7 +1095,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), dbuf, unit_voff, 0, 0);
       }
       if (t + 1 < p.T) {
-        xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(t + 1) * B * Rx * 4, 0));
+        xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(t + 1) * x_step, 0));
         load_saved(time_of(t + 1));
       }
     } else if constexpr (BWD) {
@@ -1093,7 +1129,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
           i32x2 mark;
           mark.x = (int)kSentinelHalfPair;
           mark.y = (int)kSentinelHalfPair;
-          if (p.one_xcd) {
+          if (local) {
             __builtin_amdgcn_raw_buffer_store_b64(pair, ring, ring_voff, slot_byte, 0);
             if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, 0);
           } else {
@@ -1118,7 +1154,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           i32x4 mark;
           mark.x = mark.y = mark.z = mark.w = (int)kSentinelHalfPair;
-          if (p.one_xcd) {
+          if (local) {
             __builtin_amdgcn_raw_buffer_store_b128(column, ring, ring_voff, slot_byte, 0);
             if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, 0);
           } else {
@@ -1131,7 +1167,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       if (ring_voff != kOutOfRange) *reinterpret_cast<float*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = hval;
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (p.one_xcd) {   // every workgroup shares one L2: plain stores reach it and need not go further
+      if (local) {   // every workgroup of the part shares one L2: plain stores reach it and need not go further
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), ring, ring_voff, slot_byte, 0);
         if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, 0);
       } else {
@@ -1148,20 +1184,20 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       // The cell state and (training) the kept gate values leave after the publish: the publish waits for every
       // earlier store of the wavefront, and these would sit in front of it.
       if (!gru) {
-        const __amdgpu_buffer_rsrc_t cbuf = __builtin_amdgcn_make_buffer_rsrc(p.c_out, 0, p.T * B * H * 4, kBufWord3);
+        const __amdgpu_buffer_rsrc_t cbuf = __builtin_amdgcn_make_buffer_rsrc(p.c_out, 0, p.T * Bt * H * 4, kBufWord3);
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, c_new), cbuf, out_voff, out_soff, 0);
       }
       if (p.gates_out) {   // [T][B][4H]: i | f | g | o after their activations, or r | z | n | q for the GRU
-        const __amdgpu_buffer_rsrc_t gbuf = __builtin_amdgcn_make_buffer_rsrc(p.gates_out, 0, p.T * B * H * 16, kBufWord3);
-        const int gate_voff = cell_unit >= 0 ? ((lane % B) * 4 * H + cell_unit) * 4 : kOutOfRange;
+        const __amdgpu_buffer_rsrc_t gbuf = __builtin_amdgcn_make_buffer_rsrc(p.gates_out, 0, p.T * Bt * H * 16, kBufWord3);
+        const int gate_voff = cell_unit >= 0 ? ((b0 + lane % B) * 4 * H + cell_unit) * 4 : kOutOfRange;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, kept[q]), gbuf, gate_voff, out_soff * 4 + q * H * 4, 0);
       }
     }
     if (t + 1 < p.T) {
-      xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(t + 1) * B * Rx * 4, 0));
-      if constexpr (BWD) an = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time_of(t + 1) * B * H * 4, 0));
+      xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(t + 1) * x_step, 0));
+      if constexpr (BWD) an = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time_of(t + 1) * h_step, 0));
     }
     }
     if constexpr (WGRAD) {
