@@ -348,13 +348,16 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
                                : (m.seg_rounds ? persistent_overlap_kernel_for(m.batch, m.template_words, m.timeline != 0)
                                   : (m.half ? persistent_half_kernel_for(m.batch, m.template_words)
                                             : persistent_kernel_for(m.batch, m.template_words, m.cell, m.timeline != 0))));
-  // a short h (at most three rounds of the copy): the instantiation that issues exactly that many loads
-  const bool short_copy = !pool && !m.compact && m.grid > 1 && (m.h_bytes / 16 + m.block - 1) / m.block <= 3;
-  const bool gated_backward = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;
-  if (short_copy && !m.narrow && !m.seg_rounds && !m.half && !m.timeline && (m.cell <= SPRNN_CELL_GRU || gated_backward)) {
-    const void* k = persistent_short_kernel_for(m.batch, m.template_words, m.cell);
-    if (k) h->kernel = k;
-  }
+  // nothing asked for that the general form has branches for: the instantiation without them, by the rounds of the copy
+  const int copy_rounds = (m.h_bytes / 16 + m.block - 1) / m.block;
+  const bool plain = !pool && !m.compact && m.grid > 1 && m.sync == SPRNN_SYNC_TAGGED && !m.jitter && !m.narrow && !m.seg_rounds && !m.timeline;
+  auto plain_kernel_for = [&](int cell) -> const void* {
+    if (!plain) return nullptr;
+    return copy_rounds <= 3 ? persistent_short_kernel_for(m.batch, m.template_words, cell, m.half != 0)
+                            : (copy_rounds == 4 ? persistent_four_kernel_for(m.batch, m.template_words, cell, m.half != 0)
+                                                : persistent_long_kernel_for(m.batch, m.template_words, cell, m.half != 0));
+  };
+  if (const void* k = plain_kernel_for(m.cell)) h->kernel = k;
   if (!h->kernel) { release(h); return SPRNN_ERR_UNSUPPORTED; }
 
   // One workgroup per CU: ask for more than half of a CU's LDS so that two can never share one.
@@ -369,8 +372,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   if (m.cell <= SPRNN_ACT_IDENTITY && !m.timeline && !m.narrow && !m.half) {
     // the backward pass of a vanilla cell runs on a handle that holds the transposed matrix: same shape, same LDS
     h->kernel_bwd = pool ? pool_kernel_for(m.batch, m.template_words, kCellBackward)
-                         : (short_copy ? persistent_short_kernel_for(m.batch, m.template_words, kCellBackward)
-                                       : persistent_kernel_for(m.batch, m.template_words, kCellBackward, false));
+                         : (plain ? plain_kernel_for(kCellBackward) : persistent_kernel_for(m.batch, m.template_words, kCellBackward, false));
     if (h->kernel_bwd && !SPRNN_HIP(hipFuncSetAttribute(h->kernel_bwd, hipFuncAttributeMaxDynamicSharedMemorySize, lds_cu))) { release(h); return SPRNN_ERR_HIP; }
     // it spins on its neighbours like the forward kernel: usable only if the same grid is co-resident with it
     int per_cu_bwd = 0;

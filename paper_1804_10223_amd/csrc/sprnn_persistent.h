@@ -528,18 +528,23 @@ __device__ __forceinline__ bool copy_two_parts(__amdgpu_buffer_rsrc_t ring, int 
 // 11 = the vanilla cell's forward pass with h exchanged and kept in LDS as binary16 (batch 4; options.activations;
 // Section 6 names lower-precision activations as future work): one 8-byte gather per nonzero, products and sums in
 // binary32, every h_t rounded to nearest once before it is published (h_out keeps the unrounded value),
-// 12 .. 17 = the passes 0, 1, 2, 3, 5, 7 for a layer whose h takes at most three rounds of the copy (one 16-byte piece
-// per lane and round): the copy issues exactly that many loads.  The general code always issues four (rounds past the
-// end re-fetch the clamped last piece), which costs a small layer 0.1 us per surplus round; choosing between the two
-// inside one kernel cost the four-round layers 3 %, hence separate instantiations (backward pass, 701 units, batch 2, one
-// round: 1.48 -> 1.25 us per step).  Copies of more than four rounds gain nothing that way: with exactly the rounds that
-// are left in the last batch, or with all rounds in flight at once, 5120 x batch 4 (seven rounds) took 3 % longer and 2560 x
-// batch 8 (ten) 5 to 12 %: the loads past the end all ask for one line, and while the first batch of eight is on its way
-// the slower workgroups publish what the second asks for.
-template <int B, int NW, int CELLX, bool TL>
-__global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELLX == 8) && NW >= 24 ? 512 : 768)) void persistent_kernel(const KernelArgs p) {
-  constexpr bool kShort = CELLX >= 12 && CELLX <= 17;        // a pass for a short h (see the list above)
-  constexpr int CELL = kShort ? (CELLX <= 15 ? CELLX - 12 : 2 * CELLX - 27) : CELLX;
+// (CELL 9 and 10 exist as ablations, in the general form only.)
+//
+// FORM: kFormGeneral has every option of the handle as a run-time branch: a grid barrier, pauses, column compaction, a single
+// workgroup, any number of copy rounds (one 16-byte piece per lane and round).  The passes 0, 1, 2, 3, 5, 7 and 11 exist
+// without all that, for the tagged hand-off with h copied whole: a step of the general form is some 700 instructions of
+// which the path taken is a third, reached over taken branches and with its uniform values in spilled scalar registers.
+// They differ in the copy: kFormShort has exactly one, two or three rounds (the general code always issues four, of which
+// the ones past the end re-fetch the clamped last piece: 0.1 us per surplus round), kFormFour four, kFormLong as many groups
+// of eight as it takes.  Copies of more than four rounds gain nothing by exact counts: with exactly the rounds that are left
+// in the last batch, or with all rounds in flight at once, 5120 x batch 4 (seven rounds) took 3 % longer and 2560 x batch 8
+// (ten) 5 to 12 %: the loads past the end all ask for one line, and while the first batch of eight is on its way the slower
+// workgroups publish what the second asks for.
+constexpr int kFormGeneral = 0, kFormShort = 1, kFormFour = 2, kFormLong = 3;
+
+template <int B, int NW, int CELL, bool TL, int FORM = kFormGeneral>
+__global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL == 8) && NW >= 24 ? 512 : 768)) void persistent_kernel(const KernelArgs p) {
+  constexpr bool kGeneral = FORM == kFormGeneral;
   constexpr bool LSTM = CELL == 1 || CELL == 2;   // gated cell: four row groups per unit, cell lanes
   constexpr bool LBWD = CELL >= 5 && CELL <= 8;                // backward pass of a gated cell
   constexpr bool GBWD = CELL == 7 || CELL == 8;                // ... of the GRU
@@ -623,7 +628,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
   }
   // samples of the call, first sample of this part (which the lanes' offsets carry)
   const int Bt = kParts ? p.batch : B, b0 = kParts ? part * B : 0;
-  const bool solo = grid_x == 1;   // no other workgroup to exchange with
+  const bool solo = kGeneral && grid_x == 1;   // no other workgroup to exchange with
   unsigned char* const lds_tail = lds + (solo ? 2 : 1) * p.lds_h_bytes;
   // abort flags, indexed by step parity so that a fast wave's next-step flag cannot be read one step early
   const uint32_t s_abort = lds_address(lds_tail);   // LDS address of the two flags
@@ -634,7 +639,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
   const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
   const int H = p.hidden, L = p.lanes_per_row;
   const int R = LSTM ? 4 * H : H;
-  const bool compacted = p.fill_src != nullptr;   // LDS holds only the chunks of h that this workgroup's rows read
+  const bool compacted = kGeneral && p.fill_src != nullptr;   // LDS holds only the chunks of h that this workgroup's rows read
   // distance of the two planes of a batch-8 layout inside the LDS copy (the ring always uses H * 16)
   const int plane_bytes = (B == 8 && compacted) ? __builtin_amdgcn_readfirstlane(p.wg_plane[wg]) : H * 16;
 
@@ -826,6 +831,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
     tl_launch_wall = (long long)wall_clock64();
   }
 
+  const bool tagged = !kGeneral || p.sync == SPRNN_SYNC_TAGGED;
   const uint32_t wave_id = (uint32_t)(wg * (block >> 6) + wave);
   int cur = 0;   // LDS copy that holds h_{t-1}; stays 0 unless solo
   long long tl_prev = 0;
@@ -853,7 +859,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       const int slot_byte = (int)((g - 1) & (kRingSlotsDev - 1)) * p.h_bytes;
       unsigned char* dst = lds;
       bool failed = false;
-      if (p.sync == SPRNN_SYNC_BARRIER) {
+      if (kGeneral && p.sync == SPRNN_SYNC_BARRIER) {
         // grid barrier (Section 3.2): all stores performed, one arrival per workgroup, wait for everyone
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
@@ -893,7 +899,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
         // otherwise have to be covered by a longer back-off in every workgroup).
         __syncthreads();
         for (int d = 0; d < p.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
-        jitter_pause(p.jitter, wave_id, g, 1);
+        if constexpr (kGeneral) jitter_pause(p.jitter, wave_id, g, 1);
       }
       ts4 = tick<TL>(tl_on);
       if constexpr (kTwoPart) {
@@ -916,21 +922,23 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
           ts5 = ts4;
         }
       } else if (!failed) {   // (after a grid barrier every chunk is valid at the first load)
-        if (chunk_rounds <= 4) {
+        if constexpr (FORM == kFormShort) {   // (the host selects these instantiations only for one to three rounds)
+          if (chunk_rounds <= 1) {
+            const int one[1] = {fsrc[0]};
+            failed = !copy_chunks<1, false, kHalf>(ring, slot_byte, one, one, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
+          } else if (chunk_rounds == 2) {
+            const int two[2] = {fsrc[0], fsrc[1]};
+            failed = !copy_chunks<2, false, kHalf>(ring, slot_byte, two, two, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
+          } else {
+            const int three[3] = {fsrc[0], fsrc[1], fsrc[2]};
+            failed = !copy_chunks<3, false, kHalf>(ring, slot_byte, three, three, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
+          }
+        } else if constexpr (FORM == kFormFour) {
+          failed = !copy_chunks<4, false, kHalf>(ring, slot_byte, fsrc, fsrc, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
+        } else if (FORM != kFormLong && chunk_rounds <= 4) {
           if (!compacted) {
-            if constexpr (kShort) {   // (the host selects these instantiations only for one to three rounds)
-              if (chunk_rounds <= 1) {
-                const int one[1] = {fsrc[0]};
-                failed = !copy_chunks<1, false>(ring, slot_byte, one, one, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
-              } else if (chunk_rounds == 2) {
-                const int two[2] = {fsrc[0], fsrc[1]};
-                failed = !copy_chunks<2, false>(ring, slot_byte, two, two, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
-              } else {
-                const int three[3] = {fsrc[0], fsrc[1], fsrc[2]};
-                failed = !copy_chunks<3, false>(ring, slot_byte, three, three, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
-              }
-            } else if (kHalf && chunk_rounds <= 2) {
-              // half the bytes, half the rounds (see instantiations 12..14 for why the count is matched)
+            if (kHalf && chunk_rounds <= 2) {
+              // half the bytes, half the rounds (see kFormShort for why the count is matched)
               const int two[2] = {fsrc[0], fsrc[1]};
               failed = !copy_chunks<2, false, kHalf>(ring, slot_byte, two, two, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
             } else {
@@ -969,7 +977,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
         }
         ts5 = ts4;
       }
-      jitter_pause(p.jitter, wave_id, g, 2);
+      if constexpr (kGeneral) jitter_pause(p.jitter, wave_id, g, 2);
       ts6 = tick<TL>(tl_on);
       if (failed) {
         lds_store_int(s_abort + 4 * (t & 1), 1);
@@ -1062,7 +1070,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
           c_cur = c_prev;
         }
       }
-      jitter_pause(p.jitter, wave_id, g, 3);
+      if constexpr (kGeneral) jitter_pause(p.jitter, wave_id, g, 3);
       if (solo) {
         if (ring_voff != kOutOfRange) {
 #pragma unroll
@@ -1073,7 +1081,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
 #pragma unroll
         for (int q = 0; q < NG; ++q)
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dp[q]), ring, ring_voff, slot_byte + q * gate_ring_bytes, kAuxCoherent);
-        if (p.sync == SPRNN_SYNC_TAGGED) {
+        if (tagged) {
 #pragma unroll
           for (int q = 0; q < NG; ++q)
             __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte + q * gate_ring_bytes, kAuxCoherent);
@@ -1110,7 +1118,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
     }
     ts2 = tick<TL>(tl_on);
     if constexpr (!LBWD) {   // (the LSTM's backward pass has published its four elements above)
-    jitter_pause(p.jitter, wave_id, g, 3);
+    if constexpr (kGeneral) jitter_pause(p.jitter, wave_id, g, 3);
     if constexpr (kHalf) {
       const int mine = (int)half_bits_for_exchange(hval);
       if constexpr (B == 4) {
@@ -1131,10 +1139,10 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
           mark.y = (int)kSentinelHalfPair;
           if (local) {
             __builtin_amdgcn_raw_buffer_store_b64(pair, ring, ring_voff, slot_byte, 0);
-            if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, 0);
+            if (tagged) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, 0);
           } else {
             __builtin_amdgcn_raw_buffer_store_b64(pair, ring, ring_voff, slot_byte, kAuxCoherent);
-            if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
+            if (tagged) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
           }
         }
       } else {
@@ -1156,10 +1164,10 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
           mark.x = mark.y = mark.z = mark.w = (int)kSentinelHalfPair;
           if (local) {
             __builtin_amdgcn_raw_buffer_store_b128(column, ring, ring_voff, slot_byte, 0);
-            if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, 0);
+            if (tagged) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, 0);
           } else {
             __builtin_amdgcn_raw_buffer_store_b128(column, ring, ring_voff, slot_byte, kAuxCoherent);
-            if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
+            if (tagged) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
           }
         }
       }
@@ -1169,10 +1177,10 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (local) {   // every workgroup of the part shares one L2: plain stores reach it and need not go further
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), ring, ring_voff, slot_byte, 0);
-        if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, 0);
+        if (tagged) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, 0);
       } else {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), ring, ring_voff, slot_byte, kAuxCoherent);
-        if (p.sync == SPRNN_SYNC_TAGGED) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, kAuxCoherent);
+        if (tagged) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, kAuxCoherent);
       }
     }
     if (BWD && t == p.T) {
@@ -1251,30 +1259,43 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELLX == 4 || CELLX == 6 || CELL
 }
 
 // ---- instantiation tables: kernel for a batch size and a number of register slots per lane
-template <int B, int CELL, bool TL>
+template <int B, int CELL, bool TL, int FORM = kFormGeneral>
 static const void* pick_nw(int nw) {
   switch (nw) {
-    case 8: return (const void*)persistent_kernel<B, 8, CELL, TL>;
-    case 16: return (const void*)persistent_kernel<B, 16, CELL, TL>;
-    case 24: return (const void*)persistent_kernel<B, 24, CELL, TL>;
-    case 32: return (const void*)persistent_kernel<B, 32, CELL, TL>;
-    case 48: return (const void*)persistent_kernel<B, 48, CELL, TL>;
+    case 8: return (const void*)persistent_kernel<B, 8, CELL, TL, FORM>;
+    case 16: return (const void*)persistent_kernel<B, 16, CELL, TL, FORM>;
+    case 24: return (const void*)persistent_kernel<B, 24, CELL, TL, FORM>;
+    case 32: return (const void*)persistent_kernel<B, 32, CELL, TL, FORM>;
+    case 48: return (const void*)persistent_kernel<B, 48, CELL, TL, FORM>;
     case 64:   // (with the weight gradient fused in, batch 8 and 64 words per lane no longer fit in registers: not built)
       if constexpr (B == 8 && (CELL == 4 || CELL == 6 || CELL == 8)) return nullptr;
-      else return (const void*)persistent_kernel<B, 64, CELL, TL>;
+      else return (const void*)persistent_kernel<B, 64, CELL, TL, FORM>;
     default: return nullptr;
   }
 }
 
-template <int CELL, bool TL>
+template <int CELL, bool TL, int FORM = kFormGeneral>
 static const void* pick_b(int batch, int nw) {
   switch (batch) {
-    case 1: return pick_nw<1, CELL, TL>(nw);
-    case 2: return pick_nw<2, CELL, TL>(nw);
-    case 4: return pick_nw<4, CELL, TL>(nw);
-    case 8: return pick_nw<8, CELL, TL>(nw);
+    case 1: return pick_nw<1, CELL, TL, FORM>(nw);
+    case 2: return pick_nw<2, CELL, TL, FORM>(nw);
+    case 4: return pick_nw<4, CELL, TL, FORM>(nw);
+    case 8: return pick_nw<8, CELL, TL, FORM>(nw);
     default: return nullptr;
   }
+}
+
+// The forms without options (see the kernel): forward passes, kCellBackward, SPRNN_CELL_*_BACKWARD; `half` = binary16 activations.
+template <int FORM>
+static const void* pick_plain(int batch, int nw, int cell, bool half) {
+  if (half) return batch == 4 ? pick_nw<4, 11, false, FORM>(nw) : (batch == 8 ? pick_nw<8, 11, false, FORM>(nw) : nullptr);
+  if (cell >= SPRNN_ACT_RELU && cell <= SPRNN_ACT_IDENTITY) return pick_b<0, false, FORM>(batch, nw);
+  if (cell == SPRNN_CELL_LSTM) return pick_b<1, false, FORM>(batch, nw);
+  if (cell == SPRNN_CELL_GRU) return pick_b<2, false, FORM>(batch, nw);
+  if (cell == kCellBackward) return pick_b<3, false, FORM>(batch, nw);
+  if (cell == SPRNN_CELL_LSTM_BACKWARD) return pick_b<5, false, FORM>(batch, nw);
+  if (cell == SPRNN_CELL_GRU_BACKWARD) return pick_b<7, false, FORM>(batch, nw);
+  return nullptr;
 }
 
 }  // namespace sprnn
