@@ -353,9 +353,14 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   const bool plain = !pool && !m.compact && m.grid > 1 && m.sync == SPRNN_SYNC_TAGGED && !m.jitter && !m.narrow && !m.seg_rounds && !m.timeline;
   auto plain_kernel_for = [&](int cell) -> const void* {
     if (!plain) return nullptr;
-    return copy_rounds <= 3 ? persistent_short_kernel_for(m.batch, m.template_words, cell, m.half != 0)
-                            : (copy_rounds == 4 ? persistent_four_kernel_for(m.batch, m.template_words, cell, m.half != 0)
-                                                : persistent_long_kernel_for(m.batch, m.template_words, cell, m.half != 0));
+    // (few mappings have more than 32 words per lane: one form serves all their short copies)
+    switch (m.template_words > 32 ? std::max(copy_rounds, 3) : copy_rounds) {
+      case 1: return persistent_plain1_kernel_for(m.batch, m.template_words, cell, m.half != 0);
+      case 2: return persistent_plain2_kernel_for(m.batch, m.template_words, cell, m.half != 0);
+      case 3: return persistent_plain3_kernel_for(m.batch, m.template_words, cell, m.half != 0);
+      case 4: return persistent_plain4_kernel_for(m.batch, m.template_words, cell, m.half != 0);
+      default: return persistent_plain5_kernel_for(m.batch, m.template_words, cell, m.half != 0);
+    }
   };
   if (const void* k = plain_kernel_for(m.cell)) h->kernel = k;
   if (!h->kernel) { release(h); return SPRNN_ERR_UNSUPPORTED; }

@@ -82,11 +82,13 @@ const void* persistent_kernel_for(int batch, int template_words, int cell, bool 
 // (the instantiations live in translation units of their own; persistent_kernel_for forwards to some of these)
 const void* persistent_timeline_kernel_for(int batch, int template_words, bool lstm);        // forward pass with the phase timeline
 const void* persistent_overlap_kernel_for(int batch, int template_words, bool timeline);     // vanilla forward with the copy of h consumed in two parts (batch <= 4; timeline: batch 4)
-// without run-time options (tagged hand-off, h copied whole among several workgroups, no pauses), for a copy of one to three rounds,
-// of four, and of more: forward passes, kCellBackward, SPRNN_CELL_*_BACKWARD
-const void* persistent_short_kernel_for(int batch, int template_words, int cell, bool half);
-const void* persistent_four_kernel_for(int batch, int template_words, int cell, bool half);
-const void* persistent_long_kernel_for(int batch, int template_words, int cell, bool half);
+// Without run-time options (tagged hand-off, h copied whole among several workgroups, no pauses), for a copy of one, two, three, four
+// and more rounds: forward passes, kCellBackward, SPRNN_CELL_*_BACKWARD.  (More than 32 words per lane: from three rounds up.)
+const void* persistent_plain1_kernel_for(int batch, int template_words, int cell, bool half);
+const void* persistent_plain2_kernel_for(int batch, int template_words, int cell, bool half);
+const void* persistent_plain3_kernel_for(int batch, int template_words, int cell, bool half);
+const void* persistent_plain4_kernel_for(int batch, int template_words, int cell, bool half);
+const void* persistent_plain5_kernel_for(int batch, int template_words, int cell, bool half);
 const void* persistent_half_kernel_for(int batch, int template_words);                       // vanilla forward with h exchanged as binary16 (batch 4, 8)
 const void* persistent_narrow_kernel_for(int batch, int template_words);                     // vanilla forward, batch 4, 4-byte gathers (ablation)
 const void* persistent_backward_kernel_for(int batch, int template_words, int cell);         // kCellBackward, kCellBackwardGrad

@@ -1,0 +1,12 @@
+// Device code of libsprnn: the persistent kernel without run-time options, for layers whose h takes
+// two rounds of the copy: forward passes of the vanilla cells, also with binary16 activations, of the LSTM and the GRU,
+// and the backward passes.
+#include "sprnn_persistent.h"
+
+namespace sprnn {
+
+const void* persistent_plain2_kernel_for(int batch, int template_words, int cell, bool half) {
+  return pick_plain<2>(batch, template_words, cell, half);
+}
+
+}  // namespace sprnn

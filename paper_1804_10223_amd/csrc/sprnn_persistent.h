@@ -134,6 +134,33 @@ __device__ __forceinline__ float reduce_rows(float (&acc)[B], int L, int lane) {
   return 0.0f;
 }
 
+// The same sums for the owner lanes with a select per stage that not every L has, in place of a jump to one of seven bodies
+// (every uniform branch costs a handful of scalar instructions and a jump or two): the in-row stages always run.
+template <int B, bool WIDE>
+__device__ __forceinline__ float reduce_rows_select(float (&v)[B], int L, int lane) {
+  constexpr int SPLITS = ilog2(B);
+  if constexpr (SPLITS >= 1) halving_stage<B, B, 0>(v, lane);
+  if constexpr (SPLITS >= 2) halving_stage<B, B / 2, 1>(v, lane);
+  if constexpr (SPLITS >= 3) halving_stage<B, B / 4, 2>(v, lane);
+  float t = v[0];
+  if constexpr (SPLITS <= 0) { const float s = t + from_partner<0>(t); t = L > 1 ? s : t; }
+  if constexpr (SPLITS <= 1) { const float s = t + from_partner<1>(t); t = L > 2 ? s : t; }
+  if constexpr (SPLITS <= 2) {   // the next quad: the partner of an owner, whose quad is the row's first
+    const float s = t + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x12C, 0xf, 0xf, false));   // row_ror:12
+    t = L > 4 ? s : t;
+  }
+  const float s = t + from_partner<3>(t);
+  t = L > 8 ? s : t;
+  if constexpr (WIDE) {
+    if (L > 16) {
+      t = cross_row_sum<4>(t);
+      const float u = cross_row_sum<5>(t);
+      t = L > 32 ? u : t;
+    }
+  }
+  return t;
+}
+
 // Logistic function and tanh from the hardware exp2 / reciprocal instructions (about 1 ulp each):
 // absolute error of a few 1e-7, far inside the 1e-3 parity bound, at a handful of instructions.
 __device__ __forceinline__ float sigmoidf_(float z) {
@@ -144,10 +171,8 @@ __device__ __forceinline__ float tanhf_(float z) {
 }
 
 __device__ __forceinline__ float activate(int act, float pre) {
-  float h;
-  if (act == SPRNN_ACT_RELU) h = fmaxf(pre, 0.0f);
-  else if (act == SPRNN_ACT_TANH) h = tanhf_(pre);
-  else h = pre;
+  float h = act == SPRNN_ACT_RELU ? fmaxf(pre, 0.0f) : pre;
+  if (act == SPRNN_ACT_TANH) h = tanhf_(pre);
   return h + 0.0f;   // -0.0 -> +0.0: -0.0 is reserved as the "not written" mark
 }
 
@@ -456,6 +481,44 @@ __device__ __forceinline__ bool copy_chunks(__amdgpu_buffer_rsrc_t ring, int slo
   return ok;
 }
 
+// The same for the forms without options: LDS mirrors the ring slot.
+template <int D, bool HALF>
+__device__ __forceinline__ bool copy_whole(__amdgpu_buffer_rsrc_t ring, int slot_byte, const int (&off)[D], unsigned char* dst, int spin_limit,
+                                           const uint32_t* status_word) {
+  i32x4 v[D];
+  auto pending = [&]() -> bool {
+    if constexpr (HALF) {
+      uint32_t key = unwritten_key_half(v[0]);
+#pragma unroll
+      for (int c = 1; c < D; ++c) key = min(key, unwritten_key_half(v[c]));
+      return __builtin_amdgcn_ballot_w64(key == 0u) != 0;
+    } else {
+      int low = min_word(v[0]);
+#pragma unroll
+      for (int c = 1; c < D; ++c) low = min(low, min_word(v[c]));
+      return __builtin_amdgcn_ballot_w64(low == (int)kSentinelBits) != 0;
+    }
+  };
+#pragma unroll
+  for (int c = 0; c < D; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b128(ring, off[c], slot_byte, kAuxCoherent);
+  bool ok = true;
+  if (pending()) {
+    int spins = 0;
+    do {
+      ++spins;
+      if (spins > spin_limit || ((spins & 1023) == 0 && __hip_atomic_load(status_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        ok = false;
+        break;
+      }
+#pragma unroll
+      for (int c = 0; c < D; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b128(ring, off[c], slot_byte, kAuxCoherent);
+    } while (pending());
+  }
+#pragma unroll
+  for (int c = 0; c < D; ++c) *reinterpret_cast<i32x4*>(dst + off[c]) = v[c];
+  return ok;
+}
+
 // Test aid: a pause of 0..15 x 64 clocks that differs per wavefront, step and call site (seed != 0 only).
 __device__ __forceinline__ void jitter_pause(int seed, uint32_t wave_id, uint32_t step, uint32_t site) {
   if (seed == 0) return;
@@ -534,13 +597,13 @@ __device__ __forceinline__ bool copy_two_parts(__amdgpu_buffer_rsrc_t ring, int 
 // workgroup, any number of copy rounds (one 16-byte piece per lane and round).  The passes 0, 1, 2, 3, 5, 7 and 11 exist
 // without all that, for the tagged hand-off with h copied whole: a step of the general form is some 700 instructions of
 // which the path taken is a third, reached over taken branches and with its uniform values in spilled scalar registers.
-// They differ in the copy: kFormShort has exactly one, two or three rounds (the general code always issues four, of which
-// the ones past the end re-fetch the clamped last piece: 0.1 us per surplus round), kFormFour four, kFormLong as many groups
+// They differ in the copy: forms 1 to 4 have exactly that many rounds (the general code always issues four, of which the ones
+// past the end re-fetch the clamped last piece: 0.1 us per surplus round), kFormLong as many groups
 // of eight as it takes.  Copies of more than four rounds gain nothing by exact counts: with exactly the rounds that are left
 // in the last batch, or with all rounds in flight at once, 5120 x batch 4 (seven rounds) took 3 % longer and 2560 x batch 8
 // (ten) 5 to 12 %: the loads past the end all ask for one line, and while the first batch of eight is on its way the slower
 // workgroups publish what the second asks for.
-constexpr int kFormGeneral = 0, kFormShort = 1, kFormFour = 2, kFormLong = 3;
+constexpr int kFormGeneral = 0, kFormLong = 5;   // 1, 2, 3, 4: that many rounds
 
 template <int B, int NW, int CELL, bool TL, int FORM = kFormGeneral>
 __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL == 8) && NW >= 24 ? 512 : 768)) void persistent_kernel(const KernelArgs p) {
@@ -708,7 +771,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   const __amdgpu_buffer_rsrc_t cfbuf = __builtin_amdgcn_make_buffer_rsrc(LBWD ? p.c_out : p.h_out, 0, LBWD ? p.T * Bt * Hu * 4 : 0, kBufWord3);
   const __amdgpu_buffer_rsrc_t c0buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(LBWD && p.c0 ? p.c0 : p.x), 0, (LBWD && p.c0) ? Bt * Hu * 4 : 0, kBufWord3);
   const __amdgpu_buffer_rsrc_t dc0buf = __builtin_amdgcn_make_buffer_rsrc(LBWD && p.dc0 ? p.dc0 : p.h_out, 0, (LBWD && p.dc0) ? Bt * Hu * 4 : 0, kBufWord3);
-  const int unit_voff = (LBWD && owner) ? ((b0 + sample) * Hu + row) * 4 : kOutOfRange;
+  const int unit_voff = LBWD ? x_voff : kOutOfRange;   // (the gated backward passes have one e_t per unit)
   const int gate_ring_bytes = Hu * (B < 4 ? B : 4) * 4;
 
   // ---- the copy of h into LDS: 16-byte chunks.  In round c a lane copies the chunk at ring offset src to LDS
@@ -773,29 +836,41 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   const int stage_write = ((lane / (4 * L)) * B + sample) * 4 + ((lane / L) & 3);   // [unit slot][sample][gate]
   const int stage_read = min(lane, (64 / (4 * L)) * B - 1) * 4;
 
-  // b'_t of this row is fetched one step ahead: a first-touch read from HBM takes about as long as a
-  // whole timestep, so the load for step t+1 is issued before step t's wait for h_t.
+  // What step t reads of the caller's arrays for this lane's element: b'_t (backward pass: e_t); the vanilla backward pass's
+  // forward output h_t; the gated ones' kept gate values and c_{t-1} (h_{t-1} for the GRU).  A first touch of device memory
+  // takes about as long as a whole timestep, so the reads for step t + 1 go out in step t: in the general form behind the
+  // publish, in the others once h_{t-1} is in LDS, a whole step ahead of their use, into the other of two register sets.  (A
+  // wavefront's memory operations complete in order, so behind the publish they hold up the next step's polls; behind the polls
+  // they take the CU's memory port from the other wavefronts' part of the copy: 2304 x batch 4 0.09 us per step.)
   // (scalar offsets select the timestep and the sample; the host keeps one launch below 1 GiB of x, so an
   // out-of-range lane offset stays out of range whatever scalar offset is added to it)
-  float xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(0) * x_step, 0));
-  float an = 0.0f;   // backward pass: forward output h_t of the same element
-  if constexpr (BWD) an = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time_of(0) * h_step, 0));
-  // LSTM backward: gate values i, f, g, o and the cell states c_t, c_{t-1} of this lane's (unit, sample), fetched one
-  // step ahead like e_t; carry = dc_{t+1} f_{t+1}
-  float gn[4] = {0.0f, 0.0f, 0.0f, 0.0f}, c_cur = 0.0f, c_prev = 0.0f, carry = 0.0f;
-  auto load_saved = [&](int time) {   // c_cur of this time is the c_prev of the step before
+  struct Inputs { float x, a, g[4], prev; };
+  Inputs in[2] = {};
+  float c_cur = 0.0f, carry = 0.0f;   // LSTM backward: c_t; carry = dc_{t+1} f_{t+1}
+  auto read_inputs = [&](Inputs& to, int time) {
+    to.x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time * x_step, 0));
+    if constexpr (BWD) to.a = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time * h_step, 0));
+    if constexpr (LBWD) {             // (the c_{t-1} of a step is the c_t of the next)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      gn[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, gates_voff, time * unit_step * 4 + q * Hu * 4, 0));
-    c_prev = __builtin_bit_cast(float, time > 0 ? __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, (time - 1) * unit_step, 0)
-                                                : __builtin_amdgcn_raw_buffer_load_b32(c0buf, unit_voff, 0, 0));
-  };
-  if constexpr (LBWD) {
-    if (p.T > 0) {
-      if constexpr (!GBWD) c_cur = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, time_of(0) * unit_step, 0));
-      load_saved(time_of(0));
+      for (int q = 0; q < 4; ++q)
+        to.g[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, gates_voff, time * unit_step * 4 + q * Hu * 4, 0));
+      if constexpr (kGeneral)
+        to.prev = __builtin_bit_cast(float, time > 0 ? __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, (time - 1) * unit_step, 0)
+                                                     : __builtin_amdgcn_raw_buffer_load_b32(c0buf, unit_voff, 0, 0));
+      else
+        to.prev = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, max(time - 1, 0) * unit_step, 0));
     }
-  }
+  };
+  auto fetch_inputs = [&](Inputs& to, int t) {   // of step t, if there is one
+    if constexpr (kGeneral) {
+      if (t < p.T) read_inputs(to, time_of(t));
+    } else {
+      read_inputs(to, time_of(min(t, p.T - 1)));   // (read once more behind the last: no branch)
+    }
+  };
+  const float c_first = LBWD && !kGeneral ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(c0buf, unit_voff, 0, 0)) : 0.0f;
+  if constexpr (LBWD && !GBWD) c_cur = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, time_of(0) * unit_step, 0));
+  read_inputs(in[0], time_of(0));
   // weight gradient: forward output of this lane's row for every sample (h_0 in the extra step), one accumulator per word
   float side[B], gacc[WGRAD ? NW : 1];
   const int row_voff = row >= 0 ? row * 4 : kOutOfRange;
@@ -831,17 +906,23 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     tl_launch_wall = (long long)wall_clock64();
   }
 
-  const bool tagged = !kGeneral || p.sync == SPRNN_SYNC_TAGGED;
+  auto tagged = [&]() { return !kGeneral || p.sync == SPRNN_SYNC_TAGGED; };
   const uint32_t wave_id = (uint32_t)(wg * (block >> 6) + wave);
   int cur = 0;   // LDS copy that holds h_{t-1}; stays 0 unless solo
   long long tl_prev = 0;
-  for (int t = 0; t < steps; ++t) {
+  // One step; false: leave the loop, a wait was given up.  `opening`: step 0 (in the general form any step), which has h_0 in LDS
+  // already.  (With the first step in the loop the compiler would have every other step wait for whatever is in flight.)
+  auto step = [&](int t, auto parity, auto opening) -> bool {
+    constexpr bool kOpening = decltype(opening)::value;
+    Inputs& now = in[decltype(parity)::value];
+    Inputs& next = in[kGeneral ? 0 : 1 - decltype(parity)::value];
     const uint32_t g = p.step_base + (uint32_t)t;         // global step index: the slot number is the timestep tag
     long long ts0 = 0, ts1 = 0, ts2 = 0, ts3 = 0, ts4 = 0, ts5 = 0, ts6 = 0, ts7 = 0;
     unsigned long long repolls = 0;
     float acc[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) acc[b] = 0.0f;
+    int gave_up = 0;  // non-zero: a wait of this step was given up, here or in another wavefront of the workgroup
     int k_done = 0;   // words of this step's operate stage already worked through during the copy
 
     // ---- load: h_{t-1} (published by every workgroup in step t-1) into the other LDS copy
@@ -855,7 +936,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
 #pragma unroll
         for (int k = 0; k < NW; ++k) w_off[k] += delta;
       }
-    } else if (t > 0) {
+    } else if (kGeneral ? t > 0 : !kOpening) {
       const int slot_byte = (int)((g - 1) & (kRingSlotsDev - 1)) * p.h_bytes;
       unsigned char* dst = lds;
       bool failed = false;
@@ -897,7 +978,8 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         // The wavefronts of a workgroup finish a step at different times; they wait for each other here, so that
         // the back-off counts from the moment the whole workgroup has published (the skew inside a workgroup would
         // otherwise have to be covered by a longer back-off in every workgroup).
-        __syncthreads();
+        if constexpr (kGeneral) __syncthreads();
+        else lds_barrier();
         for (int d = 0; d < p.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
         if constexpr (kGeneral) jitter_pause(p.jitter, wave_id, g, 1);
       }
@@ -922,23 +1004,23 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
           ts5 = ts4;
         }
       } else if (!failed) {   // (after a grid barrier every chunk is valid at the first load)
-        if constexpr (FORM == kFormShort) {   // (the host selects these instantiations only for one to three rounds)
-          if (chunk_rounds <= 1) {
-            const int one[1] = {fsrc[0]};
-            failed = !copy_chunks<1, false, kHalf>(ring, slot_byte, one, one, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
-          } else if (chunk_rounds == 2) {
-            const int two[2] = {fsrc[0], fsrc[1]};
-            failed = !copy_chunks<2, false, kHalf>(ring, slot_byte, two, two, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
-          } else {
-            const int three[3] = {fsrc[0], fsrc[1], fsrc[2]};
-            failed = !copy_chunks<3, false, kHalf>(ring, slot_byte, three, three, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
+        const uint32_t* const status_word = p.ctrl + kCtrlStatus;
+        if constexpr (FORM >= 1 && FORM <= 4) {   // (the host selects these for copies of at most this many rounds)
+          int off[FORM];
+#pragma unroll
+          for (int c = 0; c < FORM; ++c) off[c] = fsrc[c];
+          failed = !copy_whole<FORM, kHalf>(ring, slot_byte, off, dst, p.spin_limit, status_word);
+        } else if constexpr (FORM == kFormLong) {
+          for (int r0 = 0; r0 < chunk_rounds && !failed; r0 += 8) {
+            int off[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) off[c] = copy_src(r0 + c);
+            failed = !copy_whole<8, kHalf>(ring, slot_byte, off, dst, p.spin_limit, status_word);
           }
-        } else if constexpr (FORM == kFormFour) {
-          failed = !copy_chunks<4, false, kHalf>(ring, slot_byte, fsrc, fsrc, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
-        } else if (FORM != kFormLong && chunk_rounds <= 4) {
+        } else if (chunk_rounds <= 4) {
           if (!compacted) {
             if (kHalf && chunk_rounds <= 2) {
-              // half the bytes, half the rounds (see kFormShort for why the count is matched)
+              // half the bytes, half the rounds (see the forms for why the count is matched)
               const int two[2] = {fsrc[0], fsrc[1]};
               failed = !copy_chunks<2, false, kHalf>(ring, slot_byte, two, two, dst, p.spin_limit, p.ctrl + kCtrlStatus, repolls);
             } else {
@@ -983,11 +1065,17 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         lds_store_int(s_abort + 4 * (t & 1), 1);
         __hip_atomic_store(p.ctrl + kCtrlStatus, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      __syncthreads();
+      if constexpr (kGeneral) __syncthreads();
+      else lds_barrier();   // (the inputs of the next step stay on their way)
       // every wave of the workgroup leaves together; other workgroups see the status word
       // (readfirstlane: the flag is the same for every lane, and a scalar exit keeps the loop counter scalar)
-      if (__builtin_amdgcn_readfirstlane(lds_load_int(s_abort + 4 * (t & 1)))) break;
+      if constexpr (!kGeneral) gave_up = lds_load_int(s_abort + 4 * (t & 1));
+      if (kGeneral && __builtin_amdgcn_readfirstlane(lds_load_int(s_abort + 4 * (t & 1)))) return false;
       ts7 = tick<TL>(tl_on);
+    }
+    if constexpr (!kGeneral) {
+      fetch_inputs(next, t + 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
     ts0 = tick<TL>(tl_on);
 
@@ -1008,11 +1096,17 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     ts1 = tick<TL>(tl_on);
 
     // ---- reduce over the lanes of the row: every lane ends up with the sum of its own sample
-    const float red = reduce_rows<B>(acc, L, lane);
-    const float pre = red + xn;
+    const float red = kGeneral ? reduce_rows<B>(acc, L, lane) : reduce_rows_select<B, !LSTM>(acc, L, lane);
+    const float pre = red + now.x;
+    // (without options the flag is read ahead of the gathers and looked at behind them: what they read is then of no account)
+    if constexpr (!kGeneral) {
+      if (__builtin_amdgcn_readfirstlane(gave_up)) return false;
+    }
 
     // ---- epilogue and hand-off: publish h_t, write the outputs (only the owners' stores land).
-    // The re-arm stores issued one step ago must be performed before this step's data can be seen, hence the wait.
+    // The re-arm stores issued one step ago must be performed before this step's data can be seen, hence the wait.  (Without
+    // options every wavefront has seen the data of polls that it issued behind those stores in this very step, and a
+    // wavefront's memory operations complete in order: nothing is left to wait for, and the inputs on their way are not.)
     const int slot_byte = (int)(g & (kRingSlotsDev - 1)) * p.h_bytes;
     const int rearm_byte = (int)((g + 2) & (kRingSlotsDev - 1)) * p.h_bytes;
     const int out_soff = time_of(t) * h_step;
@@ -1021,7 +1115,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     if constexpr (LSTM) {
       if (gru) {
         if (owner && gate < 2) stage[stage_write] = pre;
-        if (owner && gate == 2) { stage[stage_write] = red + bhn; stage[stage_write + 1] = xn; }
+        if (owner && gate == 2) { stage[stage_write] = red + bhn; stage[stage_write + 1] = now.x; }
       } else if (owner) {
         stage[stage_write] = pre;
       }
@@ -1049,25 +1143,26 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
 #pragma unroll
       for (int q = 0; q < NG; ++q) dp[q] = 0.0f;
       hval = (GBWD ? red + carry : red) + 0.0f;   // the extra step: dL/dh_0 (the GRU adds the update gate's direct path)
+      const float prev = kGeneral || time_of(t) > 0 ? now.prev : c_first;
       if (t < p.T) {
         if constexpr (GBWD) {
-          const float gr = gn[0], gz = gn[1], gc = gn[2], gq = gn[3];
+          const float gr = now.g[0], gz = now.g[1], gc = now.g[2], gq = now.g[3];
           const float dh = pre + carry;                                  // pre = e_t + U^T v_{t+1}
           dx_n = dh * (1.0f - gz) * fmaf(-gc, gc, 1.0f) + 0.0f;
           dp[0] = dx_n * gq * gr * (1.0f - gr) + 0.0f;                   // + 0.0f: never the "not written" mark
-          dp[1] = dh * (c_prev - gc) * gz * (1.0f - gz) + 0.0f;          // c_prev holds h_{t-1}
+          dp[1] = dh * (prev - gc) * gz * (1.0f - gz) + 0.0f;            // prev is h_{t-1}
           dp[2] = dx_n * gr + 0.0f;
           carry = dh * gz;
         } else {
-          const float gi = gn[0], gf = gn[1], gg = gn[2], go = gn[3];
+          const float gi = now.g[0], gf = now.g[1], gg = now.g[2], go = now.g[3];
           const float tc = tanhf_(c_cur);
           const float dc = fmaf(pre * go, fmaf(-tc, tc, 1.0f), carry);   // pre = dh_t
           dp[0] = dc * gg * gi * (1.0f - gi) + 0.0f;
-          dp[1] = dc * c_prev * gf * (1.0f - gf) + 0.0f;
+          dp[1] = dc * prev * gf * (1.0f - gf) + 0.0f;
           dp[2] = dc * gi * fmaf(-gg, gg, 1.0f) + 0.0f;
           dp[3] = pre * tc * go * (1.0f - go) + 0.0f;
           carry = dc * gf;
-          c_cur = c_prev;
+          c_cur = prev;
         }
       }
       if constexpr (kGeneral) jitter_pause(p.jitter, wave_id, g, 3);
@@ -1077,11 +1172,11 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
           for (int q = 0; q < NG; ++q) *reinterpret_cast<float*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff + q * gate_ring_bytes) = dp[q];
         }
       } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int q = 0; q < NG; ++q)
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dp[q]), ring, ring_voff, slot_byte + q * gate_ring_bytes, kAuxCoherent);
-        if (tagged) {
+        if (tagged()) {
 #pragma unroll
           for (int q = 0; q < NG; ++q)
             __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte + q * gate_ring_bytes, kAuxCoherent);
@@ -1102,13 +1197,10 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
       } else if (p.dh0) {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), dbuf, unit_voff, 0, 0);
       }
-      if (t + 1 < p.T) {
-        xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(t + 1) * x_step, 0));
-        load_saved(time_of(t + 1));
-      }
+      if constexpr (kGeneral) fetch_inputs(next, t + 1);
     } else if constexpr (BWD) {
       if (t < p.T) {
-        const float slope = p.act == SPRNN_ACT_RELU ? (an > 0.0f ? 1.0f : 0.0f) : (p.act == SPRNN_ACT_TANH ? fmaf(-an, an, 1.0f) : 1.0f);
+        const float slope = p.act == SPRNN_ACT_RELU ? (now.a > 0.0f ? 1.0f : 0.0f) : (p.act == SPRNN_ACT_TANH ? fmaf(-now.a, now.a, 1.0f) : 1.0f);
         hval = slope * pre + 0.0f;   // + 0.0f: 0 * negative is -0.0, the "not written" mark
       } else {
         hval = red + 0.0f;           // the extra step: U^T delta_1, no e, no g'
@@ -1133,16 +1225,16 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         if (solo) {
           if (ring_voff != kOutOfRange) *reinterpret_cast<i32x2*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = pair;
         } else {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           i32x2 mark;
           mark.x = (int)kSentinelHalfPair;
           mark.y = (int)kSentinelHalfPair;
           if (local) {
             __builtin_amdgcn_raw_buffer_store_b64(pair, ring, ring_voff, slot_byte, 0);
-            if (tagged) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, 0);
+            if (tagged()) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, 0);
           } else {
             __builtin_amdgcn_raw_buffer_store_b64(pair, ring, ring_voff, slot_byte, kAuxCoherent);
-            if (tagged) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
+            if (tagged()) __builtin_amdgcn_raw_buffer_store_b64(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
           }
         }
       } else {
@@ -1159,28 +1251,28 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         if (solo) {
           if (ring_voff != kOutOfRange) *reinterpret_cast<i32x4*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = column;
         } else {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           i32x4 mark;
           mark.x = mark.y = mark.z = mark.w = (int)kSentinelHalfPair;
           if (local) {
             __builtin_amdgcn_raw_buffer_store_b128(column, ring, ring_voff, slot_byte, 0);
-            if (tagged) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, 0);
+            if (tagged()) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, 0);
           } else {
             __builtin_amdgcn_raw_buffer_store_b128(column, ring, ring_voff, slot_byte, kAuxCoherent);
-            if (tagged) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
+            if (tagged()) __builtin_amdgcn_raw_buffer_store_b128(mark, ring, ring_voff, rearm_byte, kAuxCoherent);
           }
         }
       }
     } else if (solo) {
       if (ring_voff != kOutOfRange) *reinterpret_cast<float*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = hval;
     } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (local) {   // every workgroup of the part shares one L2: plain stores reach it and need not go further
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), ring, ring_voff, slot_byte, 0);
-        if (tagged) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, 0);
+        if (tagged()) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, 0);
       } else {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hval), ring, ring_voff, slot_byte, kAuxCoherent);
-        if (tagged) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, kAuxCoherent);
+        if (tagged()) __builtin_amdgcn_raw_buffer_store_b32((int)kSentinelBits, ring, ring_voff, rearm_byte, kAuxCoherent);
       }
     }
     if (BWD && t == p.T) {
@@ -1203,10 +1295,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, kept[q]), gbuf, gate_voff, out_soff * 4 + q * H * 4, 0);
       }
     }
-    if (t + 1 < p.T) {
-      xn = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time_of(t + 1) * x_step, 0));
-      if constexpr (BWD) an = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(abuf, x_voff, time_of(t + 1) * h_step, 0));
-    }
+    if constexpr (kGeneral) fetch_inputs(next, t + 1);
     }
     if constexpr (WGRAD) {
       if (t + 1 < steps) load_side(t + 1);
@@ -1233,6 +1322,18 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         s_tl[9] += 1ull;                                    // steps counted
       }
       tl_prev = ts3;
+    }
+    return true;
+  };
+  using even = std::integral_constant<int, 0>;
+  using odd = std::integral_constant<int, 1>;
+  if constexpr (kGeneral) {
+    for (int t = 0; t < steps; ++t)
+      if (!step(t, even(), std::true_type())) break;
+  } else if (steps > 0 && step(0, even(), std::true_type())) {
+    for (int t = 1; t < steps; t += 2) {
+      if (!step(t, odd(), std::false_type())) break;
+      if (t + 1 >= steps || !step(t + 1, even(), std::false_type())) break;
     }
   }
   if constexpr (WGRAD) {   // the sums leave through the packer's word -> CSR position map (of the transposed matrix)
@@ -1266,9 +1367,11 @@ static const void* pick_nw(int nw) {
     case 16: return (const void*)persistent_kernel<B, 16, CELL, TL, FORM>;
     case 24: return (const void*)persistent_kernel<B, 24, CELL, TL, FORM>;
     case 32: return (const void*)persistent_kernel<B, 32, CELL, TL, FORM>;
-    case 48: return (const void*)persistent_kernel<B, 48, CELL, TL, FORM>;
+    case 48:
+      if constexpr (FORM == 1 || FORM == 2) return nullptr;
+      else return (const void*)persistent_kernel<B, 48, CELL, TL, FORM>;
     case 64:   // (with the weight gradient fused in, batch 8 and 64 words per lane no longer fit in registers: not built)
-      if constexpr (B == 8 && (CELL == 4 || CELL == 6 || CELL == 8)) return nullptr;
+      if constexpr ((B == 8 && (CELL == 4 || CELL == 6 || CELL == 8)) || FORM == 1 || FORM == 2) return nullptr;
       else return (const void*)persistent_kernel<B, 64, CELL, TL, FORM>;
     default: return nullptr;
   }
