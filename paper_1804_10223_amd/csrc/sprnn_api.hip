@@ -363,12 +363,17 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
     }
   };
   if (const void* k = plain_kernel_for(m.cell)) h->kernel = k;
+  int solo_bytes = 0;   // LDS of the two copies in the form for a single workgroup
+  if (!pool && m.grid == 1 && m.h_bytes <= kSoloCopyBytes - 16 && m.sync == SPRNN_SYNC_TAGGED && !m.jitter && !m.narrow && !m.half && !m.timeline) {
+    const void* k = persistent_solo_kernel_for(m.batch, m.template_words, m.cell);
+    if (k) { h->kernel = k; solo_bytes = 2 * kSoloCopyBytes; }
+  }
   if (!h->kernel) { release(h); return SPRNN_ERR_UNSUPPORTED; }
 
   // One workgroup per CU: ask for more than half of a CU's LDS so that two can never share one.
   // (sharedMemPerMultiprocessor is not used: some runtime versions report the whole chip's LDS there.)
   const int lds_cu = prop.sharedMemPerBlockOptin > 0 ? (int)prop.sharedMemPerBlockOptin : (int)prop.sharedMemPerBlock;
-  const int lds_need = m.lds_bytes + kLdsTailBytes + m.stage_bytes;      // h + the abort flags (+ the LSTM hand-over area)
+  const int lds_need = std::max(m.lds_bytes, solo_bytes) + kLdsTailBytes + m.stage_bytes;   // h + the abort flags (+ the LSTM hand-over area)
   h->launch_lds = std::max(lds_need, lds_cu / 2 + 1024);
   if (h->launch_lds > lds_cu) { release(h); return SPRNN_ERR_CAPACITY; }
   // (the per-kernel limit on dynamic LDS is state shared by every handle that uses the same instantiation: it is

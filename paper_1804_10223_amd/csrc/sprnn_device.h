@@ -21,6 +21,7 @@ constexpr int kCellBackward = 100;                // persistent_kernel_for: back
 constexpr int kCellBackwardGrad = 101;            // the same with the weight gradient fused in
 constexpr int kCellLstmBackwardGrad = 102;        // backward pass of the LSTM with the weight gradient fused in
 constexpr int kCellGruBackwardGrad = 103;         // backward pass of the GRU with the weight gradient fused in
+constexpr int kSoloCopyBytes = 32768;             // single workgroup, form without options: distance of the two LDS copies of h
 constexpr int kTimelineSlots = 16;                // 64-bit accumulators per workgroup in the phase timeline
 constexpr int kLdsTailBytes = 16 + 8 * kTimelineSlots;   // LDS after h: abort flags, timeline sums
 
@@ -89,6 +90,7 @@ const void* persistent_plain2_kernel_for(int batch, int template_words, int cell
 const void* persistent_plain3_kernel_for(int batch, int template_words, int cell, bool half);
 const void* persistent_plain4_kernel_for(int batch, int template_words, int cell, bool half);
 const void* persistent_plain5_kernel_for(int batch, int template_words, int cell, bool half);
+const void* persistent_solo_kernel_for(int batch, int template_words, int cell);              // the same for a single workgroup (per part): forward passes, h of at most kSoloCopyBytes - 16
 const void* persistent_half_kernel_for(int batch, int template_words);                       // vanilla forward with h exchanged as binary16 (batch 4, 8)
 const void* persistent_narrow_kernel_for(int batch, int template_words);                     // vanilla forward, batch 4, 4-byte gathers (ablation)
 const void* persistent_backward_kernel_for(int batch, int template_words, int cell);         // kCellBackward, kCellBackwardGrad

@@ -278,12 +278,13 @@ __device__ __forceinline__ float dot_column(const float (&s)[B], const Column<B>
 
 // With GRAD, the gathered column also feeds the weight gradient of its nonzero: g[j] += sum_b side[b] * column[b]
 // (backward pass: the column is delta_{t+1} of the nonzero's column, side is the forward output of the lane's row).
-template <int B, int N, bool GRAD = false, bool NARROW = false>
+// AT: bytes added to every address (an immediate of the read).
+template <int B, int N, bool GRAD = false, bool NARROW = false, int AT = 0>
 __device__ __forceinline__ void mac_words(float (&acc)[B], const uint32_t* off, const float* wv, int plane_bytes,
                                           float* g = nullptr, const float (*side)[B] = nullptr) {
   Column<B> c[N];
 #pragma unroll
-  for (int j = 0; j < N; ++j) c[j] = gather_column<B, NARROW>(off[j], plane_bytes);
+  for (int j = 0; j < N; ++j) c[j] = gather_column<B, NARROW>(off[j] + AT, plane_bytes);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int j = 0; j < N; ++j) {
@@ -352,26 +353,43 @@ constexpr int kOutOfRange = 0x7ffffff0;   // a byte offset beyond every buffer t
 // The n_w (wavefront-uniform) packed words of a lane (w_off: absolute LDS addresses of their columns): gathers in
 // groups of four so the LDS reads are issued back to back; no early exit, so every register index stays static.
 // GS: words per group, 4 or 8 (see the kernel's choice).
-template <int B, int NW, bool GRAD = false, int GS = 4, bool NARROW = false>
+template <int B, int NW, bool GRAD = false, int GS = 4, bool NARROW = false, int AT = 0>
 __device__ __forceinline__ void operate(float (&acc)[B], const uint32_t (&w_off)[NW], const float (&w_val)[NW], int n_w,
                                         int plane_bytes, float* g = nullptr, const float (*side)[B] = nullptr) {
 #pragma unroll
   for (int k = 0; k < NW; k += GS) {
     float* gk = GRAD ? g + k : nullptr;
     if (k + GS <= n_w) {
-      mac_words<B, GS, GRAD, NARROW>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
+      mac_words<B, GS, GRAD, NARROW, AT>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
     } else if (k < n_w) {   // ragged tail
       const int rem = n_w - k;
       if (GS == 8 && rem >= 4) {
-        mac_words<B, 4, GRAD, NARROW>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
+        mac_words<B, 4, GRAD, NARROW, AT>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
         float* gk4 = GRAD ? gk + 4 : nullptr;   // the second half's sums belong to words k + 4 ..
-        if (rem == 7) mac_words<B, 3, GRAD, NARROW>(acc, &w_off[k + 4], &w_val[k + 4], plane_bytes, gk4, side);
-        else if (rem == 6) mac_words<B, 2, GRAD, NARROW>(acc, &w_off[k + 4], &w_val[k + 4], plane_bytes, gk4, side);
-        else if (rem == 5) mac_words<B, 1, GRAD, NARROW>(acc, &w_off[k + 4], &w_val[k + 4], plane_bytes, gk4, side);
-      } else if (rem == 3) mac_words<B, 3, GRAD, NARROW>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
-      else if (rem == 2) mac_words<B, 2, GRAD, NARROW>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
-      else mac_words<B, 1, GRAD, NARROW>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
+        if (rem == 7) mac_words<B, 3, GRAD, NARROW, AT>(acc, &w_off[k + 4], &w_val[k + 4], plane_bytes, gk4, side);
+        else if (rem == 6) mac_words<B, 2, GRAD, NARROW, AT>(acc, &w_off[k + 4], &w_val[k + 4], plane_bytes, gk4, side);
+        else if (rem == 5) mac_words<B, 1, GRAD, NARROW, AT>(acc, &w_off[k + 4], &w_val[k + 4], plane_bytes, gk4, side);
+      } else if (rem == 3) mac_words<B, 3, GRAD, NARROW, AT>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
+      else if (rem == 2) mac_words<B, 2, GRAD, NARROW, AT>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
+      else mac_words<B, 1, GRAD, NARROW, AT>(acc, &w_off[k], &w_val[k], plane_bytes, gk, side);
     }
+  }
+}
+
+// The operate stage of the forms without options, batch <= 4.  Nearly every wavefront fills its instantiation to within eight
+// words (NW is chosen so): groups of eight gathers, and then the last LAST - 4 or LAST at once, so that there is one choice to
+// make and the LDS is waited for as few times as the registers allow.  Words beyond the wavefront's own are there with weight 0
+// and the address of 16 zero bytes: up to three idle gathers per lane cost less than the three or four uniform branches
+// (each of them several scalar instructions and a jump or two) that picking their number takes, and add exactly nothing.
+template <int B, int NW, int LAST, int AT>
+__device__ __forceinline__ void operate_plain(float (&acc)[B], const uint32_t (&w_off)[NW], const float (&w_val)[NW], int n_w, int plane_bytes) {
+  if (n_w > NW - 8) {
+#pragma unroll
+    for (int k = 0; k < NW - LAST; k += 8) mac_words<B, 8, false, false, AT>(acc, &w_off[k], &w_val[k], plane_bytes);
+    if (n_w > NW - 4) mac_words<B, LAST, false, false, AT>(acc, &w_off[NW - LAST], &w_val[NW - LAST], plane_bytes);
+    else mac_words<B, LAST - 4, false, false, AT>(acc, &w_off[NW - LAST], &w_val[NW - LAST], plane_bytes);
+  } else {
+    operate<B, NW, false, 8, false, AT>(acc, w_off, w_val, n_w, plane_bytes);
   }
 }
 
@@ -603,11 +621,14 @@ __device__ __forceinline__ bool copy_two_parts(__amdgpu_buffer_rsrc_t ring, int 
 // in the last batch, or with all rounds in flight at once, 5120 x batch 4 (seven rounds) took 3 % longer and 2560 x batch 8
 // (ten) 5 to 12 %: the loads past the end all ask for one line, and while the first batch of eight is on its way the slower
 // workgroups publish what the second asks for.
-constexpr int kFormGeneral = 0, kFormLong = 5;   // 1, 2, 3, 4: that many rounds
+// kFormSolo is the forward pass (0, 1, 2) of a single workgroup (or of one per part): nothing is exchanged, h alternates between
+// two copies in LDS at a fixed distance (which the reads take as an immediate: no address changes from step to step), and the
+// inputs are requested four steps ahead, since a step of 0.3 us is shorter than a first touch of device memory.
+constexpr int kFormGeneral = 0, kFormLong = 5, kFormSolo = 6;   // 1, 2, 3, 4: that many rounds
 
 template <int B, int NW, int CELL, bool TL, int FORM = kFormGeneral>
 __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL == 8) && NW >= 24 ? 512 : 768)) void persistent_kernel(const KernelArgs p) {
-  constexpr bool kGeneral = FORM == kFormGeneral;
+  constexpr bool kGeneral = FORM == kFormGeneral, kSolo = FORM == kFormSolo;
   constexpr bool LSTM = CELL == 1 || CELL == 2;   // gated cell: four row groups per unit, cell lanes
   constexpr bool LBWD = CELL >= 5 && CELL <= 8;                // backward pass of a gated cell
   constexpr bool GBWD = CELL == 7 || CELL == 8;                // ... of the GRU
@@ -691,8 +712,8 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   }
   // samples of the call, first sample of this part (which the lanes' offsets carry)
   const int Bt = kParts ? p.batch : B, b0 = kParts ? part * B : 0;
-  const bool solo = kGeneral && grid_x == 1;   // no other workgroup to exchange with
-  unsigned char* const lds_tail = lds + (solo ? 2 : 1) * p.lds_h_bytes;
+  const bool solo = kSolo || (kGeneral && grid_x == 1);   // no other workgroup to exchange with
+  unsigned char* const lds_tail = lds + (kSolo ? 2 * kSoloCopyBytes : (solo ? 2 : 1) * p.lds_h_bytes);
   // abort flags, indexed by step parity so that a fast wave's next-step flag cannot be read one step early
   const uint32_t s_abort = lds_address(lds_tail);   // LDS address of the two flags
   unsigned long long* s_tl = reinterpret_cast<unsigned long long*>(lds_tail + 16);
@@ -716,12 +737,16 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   constexpr bool kHalf = CELL == 11;   // h travels and sits in LDS as binary16: [H][B] halves, 8 bytes per column at batch 4, 16 at batch 8
   static_assert(!kHalf || B == 4 || B == 8, "binary16 activations are built for batch 4 and 8");
   const int k_early = kTwoPart ? __builtin_amdgcn_readfirstlane(p.wave_early[wg * (block >> 6) + wave]) : 0;
+  // 16 bytes of zeros that words beyond a wavefront's own read (operate_plain): where the general form has its timeline sums; for
+  // the two copies of a single workgroup at the end of each
+  const uint32_t zeros = lds_address(kSolo ? lds + kSoloCopyBytes - 16 : lds_tail + 16);
   uint32_t w_off[NW];
   float w_val[NW];
 #pragma unroll
   for (int k = 0; k < NW; ++k) {
     const uint32_t word = (k < n_w) ? p.words[((size_t)wg * NW + k) * block + tid] : 0u;
     w_off[k] = lds_address(lds) + ((word >> 16) << p.index_shift);   // (the 16-bit index counts columns when byte offsets would not fit)
+    if (!kGeneral && k >= n_w) w_off[k] = zeros;
     w_val[k] = half_bits_to_float(word);
   }
   // After the reduction (reduce_scatter) the first B lanes of a row group each own one sample of the row: they
@@ -779,7 +804,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   // indices past the end are clamped to the last chunk (a few lanes then copy it twice), which keeps that path free
   // of per-lane branches.  With compaction the sources come from the workgroup's copy list, the destinations are
   // consecutive, and an entry past the end of the list is empty (src out of range, dst < 0).
-  // The first four rounds have their sources in registers.
+  // The first rounds have their sources in registers: four, in the form for long copies eight (where they fit).
   const int n4 = p.h_bytes >> 4;               // 16-byte chunks in a ring slot
   const int last_chunk = n4 - 1;
   const int chunk_rounds = compacted ? p.fill_rows : (n4 + block - 1) / block;
@@ -789,12 +814,17 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     return min(tid + c * block, last_chunk) * 16;
   };
   auto copy_dst = [&](int c, int src) -> int { return compacted ? (src == kOutOfRange ? -1 : (tid + c * block) * 16) : src; };
-  int fsrc[4];
+  constexpr int kHeld = FORM == kFormLong && !(LSTM && B == 8 && NW >= 32) ? 8 : 4;
+  int fsrc[kHeld];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) fsrc[c] = copy_src(c);
+  for (int c = 0; c < kHeld; ++c) fsrc[c] = copy_src(c);
 
   // ---- h_0 into LDS copy 0, cell state into registers
   if (tid < 2) lds_store_int(s_abort + 4 * tid, 0);
+  if (!kGeneral && tid < 4) {
+    lds_store_int(zeros + 4 * tid, 0);
+    if (kSolo) lds_store_int(zeros + kSoloCopyBytes + 4 * tid, 0);
+  }
   if (TL && tid < kTimelineSlots) s_tl[tid] = 0ull;
   if (!compacted) {
     for (int e = tid; e < H * B; e += block) {
@@ -845,7 +875,8 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   // (scalar offsets select the timestep and the sample; the host keeps one launch below 1 GiB of x, so an
   // out-of-range lane offset stays out of range whatever scalar offset is added to it)
   struct Inputs { float x, a, g[4], prev; };
-  Inputs in[2] = {};
+  constexpr int kSets = kGeneral ? 1 : (kSolo ? 4 : 2);
+  Inputs in[kSets] = {};
   float c_cur = 0.0f, carry = 0.0f;   // LSTM backward: c_t; carry = dc_{t+1} f_{t+1}
   auto read_inputs = [&](Inputs& to, int time) {
     to.x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_voff, time * x_step, 0));
@@ -871,6 +902,10 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   const float c_first = LBWD && !kGeneral ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(c0buf, unit_voff, 0, 0)) : 0.0f;
   if constexpr (LBWD && !GBWD) c_cur = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cfbuf, unit_voff, time_of(0) * unit_step, 0));
   read_inputs(in[0], time_of(0));
+  if constexpr (kSolo) {
+#pragma unroll
+    for (int t = 1; t < kSets; ++t) fetch_inputs(in[t], t);
+  }
   // weight gradient: forward output of this lane's row for every sample (h_0 in the extra step), one accumulator per word
   float side[B], gacc[WGRAD ? NW : 1];
   const int row_voff = row >= 0 ? row * 4 : kOutOfRange;
@@ -908,14 +943,17 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
 
   auto tagged = [&]() { return !kGeneral || p.sync == SPRNN_SYNC_TAGGED; };
   const uint32_t wave_id = (uint32_t)(wg * (block >> 6) + wave);
-  int cur = 0;   // LDS copy that holds h_{t-1}; stays 0 unless solo
+  int cur = 0;   // LDS copy that holds h_{t-1} (general form); stays 0 unless solo
   long long tl_prev = 0;
   // One step; false: leave the loop, a wait was given up.  `opening`: step 0 (in the general form any step), which has h_0 in LDS
   // already.  (With the first step in the loop the compiler would have every other step wait for whatever is in flight.)
   auto step = [&](int t, auto parity, auto opening) -> bool {
     constexpr bool kOpening = decltype(opening)::value;
-    Inputs& now = in[decltype(parity)::value];
-    Inputs& next = in[kGeneral ? 0 : 1 - decltype(parity)::value];
+    constexpr int kSet = decltype(parity)::value;
+    Inputs& now = in[kSet];
+    Inputs& next = in[kGeneral || kSolo ? kSet : 1 - kSet];
+    constexpr int kRead = kSolo && (kSet & 1) ? kSoloCopyBytes : 0;               // the copy of h that this step reads
+    auto write_at = [&]() { return kSolo ? kSoloCopyBytes - kRead : (cur ^ 1) * p.lds_h_bytes; };   // solo: the one that it writes
     const uint32_t g = p.step_base + (uint32_t)t;         // global step index: the slot number is the timestep tag
     long long ts0 = 0, ts1 = 0, ts2 = 0, ts3 = 0, ts4 = 0, ts5 = 0, ts6 = 0, ts7 = 0;
     unsigned long long repolls = 0;
@@ -926,7 +964,9 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     int k_done = 0;   // words of this step's operate stage already worked through during the copy
 
     // ---- load: h_{t-1} (published by every workgroup in step t-1) into the other LDS copy
-    if (solo) {
+    if constexpr (kSolo) {
+      if constexpr (!kOpening) lds_barrier();
+    } else if (solo) {
       // a single workgroup keeps h in LDS: the owners wrote h_{t-1} straight into the other copy
       if (t > 0) {
         __syncthreads();
@@ -1011,7 +1051,8 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
           for (int c = 0; c < FORM; ++c) off[c] = fsrc[c];
           failed = !copy_whole<FORM, kHalf>(ring, slot_byte, off, dst, p.spin_limit, status_word);
         } else if constexpr (FORM == kFormLong) {
-          for (int r0 = 0; r0 < chunk_rounds && !failed; r0 += 8) {
+          if constexpr (kHeld == 8) failed = !copy_whole<8, kHalf>(ring, slot_byte, fsrc, dst, p.spin_limit, status_word);
+          for (int r0 = kHeld == 8 ? 8 : 0; r0 < chunk_rounds && !failed; r0 += 8) {
             int off[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) off[c] = copy_src(r0 + c);
@@ -1073,7 +1114,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
       if (kGeneral && __builtin_amdgcn_readfirstlane(lds_load_int(s_abort + 4 * (t & 1)))) return false;
       ts7 = tick<TL>(tl_on);
     }
-    if constexpr (!kGeneral) {
+    if constexpr (!kGeneral && !kSolo) {
       fetch_inputs(next, t + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1091,7 +1132,9 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
       // waits for the LDS: 2.5 % on the headline shape); four otherwise: eight would spill at batch 8, measured no
       // better at batch 2 and for vanilla cells at batch 1, 15-20 % slower for the gated cells at batch 1, and at
       // batch 4 a few per cent either way for them depending on the words per lane.
-      operate<B, NW, false, (B == 4 && !LSTM) ? 8 : 4, CELL == 9>(acc, w_off, w_val, n_w, plane_bytes);
+      constexpr int kLast = B == 1 ? (NW <= 32 ? NW : 16) : (B == 2 ? (NW <= 24 ? NW : 16) : (NW <= 16 || NW >= 48 ? (NW < 16 ? NW : 16) : 8));
+      if constexpr (kGeneral || B == 8) operate<B, NW, false, (B == 4 && !LSTM) ? 8 : 4, CELL == 9, kRead>(acc, w_off, w_val, n_w, plane_bytes);
+      else operate_plain<B, NW, kLast, kRead>(acc, w_off, w_val, n_w, plane_bytes);
     }
     ts1 = tick<TL>(tl_on);
 
@@ -1099,7 +1142,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     const float red = kGeneral ? reduce_rows<B>(acc, L, lane) : reduce_rows_select<B, !LSTM>(acc, L, lane);
     const float pre = red + now.x;
     // (without options the flag is read ahead of the gathers and looked at behind them: what they read is then of no account)
-    if constexpr (!kGeneral) {
+    if constexpr (!kGeneral && !kSolo) {
       if (__builtin_amdgcn_readfirstlane(gave_up)) return false;
     }
 
@@ -1169,7 +1212,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
       if (solo) {
         if (ring_voff != kOutOfRange) {
 #pragma unroll
-          for (int q = 0; q < NG; ++q) *reinterpret_cast<float*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff + q * gate_ring_bytes) = dp[q];
+          for (int q = 0; q < NG; ++q) *reinterpret_cast<float*>(lds + write_at() + ring_voff + q * gate_ring_bytes) = dp[q];
         }
       } else {
         if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1223,7 +1266,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         pair.x = mine | (s1 << 16);
         pair.y = s2 | (s3 << 16);
         if (solo) {
-          if (ring_voff != kOutOfRange) *reinterpret_cast<i32x2*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = pair;
+          if (ring_voff != kOutOfRange) *reinterpret_cast<i32x2*>(lds + write_at() + ring_voff) = pair;
         } else {
           if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           i32x2 mark;
@@ -1249,7 +1292,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         column.z = __builtin_amdgcn_update_dpp(0, both, 0x55, 0xf, 0xf, false);          // lane 1: samples 4, 5
         column.w = __builtin_amdgcn_update_dpp(0, both, 0xFF, 0xf, 0xf, false);          // lane 3: samples 6, 7
         if (solo) {
-          if (ring_voff != kOutOfRange) *reinterpret_cast<i32x4*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = column;
+          if (ring_voff != kOutOfRange) *reinterpret_cast<i32x4*>(lds + write_at() + ring_voff) = column;
         } else {
           if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           i32x4 mark;
@@ -1264,7 +1307,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
         }
       }
     } else if (solo) {
-      if (ring_voff != kOutOfRange) *reinterpret_cast<float*>(lds + (cur ^ 1) * p.lds_h_bytes + ring_voff) = hval;
+      if (ring_voff != kOutOfRange) *reinterpret_cast<float*>(lds + write_at() + ring_voff) = hval;
     } else {
       if constexpr (kGeneral) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (local) {   // every workgroup of the part shares one L2: plain stores reach it and need not go further
@@ -1296,6 +1339,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
       }
     }
     if constexpr (kGeneral) fetch_inputs(next, t + 1);
+    if constexpr (kSolo) fetch_inputs(next, t + kSets);   // (the set that this step has used up)
     }
     if constexpr (WGRAD) {
       if (t + 1 < steps) load_side(t + 1);
@@ -1330,6 +1374,18 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   if constexpr (kGeneral) {
     for (int t = 0; t < steps; ++t)
       if (!step(t, even(), std::true_type())) break;
+  } else if constexpr (kSolo) {
+    step(0, even(), std::true_type());
+    int t = 1;
+    for (; t + 4 <= steps; t += 4) {
+      step(t, odd(), std::false_type());
+      step(t + 1, std::integral_constant<int, 2>(), std::false_type());
+      step(t + 2, std::integral_constant<int, 3>(), std::false_type());
+      step(t + 3, even(), std::false_type());
+    }
+    if (t < steps) step(t, odd(), std::false_type());
+    if (t + 1 < steps) step(t + 1, std::integral_constant<int, 2>(), std::false_type());
+    if (t + 2 < steps) step(t + 2, std::integral_constant<int, 3>(), std::false_type());
   } else if (steps > 0 && step(0, even(), std::true_type())) {
     for (int t = 1; t < steps; t += 2) {
       if (!step(t, odd(), std::false_type())) break;
@@ -1366,7 +1422,9 @@ static const void* pick_nw(int nw) {
     case 8: return (const void*)persistent_kernel<B, 8, CELL, TL, FORM>;
     case 16: return (const void*)persistent_kernel<B, 16, CELL, TL, FORM>;
     case 24: return (const void*)persistent_kernel<B, 24, CELL, TL, FORM>;
-    case 32: return (const void*)persistent_kernel<B, 32, CELL, TL, FORM>;
+    case 32:   // (a single workgroup's four sets of inputs do not fit beside eight samples and 32 words)
+      if constexpr (FORM == kFormSolo && B == 8) return nullptr;
+      else return (const void*)persistent_kernel<B, 32, CELL, TL, FORM>;
     case 48:
       if constexpr (FORM == 1 || FORM == 2) return nullptr;
       else return (const void*)persistent_kernel<B, 48, CELL, TL, FORM>;
@@ -1391,6 +1449,13 @@ static const void* pick_b(int batch, int nw) {
 // The forms without options (see the kernel): forward passes, kCellBackward, SPRNN_CELL_*_BACKWARD; `half` = binary16 activations.
 template <int FORM>
 static const void* pick_plain(int batch, int nw, int cell, bool half) {
+  if constexpr (FORM == kFormSolo) {
+    if (half) return nullptr;
+    if (cell >= SPRNN_ACT_RELU && cell <= SPRNN_ACT_IDENTITY) return pick_b<0, false, FORM>(batch, nw);
+    if (cell == SPRNN_CELL_LSTM) return pick_b<1, false, FORM>(batch, nw);
+    if (cell == SPRNN_CELL_GRU) return pick_b<2, false, FORM>(batch, nw);
+    return nullptr;
+  } else {
   if (half) return batch == 4 ? pick_nw<4, 11, false, FORM>(nw) : (batch == 8 ? pick_nw<8, 11, false, FORM>(nw) : nullptr);
   if (cell >= SPRNN_ACT_RELU && cell <= SPRNN_ACT_IDENTITY) return pick_b<0, false, FORM>(batch, nw);
   if (cell == SPRNN_CELL_LSTM) return pick_b<1, false, FORM>(batch, nw);
@@ -1399,6 +1464,7 @@ static const void* pick_plain(int batch, int nw, int cell, bool half) {
   if (cell == SPRNN_CELL_LSTM_BACKWARD) return pick_b<5, false, FORM>(batch, nw);
   if (cell == SPRNN_CELL_GRU_BACKWARD) return pick_b<7, false, FORM>(batch, nw);
   return nullptr;
+  }
 }
 
 }  // namespace sprnn
