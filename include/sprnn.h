@@ -185,7 +185,7 @@ int sprnn_create(sprnn_handle_t* out, int hidden, int batch, int activation, con
  * the layer needs only a few more than one XCD has compute units, or another number of wavefronts per workgroup when
  * that copies a large h with at least a tenth fewer loads; and twice and half the lanes per row.  With several samples the
  * batch shared out to 2, 4 and 8 parts (SPRNN_XCD_PARTS) is measured as well, where the layer fits that share of the CUs.
- * Creation then takes 0.1 to 0.3 s depending on the size of the matrix (the packing runs on several host threads).
+ * Creation then takes 0.1 to 0.4 s depending on the size of the matrix (the packing runs on several host threads).
  * Results are bit-for-bit the same from call to call on one handle, and between handles with the same lanes_per_row
  * (which fixes the order in which a row's products are added, however the samples are shared out); a caller who needs that
  * across handles passes the value sprnn_get_info reported for the first. */

@@ -614,7 +614,8 @@ __device__ __forceinline__ bool copy_two_parts(__amdgpu_buffer_rsrc_t ring, int 
 // FORM: kFormGeneral has every option of the handle as a run-time branch: a grid barrier, pauses, column compaction, a single
 // workgroup, any number of copy rounds (one 16-byte piece per lane and round).  The passes 0, 1, 2, 3, 5, 7 and 11 exist
 // without all that, for the tagged hand-off with h copied whole: a step of the general form is some 700 instructions of
-// which the path taken is a third, reached over taken branches and with its uniform values in spilled scalar registers.
+// which the path taken is a third, reached over taken branches and with its uniform values in spilled scalar registers
+// (2304 x batch 4 in two parts 1.72 -> 1.62 us per step without them, 1152 x batch 4 in four 1.03 -> 0.97).
 // They differ in the copy: forms 1 to 4 have exactly that many rounds (the general code always issues four, of which the ones
 // past the end re-fetch the clamped last piece: 0.1 us per surplus round), kFormLong as many groups
 // of eight as it takes.  Copies of more than four rounds gain nothing by exact counts: with exactly the rounds that are left
@@ -623,7 +624,8 @@ __device__ __forceinline__ bool copy_two_parts(__amdgpu_buffer_rsrc_t ring, int 
 // workgroups publish what the second asks for.
 // kFormSolo is the forward pass (0, 1, 2) of a single workgroup (or of one per part): nothing is exchanged, h alternates between
 // two copies in LDS at a fixed distance (which the reads take as an immediate: no address changes from step to step), and the
-// inputs are requested four steps ahead, since a step of 0.3 us is shorter than a first touch of device memory.
+// inputs are requested four steps ahead, since a step of 0.3 us is shorter than a first touch of device memory
+// (256 x batch 1, 16 steps: 13.0 -> 8.9 us a call).
 constexpr int kFormGeneral = 0, kFormLong = 5, kFormSolo = 6;   // 1, 2, 3, 4: that many rounds
 
 template <int B, int NW, int CELL, bool TL, int FORM = kFormGeneral>
@@ -645,7 +647,8 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   // matrix, advances B of the p.batch samples and exchanges with nobody else: a part copies its own samples' share of
   // h instead of all of it and waits for its own workgroups only.  The dispatcher deals workgroups to the eight XCDs in
   // turn, so a part that takes consecutive XCDs has 1 / p.parts of the traffic of every L2 to itself; that only is a
-  // matter of speed, the exchange works wherever the workgroups run.
+  // matter of speed, the exchange works wherever the workgroups run.  (us per step, one part / several, in the general form: LSTM
+  // 1024 x batch 8 2.07 / 1.67, its backward pass 3.32 / 2.4, 1152 x batch 4 1.21 / 1.03, 2304 x batch 4 1.78 / 1.72.)
   // One-XCD mode (at most 32 workgroups a part): the launch holds eight times the workgroups of a part.  Every workgroup
   // reports the XCD it runs on, waits until all have reported, and the first p.parts XCDs that received enough of them
   // take a part each; their workgroups number themselves in the order they arrived, all others leave.  The exchange then
@@ -742,9 +745,13 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   const uint32_t zeros = lds_address(kSolo ? lds + kSoloCopyBytes - 16 : lds_tail + 16);
   uint32_t w_off[NW];
   float w_val[NW];
+  uint32_t held[NW];
+#pragma unroll
+  for (int k = 0; k < NW; ++k)   // (without options: every slot, on its way together with the count; the unused ones hold zeros)
+    held[k] = (!kGeneral || k < n_w) ? p.words[((size_t)wg * NW + k) * block + tid] : 0u;
 #pragma unroll
   for (int k = 0; k < NW; ++k) {
-    const uint32_t word = (k < n_w) ? p.words[((size_t)wg * NW + k) * block + tid] : 0u;
+    const uint32_t word = held[k];
     w_off[k] = lds_address(lds) + ((word >> 16) << p.index_shift);   // (the 16-bit index counts columns when byte offsets would not fit)
     if (!kGeneral && k >= n_w) w_off[k] = zeros;
     w_val[k] = half_bits_to_float(word);
@@ -827,11 +834,21 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   }
   if (TL && tid < kTimelineSlots) s_tl[tid] = 0ull;
   if (!compacted) {
-    for (int e = tid; e < H * B; e += block) {
-      const int j = e / B, b = e % B;
-      const float v = p.h0 ? p.h0[(size_t)(b0 + b) * H + j] : 0.0f;
-      if constexpr (kHalf) *reinterpret_cast<_Float16*>(lds + (j * B + b) * 2) = (_Float16)v;
-      else *reinterpret_cast<float*>(lds + lds_offset<B>(j, b, H)) = v;
+    constexpr int kBatch = 8;   // reads in flight: a lane has one element per round of the copy and more
+    for (int e0 = tid; e0 < H * B; e0 += kBatch * block) {
+      float v[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int e = min(e0 + i * block, H * B - 1);
+        v[i] = p.h0 ? p.h0[(size_t)(b0 + e % B) * H + e / B] : 0.0f;
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int e = e0 + i * block, j = e / B, b = e % B;
+        if (e >= H * B) continue;
+        if constexpr (kHalf) *reinterpret_cast<_Float16*>(lds + (j * B + b) * 2) = (_Float16)v[i];
+        else *reinterpret_cast<float*>(lds + lds_offset<B>(j, b, H)) = v[i];
+      }
     }
   } else {
     // the same chunks the step loop will copy, taken from the caller's [B][H] array
@@ -1126,12 +1143,12 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     } else if constexpr (kTwoPart) {
       operate_span<B, NW>(acc, w_off, w_val, k_done, n_w, plane_bytes);
     } else if constexpr (kHalf) {
-      operate_half<NW, B>(acc, w_off, w_val, n_w);
+      operate_half<NW, B>(acc, w_off, w_val, n_w);   // (the last 16 words at once, as in operate_plain: 2560 x batch 8 1.46 -> 1.56 us)
     } else {
-      // Groups of eight words for batch 4 in the one-row-per-unit layouts (eight gathers in flight, half as many
-      // waits for the LDS: 2.5 % on the headline shape); four otherwise: eight would spill at batch 8, measured no
-      // better at batch 2 and for vanilla cells at batch 1, 15-20 % slower for the gated cells at batch 1, and at
-      // batch 4 a few per cent either way for them depending on the words per lane.
+      // General form: groups of eight words for batch 4 in the one-row-per-unit layouts (2.5 % on the headline shape), four
+      // otherwise: eight would spill at batch 8, and behind that form's branches gained nothing at batch 1 and 2.  Without options:
+      // as many of the last words at once as fit beside the two registers per word (2304 x batch 4: groups of four 1.56 us per
+      // step, of eight 1.43, this 1.37; LSTM 1024 x batch 8: 1.50, 1.36, 1.27).
       constexpr int kLast = B == 1 ? (NW <= 32 ? NW : 16) : (B == 2 ? (NW <= 24 ? NW : 16) : (NW <= 16 || NW >= 48 ? (NW < 16 ? NW : 16) : 8));
       if constexpr (kGeneral || B == 8) operate<B, NW, false, (B == 4 && !LSTM) ? 8 : 4, CELL == 9, kRead>(acc, w_off, w_val, n_w, plane_bytes);
       else operate_plain<B, NW, kLast, kRead>(acc, w_off, w_val, n_w, plane_bytes);
