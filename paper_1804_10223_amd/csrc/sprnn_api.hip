@@ -55,6 +55,8 @@ struct sprnn_handle_s {
   bool poisoned = false;         // a watchdog trip was observed: the ring no longer holds a consistent state
   bool used_shared_exchange = false;   // sprnn_forward_noalloc ran on this handle: sprnn_check also reads its status word
   float calibrated_us = 0.0f;    // microseconds per step of the setting the calibration kept (0: not measured)
+  float calibrated_short_us = 0.0f;   // microseconds of a whole call of kShortSteps steps at that setting (0: not measured)
+  bool by_length = false;        // several parts: calls too short for them run on `whole`
   float calibrated_grad_us = 0.0f;   // ... of the pass with the weight gradient fused in (0: not measured, not part of a comparison)
 };
 
@@ -223,6 +225,7 @@ static hipError_t launch_in_order(int device, const void* kernel, int grid, int 
 }
 
 static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_runs, const sprnn_handle_s* incumbent);
+constexpr int kLongSteps = 160, kShortSteps = 16;   // lengths that handles are compared at
 
 // The weight gradient asked of a backward call: summed inside the recurrence (one more gather-fed accumulator per nonzero
 // and step), or as one product on the matrix cores behind it.  The former costs every step 0.1 us and 0.006 us per word of
@@ -412,7 +415,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
     for (int s = 0; s < ring_slots; ++s)
       for (size_t i = used; i < (size_t)m.h_bytes / 4; ++i) ring[(size_t)s * m.h_bytes / 4 + i] = 0u;
   }
-  std::vector<uint32_t> ctrl(kCtrlWords, 0u);
+  std::vector<uint32_t> ctrl(kOwnCtrlWords, 0u);
   const int rows = m.rows;
   bool ok = SPRNN_HIP(upload(&h->d_words, P.words.data(), P.words.size())) &&
             SPRNN_HIP(upload(&h->d_lane_row, P.lane_row.data(), P.lane_row.size())) &&
@@ -653,6 +656,10 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
       first = same;
     }
     split->whole = first;
+    split->by_length = first->calibrated_us > 0.0f && first->calibrated_short_us > 0.0f && split->calibrated_short_us > 0.0f;
+    static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
+    if (verbose) std::fprintf(stderr, "sprnn_create: one part %.3f us per step, %.1f us for %d steps; %d parts %.3f and %.1f\n", first->calibrated_us,
+                              first->calibrated_short_us, kShortSteps, split->map.parts, split->calibrated_us, split->calibrated_short_us);
     prepare_weight_gradient_product(first, split);
     *out = split;
     return SPRNN_OK;
@@ -667,8 +674,21 @@ int sprnn_create(sprnn_handle_t* out, int hidden, int batch, int activation, con
   return sprnn_create_ex(out, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, nullptr);
 }
 
+// Calls of T steps on a handle of several parts: a launch of more workgroups, and in the one-XCD mode their roll call, takes a
+// few microseconds longer, which a short call does not win back (LSTM 837 x batch 2, 22 steps: 36.4 us in two parts, 33.6 in
+// one).  Both handles give the same bits; a straight line through the two measured lengths decides.
+static sprnn_handle_s* handle_for_length(sprnn_handle_s* h, int T) {
+  if (!h->by_length) return h;
+  auto estimate = [&](const sprnn_handle_s* c) {
+    const double step = ((double)c->calibrated_us * kLongSteps - c->calibrated_short_us) / (kLongSteps - kShortSteps);
+    return c->calibrated_short_us + (T - kShortSteps) * step;
+  };
+  return estimate(h->whole) < estimate(h) ? h->whole : h;
+}
+
 static int forward_persistent(sprnn_handle_t h, int T, const float* x, const float* h0, const float* c0,
                               float* h_out, float* c_out, void* stream, const LaunchExtras& ex) {
+  h = handle_for_length(h, T);
   if (h->poisoned) return SPRNN_ERR_STATE;
   if (T == 0) return SPRNN_OK;
   DeviceGuard guard(h->device);
@@ -712,6 +732,8 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
     a.wave_early = ex.backward ? nullptr : h->d_wave_early;   // (only the forward pass consumes h in two parts)
     a.seg_rounds = ex.backward ? 0 : m.seg_rounds;
     a.one_xcd = h->one_xcd ? 1 : 0;
+    a.placement = ctrl + (ex.shared_exchange ? kCtrlPlacement : kCtrlWords);   // (no room to spread them in the static array)
+    a.placement_stride = ex.shared_exchange ? 1 : kPlacementStride;
     a.launch_epoch = ex.shared_exchange ? 0u : h->launch_epoch;
     a.lds_h_bytes = m.grid == 1 ? m.lds_bytes / 2 : m.lds_bytes;
     a.ring = ring; a.ctrl = ctrl;
@@ -764,7 +786,7 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
   const Mapping& m = h->map;
   // (a launch of the one-XCD mode holds eight times the workgroups and costs a few microseconds more to start: the
   // comparison of the two placements runs long enough for the per-step time to decide, as it does at real lengths)
-  const int T = (try_one_xcd || long_runs) ? 160 : 48;
+  const int T = (try_one_xcd || long_runs) ? kLongSteps : 48;
   // (the gated cells' backward passes read [T][B][4H] kept gate values from the zero buffer)
   const size_t xn = (size_t)T * m.samples() * std::max(std::max(m.rows, m.cols), 4 * m.hidden), hn = (size_t)T * m.samples() * m.cols;
   float *d_x = nullptr, *d_h = nullptr, *d_c = nullptr, *d_v = nullptr;
@@ -821,6 +843,23 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
       }
     }
     best_ms_kept = best_ms;
+    if (long_runs && best_ms > 0.0f) {
+      h->map.poll_delay = best;
+      h->one_xcd = best_one_xcd;
+      float shortest = 0.0f;
+      for (int rep = 0; rep < 6 && ok && rc == SPRNN_OK; ++rep) {
+        float ms = 0.0f;
+        LaunchExtras ex;
+        const bool gated_bwd = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;
+        if (gated_bwd) { ex.backward = true; ex.saved = d_x; ex.gates_out = d_v; }
+        if (!SPRNN_HIP(hipEventRecord(e0, nullptr))) { ok = false; break; }
+        rc = forward_persistent(h, kShortSteps, d_x, nullptr, nullptr, d_h, gated_bwd ? d_x : d_c, nullptr, ex);
+        if (rc != SPRNN_OK) break;
+        if (!SPRNN_HIP(hipEventRecord(e1, nullptr)) || !SPRNN_HIP(hipEventSynchronize(e1)) || !SPRNN_HIP(hipEventElapsedTime(&ms, e0, e1))) { ok = false; break; }
+        if (rep > 0 && (shortest == 0.0f || ms < shortest)) shortest = ms;
+      }
+      if (ok && rc == SPRNN_OK) h->calibrated_short_us = shortest * 1000.0f;
+    }
     // A gated cell's backward handle serves two kernels, the plain pass and the one with the weight gradient fused in,
     // and a mapping that suits one may not suit the other: both are measured where the first handle uses the latter.
     const bool gated_bwd_cell = m.cell == SPRNN_CELL_LSTM_BACKWARD || m.cell == SPRNN_CELL_GRU_BACKWARD;

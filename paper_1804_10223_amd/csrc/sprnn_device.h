@@ -14,8 +14,10 @@ constexpr int kRingSlotsDev = 4;                  // exchange ring depth (power 
 constexpr uint32_t kSentinelBits = 0x80000000u;   // -0.0f marks a ring element that is not written yet
 constexpr int kCtrlStatus = 0;                    // ctrl[0]: non-zero once a spin watchdog tripped
 constexpr int kCtrlBarrier = 32;                  // grid-barrier mode: ctrl[32] top counter, ctrl[32 + 16 (1 + g)] counter of group g (64 bytes apart)
-constexpr int kCtrlPlacement = kCtrlBarrier + 16 * 9;   // one-XCD mode: two sets (launch parity) of 16 words: workgroups seen per XCD [0..7], arrivals [8]
+constexpr int kCtrlPlacement = kCtrlBarrier + 16 * 9;   // one-XCD mode: two sets (launch parity) of 16 words: workgroups seen per XCD [0..7]
 constexpr int kCtrlWords = kCtrlPlacement + 32;
+constexpr int kPlacementStride = 16;              // words between the counters of two XCDs where there is room for it: behind a handle's own control words
+constexpr int kOwnCtrlWords = kCtrlWords + 2 * 8 * kPlacementStride;
 constexpr uint32_t kStatusWatchdog = 1u, kStatusPlacement = 2u;   // bits of the status word
 constexpr int kCellBackward = 100;                // persistent_kernel_for: backward pass of a vanilla cell
 constexpr int kCellBackwardGrad = 101;            // the same with the weight gradient fused in
@@ -59,6 +61,8 @@ struct KernelArgs {
   int batch;                  // samples of the call: the layout's batch x parts (x, h_out, ... hold this many per timestep)
   int parts;                  // groups of workgroups that each advance their share of the samples: 1, 2, 4 or 8
   int part_grid;              // workgroups of a part
+  uint32_t* placement;        // one-XCD mode: two sets of max(16, 8 placement_stride) words, XCD x's workgroups counted in word x * placement_stride
+  int placement_stride;
   uint32_t launch_epoch;      // launches of this handle so far (parity selects the placement counters)
   int seg_rounds;             // > 0: the copy of h is consumed in two parts, its first seg_rounds rounds first (see persistent_kernel)
   int gather_waves;           // lane-pool layout: wavefronts of a workgroup that hold weights (the others own the outputs)
