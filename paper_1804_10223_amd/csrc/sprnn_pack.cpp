@@ -263,7 +263,9 @@ static int64_t all_cycles(const std::vector<Seg>& segs, int trip, const std::vec
   return total;
 }
 
-static void order_segments(std::vector<Seg>& segs, int trip, const std::vector<PassModel>& models, bool bank_aware) {
+// `empty_cycles`: what a pass without nonzeros is taken to cost.  One is what it does cost, and lets the first nonzero of a pass
+// in for nothing (4000 x batch 1 at 10 %: 1.02 of a conflict-free layout against 1.21 with zero).
+static void order_segments(std::vector<Seg>& segs, int trip, const std::vector<PassModel>& models, int empty_cycles, bool bank_aware) {
   for (auto& q : segs) {
     q.pos.assign((size_t)trip * q.n, -1);
     for (int i = 0; i < (int)q.items.size(); ++i) q.pos[i] = i;   // CSR order: item i -> lane i % n, slot i / n
@@ -280,7 +282,7 @@ static void order_segments(std::vector<Seg>& segs, int trip, const std::vector<P
   std::vector<int> shift(nm, 0);                   // finest passes per pass of a model: 1 << shift
   for (int i = 0; i < nm; ++i) {
     while ((models[i].npass << shift[i]) < np) ++shift[i];
-    cycles[i].assign(P >> shift[i], 1);             // (every pass takes a cycle, however empty)
+    cycles[i].assign(P >> shift[i], empty_cycles);
     mult[i].assign((size_t)(P >> shift[i]) * models[i].classes, 0);
   }
   std::vector<int64_t> coarse_total(coarse, 0), fine_total(fine, 0);
@@ -344,10 +346,10 @@ static void order_segments(std::vector<Seg>& segs, int trip, const std::vector<P
 }
 
 // Place the nonzeros of all rows of one wavefront of the one-group-per-row layout: every row group is one segment.
-static void order_wave(std::vector<RowGroup>& rg, int L, int trip, const std::vector<PassModel>& pm, bool bank_aware) {
+static void order_wave(std::vector<RowGroup>& rg, int L, int trip, const std::vector<PassModel>& pm, int empty_cycles, bool bank_aware) {
   std::vector<Seg> segs(rg.size());
   for (size_t q = 0; q < rg.size(); ++q) { segs[q].lane0 = rg[q].lane0; segs[q].n = L; segs[q].row = rg[q].row; segs[q].items = rg[q].items; }
-  order_segments(segs, trip, pm, bank_aware);
+  order_segments(segs, trip, pm, empty_cycles, bank_aware);
   for (size_t q = 0; q < rg.size(); ++q) rg[q].pos = std::move(segs[q].pos);
 }
 
@@ -368,7 +370,7 @@ static int phase_words(const std::vector<RowGroup>& rg, int L, int trip, int seg
   return k1;
 }
 
-static void order_wave_phased(std::vector<RowGroup>& rg, int L, int trip, int k1, int seg_col, const std::vector<PassModel>& pm, bool bank_aware) {
+static void order_wave_phased(std::vector<RowGroup>& rg, int L, int trip, int k1, int seg_col, const std::vector<PassModel>& pm, int empty_cycles, bool bank_aware) {
   std::vector<Seg> early(rg.size()), late(rg.size());
   std::vector<std::vector<int>> early_of(rg.size()), late_of(rg.size());   // index into the row's items
   for (size_t q = 0; q < rg.size(); ++q) {
@@ -381,8 +383,8 @@ static void order_wave_phased(std::vector<RowGroup>& rg, int L, int trip, int k1
       (first ? early[q] : late[q]).items.push_back(rg[q].items[i]);
     }
   }
-  order_segments(early, k1, pm, bank_aware);
-  order_segments(late, trip - k1, pm, bank_aware);
+  order_segments(early, k1, pm, empty_cycles, bank_aware);
+  order_segments(late, trip - k1, pm, empty_cycles, bank_aware);
   for (size_t q = 0; q < rg.size(); ++q) {
     rg[q].pos.assign((size_t)trip * L, -1);
     for (int k = 0; k < trip; ++k)
@@ -598,7 +600,7 @@ static int pack_pool(int hidden, int batch, int cell, const int32_t* row_ptr, co
       const int trip = P.wave_words[(size_t)wg * m.waves + wave];
       used_words_max = std::max(used_words_max, trip);
       padded += (int64_t)trip * kWave;
-      order_segments(wave_segs[wave], trip, pm, m.bank_aware == 1);
+      order_segments(wave_segs[wave], trip, pm, 1, m.bank_aware == 1);
       for (const Seg& q : wave_segs[wave]) {
         const size_t tid0 = (size_t)wg * m.block + (size_t)wave * kWave + q.lane0;
         for (int j = 0; j < q.n; ++j) P.lane_row[tid0 + j] = q.row;
@@ -810,9 +812,14 @@ static int pack_part(int hidden, int batch, int order_batch, int cell, const int
   if (m.seg_rounds) P.wave_early.assign(total_waves, 0);
 
   const PassModel pm = make_pass_model(lb);
-  // (narrow gathers and the two-part copy are never offered with several parts: one geometry)
+  // (Narrow gathers and the two-part copy are never offered with several parts: one geometry.  With binary16 activations another
+  // order moves a result by more than its sums' rounding: where a sum falls on the other side of a binary16 boundary, by 2^-11
+  // of h.  Their order is therefore fixed, that of the whole batch's geometry alone with empty passes at zero, however the
+  // samples are shared out.  2560 x batch 8 in two parts has 2.4 instead of 1.6 of a conflict-free layout for it, which costs
+  // 0.5 to 1.3 % of the speech layer's 920 us: the exchange is what bounds the step.)
   const int whole_lb = m.half ? order_batch / 2 : order_batch;
-  const std::vector<PassModel> models = make_pass_models(whole_lb, m.narrow || m.seg_rounds ? whole_lb : (m.half ? 2 : 1));
+  const std::vector<PassModel> models = make_pass_models(whole_lb, m.narrow || m.seg_rounds || m.half ? whole_lb : 1);
+  const int empty_cycles = m.half ? 0 : 1;
   auto pad_word = [&](int lane_in_wave, int k, int ncols) -> uint32_t {
     // zero-valued filler (place_fillers gives it a bank class that is free in its pass afterwards)
     int col = (lane_in_wave + k * L) % pm.classes;
@@ -880,11 +887,11 @@ static int pack_part(int hidden, int batch, int order_batch, int cell, const int
           if (m.seg_rounds) {
             const int k1 = phase_words(rg, L, trip, seg_col);
             P.wave_early[gw] = k1;
-            order_wave_phased(rg, L, trip, k1, seg_col, models, m.bank_aware == 1);
+            order_wave_phased(rg, L, trip, k1, seg_col, models, empty_cycles, m.bank_aware == 1);
           } else if (known && !make_known && wave_rows[gw] >= 0) {
             for (size_t q = 0; q < rg.size(); ++q) rg[q].pos = known->pos[wave_rows[gw]][q];
           } else {
-            order_wave(rg, L, trip, models, m.bank_aware == 1);
+            order_wave(rg, L, trip, models, empty_cycles, m.bank_aware == 1);
             if (make_known && wave_rows[gw] >= 0)
               for (const RowGroup& q : rg) known->pos[wave_rows[gw]].push_back(q.pos);
           }

@@ -93,8 +93,16 @@ __device__ __forceinline__ void halving_stage(float (&v)[B], int lane) {
   }
 }
 
+// Sum with the next quad of the lane's row of 16 lanes, or with the one before it (`back`).
+__device__ __forceinline__ float add_quad(float t, bool back) {
+  const int bits = __builtin_bit_cast(int, t);
+  const float next = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits, 0x12C, 0xf, 0xf, false));   // row_ror:12
+  if (!back) return t + next;
+  return t + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits, 0x124, 0xf, 0xf, false));           // row_ror:4
+}
+
 template <int L, int B>
-__device__ __forceinline__ float reduce_scatter(float (&v)[B], int lane) {
+__device__ __forceinline__ float reduce_scatter(float (&v)[B], int lane, bool back = false) {
   static_assert(L >= B, "a row needs at least as many lanes as there are samples");
   constexpr int SPLITS = ilog2(B), STAGES = ilog2(L);
   if constexpr (SPLITS >= 1) halving_stage<B, B, 0>(v, lane);
@@ -106,8 +114,8 @@ __device__ __forceinline__ float reduce_scatter(float (&v)[B], int lane) {
   if constexpr (SPLITS <= 2 && STAGES > 3) {
     // both in-row stages are plain: two rotations sum the four lanes that share lane % 4.  (From the next quad first: the
     // owners, in the first quad of a row, then add the same pairs as the halving stages of a larger B do, so that the bits of
-    // a result do not depend on how many samples the workgroup advances.)
-    t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x12C, 0xf, 0xf, false));   // row_ror:12
+    // a result do not depend on how many samples the workgroup advances.  `back`: the other pairs, see the kernel's use.)
+    t = add_quad(t, back);
     t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x128, 0xf, 0xf, false));   // row_ror:8
   } else {
     if constexpr (SPLITS <= 2 && STAGES > 2) t += from_partner<2>(t);
@@ -120,11 +128,11 @@ __device__ __forceinline__ float reduce_scatter(float (&v)[B], int lane) {
 
 // One jump on the (kernel-uniform) lanes-per-row, then straight-line code.
 template <int B>
-__device__ __forceinline__ float reduce_rows(float (&acc)[B], int L, int lane) {
+__device__ __forceinline__ float reduce_rows(float (&acc)[B], int L, int lane, bool back = false) {
   switch (L) {
-    case 64: return reduce_scatter<64, B>(acc, lane);
-    case 32: return reduce_scatter<32, B>(acc, lane);
-    case 16: return reduce_scatter<16, B>(acc, lane);
+    case 64: return reduce_scatter<64, B>(acc, lane, back);
+    case 32: return reduce_scatter<32, B>(acc, lane, back);
+    case 16: return reduce_scatter<16, B>(acc, lane, back);
     case 8: return reduce_scatter<8, B>(acc, lane);
     case 4: if constexpr (B <= 4) return reduce_scatter<4, B>(acc, lane); else break;
     case 2: if constexpr (B <= 2) return reduce_scatter<2, B>(acc, lane); else break;
@@ -137,7 +145,7 @@ __device__ __forceinline__ float reduce_rows(float (&acc)[B], int L, int lane) {
 // The same sums for the owner lanes with a select per stage that not every L has, in place of a jump to one of seven bodies
 // (every uniform branch costs a handful of scalar instructions and a jump or two): the in-row stages always run.
 template <int B, bool WIDE>
-__device__ __forceinline__ float reduce_rows_select(float (&v)[B], int L, int lane) {
+__device__ __forceinline__ float reduce_rows_select(float (&v)[B], int L, int lane, bool back = false) {
   constexpr int SPLITS = ilog2(B);
   if constexpr (SPLITS >= 1) halving_stage<B, B, 0>(v, lane);
   if constexpr (SPLITS >= 2) halving_stage<B, B / 2, 1>(v, lane);
@@ -146,7 +154,7 @@ __device__ __forceinline__ float reduce_rows_select(float (&v)[B], int L, int la
   if constexpr (SPLITS <= 0) { const float s = t + from_partner<0>(t); t = L > 1 ? s : t; }
   if constexpr (SPLITS <= 1) { const float s = t + from_partner<1>(t); t = L > 2 ? s : t; }
   if constexpr (SPLITS <= 2) {   // the next quad: the partner of an owner, whose quad is the row's first
-    const float s = t + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x12C, 0xf, 0xf, false));   // row_ror:12
+    const float s = add_quad(t, back && L > 8);
     t = L > 4 ? s : t;
   }
   const float s = t + from_partner<3>(t);
@@ -1161,7 +1169,10 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
     ts1 = tick<TL>(tl_on);
 
     // ---- reduce over the lanes of the row: every lane ends up with the sum of its own sample
-    const float red = kGeneral ? reduce_rows<B>(acc, L, lane) : reduce_rows_select<B, !LSTM>(acc, L, lane);
+    // (Binary16 activations keep the order of their sums, see pack_part: at batch 4 that is the one with the quads paired the
+    // other way round, unless the four samples are a part of eight, which have the first.)
+    const bool back = kHalf && B == 4 && parts == 1;
+    const float red = kGeneral ? reduce_rows<B>(acc, L, lane, back) : reduce_rows_select<B, !LSTM>(acc, L, lane, back);
     const float pre = red + now.x;
     // (without options the flag is read ahead of the gathers and looked at behind them: what they read is then of no account)
     if constexpr (!kGeneral && !kSolo) {

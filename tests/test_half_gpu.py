@@ -163,3 +163,44 @@ def test_calls_that_are_not_built_for_binary16_activations_are_refused():
         want = oracle.rnn_forward(512, 4, "relu", w.row_ptr, w.col_idx, w.val_bits, w.x, None)
         assert np.abs(s.cpu().numpy() - want).max() <= 1e-5 * np.abs(want).max()
         assert rnn.check() == binding.SPRNN_OK
+
+
+def _sum_in_order(w, batch, held, lanes, h, quads_back):
+    """The kernel's sums of one step, addition by addition: a lane's products in the order of its slots, then the lanes in pairs.
+    (A product of two binary16 values and one binary32 addition to it are exact in binary64, so each step rounds once.)"""
+    rows = w.hidden
+    acc = np.zeros((rows, lanes, batch), np.float32)
+    for (row, lane, _), (col, bits) in sorted(held.items(), key=lambda kv: kv[0][2]):
+        weight = np.uint16(bits).view(np.float16).astype(np.float64)
+        acc[row, lane] = (acc[row, lane].astype(np.float64) + weight * h[:, col].astype(np.float64)).astype(np.float32)
+    for stage in (1, 2):                                        # lane ^ 1, lane ^ 2: what is left of a quad is its sum
+        other = acc[:, np.arange(lanes) ^ stage]
+        acc = acc + other
+    quad = acc[:, ::4]                                          # [rows][quad][batch]
+    pairs = ((0, 3), (2, 1)) if quads_back else ((0, 1), (2, 3))
+    (a, b), (c, d) = pairs
+    row16 = [(quad[:, r + a] + quad[:, r + b]) + (quad[:, r + c] + quad[:, r + d]) for r in range(0, lanes // 4, 4)]
+    while len(row16) > 1:
+        row16 = [row16[i] + row16[i + 1] for i in range(0, len(row16), 2)]
+    return row16[0].T                                           # [batch][rows]
+
+
+@pytest.mark.parametrize("batch,parts,lanes,jitter", [(4, 1, 16, 0), (4, 1, 64, 0), (4, 1, 32, 3), (8, 1, 16, 0), (8, 2, 32, 0), (8, 2, 16, 0)])
+def test_the_order_of_the_sums_is_fixed(batch, parts, lanes, jitter):
+    """A sum taken in another order may fall on the other side of a binary16 boundary, which moves h by 2^-11, so with these
+    activations the order is part of the result (test_parts_order.py pins where the packer puts the nonzeros)."""
+    H = 333
+    w = wl.make_workload("sums", "identity", H, batch, 1, 0.3, seed=batch + lanes, row_nnz="poisson", h0_std=1.0)
+    opts = dict(lanes_per_row=lanes, waves=4, activations="binary16", compact=2, **({"parts": parts} if parts > 1 else {}))
+    words, lane_row, _, info = binding.pack_host(H, batch, w.cell, w.row_ptr, w.col_idx, w.val_bits, **opts)
+    stride, held = 2 * min(batch // parts, 8), {}
+    assert H * stride <= 65536 and info["parts"] == parts
+    for wg, k, tid in zip(*np.nonzero(words & 0x7FFF)):
+        word = int(words[wg, k, tid])
+        held[int(lane_row[wg, tid]), int(tid) % lanes, int(k)] = ((word >> 16) // stride, word & 0xFFFF)
+    h = w.h0.astype(np.float16)
+    want = _sum_in_order(w, batch, held, lanes, h, quads_back=batch == 4) + w.x[0]
+    with binding.SparseRNN(H, batch, w.cell, w.row_ptr, w.col_idx, w.val_bits, jitter=jitter, **opts) as rnn:
+        got = rnn.forward(_dev(w.x), _dev(w.h0))[0].cpu().numpy()
+        assert rnn.check() == binding.SPRNN_OK and rnn.info()["grid"] > 1
+    assert np.array_equal(got, want), np.count_nonzero(got != want)

@@ -1,5 +1,7 @@
 """The order of a row's nonzeros is one for every way of sharing out the samples (CPU): which lane of the row holds which
 nonzero in which slot may depend on the lanes per row only, because that is the order in which the products are added."""
+import zlib
+
 import numpy as np
 import pytest
 
@@ -37,3 +39,19 @@ def test_every_share_of_the_batch_has_the_order_of_the_whole(cell, H, batch, par
     shared, shared_info = _slots(w, batch, lanes_per_row=L, parts=parts, **opts)
     assert info["parts"] == 1 and shared_info["parts"] == parts and info["batch"] == shared_info["batch"] == batch
     assert len(whole) == np.count_nonzero(w.val_bits & 0x7FFF) and whole == shared
+
+
+def test_binary16_activations_keep_their_order():
+    """A result with binary16 activations moves by 2^-11 of h where a sum taken in another order falls on the other side of a
+    rounding boundary, so the order is fixed: which slot of which lane holds which nonzero is pinned here, for both batch sizes."""
+    H = 320
+    per_row = np.array([24 + (5 * r) % 17 for r in range(H)])
+    row_ptr = np.concatenate([[0], np.cumsum(per_row)]).astype(np.int32)
+    col = np.concatenate([np.sort((np.arange(n) * 53 + 7 * r) % H) for r, n in enumerate(per_row)]).astype(np.int32)
+    val = (0x3000 + np.arange(col.size) % 0x0800).astype(np.uint16)
+    w = wl.Workload("pinned", "relu", H, 8, 1, row_ptr, col, val, None, None)
+    for batch, parts, want in ((8, 1, 2550844915), (4, 1, 3065920774), (8, 2, 2550844915)):
+        held, info = _slots(w, batch, lanes_per_row=16, activations="binary16", compact=2, **({"parts": parts} if parts > 1 else {}))
+        assert info["parts"] == parts and info["activations"] == 2 and len(held) == col.size
+        order = np.array([key + value for key, value in sorted(held.items())], dtype=np.int64)
+        assert zlib.crc32(order.tobytes()) == want, (batch, parts)
