@@ -233,15 +233,14 @@ constexpr int kLongSteps = 160, kShortSteps = 16;   // lengths that handles are 
 // of 32 vectors takes a workgroup.  Whole calls measured, inside / behind: 2304 at 30 %, batch 4, T 256 620 / 541 us;
 // 1152 at 10 %, batch 4, T 64 146 / 110; LSTM 1024 at 20 %, batch 8, T 128 810 / 767 (step with its forward pass); but
 // 4096 at 8 %, batch 4, T 64 173 / 208, 5000 at 2 %, batch 1, T 128 267 / 311, LSTM 2000 at 5 %, batch 1, T 64 241 / 260.
-// The sums inside need all samples in one part; where the handle has several, the recurrence ahead of the product is faster
-// than that by what creation measured.
+// The two round differently, so the choice follows from the matrix, its lanes per row and T alone and not from anything that was
+// measured at creation (the recurrence ahead of the product is faster on a handle of several parts, the sums inside need all
+// samples in one): handles with the same lanes per row give the same bits, divided or not.
 static bool product_is_faster(const sprnn_handle_s* handle, int T) {
-  const sprnn_handle_s* const h = handle->whole ? handle->whole : handle;
-  const Mapping& m = h->map;
-  const double vectors = (double)T * m.samples();
-  const double saved = handle->whole ? std::max(0.0, (double)h->calibrated_us - handle->calibrated_us) : 0.0;
+  const Mapping& m = (handle->whole ? handle->whole : handle)->map;
+  const double vectors = (double)T * m.batch;
   const double behind = 5.0 + std::max(vectors * m.rows * m.cols * 13.4e-9, vectors / 32.0 * 0.35);
-  return behind < (T + 1) * (0.1 + 0.006 * m.words_max * m.batch + saved);
+  return behind < (T + 1) * (0.1 + 0.006 * m.words_max * m.batch);
 }
 
 static WGradCall weight_gradient_call(const sprnn_handle_s* h, int T) {
@@ -515,13 +514,13 @@ static bool fits_scratch(const Mapping& m) { return (size_t)kRingSlots * m.h_byt
 
 // The table of the product, made once for the handle that is kept, where some length of call takes the product (a wide layer's
 // table is larger than its packed weights).  Without it, for want of memory too, the calls go the other way.
-// `caller` is the handle the user holds: `h` itself, or the one of several parts in front of it.
-static void prepare_weight_gradient_product(sprnn_handle_s* h, const sprnn_handle_s* caller) {
+// `h` holds all samples in one part.
+static void prepare_weight_gradient_product(sprnn_handle_s* h) {
   const int rows = h->map.rows, cols = h->map.cols;
   h->wgrad_tile = choose_weight_gradient_tile(rows, cols, h->num_cus);
   bool used = false;
   for (const int T : {1, 1 << 24})   // (both ways' times are linear in the length)
-    used |= (h->has_wgrad && !(h->kernel_lane_sums && lane_sums_are_faster(weight_gradient_call(h, T)))) || (h->kernel_bwd_grad && product_is_faster(caller, T));
+    used |= (h->has_wgrad && !(h->kernel_lane_sums && lane_sums_are_faster(weight_gradient_call(h, T)))) || (h->kernel_bwd_grad && product_is_faster(h, T));
   if (!used || h->map.nnz == 0) return;
   const size_t entries = (size_t)rows * ((cols + h->wgrad_tile.cols - 1) / h->wgrad_tile.cols + 1);
   if (SPRNN_HIP(hipMalloc((void**)&h->d_wgrad_starts, entries * 4)) &&
@@ -567,7 +566,7 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
     const int rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
                                false, true, nullptr, nullptr, &orders);
     if (rc2 != SPRNN_OK) { release(first); return rc2; }
-    prepare_weight_gradient_product(first->whole, first);
+    prepare_weight_gradient_product(first->whole);
     *out = first;
     return SPRNN_OK;
   }
@@ -660,11 +659,11 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
     static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
     if (verbose) std::fprintf(stderr, "sprnn_create: one part %.3f us per step, %.1f us for %d steps; %d parts %.3f and %.1f\n", first->calibrated_us,
                               first->calibrated_short_us, kShortSteps, split->map.parts, split->calibrated_us, split->calibrated_short_us);
-    prepare_weight_gradient_product(first, split);
+    prepare_weight_gradient_product(first);
     *out = split;
     return SPRNN_OK;
   }
-  prepare_weight_gradient_product(first, first);
+  prepare_weight_gradient_product(first);
   *out = first;
   return SPRNN_OK;
 }

@@ -1,0 +1,54 @@
+"""Handles with nothing fixed about the mapping, which sprnn_create chooses by measuring: what may not depend on its choice.
+
+Shapes that are divided into parts by themselves on an otherwise idle device (the tests hold whatever is chosen)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1804_10223_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+GATES = {"lstm": 4, "gru": 3}
+
+
+def _dev(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _normal(rng, *shape):
+    return _dev(rng.standard_normal(shape).astype(np.float32))
+
+
+@pytest.mark.parametrize("cell,H,B,dens,lengths", [
+    # lengths on both sides of where the product behind the recurrence takes over from the sums inside it, and between that and
+    # where it would if the time that a division saves were counted
+    ("tanh", 1152, 4, 0.1, (3, 12, 40)),
+    ("relu", 701, 2, 0.15, (5, 20, 80)),
+    ("lstm", 1024, 8, 0.2, (2, 3, 12)),
+    ("gru", 1024, 4, 0.2, (4, 12, 40)),
+])
+def test_the_weight_gradient_of_a_backward_call_has_the_bits_of_any_handle_with_these_lanes(cell, H, B, dens, lengths):
+    w = wl.make_workload("default", cell, H, B, 1, dens, seed=H)
+    t_csr = binding.transpose_csr(w.rows, H, w.row_ptr, w.col_idx, w.val_bits)
+    name = cell + "_backward" if cell in GATES else cell
+    rng = np.random.Generator(np.random.PCG64(11))
+    T = max(lengths)
+    e, h, h0 = _normal(rng, T, B, H), _normal(rng, T, B, H).tanh_(), _normal(rng, B, H)
+    gates, c, c0 = _normal(rng, T, B, 4 * H).sigmoid_(), _normal(rng, T, B, H), _normal(rng, B, H)
+
+    def passes(bwd, steps):
+        head = lambda a: a[:steps].contiguous()
+        if cell == "lstm":
+            return bwd.backward_lstm_with_weights(head(e), head(gates), head(c), head(h), c0, h0)
+        if cell == "gru":
+            return bwd.backward_gru_with_weights(head(e), head(gates), head(h), h0)
+        return bwd.backward_with_weights(head(e), head(h), h0)
+
+    with binding.SparseRNN(H, B, name, *t_csr) as chosen:
+        info = chosen.info()
+        print("case", cell, H, B, "parts", info["parts"], "lanes", info["lanes_per_row"], flush=True)
+        with binding.SparseRNN(H, B, name, *t_csr, lanes_per_row=info["lanes_per_row"]) as fixed:
+            for steps in lengths:
+                for k, (a, b) in enumerate(zip(passes(chosen, steps), passes(fixed, steps))):
+                    assert torch.equal(a, b), (steps, k, (a - b).abs().max().item())
+            assert chosen.check() == binding.SPRNN_OK and fixed.check() == binding.SPRNN_OK
