@@ -98,7 +98,8 @@ typedef struct sprnn_options_s {
                         results must not change                                                   */
   int compact;       /* column compaction: a workgroup copies only the 16-byte pieces of h that its rows
                         read, into consecutive LDS positions.  0 auto (when all of h does not fit in
-                        LDS, or every workgroup needs less than half of it), 1 on, 2 off            */
+                        LDS, or every workgroup needs less than half of it; with several parts only
+                        when a part's samples of h do not fit), 1 on, 2 off                          */
   int layout;        /* how the lanes of a workgroup are given to rows (vanilla cells, more than one workgroup):
                         0 auto, 1 = one power-of-two lane group per row, every wavefront does every stage,
                         2 = lane pool: a row takes as many groups of `batch` lanes as its nonzeros need out of a
@@ -187,8 +188,9 @@ int sprnn_create(sprnn_handle_t* out, int hidden, int batch, int activation, con
  * batch shared out to 2, 4 and 8 parts (SPRNN_XCD_PARTS) is measured as well, where the layer fits that share of the CUs.
  * Creation then takes 0.1 to 0.4 s depending on the size of the matrix (the packing runs on several host threads).
  * Results are bit-for-bit the same from call to call on one handle, and between handles with the same lanes_per_row
- * (which fixes the order in which a row's products are added, however the samples are shared out); a caller who needs that
- * across handles passes the value sprnn_get_info reported for the first. */
+ * that copy h whole (compact 0 in sprnn_info_t: the lanes then fix the order in which a row's products are added, however the
+ * samples are shared out; with column compaction it follows the places of the columns in LDS, which grid and waves decide as
+ * well); a caller who needs that across handles passes the value sprnn_get_info reported for the first, with compact 2. */
 int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
                     const int32_t* col_idx, const uint16_t* val_fp16_bits, int device_id,
                     const sprnn_options_t* opt);

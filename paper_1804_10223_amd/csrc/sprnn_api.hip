@@ -562,9 +562,15 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
     if (rc != SPRNN_OK) return rc;
     sprnn_options_t one = with_parts(base, 1);
     one.grid = one.waves = one.fill_waves = one.xcd = 0;
-    one.lanes_per_row = first->map.lanes_per_row;   // (the same sums, bit for bit)
-    const int rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
-                               false, true, nullptr, nullptr, &orders);
+    one.lanes_per_row = first->map.lanes_per_row;   // (the same sums, bit for bit, where neither copies only some columns)
+    if (!first->map.compact) one.compact = 2;
+    int rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
+                         false, true, nullptr, nullptr, &orders);
+    if (rc2 == SPRNN_ERR_CAPACITY && one.compact != base.compact) {   // (h of all samples does not fit in LDS whole)
+      one.compact = base.compact;
+      rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
+                       false, true, nullptr, nullptr, &orders);
+    }
     if (rc2 != SPRNN_OK) { release(first); return rc2; }
     prepare_weight_gradient_product(first->whole);
     *out = first;

@@ -637,7 +637,15 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
   if (parts > 1) {
     if (batch < parts || opt->layout == 2 || opt->sync == SPRNN_SYNC_BARRIER || opt->timeline || opt->gather == 2 || opt->overlap == 2) return SPRNN_ERR_UNSUPPORTED;
   }
-  rc = pack_part(hidden, batch / parts, batch, cell, row_ptr, col_idx, val_bits, opt, num_cus / parts, out, cache);
+  rc = SPRNN_ERR_CAPACITY;
+  if (parts > 1 && opt->compact == 0) {
+    // Nothing said about column compaction: none where h fits.  The order of a row's nonzeros would follow the places of its
+    // columns in LDS, which differ between a part and all samples in one.
+    sprnn_options_t all_columns = *opt;
+    all_columns.compact = 2;
+    rc = pack_part(hidden, batch / parts, batch, cell, row_ptr, col_idx, val_bits, &all_columns, num_cus / parts, out, cache);
+  }
+  if (rc == SPRNN_ERR_CAPACITY) rc = pack_part(hidden, batch / parts, batch, cell, row_ptr, col_idx, val_bits, opt, num_cus / parts, out, cache);
   if (rc == SPRNN_OK) out->map.parts = parts;
   return rc;
 }

@@ -121,6 +121,31 @@ def test_the_results_do_not_depend_on_how_the_samples_are_shared_out(cell, H, B,
             hnd.close()
 
 
+@pytest.mark.parametrize("H,B,P,lanes,dens", [(2000, 8, 4, 8, 0.005), (4096, 4, 2, 8, 0.01)])
+def test_sparse_parts_copy_h_whole_unless_told_otherwise(H, B, P, lanes, dens):
+    """Layers whose workgroups would copy only some columns if all samples were in one part: with parts they copy h whole, so that
+    the weight gradients are offered and the bits are those of a handle with these lanes that copies h whole."""
+    T = 5
+    w = wl.make_workload("sparse", "tanh", H, B, T, dens, seed=H, h0_std=0.5)
+    rng = np.random.Generator(np.random.PCG64(5))
+    x, h0, e = _dev(w.x), _dev(w.h0), _dev(rng.standard_normal((T, B, H)).astype(np.float32))
+    csr = (w.row_ptr, w.col_idx, w.val_bits)
+    t_csr = binding.transpose_csr(H, H, *csr)
+    with binding.SparseRNN(H, B, "tanh", *csr, lanes_per_row=lanes) as auto:
+        assert auto.info()["compact"] == 1
+    results = []
+    for extra in ({"parts": P}, {"compact": 2}):
+        with binding.SparseRNN(H, B, "tanh", *csr, lanes_per_row=lanes, **extra) as rnn, \
+             binding.SparseRNN(H, B, "tanh", *t_csr, lanes_per_row=lanes, **extra) as bwd:
+            assert rnn.info()["compact"] == bwd.info()["compact"] == 0
+            h = rnn.forward(x, h0)
+            delta, dh0 = bwd.backward(e, h)
+            results.append([h, delta, dh0, rnn.weight_gradient(delta, h, h0)] + list(bwd.backward_with_weights(e, h, h0)))
+            assert rnn.check() == bwd.check() == binding.SPRNN_OK
+    for k, (a, b) in enumerate(zip(*results)):
+        assert torch.equal(a, b), (k, (a - b).abs().max().item())
+
+
 def test_refusals():
     w = wl.make_workload("refuse", "relu", 64, 2, 1, 0.2, seed=1)
     for kw, code in (({"parts": 4}, binding.SPRNN_ERR_UNSUPPORTED), ({"parts": 2, "layout": 2}, binding.SPRNN_ERR_UNSUPPORTED),

@@ -41,6 +41,16 @@ def test_every_share_of_the_batch_has_the_order_of_the_whole(cell, H, batch, par
     assert len(whole) == np.count_nonzero(w.val_bits & 0x7FFF) and whole == shared
 
 
+@pytest.mark.parametrize("H,batch,parts,L,dens", [(4096, 4, 2, 8, 0.01), (6000, 8, 2, 8, 0.004), (2000, 8, 4, 8, 0.005)])
+def test_parts_copy_h_whole_where_it_fits(H, batch, parts, L, dens):
+    """Column compaction (here the choice for all samples in one part) orders a row's nonzeros by their columns' places in LDS."""
+    w = wl.make_workload("sparse", "relu", H, batch, 1, dens, seed=H)
+    options = dict(lanes_per_row=L)
+    assert binding.pack_host(H, batch, "relu", w.row_ptr, w.col_idx, w.val_bits, **options)[3]["compact"] == 1
+    assert binding.pack_host(H, batch, "relu", w.row_ptr, w.col_idx, w.val_bits, parts=parts, **options)[3]["compact"] == 0
+    assert binding.pack_host(H, batch, "relu", w.row_ptr, w.col_idx, w.val_bits, parts=parts, compact=1, **options)[3]["compact"] == 1
+
+
 def test_binary16_activations_keep_their_order():
     """A result with binary16 activations moves by 2^-11 of h where a sum taken in another order falls on the other side of a
     rounding boundary, so the order is fixed: which slot of which lane holds which nonzero is pinned here, for both batch sizes."""
