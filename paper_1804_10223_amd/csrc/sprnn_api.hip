@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "sprnn.h"
+#include "sprnn_contest.h"
 #include "sprnn_device.h"
 #include "sprnn_pack.h"
 #include "sprnn_wgrad.h"
@@ -152,8 +153,6 @@ unsigned char* scratch_on_device(int device) {
 }
 
 }  // namespace
-
-static int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
 
 // What a launch of the persistent kernel takes beyond the forward pass's five buffers.
 struct LaunchExtras {
@@ -296,13 +295,6 @@ int sprnn_pack_host(int hidden, int batch, int activation, const int32_t* row_pt
   fill_info(P.map, 0, lds_pass_factor(P), info);
   return SPRNN_OK;
 }
-
-// A second mapping worth measuring against the library's own choice (0 = none): fewer, larger workgroups that fit one
-// XCD, or more wavefronts per workgroup so that the copy of h issues fewer surplus loads.
-struct Alternative {
-  int grid = 0;
-  int fill_waves = 0;
-};
 
 // One handle for one set of options: mapping, packing, upload, kernel choice, calibration.  `long_runs` makes the
 // calibration time runs long enough to be compared between two handles of different launch size; `incumbent` is the
@@ -531,6 +523,61 @@ static void prepare_weight_gradient_product(sprnn_handle_s* h) {
   h->d_wgrad_starts = nullptr;
 }
 
+// What a handle's mapping lets it do.  (A handle of several parts leaves the weight gradients to the one behind it.)
+static Abilities abilities(const sprnn_handle_s* h) {
+  Abilities can;
+  can.backward = h->kernel_bwd != nullptr;
+  can.backward_weights = h->kernel_bwd_grad && h->d_word_src;
+  can.weights = h->has_wgrad;
+  can.noalloc = fits_scratch(h->map);
+  return can;
+}
+
+// One matrix and device: what all handles of one creation are made from.
+struct Creation {
+  int hidden, batch, activation;
+  const int32_t *row_ptr, *col_idx;
+  const uint16_t* val_fp16_bits;
+  int device_id;
+  hipDeviceProp_t prop;
+  OrderCache orders;
+
+  int operator()(const sprnn_options_t& opt, bool long_runs, const sprnn_handle_s* incumbent, Alternative* alternative, sprnn_handle_t* out) {
+    return create_one(out, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &opt, prop, alternative != nullptr,
+                      long_runs, incumbent, alternative, &orders);
+  }
+};
+
+// The contending mappings (see contest) as handles.
+struct ContestBuilder {
+  Creation& make;
+  const sprnn_options_t& base;
+
+  sprnn_handle_s* build(const Request& r, const sprnn_handle_s* incumbent, Alternative* proposed) {
+    sprnn_options_t o = with_parts(base, r.parts);
+    o.lanes_per_row = r.lanes;
+    o.grid = r.alternative.grid;
+    o.fill_waves = r.alternative.fill_waves;
+    if (r.parts > 1) o.compact = 2;
+    sprnn_handle_t built = nullptr;
+    const int rc = make(o, true, incumbent, proposed, &built);
+    static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
+    if (verbose)
+      std::fprintf(stderr, "sprnn_create: contender (parts %d, lanes %d, grid %d, fill %d) -> %s, %d x %d, %d lanes, %.3f us per step against %.3f\n",
+                   r.parts, r.lanes, o.grid, o.fill_waves, sprnn_status_string(rc), built ? built->map.grid : 0, built ? built->map.block : 0,
+                   built ? built->map.lanes_per_row : 0, built ? built->calibrated_us : 0.0f, incumbent->calibrated_us);
+    return built;
+  }
+  Facts facts(const sprnn_handle_s* h) const {
+    Facts f;
+    f.parts = h->map.parts; f.lanes = h->map.lanes_per_row; f.compact = h->map.compact != 0;
+    f.us = h->calibrated_us; f.with_weights_us = h->calibrated_grad_us;
+    f.can = abilities(h);
+    return f;
+  }
+  void release(sprnn_handle_s* h) const { ::release(h); }
+};
+
 int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, const int32_t* row_ptr,
                     const int32_t* col_idx, const uint16_t* val_fp16_bits, int device_id,
                     const sprnn_options_t* opt) {
@@ -541,35 +588,32 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
   if (device_id < 0 || device_id >= ndev) return SPRNN_ERR_INVALID;
   DeviceGuard guard(device_id);
   if (!guard.ok) return SPRNN_ERR_HIP;
-  hipDeviceProp_t prop;
-  if (!SPRNN_HIP(hipGetDeviceProperties(&prop, device_id))) return SPRNN_ERR_HIP;
-  if (opt && opt->launch == 2 && !prop.cooperativeLaunch) return SPRNN_ERR_UNSUPPORTED;
+  Creation make{hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, {}, {}};
+  if (!SPRNN_HIP(hipGetDeviceProperties(&make.prop, device_id))) return SPRNN_ERR_HIP;
+  if (opt && opt->launch == 2 && !make.prop.cooperativeLaunch) return SPRNN_ERR_UNSUPPORTED;
 
   // A layer whose own mapping needs a few more workgroups than one XCD has CUs may run faster on fewer, larger
   // workgroups that fit one XCD (the exchange then stays inside one L2), and a layer with a large h on workgroups of
-  // more wavefronts (see create_one).  Which is faster depends on the matrix, so when nothing about the mapping was
-  // asked for, both are built and calibrated with runs of the same length, and the faster handle is kept.
+  // more wavefronts (see create_one), or with other lanes per row, or with its samples shared out.  Which is fastest depends
+  // on the matrix, so when nothing about the mapping was asked for, all are built and calibrated with runs of the same length,
+  // and the fastest handle is kept (see contest).
   const bool free_choice = !opt || (opt->grid == 0 && opt->waves == 0 && opt->fill_waves == 0 && opt->lanes_per_row == 0 &&
                                     opt->layout == 0 && opt->poll_delay == 0 && opt->xcd == 0 && opt->sync == 0 &&
                                     opt->timeline == 0 && opt->gather == 0 && opt->overlap == 0 && opt->compact == 0);
   sprnn_options_t base = opt ? *opt : sprnn_options_t();
   if (!opt) std::memset(&base, 0, sizeof(base));
-  OrderCache orders;
   sprnn_handle_t first = nullptr;
   if (parts_asked(opt) > 1) {   // asked for: the handle of several parts, and behind it one with all samples for the other calls
-    const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &base, prop,
-                              false, true, nullptr, nullptr, &orders);
+    const int rc = make(base, true, nullptr, nullptr, &first);
     if (rc != SPRNN_OK) return rc;
     sprnn_options_t one = with_parts(base, 1);
     one.grid = one.waves = one.fill_waves = one.xcd = 0;
     one.lanes_per_row = first->map.lanes_per_row;   // (the same sums, bit for bit, where neither copies only some columns)
     if (!first->map.compact) one.compact = 2;
-    int rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
-                         false, true, nullptr, nullptr, &orders);
+    int rc2 = make(one, true, nullptr, nullptr, &first->whole);
     if (rc2 == SPRNN_ERR_CAPACITY && one.compact != base.compact) {   // (h of all samples does not fit in LDS whole)
       one.compact = base.compact;
-      rc2 = create_one(&first->whole, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &one, prop,
-                       false, true, nullptr, nullptr, &orders);
+      rc2 = make(one, true, nullptr, nullptr, &first->whole);
     }
     if (rc2 != SPRNN_OK) { release(first); return rc2; }
     prepare_weight_gradient_product(first->whole);
@@ -577,100 +621,26 @@ int sprnn_create_ex(sprnn_handle_t* out, int hidden, int batch, int activation, 
     return SPRNN_OK;
   }
   Alternative alt;
-  const int rc = create_one(&first, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, opt, prop,
-                            free_choice, free_choice, nullptr, &alt, &orders);
+  const int rc = make(base, free_choice, nullptr, free_choice ? &alt : nullptr, &first);
   if (rc != SPRNN_OK) return rc;
-  int compacts[7] = {-1, -1, -1, -1, -1, -1, -1};   // with 2^i lanes per row and all samples in one part: column compaction (-1: not seen)
-  compacts[ilog2(first->map.lanes_per_row)] = first->map.compact;
-  // Builds the mapping `other` asks for, measures it like the one in `best`, and keeps the faster of the two there; with
-  // nothing in `best` it is compared with `reference` and kept if it is faster than that.
-  auto contend = [&](const sprnn_options_t& other, sprnn_handle_t* best, const sprnn_handle_s* reference, Alternative* alternative) {
-    const sprnn_handle_s* const incumbent = *best ? *best : reference;
-    sprnn_handle_t second = nullptr;
-    const int rc2 = create_one(&second, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &other, prop,
-                               alternative != nullptr, true, incumbent, alternative, &orders);
-    // like with like: by the plain pass alone unless both were measured with the weight gradient as well
-    const bool both = rc2 == SPRNN_OK && incumbent->calibrated_grad_us > 0.0f && second->calibrated_grad_us > 0.0f;
-    const float incumbent_us = incumbent->calibrated_us + (both ? incumbent->calibrated_grad_us : 0.0f);
-    const float contender_us = rc2 != SPRNN_OK || second->calibrated_us <= 0.0f ? 0.0f : second->calibrated_us + (both ? second->calibrated_grad_us : 0.0f);
-    static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
-    if (verbose)
-      std::fprintf(stderr, "sprnn_create: %s (parts %d, lanes %d, grid %d, fill %d) -> %s, %d x %d, %d lanes, %.3f us per step against %.3f%s\n",
-                   parts_asked(&other) > 1 ? "shared out" : "contender", parts_asked(&other), other.lanes_per_row, other.grid, other.fill_waves, sprnn_status_string(rc2), rc2 == SPRNN_OK ? second->map.grid : 0,
-                   rc2 == SPRNN_OK ? second->map.block : 0, rc2 == SPRNN_OK ? second->map.lanes_per_row : 0, contender_us, incumbent_us, both ? ", with and without weights" : "");
-    if (rc2 != SPRNN_OK) return false;
-    if (second->map.parts == 1) compacts[ilog2(second->map.lanes_per_row)] = second->map.compact;
-    // (what the incumbent can do must stay possible: the vanilla backward pass, the call on the device's static ring)
-    const bool able = (second->map.parts == 1 || compacts[ilog2(second->map.lanes_per_row)] == 0) && (second->kernel_bwd || !first->kernel_bwd) && (fits_scratch(second->map) || !fits_scratch(first->map));
-    if (able && contender_us > 0.0f && contender_us < 0.98f * incumbent_us) {
-      release(*best);
-      *best = second;
-      return true;
-    }
-    release(second);
-    return false;
-  };
-  const bool compare = free_choice && first->calibrated_us > 0.0f;
-  // (1) fewer, larger workgroups on one XCD, or a wavefront count that copies h with fewer loads (see create_one)
-  auto contend_alternative = [&](const Alternative& a, int parts, sprnn_handle_t* best, const sprnn_handle_s* reference) {
-    if (a.grid == 0 && a.fill_waves == 0) return;
-    sprnn_options_t other = with_parts(base, parts);
-    other.grid = a.grid;
-    other.fill_waves = a.fill_waves;
-    if (parts > 1) other.compact = 2;
-    contend(other, best, reference, nullptr);
-  };
-  if (compare) contend_alternative(alt, 1, &first, nullptr);
-  // (2) The lanes a row is spread over: the packer's rule of thumb (at least eight nonzeros per lane) is not the best
-  // for every shape; twice and half as many lanes are measured too, each with the mapping the packer picks for it.
-  const bool gated_rows = first->map.cell == SPRNN_CELL_LSTM || first->map.cell == SPRNN_CELL_GRU;
-  auto contend_lanes = [&](int parts, sprnn_handle_t* best) {
-    const int own_lanes = (*best)->map.lanes_per_row;
-    for (int pass = 0; pass < 2; ++pass) {
-      const int lanes = pass == 0 ? own_lanes * 2 : own_lanes / 2;
-      if (lanes < batch || lanes < 1 || lanes > (gated_rows ? 16 : kWave)) continue;
-      sprnn_options_t other = with_parts(base, parts);
-      other.lanes_per_row = lanes;
-      if (parts > 1) other.compact = 2;
-      contend(other, best, nullptr, nullptr);
-    }
-  };
-  if (compare) contend_lanes(1, &first);
-  // (3) The samples shared out to several groups of workgroups (see persistent_kernel): every one that the batch can be
-  // divided into, each with the packer's mapping and its alternative; then the lanes of the best.  The order of a row's sums
-  // is the one that all samples in one part would have with these lanes, unless that mapping copies only the columns its
-  // rows read (the order follows their places): such lanes are left to it.
-  sprnn_handle_t split = nullptr;
-  for (int parts = 2; compare && parts <= batch; parts *= 2) {
-    sprnn_options_t other = with_parts(base, parts);
-    other.compact = 2;
-    Alternative alt_split;
-    contend(other, &split, first, &alt_split);
-    contend_alternative(alt_split, parts, &split, first);
+  Winner<sprnn_handle_s> winner;
+  winner.kept = first;
+  if (free_choice && first->calibrated_us > 0.0f) {
+    ContestBuilder builder{make, base};
+    const bool gated_rows = first->map.cell == SPRNN_CELL_LSTM || first->map.cell == SPRNN_CELL_GRU;
+    winner = contest(builder, first, alt, batch, gated_rows ? 16 : kWave);
   }
-  if (split) {
-    contend_lanes(split->map.parts, &split);
-    if (first->map.lanes_per_row != split->map.lanes_per_row) {   // (all the handle's calls add a row's products in one order)
-      sprnn_options_t other = base;
-      other.lanes_per_row = split->map.lanes_per_row;
-      sprnn_handle_t same = nullptr;
-      const int rc2 = create_one(&same, hidden, batch, activation, row_ptr, col_idx, val_fp16_bits, device_id, &other, prop,
-                                 false, true, nullptr, nullptr, &orders);
-      if (rc2 != SPRNN_OK) { release(split); release(first); return rc2; }
-      release(first);
-      first = same;
-    }
-    split->whole = first;
-    split->by_length = first->calibrated_us > 0.0f && first->calibrated_short_us > 0.0f && split->calibrated_short_us > 0.0f;
+  sprnn_handle_s* const kept = winner.kept;
+  sprnn_handle_s* const whole = winner.whole;
+  if (whole) {
+    kept->whole = whole;
+    kept->by_length = whole->calibrated_us > 0.0f && whole->calibrated_short_us > 0.0f && kept->calibrated_short_us > 0.0f;
     static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
-    if (verbose) std::fprintf(stderr, "sprnn_create: one part %.3f us per step, %.1f us for %d steps; %d parts %.3f and %.1f\n", first->calibrated_us,
-                              first->calibrated_short_us, kShortSteps, split->map.parts, split->calibrated_us, split->calibrated_short_us);
-    prepare_weight_gradient_product(first);
-    *out = split;
-    return SPRNN_OK;
+    if (verbose) std::fprintf(stderr, "sprnn_create: one part %.3f us per step, %.1f us for %d steps; %d parts %.3f and %.1f\n", whole->calibrated_us,
+                              whole->calibrated_short_us, kShortSteps, kept->map.parts, kept->calibrated_us, kept->calibrated_short_us);
   }
-  prepare_weight_gradient_product(first);
-  *out = first;
+  prepare_weight_gradient_product(whole ? whole : kept);
+  *out = kept;
   return SPRNN_OK;
 }
 
@@ -844,7 +814,8 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
         }
         if (best_ms == 0.0f || ms < best_ms) { best_ms = ms; best = h->map.poll_delay; best_one_xcd = mode == 1; }
         // (a contender that is a fifth behind after half of a placement's back-offs will not win with another one)
-        if (incumbent && incumbent->calibrated_us > 0.0f && ci * 2 >= ncand && best_ms * 1000.0f > 1.2f * incumbent->calibrated_us * (float)T) break;
+        // (one with all samples in one part may still be needed behind one of several parts: at its own best back-off)
+        if (incumbent && m.parts > 1 && incumbent->calibrated_us > 0.0f && ci * 2 >= ncand && best_ms * 1000.0f > 1.2f * incumbent->calibrated_us * (float)T) break;
       }
     }
     best_ms_kept = best_ms;

@@ -19,6 +19,34 @@ def _normal(rng, *shape):
     return _dev(rng.standard_normal(shape).astype(np.float32))
 
 
+def _offered(handle, cell):
+    """Which calls a handle offers: asked without a place for the result, so that what is offered is refused as INVALID (or, with
+    no steps, done) before anything is launched, and the rest as UNSUPPORTED."""
+    lib, h, none = binding.load_library(), handle._h, [None]
+    codes = {"weight_gradient": lib.sprnn_weight_gradient(h, 0, *none * 5)}
+    if cell == "lstm_backward":
+        codes["with_weights"] = lib.sprnn_backward_lstm_with_weights(h, 0, *none * 11)
+    elif cell == "gru_backward":
+        codes["with_weights"] = lib.sprnn_backward_gru_with_weights(h, 0, *none * 9)
+    elif cell not in GATES:
+        codes["with_weights"] = lib.sprnn_backward_with_weights(h, 0, *none * 7)
+        codes["backward"] = lib.sprnn_backward(h, 0, *none * 5)
+        codes["noalloc"] = lib.sprnn_forward_noalloc(h, 0, *none * 4)
+    return {k for k, code in codes.items() if code in (binding.SPRNN_OK, binding.SPRNN_ERR_INVALID)}
+
+
+@pytest.mark.parametrize("cell,H,B,dens", [("relu", 1152, 4, 0.1), ("relu", 4096, 4, 0.01), ("tanh", 2000, 8, 0.03), ("lstm", 1024, 8, 0.05),
+                                           ("lstm_backward", 1024, 8, 0.2), ("lstm_backward", 1024, 4, 0.05), ("gru_backward", 1500, 4, 0.1)])
+def test_no_call_is_lost_to_a_faster_mapping(cell, H, B, dens):
+    w = wl.make_workload("offer", cell.replace("_backward", ""), H, B, 1, dens, seed=H + B)
+    csr = (w.row_ptr, w.col_idx, w.val_bits)
+    if cell.endswith("_backward"):
+        csr = binding.transpose_csr(w.rows, H, *csr)[:3]
+    with binding.SparseRNN(H, B, cell, *csr, xcd="spread") as own, binding.SparseRNN(H, B, cell, *csr) as chosen:
+        print("case", cell, H, B, "lanes", own.info()["lanes_per_row"], chosen.info()["lanes_per_row"], "parts", chosen.info()["parts"], flush=True)
+        assert _offered(own, cell) <= _offered(chosen, cell)
+
+
 @pytest.mark.parametrize("cell,H,B,dens,lengths", [
     # lengths on both sides of where the product behind the recurrence takes over from the sums inside it, and between that and
     # where it would if the time that a division saves were counted
