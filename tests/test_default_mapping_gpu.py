@@ -47,6 +47,76 @@ def test_no_call_is_lost_to_a_faster_mapping(cell, H, B, dens):
         assert _offered(own, cell) <= _offered(chosen, cell)
 
 
+LONG = 160
+
+
+@pytest.mark.parametrize("cell,H,B,dens,rows,options", [
+    ("relu", 1152, 4, 0.1, "fixed", {}),
+    ("tanh", 701, 2, 0.15, "poisson", {}),
+    ("relu", 2304, 4, 0.3, "fixed", {}),
+    ("relu", 2560, 8, 0.12, "fixed", {"activations": "binary16"}),
+    ("lstm", 837, 2, 0.1, "poisson", {}),
+    ("lstm", 1024, 8, 0.2, "fixed", {}),
+    ("gru", 771, 4, 0.15, "poisson", {}),
+])
+def test_calls_of_every_length_have_the_bits_of_any_handle_with_these_lanes(cell, H, B, dens, rows, options):
+    """A divided handle runs short calls undivided (from which length on, creation measures): calls on both sides of that, in
+    turn, against one long call, and that against a handle with these lanes that is not divided."""
+    w = wl.make_workload("length", cell, H, B, LONG, dens, seed=H, row_nnz=rows, h0_std=0.5)
+    csr = (w.row_ptr, w.col_idx, w.val_bits)
+    rng = np.random.Generator(np.random.PCG64(2))
+    x, h0, b_hn = _dev(w.x), _dev(w.h0), _dev(getattr(w, "b_hn", None))
+    c0, e = _normal(rng, B, H), _normal(rng, LONG, B, H)
+    gated, half = cell in GATES, bool(options)
+
+    def forward(rnn, steps):
+        xs = x[:steps].contiguous()
+        if cell == "lstm":
+            return rnn.forward_lstm_train(xs, h0, c0)
+        return rnn.forward_gru_train(xs, b_hn, h0) if cell == "gru" else (rnn.forward(xs, h0),)
+
+    def backward(bwd, kept, steps):   # of the last `steps` of the long call: nothing flows in from beyond its end
+        tail = lambda a: a[LONG - steps:].contiguous()
+        before = lambda a, first: first if steps == LONG else a[LONG - steps - 1].contiguous()
+        if cell == "lstm":
+            h, c, gates = kept
+            return bwd.backward_lstm(tail(e), tail(gates), tail(c), before(c, c0))[:1]
+        if cell == "gru":
+            h, gates = kept
+            return bwd.backward_gru(tail(e), tail(gates), tail(h), before(h, h0))[:2]
+        return bwd.backward(tail(e), tail(kept[0]))[:1]
+
+    name = cell + "_backward" if gated else cell
+    t_csr = None if half else binding.transpose_csr(w.rows, H, *csr)[:3]
+    with binding.SparseRNN(H, B, cell, *csr, **options) as rnn:
+        info = rnn.info()
+        print("case", cell, H, B, {k: info[k] for k in ("parts", "one_xcd", "lanes_per_row", "grid", "block")}, flush=True)
+        want = forward(rnn, LONG)
+        for steps in (1, 90, 2, 3, 60, 5, 8, 40, 13, 22, 30, LONG):
+            for k, (a, b) in enumerate(zip(forward(rnn, steps), want)):
+                assert torch.equal(a, b[:steps]), (steps, k)
+        assert rnn.check() == binding.SPRNN_OK
+    with binding.SparseRNN(H, B, cell, *csr, lanes_per_row=info["lanes_per_row"], jitter=3, **options) as fixed:
+        assert fixed.info()["parts"] == 1
+        for a, b in zip(forward(fixed, LONG), want):
+            assert torch.equal(a, b)
+        assert fixed.check() == binding.SPRNN_OK
+    if half:
+        return
+    with binding.SparseRNN(H, B, name, *t_csr) as bwd:
+        info = bwd.info()
+        print("   backward", {k: info[k] for k in ("parts", "one_xcd", "lanes_per_row", "grid", "block")}, flush=True)
+        grads = backward(bwd, want, LONG)
+        for steps in (1, 90, 2, 60, 5, 40, 13, 22, 30, LONG):
+            for k, (a, b) in enumerate(zip(backward(bwd, want, steps), grads)):
+                assert torch.equal(a, b[LONG - steps:]), (steps, k)
+        assert bwd.check() == binding.SPRNN_OK
+    with binding.SparseRNN(H, B, name, *t_csr, lanes_per_row=info["lanes_per_row"], jitter=3) as fixed:
+        for a, b in zip(backward(fixed, want, LONG), grads):
+            assert torch.equal(a, b)
+        assert fixed.check() == binding.SPRNN_OK
+
+
 @pytest.mark.parametrize("cell,H,B,dens,lengths", [
     # lengths on both sides of where the product behind the recurrence takes over from the sums inside it, and between that and
     # where it would if the time that a division saves were counted
