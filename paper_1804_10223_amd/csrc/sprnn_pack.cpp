@@ -676,6 +676,9 @@ static int pack_part(int hidden, int batch, int order_batch, int cell, const int
   Mapping m;
   rc = choose_mapping(hidden, batch, order_batch, cell, row_nnz, opt, num_cus, &m);
   if (rc != SPRNN_OK) return rc;
+  // (`cache` is given when the mapping is to run, with one workgroup per CU: no need to pack what will be refused then, tens of
+  // milliseconds each for the contenders that sprnn_create tries on a large layer)
+  if (cache && m.grid > num_cus) return SPRNN_ERR_CAPACITY;
 
   const int L = m.lanes_per_row;
   const int gpw = kWave / L;                      // row groups per wavefront

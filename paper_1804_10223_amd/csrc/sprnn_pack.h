@@ -77,7 +77,7 @@ struct OrderCache {
 };
 
 // Returns SPRNN_OK or an error code; on success `out` holds the mapping and the image.  `cache`, if given, belongs to this
-// matrix and this value of opt->bank_aware.
+// matrix and this value of opt->bank_aware, and mappings of more workgroups than num_cus are refused.
 int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t* col_idx,
          const uint16_t* val_bits, const sprnn_options_t* opt, int num_cus, Packed* out, OrderCache* cache = nullptr);
 
