@@ -132,16 +132,18 @@ typedef struct sprnn_options_s {
 
 /* Filled by sprnn_get_info: how the matrix was mapped onto the chip. */
 typedef struct sprnn_info_s {
-  int hidden, rows, batch, cell;
+  int hidden, rows, batch, cell;   /* batch: samples of a call, in all parts                       */
   int grid, block, waves, lanes_per_row, sync, bank_aware, balance, poll_delay;
   int words_per_lane_max;   /* largest number of packed nonzeros held by one lane                 */
   int template_words;       /* register slots per lane of the kernel instantiation in use         */
-  int lds_bytes;            /* LDS bytes per workgroup for h (one copy; two when grid is 1; less
-                               with column compaction; of one workgroup of every part together)      */
-  int resident_capacity;    /* co-resident workgroups the device can hold for this kernel         */
+  int lds_bytes;            /* LDS bytes that the samples of a call take (one copy; two when grid is 1; less with
+                               column compaction): all in each workgroup with one part, lds_bytes / parts of
+                               them in a workgroup of several parts                                  */
+  int resident_capacity;    /* co-resident workgroups the device can hold for this kernel (grid * parts
+                               of them work)                                                        */
   int64_t nnz;              /* nonzeros in the CSR input                                           */
-  int64_t padded_words;     /* packed words including zero padding                                 */
-  int64_t ring_bytes;       /* size of the exchange ring in device memory                          */
+  int64_t padded_words;     /* packed words including zero padding (every part holds that many)    */
+  int64_t ring_bytes;       /* size of the exchange ring in device memory (of all parts)           */
   double lds_pass_factor;   /* LDS passes the packed gathers need / passes of a conflict-free layout
                                (1.0 = no bank conflicts), from the 64-bank, 256 B-per-pass model     */
   int compact;              /* 1 if column compaction is in use                                      */
@@ -152,7 +154,7 @@ typedef struct sprnn_info_s {
                                the copy is overlapped with the gathers (see sprnn_options_t.overlap)     */
   int overlap_words;        /* leading slots per lane that read only that first part: least over the wavefronts */
   int activations;          /* 1 = h is exchanged as binary32, 2 = as binary16 (see sprnn_options_t.activations)   */
-  int parts;                /* groups of workgroups that share out the samples; grid and padded_words are one part's */
+  int parts;                /* groups of workgroups that share out the samples; grid is the workgroups of one          */
 } sprnn_info_t;
 
 /*

@@ -170,7 +170,7 @@ def axis(torch, wl, reps, title, cases):
         st, _ = measure(torch, w, reps, stepwise=True)
         print("| %d | %d | %.1f %% | %d | %d | %.2f | %.2f | %.1fx | %d x %d | %d | %d | %d KB%s | %s |" % (
             H, B, 100 * dens, T, w.nnz, us, st, st / us, info["grid"], info["block"], info["lanes_per_row"], info["poll_delay"],
-            info["lds_bytes"] // 1024, " (compacted)" if info["compact"] else "", "yes" if info["one_xcd"] else ""), flush=True)
+            info["lds_bytes"] // info["parts"] // 1024, " (compacted)" if info["compact"] else "", "yes" if info["one_xcd"] else ""), flush=True)
     print()
 
 
@@ -211,8 +211,8 @@ def activations(torch, wl, reps):
         a, ia, oa = measure(torch, w, reps, want_output=True)
         b, ib, ob = measure(torch, w, reps, want_output=True, activations=2)
         diff = max(float(np.abs(oa[t] - ob[t]).max() / np.abs(oa[t]).max()) for t in range(w.steps))
-        print("| %d | %d | %.1f %% | %.2f | %.2f | %d KB%s / %d KB | %.1e |" % (H, B, 100 * dens, a, b, ia["lds_bytes"] // 1024,
-              " (compacted)" if ia["compact"] else "", ib["lds_bytes"] // 1024, diff), flush=True)
+        print("| %d | %d | %.1f %% | %.2f | %.2f | %d KB%s / %d KB | %.1e |" % (H, B, 100 * dens, a, b, ia["lds_bytes"] // ia["parts"] // 1024,
+              " (compacted)" if ia["compact"] else "", ib["lds_bytes"] // ib["parts"] // 1024, diff), flush=True)
     print()
 
 
