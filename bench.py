@@ -151,14 +151,14 @@ def measure_backward(w, steps, warmup, torch, options=None):
         dU = torch.empty((w.nnz,), dtype=torch.float32, device="cuda")
         _, per_wg = time_forward(lambda: fwd.weight_gradient(d, h_fwd, None, dU), steps, warmup, torch)
     wg_ms = float(np.median(per_wg))
-    return {"kernel": "persistent_kernel<B=%d,NW=%d,backward>" % (w.batch, info["template_words"]), "ms_per_launch": ms,
-            "us_per_timestep": ms * 1e3 / w.steps, "grid": info["grid"], "block": info["block"], "poll_delay": info["poll_delay"],
+    return {"kernel": kernel_label(w, info, ",backward"), "ms_per_launch": ms,
+            "us_per_timestep": ms * 1e3 / w.steps, "grid": info["grid"], "block": info["block"], "parts": info["parts"], "poll_delay": info["poll_delay"],
             "weight_gradient_ms_per_launch": wg_ms, "weight_gradient_us_per_timestep": wg_ms * 1e3 / w.steps,
             "with_weight_gradient_ms_per_call": with_ms,
             "with_weight_gradient_us_per_timestep": None if with_ms is None else with_ms * 1e3 / w.steps}
 
 
-def measure_lstm_training(steps, warmup, torch):
+def measure_lstm_training(steps, warmup, torch, options=None):
     """One training step of the LSTM layer of cfg5, all three calls: forward keeping the gate values, backward pass
     through time on the transposed matrix (sprnn_backward_lstm), weight gradient on the forward handle."""
     from paper_1804_10223_amd import binding, workloads
@@ -168,8 +168,10 @@ def measure_lstm_training(steps, warmup, torch):
     x = torch.from_numpy(w.x).cuda()
     e = torch.randn((T, B, H), device="cuda", generator=gen)
     t_rp, t_ci, t_vb = binding.transpose_csr(4 * H, H, w.row_ptr, w.col_idx, w.val_bits)
-    with binding.SparseRNN(H, B, "lstm", w.row_ptr, w.col_idx, w.val_bits) as fwd, \
-            binding.SparseRNN(H, B, "lstm_backward", t_rp, t_ci, t_vb) as bwd:
+    # (only with the parts fixed are the back-off and the mapping: what --poll-delay alone asks for suits the benchmarked layer)
+    fixed = options if options and "parts" in options else {}
+    with binding.SparseRNN(H, B, "lstm", w.row_ptr, w.col_idx, w.val_bits, **fixed) as fwd, \
+            binding.SparseRNN(H, B, "lstm_backward", t_rp, t_ci, t_vb, **fixed) as bwd:
         # every output is allocated here, outside the timed regions: the binding allocates nothing when given them
         mk = lambda *shape: torch.empty(shape, dtype=torch.float32, device="cuda")
         h, c, g = mk(T, B, H), mk(T, B, H), mk(T, B, 4 * H)
@@ -192,7 +194,7 @@ def measure_lstm_training(steps, warmup, torch):
             "forward_keeping_gates_us_per_timestep": f_ms * 1e3 / T, "backward_us_per_timestep": b_ms * 1e3 / T,
             "weight_gradient_us_per_timestep": w_ms * 1e3 / T,
             "backward_with_weight_gradient_us_per_timestep": None if with_ms is None else with_ms * 1e3 / T,
-            "backward_grid": bi["grid"], "backward_block": bi["block"],
+            "backward_grid": bi["grid"], "backward_block": bi["block"], "backward_parts": bi["parts"],
             "backward_exchange_bytes_per_timestep": 4 * H * B * 4}
 
 
@@ -206,9 +208,11 @@ HANDOFF_FLOOR_NS = {"cross": 344.0, "same": 310.0}
 
 
 def roofline_for(w, info, probe_vals):
-    """Stated per-timestep bound for one configuration from the measured device constants."""
-    gather = 4 * w.batch                                   # fp32 activations of one column, all samples
-    lds_bytes = w.nnz * gather
+    """Stated per-timestep bound for one configuration from the measured device constants.  Several parts: each holds the
+    matrix on its share of the CUs and gathers, exchanges and copies its own samples only."""
+    share = w.batch // info["parts"]
+    gather = 4 * share                                     # fp32 activations of one column, the samples of a part
+    lds_bytes = w.nnz * gather * info["parts"]
     width = min(16, gather)
     t_lds = lds_bytes / probe_vals["lds_Bps"][width]
     t_valu = w.nnz * w.batch / probe_vals["valu_lane_ops_per_s"]       # one multiply-add per nonzero and sample
@@ -219,7 +223,7 @@ def roofline_for(w, info, probe_vals):
         t_handoff = min(probe_vals["handoff_cross_ns"], HANDOFF_FLOOR_NS["cross"]) * 1e-9
     if info["grid"] == 1:
         t_handoff = 0.0
-    h_bytes = w.hidden * w.batch * 4
+    h_bytes = w.hidden * share * 4
     t_fill = 0.0 if info["grid"] == 1 else h_bytes * probe_vals["fill_s_per_byte"]
     return dict(t_operate_us=t_operate * 1e6, t_lds_us=t_lds * 1e6, t_valu_us=t_valu * 1e6, t_handoff_us=t_handoff * 1e6,
                 t_fill_us=t_fill * 1e6, t_roof_us=(t_operate + t_handoff + t_fill) * 1e6, lds_bytes_per_step=lds_bytes, h_bytes=h_bytes)
@@ -243,10 +247,15 @@ def measure_probes(probe, torch):
     return vals
 
 
-def read_traffic_file(path, workload_name):
+def kernel_label(w, info, more=""):
+    return "persistent_kernel<B=%d,NW=%d%s>" % (w.batch // info["parts"], info["template_words"], more)
+
+
+def read_traffic_file(path, workload_name, batch, template_words):
     """HBM bytes per launch of the persistent kernel from a counter summary: text lines `key = value` written from
     rocprofv3 --pmc passes (FETCH_SIZE, WRITE_SIZE, each scaled by the same run's reference copy).  None when the
-    file is missing or describes another workload."""
+    file is missing or describes another workload or another kernel than the one for `batch` samples (of a part) and
+    `template_words` slots."""
     try:
         kv = {}
         with open(path) as f:
@@ -254,7 +263,7 @@ def read_traffic_file(path, workload_name):
                 if "=" in line and not line.lstrip().startswith("#"):
                     k, v = line.split("=", 1)
                     kv[k.strip()] = v.strip()
-        if kv.get("workload") != workload_name:
+        if kv.get("workload") != workload_name or "persistent_kernel<%d, %d," % (batch, template_words) not in kv.get("kernel", ""):
             return None
         return {"fetch_bytes_per_launch": float(kv["fetch_bytes_per_launch"]), "write_bytes_per_launch": float(kv["write_bytes_per_launch"]),
                 "source": os.path.relpath(path, ROOT)}
@@ -309,6 +318,8 @@ def main():
     ap.add_argument("--poll-delay", type=int, default=0,
                     help="fix the back-off before a step's first poll (units of 64 clocks) instead of letting "
                          "sprnn_create measure it: profiler runs then see only the timed launches")
+    ap.add_argument("--parts", type=int, default=0, choices=(0, 2, 4, 8),
+                    help="share the samples out to this many parts instead of letting sprnn_create measure it (for profiler runs)")
     args = ap.parse_args()
     if args.gpus != 1:
         log("bench.py: this build measures ONE GPU only (the persistent kernel lives on one device); "
@@ -332,7 +343,7 @@ def main():
         ["%.2f" % (t * 1e6) for t in pv["fill_times_s"].values()], list(pv["fill_times_s"].keys()),
         1e-9 / pv["fill_s_per_byte"], pv["fill_intercept_s"] * 1e6))
 
-    options = {"poll_delay": args.poll_delay} if args.poll_delay else None
+    options = {k: v for k, v in (("poll_delay", args.poll_delay), ("parts", args.parts)) if v} or None
     res = measure_config(args.config, args.steps, args.warmup, torch, options=options)
     w, info, T = res["workload"], res["info"], res["T"]
     us_per_ts = res["kernel_ms"] * 1e3 / T
@@ -346,7 +357,7 @@ def main():
     value = args.steps * T / res["wall_s"]
     log("%s: %.3f us/timestep (kernel median %.3f ms per %d timesteps), wall %.1f timesteps/s; roofline %.3f us => %.1f %%" % (
         args.config, us_per_ts, res["kernel_ms"], T, value, roof["t_roof_us"], 100 * roof["t_roof_us"] / us_per_ts))
-    log("  mapping: " + json.dumps({k: info[k] for k in ("grid", "block", "lanes_per_row", "template_words", "words_per_lane_max", "lds_bytes", "sync", "bank_aware", "balance", "poll_delay", "lds_pass_factor", "padded_words", "nnz")}))
+    log("  mapping: " + json.dumps({k: info[k] for k in ("grid", "block", "parts", "lanes_per_row", "template_words", "words_per_lane_max", "lds_bytes", "sync", "bank_aware", "balance", "poll_delay", "lds_pass_factor", "padded_words", "nnz")}))
 
     proj = measure_projection(w, args.steps, args.warmup, torch, options=options)
     log("  input projection (input size %d): %.1f us per launch, %.1f TFLOP/s algorithmic; whole layer %.3f ms" % (
@@ -358,7 +369,7 @@ def main():
             "both in one call: %s us/timestep" % (bwd["us_per_timestep"], bwd["ms_per_launch"], bwd["weight_gradient_us_per_timestep"],
                                            bwd["weight_gradient_ms_per_launch"], bwd["with_weight_gradient_us_per_timestep"]))
 
-    lstm = measure_lstm_training(max(5, args.steps // 2), 2, torch)
+    lstm = measure_lstm_training(max(5, args.steps // 2), 2, torch, options)
     log("  LSTM training step at cfg5: forward keeping gates %.3f, backward %.3f, weight gradient %.3f, the last two in one call %s us/timestep" % (
         lstm["forward_keeping_gates_us_per_timestep"], lstm["backward_us_per_timestep"], lstm["weight_gradient_us_per_timestep"],
         lstm["backward_with_weight_gradient_us_per_timestep"]))
@@ -373,7 +384,7 @@ def main():
                        roofline={"bound": "lds+exchange", "achieved": us, "peak": rf["t_roof_us"], "frac": rf["t_roof_us"] / us,
                                  "unit": "us/timestep", "t_operate_us": rf["t_operate_us"], "t_handoff_us": rf["t_handoff_us"],
                                  "t_fill_us": rf["t_fill_us"]},
-                       grid=r["info"]["grid"], block=r["info"]["block"])
+                       grid=r["info"]["grid"], block=r["info"]["block"], parts=r["info"]["parts"])
             table.append(row)
             log("  %s" % json.dumps(row))
 
@@ -394,7 +405,7 @@ def main():
         log("  oracle: %.1f us/timestep single thread; %.1f us/timestep on %d cores" % (
             cpu["us_per_timestep"], cpu["all_cores"]["us_per_timestep"], cpu["all_cores"]["cores"]))
 
-    traffic = read_traffic_file(args.traffic_file, w.name)
+    traffic = read_traffic_file(args.traffic_file, w.name, w.batch // info["parts"], info["template_words"])
     out = {
         "metric": "timesteps_per_sec (hidden %d, batch %d, density %.0f%%)" % (w.hidden, w.batch, 100 * w.meta["density"]),
         "value": value,
@@ -411,7 +422,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": "%s: sparse %s RNN, hidden %d, batch %d, T %d, density %.0f%%, fp16 weights + u16 indices" % (
             w.name, w.cell, w.hidden, w.batch, T, 100 * w.meta["density"]),
-            "timesteps_per_step": T, "grid": info["grid"], "block": info["block"], "sync": "tagged" if info["sync"] == 1 else "barrier",
+            "timesteps_per_step": T, "grid": info["grid"] * info["parts"], "block": info["block"], "parts": info["parts"], "sync": "tagged" if info["sync"] == 1 else "barrier",
             "launch": "ordinary kernel launch, the library's persistent launches ordered per device (the default)"},
         "roofline": {
             "bound": "lds+exchange",
@@ -423,7 +434,7 @@ def main():
             # (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes scaled by the run's reference copy); null without one
             "traffic": None if traffic is None else traffic["fetch_bytes_per_launch"] + traffic["write_bytes_per_launch"],
             "traffic_source": None if traffic is None else traffic["source"],
-            "traffic_algorithmic": 4.0 * info["padded_words"] + 4.0 * w.x.size + 4.0 * T * w.batch * w.hidden,
+            "traffic_algorithmic": 4.0 * info["padded_words"] * info["parts"] + 4.0 * w.x.size + 4.0 * T * w.batch * w.hidden,
             "t_operate_us": roof["t_operate_us"], "t_lds_us": roof["t_lds_us"], "t_valu_us": roof["t_valu_us"],
             "t_handoff_us": roof["t_handoff_us"], "t_fill_us": roof["t_fill_us"],
             "lds_bytes_per_timestep": roof["lds_bytes_per_step"],
@@ -434,7 +445,7 @@ def main():
             "handoff_floor_ns": HANDOFF_FLOOR_NS,
             "fill_marginal_GBps_per_cu": 1e-9 / pv["fill_s_per_byte"], "fill_intercept_us": pv["fill_intercept_s"] * 1e6,
             "fill_times_us": {str(k): v * 1e6 for k, v in pv["fill_times_s"].items()},
-            "kernel": "persistent_kernel<B=%d,NW=%d>" % (w.batch, info["template_words"]),
+            "kernel": kernel_label(w, info),
             "kernel_ms_per_launch": res["kernel_ms"],
         },
         "stepwise": {"us_per_timestep": res["stepwise_ms"] * 1e3 / T, "speedup_of_persistent": res["stepwise_ms"] / res["kernel_ms"]},
