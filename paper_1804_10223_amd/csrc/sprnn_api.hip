@@ -344,7 +344,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
                                             : persistent_kernel_for(m.batch, m.template_words, m.cell, m.timeline != 0))));
   // nothing asked for that the general form has branches for: the instantiation without them, by the rounds of the copy
   const int copy_rounds = (m.h_bytes / 16 + m.block - 1) / m.block;
-  const bool plain = !pool && !m.compact && m.grid > 1 && m.sync == SPRNN_SYNC_TAGGED && !m.jitter && !m.narrow && !m.seg_rounds && !m.timeline;
+  const bool plain = !pool && !m.compact && m.grid > 1 && m.sync == SPRNN_SYNC_TAGGED && !pause_seed(m) && !m.narrow && !m.seg_rounds && !m.timeline;
   auto plain_kernel_for = [&](int cell) -> const void* {
     if (!plain) return nullptr;
     // (few mappings have more than 32 words per lane: one form serves all their short copies)
@@ -358,7 +358,7 @@ static int create_one(sprnn_handle_t* out, int hidden, int batch, int activation
   };
   if (const void* k = plain_kernel_for(m.cell)) h->kernel = k;
   int solo_bytes = 0;   // LDS of the two copies in the form for a single workgroup
-  if (!pool && m.grid == 1 && m.h_bytes <= kSoloCopyBytes - 16 && m.sync == SPRNN_SYNC_TAGGED && !m.jitter && !m.narrow && !m.half && !m.timeline) {
+  if (!pool && m.grid == 1 && m.h_bytes <= kSoloCopyBytes - 16 && m.sync == SPRNN_SYNC_TAGGED && !pause_seed(m) && !m.narrow && !m.half && !m.timeline) {
     const void* k = persistent_solo_kernel_for(m.batch, m.template_words, m.cell);
     if (k) { h->kernel = k; solo_bytes = 2 * kSoloCopyBytes; }
   }
@@ -709,6 +709,7 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
     a.one_xcd = h->one_xcd ? 1 : 0;
     a.placement = ctrl + (ex.shared_exchange ? kCtrlPlacement : kCtrlWords);   // (no room to spread them in the static array)
     a.placement_stride = ex.shared_exchange ? 1 : kPlacementStride;
+    a.placement_enough = (m.jitter & kNoPlacement) ? ~0u : (uint32_t)m.grid;
     a.launch_epoch = ex.shared_exchange ? 0u : h->launch_epoch;
     a.lds_h_bytes = m.grid == 1 ? m.lds_bytes / 2 : m.lds_bytes;
     a.ring = ring; a.ctrl = ctrl;
@@ -726,7 +727,7 @@ static int forward_persistent(sprnn_handle_t h, int T, const float* x, const flo
     a.timeline = h->d_timeline;
     { const char* tw = std::getenv("SPRNN_TIMELINE_WAVE"); a.tl_wave = tw ? std::atoi(tw) : 0; }
     a.hidden = m.cols; a.T = tn; a.lanes_per_row = m.lanes_per_row; a.act = m.cell; a.h_bytes = m.h_bytes;
-    a.index_shift = m.index_shift; a.jitter = m.jitter; a.poll_delay = m.poll_delay; a.spin_limit = m.spin_limit; a.sync = m.sync;
+    a.index_shift = m.index_shift; a.jitter = pause_seed(m); a.poll_delay = m.poll_delay; a.spin_limit = m.spin_limit; a.sync = m.sync;
     a.step_base = ex.shared_exchange ? 0u : h->step_base;
     a.barrier_base = ex.shared_exchange ? 0u : h->barrier_base;
     void* args[] = {&a};
@@ -778,7 +779,7 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
   int rc = SPRNN_OK;
   if (ok) {
     // The exchange inside one XCD is shorter, so its candidates start lower; it is tried second, and dropped for good if
-    // the dispatcher did not put enough workgroups on one XCD (the kernel flags that in the status word and leaves).
+    // the launch's workgroups did not all report in time (the kernel flags that in the status word and leaves).
     static const int spread[] = {-1, 1, 2, 3, 4, 6, 8, 10, 12, 16};   // (-1: none; a wavefront's polls queue behind its own publish anyway)
     static const int local[] = {-1, 1, 2, 3, 4, 6};
     float best_ms = 0.0f;
@@ -809,7 +810,7 @@ static int calibrate_poll_delay(sprnn_handle_s* h, bool try_one_xcd, bool long_r
         if (mode == 1) {
           uint32_t status = 0;
           if (!SPRNN_HIP(hipMemcpy(&status, h->d_ctrl + kCtrlStatus, 4, hipMemcpyDeviceToHost))) { ok = false; break; }
-          if (status & kStatusPlacement) {   // not enough workgroups on any XCD: this mode is not for this device state
+          if (status & kStatusPlacement) {   // not all of them resident at once: this mode is not for this device state
             status &= ~kStatusPlacement;
             if (!SPRNN_HIP(hipMemcpy(h->d_ctrl + kCtrlStatus, &status, 4, hipMemcpyHostToDevice))) ok = false;
             break;

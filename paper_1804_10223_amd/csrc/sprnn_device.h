@@ -16,7 +16,7 @@ constexpr int kCtrlStatus = 0;                    // ctrl[0]: non-zero once a sp
 constexpr int kCtrlBarrier = 32;                  // grid-barrier mode: ctrl[32] top counter, ctrl[32 + 16 (1 + g)] counter of group g (64 bytes apart)
 constexpr int kCtrlPlacement = kCtrlBarrier + 16 * 9;   // one-XCD mode: two sets (launch parity) of 16 words: workgroups seen per XCD [0..7]
 constexpr int kCtrlWords = kCtrlPlacement + 32;
-constexpr int kPlacementStride = 16;              // words between the counters of two XCDs where there is room for it: behind a handle's own control words
+constexpr int kPlacementStride = 16;              // words between the counters of two XCDs where there is room for it, behind a handle's own control words: two share a 128-byte line
 constexpr int kOwnCtrlWords = kCtrlWords + 2 * 8 * kPlacementStride;
 constexpr uint32_t kStatusWatchdog = 1u, kStatusPlacement = 2u;   // bits of the status word
 constexpr int kCellBackward = 100;                // persistent_kernel_for: backward pass of a vanilla cell
@@ -63,6 +63,7 @@ struct KernelArgs {
   int part_grid;              // workgroups of a part
   uint32_t* placement;        // one-XCD mode: two sets of max(16, 8 placement_stride) words, XCD x's workgroups counted in word x * placement_stride
   int placement_stride;
+  uint32_t placement_enough;  // workgroups that an XCD must have received to take a part: part_grid (or, test aid, more than there are)
   uint32_t launch_epoch;      // launches of this handle so far (parity selects the placement counters)
   int seg_rounds;             // > 0: the copy of h is consumed in two parts, its first seg_rounds rounds first (see persistent_kernel)
   int gather_waves;           // lane-pool layout: wavefronts of a workgroup that hold weights (the others own the outputs)

@@ -675,20 +675,20 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
   if (p.one_xcd) {
     const uint32_t flags = lds_address(lds);          // two words at the start of LDS, before anything else uses it
     if (threadIdx.x == 0) {
-      // (one counter per XCD, each in a cache line of its own: with 512 arrivals and all polls at one line, calls took 2 to 9 us longer)
+      // (one counter per XCD, 64 bytes apart: with 512 arrivals and all polls at one line, calls took 2 to 9 us longer)
       const int apart = p.placement_stride, set = max(16, 8 * apart);
       uint32_t* const cnt = p.placement + set * (int)(p.launch_epoch & 1u);
       const uint32_t xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID
       const uint32_t order = __hip_atomic_fetch_add(cnt + xcc * apart, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       int rank = -1, spins = 0;
       bool all_here = true;
-      uint32_t enough[8];
+      uint32_t seen_at[8];
       for (;;) {
         uint32_t seen = 0;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) enough[x] = __hip_atomic_load(cnt + x * apart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int x = 0; x < 8; ++x) seen_at[x] = __hip_atomic_load(cnt + x * apart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int x = 0; x < 8; ++x) seen += enough[x];
+        for (int x = 0; x < 8; ++x) seen += seen_at[x];
         if (seen >= gridDim.x) break;
         if (++spins > p.spin_limit) { all_here = false; break; }
       }
@@ -696,7 +696,7 @@ __global__ __launch_bounds__(NW >= 48 ? 256 : ((CELL == 4 || CELL == 6 || CELL =
       if (all_here) {
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
-          const int has = enough[x] >= (uint32_t)grid_x ? 1 : 0;
+          const int has = seen_at[x] >= p.placement_enough ? 1 : 0;
           if (has && x == (int)xcc && found < parts) mine = found;
           found += has;
         }

@@ -121,6 +121,61 @@ def test_the_results_do_not_depend_on_how_the_samples_are_shared_out(cell, H, B,
             hnd.close()
 
 
+NO_PLACEMENT = 1 << 30   # options.jitter: as if the dispatcher had put too few workgroups on every XCD
+
+
+@pytest.mark.parametrize("cell,H,B,P,dens,opts", [
+    ("relu", 1152, 4, 1, 0.1, {"lanes_per_row": 16, "waves": 9}),
+    ("tanh", 1152, 4, 2, 0.1, {"lanes_per_row": 16, "waves": 9}),
+    ("relu", 1152, 4, 4, 0.1, {"lanes_per_row": 16, "waves": 9}),
+    ("relu", 1001, 8, 8, 0.1, {"lanes_per_row": 16, "waves": 8}),
+    ("lstm", 256, 4, 4, 0.1, {"lanes_per_row": 8, "waves": 8}),
+    ("gru", 200, 2, 2, 0.2, {"lanes_per_row": 16, "waves": 8}),
+    ("relu", 1000, 8, 2, 0.1, {"lanes_per_row": 16, "waves": 8, "activations": "binary16"}),
+])
+def test_one_xcd_launches_with_too_few_workgroups_on_every_xcd(cell, H, B, P, dens, opts):
+    """The workgroups then take their places by index and the exchange leaves the XCDs: the same results, with and without
+    pauses (the general form and the one without options), also right behind a launch on one XCD with the same ring."""
+    T = 12
+    w = wl.make_workload("places", cell, H, B, T, dens, seed=H, h0_std=0.5)
+    rng = np.random.Generator(np.random.PCG64(9))
+    s = {"x": _dev(w.x), "h0": _dev(w.h0), "e": _dev(rng.standard_normal((T, B, H)).astype(np.float32)),
+         "c0": _dev(rng.standard_normal((B, H)).astype(np.float32)), "b_hn": _dev(getattr(w, "b_hn", None))}
+    csr = (w.row_ptr, w.col_idx, w.val_bits)
+    vanilla = cell not in GATES and "activations" not in opts
+    t_csr = binding.transpose_csr(H, H, *csr)[:3] if vanilla else None
+    print("case", cell, H, B, P, opts, flush=True)
+
+    def passes(jitter):
+        extra = dict(opts, xcd="one", jitter=jitter, **({"parts": P} if P > 1 else {}))
+        out = {}
+        with binding.SparseRNN(H, B, cell, *csr, **extra) as rnn:
+            info = rnn.info()
+            assert info["one_xcd"] == 1 and info["parts"] == P and 2 <= info["grid"] <= 32
+            bwd = binding.SparseRNN(H, B, cell, *t_csr, **extra) if vanilla else None
+            for again in range(3):
+                if cell == "lstm":
+                    out["h", again], out["c", again] = rnn.forward_lstm(s["x"], s["h0"], s["c0"])
+                elif cell == "gru":
+                    out["h", again] = rnn.forward_gru(s["x"], s["b_hn"], s["h0"])
+                else:
+                    out["h", again] = rnn.forward(s["x"], s["h0"])
+                if bwd:
+                    out["d", again], out["dh0", again] = bwd.backward(s["e"], out["h", again])
+                    out["noalloc", again] = torch.empty_like(out["h", again])
+                    rnn.forward_noalloc(s["x"], s["h0"], out["noalloc", again])
+            assert rnn.check() == binding.SPRNN_OK and (bwd is None or bwd.check() == binding.SPRNN_OK)
+            if bwd:
+                bwd.close()
+        return out
+
+    want = passes(0)
+    for jitter in (NO_PLACEMENT, NO_PLACEMENT + 5):
+        got = passes(jitter)
+        for k in want:
+            assert torch.equal(got[k], want[k]), (jitter, k)
+
+
 @pytest.mark.parametrize("H,B,P,lanes,dens", [(2000, 8, 4, 8, 0.005), (4096, 4, 2, 8, 0.01)])
 def test_sparse_parts_copy_h_whole_unless_told_otherwise(H, B, P, lanes, dens):
     """Layers whose workgroups would copy only some columns if all samples were in one part: with parts they copy h whole, so that

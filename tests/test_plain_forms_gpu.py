@@ -3,7 +3,8 @@
 A handle with pauses (options.jitter) runs the general form, one without the form for its number of copy rounds; with the same
 lanes per row both add a row's products in the same order.  Shapes: each number of rounds (one piece of 16 bytes per lane and
 round), two groups of eight, one workgroup; word counts at both ends of the instantiations and in wavefronts of unequal
-length; sequences of every length modulo the unrolled loops; steps that are waited for (a pause in every wavefront) or not.
+length; sequences of every length modulo the unrolled loops.  The pauses are the general form's; the forms without options are
+made to wait, or not to, by their back-off.
 """
 import numpy as np
 import pytest
@@ -96,6 +97,44 @@ def test_forms_without_options_have_the_bits_of_the_general_form(cell, H, B, den
     assert len(results[0]) == len(results[1])
     for k, (a, b) in enumerate(zip(*results)):
         assert torch.equal(a, b), (k, (a - b).abs().max().item())
+
+
+@pytest.mark.parametrize("cell,H,B,dens,rows,opts", [c for c in CASES if c[1] > 200])
+def test_forms_without_options_that_poll_at_once_or_late(cell, H, B, dens, rows, opts):
+    """No back-off: the first polls of a step come before the data, every wavefront loads again and again.  A back-off of several
+    steps' time: the data is there at the first poll."""
+    T = 40
+    w = wl.make_workload("polls", cell, H, B, T, dens, seed=H, row_nnz=rows, h0_std=0.5)
+    rng = np.random.Generator(np.random.PCG64(3))
+    x, h0, e = _dev(w.x), _dev(w.h0), _dev(rng.standard_normal((T, B, H)).astype(np.float32))
+    c0, b_hn = _dev(rng.standard_normal((B, H)).astype(np.float32)), _dev(getattr(w, "b_hn", None))
+    half, gated = opts.get("activations") == "binary16", cell in GATES
+    t_csr = None if half else binding.transpose_csr(w.rows, H, w.row_ptr, w.col_idx, w.val_bits)
+    bopts = dict(lanes_per_row=16, waves=8) if gated else opts
+    print("case", cell, H, B, opts, flush=True)
+    results = []
+    for kw in ({"poll_delay": -1}, {"poll_delay": 100}, {"jitter": 2}):
+        with binding.SparseRNN(H, B, cell, w.row_ptr, w.col_idx, w.val_bits, **opts, **kw) as rnn:
+            if cell == "lstm":
+                out = list(rnn.forward_lstm_train(x, h0, c0))
+            elif cell == "gru":
+                out = list(rnn.forward_gru_train(x, b_hn, h0))
+            else:
+                out = [rnn.forward(x, h0)]
+            assert rnn.check() == binding.SPRNN_OK
+        if not half:
+            with binding.SparseRNN(H, B, cell + "_backward" if gated else cell, *t_csr, **bopts, **kw) as bwd:
+                if cell == "lstm":
+                    out += bwd.backward_lstm(e, out[2], out[1], c0)
+                elif cell == "gru":
+                    out += bwd.backward_gru(e, out[1], out[0], h0)
+                else:
+                    out += bwd.backward(e, out[0])
+                assert bwd.check() == binding.SPRNN_OK
+        results.append(out)
+    for other in results[1:]:
+        for k, (a, b) in enumerate(zip(results[0], other)):
+            assert torch.equal(a, b), (k, (a - b).abs().max().item())
 
 
 def test_weights_beyond_a_wavefronts_own_do_not_read_h():
