@@ -562,10 +562,13 @@ struct ContestBuilder {
     sprnn_handle_t built = nullptr;
     const int rc = make(o, true, incumbent, proposed, &built);
     static const bool verbose = std::getenv("SPRNN_DEBUG") != nullptr;
-    if (verbose)
-      std::fprintf(stderr, "sprnn_create: contender (parts %d, lanes %d, grid %d, fill %d) -> %s, %d x %d, %d lanes, %.3f us per step against %.3f\n",
-                   r.parts, r.lanes, o.grid, o.fill_waves, sprnn_status_string(rc), built ? built->map.grid : 0, built ? built->map.block : 0,
-                   built ? built->map.lanes_per_row : 0, built ? built->calibrated_us : 0.0f, incumbent->calibrated_us);
+    if (verbose) {
+      const bool both = built && built->calibrated_grad_us > 0.0f && incumbent->calibrated_grad_us > 0.0f;
+      std::fprintf(stderr, "sprnn_create: %s (parts %d, lanes %d, grid %d, fill %d) -> %s, %d x %d, %d lanes, %.3f us per step against %.3f%s\n",
+                   r.parts > 1 ? "shared out" : "contender", r.parts, r.lanes, o.grid, o.fill_waves, sprnn_status_string(rc), built ? built->map.grid : 0,
+                   built ? built->map.block : 0, built ? built->map.lanes_per_row : 0, built ? built->calibrated_us + (both ? built->calibrated_grad_us : 0.0f) : 0.0f,
+                   incumbent->calibrated_us + (both ? incumbent->calibrated_grad_us : 0.0f), both ? ", with and without weights" : "");
+    }
     return built;
   }
   Facts facts(const sprnn_handle_s* h) const {
