@@ -189,7 +189,7 @@ int sprnn_create(sprnn_handle_t* out, int hidden, int batch, int activation, con
  * the layer needs only a few more than one XCD has compute units, or another number of wavefronts per workgroup when
  * that copies a large h with at least a tenth fewer loads; and twice and half the lanes per row.  With several samples the
  * batch shared out to 2, 4 and 8 parts (SPRNN_XCD_PARTS) is measured as well, where the layer fits that share of the CUs.
- * Creation then takes 0.1 to 0.4 s depending on the size of the matrix (the packing runs on several host threads).
+ * Creation then takes 0.05 to 0.4 s depending on the size of the matrix (the packing runs on several host threads).
  * Results are bit-for-bit the same from call to call on one handle, and between handles with the same lanes_per_row
  * that copy h whole (compact 0 in sprnn_info_t: the lanes then fix the order in which a row's products are added, however the
  * samples are shared out; with column compaction it follows the places of the columns in LDS, which grid and waves decide as

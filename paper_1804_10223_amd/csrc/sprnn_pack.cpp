@@ -226,25 +226,41 @@ struct Seg {
 };
 }  // namespace
 
+// The cycles of one LDS pass: the largest number of different addresses that fall into one bank class, and at least one.
+class PassCycles {
+ public:
+  void clear() { std::memset(count_, 0, sizeof(count_)); worst_ = 1; }
+  void add(uint32_t address, int bank_class) {
+    uint32_t* const seen = seen_[bank_class];
+    const int n = count_[bank_class];
+    for (int i = 0; i < n; ++i)
+      if (seen[i] == address) return;
+    seen[n] = address;
+    count_[bank_class] = (unsigned char)(n + 1);
+    worst_ = std::max(worst_, n + 1);
+  }
+  int cycles() const { return worst_; }
+
+ private:
+  uint32_t seen_[64][kWave];       // (at most 64 classes and a pass of at most 64 lanes)
+  unsigned char count_[64] = {};
+  int worst_ = 1;
+};
+
 // LDS cycles one wavefront needs for its `trip` gathers under the pass model.
 static int64_t segs_cycles(const std::vector<Seg>& segs, int trip, const PassModel& pm) {
   int64_t total = 0;
-  std::vector<std::vector<int32_t>> seen(pm.classes);
-  for (int k = 0; k < trip; ++k)
-    for (int p = 0; p < pm.npass; ++p) {
-      for (auto& v : seen) v.clear();
-      for (const Seg& q : segs)
-        for (int j = 0; j < q.n; ++j) {
-          if (pm.pass_of[q.lane0 + j] != p) continue;
-          const int i = q.pos[(size_t)k * q.n + j];
-          if (i < 0) continue;   // fillers are given a free bank class afterwards
-          auto& v = seen[q.items[i].col % pm.classes];
-          if (std::find(v.begin(), v.end(), q.items[i].col) == v.end()) v.push_back(q.items[i].col);
-        }
-      size_t worst = 1;
-      for (auto& v : seen) worst = std::max(worst, v.size());
-      total += (int64_t)worst;
-    }
+  PassCycles pass[4];
+  for (int k = 0; k < trip; ++k) {
+    for (int p = 0; p < pm.npass; ++p) pass[p].clear();
+    for (const Seg& q : segs)
+      for (int j = 0; j < q.n; ++j) {
+        const int i = q.pos[(size_t)k * q.n + j];
+        if (i < 0) continue;   // fillers are given a free bank class afterwards
+        pass[pm.pass_of[q.lane0 + j]].add((uint32_t)q.items[i].col, q.items[i].col % pm.classes);
+      }
+    for (int p = 0; p < pm.npass; ++p) total += pass[p].cycles();
+  }
   return total;
 }
 
@@ -306,40 +322,43 @@ static void order_segments(std::vector<Seg>& segs, int trip, const std::vector<P
     if (ca != cb) return ca < cb;
     return fine_total[a] > fine_total[b];
   });
-  std::vector<int> cost_of(P);
-  for (int g : order)
+  std::vector<int> in_model(nm);                   // the class under each model
+  std::vector<int> rank(P), room(P);               // of a pass for a nonzero of class g: cycles it would add, then nonzeros there; lanes of the segment still free
+  for (int g : order) {
+    for (int i = 0; i < nm; ++i) in_model[i] = g % models[i].classes;
+    auto rate = [&](int at) {                      // cycles that a nonzero of class g would add to this pass, over the models
+      int cost = 0;
+      for (int i = 0; i < nm; ++i) {
+        const int a = at >> shift[i];
+        cost += mult[i][(size_t)a * models[i].classes + in_model[i]] + 1 > cycles[i][a] ? 1 : 0;
+      }
+      rank[at] = cost << 16 | pass_load[at];
+    };
+    for (int at = 0; at < P; ++at) rate(at);
     for (size_t q = 0; q < segs.size(); ++q) {
       const Seg& sg = segs[q];
       if (bucket[q][g].empty()) continue;
-      auto price = [&](int at) {                   // cycles that a nonzero of class g would add to this pass, over the models
-        int cost = 0;
-        for (int i = 0; i < nm; ++i) {
-          const int a = at >> shift[i];
-          cost += mult[i][(size_t)a * models[i].classes + g % models[i].classes] + 1 > cycles[i][a] ? 1 : 0;
-        }
-        return cost;
-      };
-      for (int at = 0; at < P; ++at) cost_of[at] = price(at);
+      for (int at = 0; at < P; ++at) room[at] = (int)mine[q][at % np].size() - taken[q][at];
       while (!bucket[q][g].empty()) {
         int best = -1;
-        for (int at = 0; at < P; ++at) {
-          if (taken[q][at] >= (int)mine[q][at % np].size()) continue;
-          if (best < 0 || cost_of[at] < cost_of[best] || (cost_of[at] == cost_of[best] && pass_load[at] < pass_load[best])) best = at;
-        }
+        for (int at = 0; at < P; ++at)
+          if (room[at] > 0 && (best < 0 || rank[at] < rank[best])) best = at;
         const int item = bucket[q][g].back();   // (a segment never holds more than trip * n nonzeros: a free lane exists)
         bucket[q][g].pop_back();
         segs[q].pos[(size_t)(best / np) * sg.n + mine[q][best % np][taken[q][best]]] = item;
         taken[q][best] += 1;
+        room[best] -= 1;
         pass_load[best] += 1;
         for (int i = 0; i < nm; ++i) {
           const int a = best >> shift[i];
-          const int count = ++mult[i][(size_t)a * models[i].classes + g % models[i].classes];
+          const int count = ++mult[i][(size_t)a * models[i].classes + in_model[i]];
           cycles[i][a] = std::max(cycles[i][a], count);
         }
-        const int widest = 1 << shift[nm - 1], from = best / widest * widest;   // passes whose price this changed
-        for (int at = from; at < from + widest; ++at) cost_of[at] = price(at);
+        const int widest = 1 << shift[nm - 1], from = best / widest * widest;   // passes whose rank this changed
+        for (int at = from; at < from + widest; ++at) rate(at);
       }
     }
+  }
   // the greedy deal is not optimal when many short rows share a pass: never do worse than CSR order
   if (all_cycles(segs, trip, models) > csr_cycles)
     for (size_t q = 0; q < segs.size(); ++q) segs[q].pos = csr_pos[q];
@@ -969,26 +988,24 @@ static int pack_part(int hidden, int batch, int order_batch, int cell, const int
 double lds_pass_factor(const Packed& P) {
   const Mapping& m = P.map;
   const PassModel pm = make_pass_model(m.layout_batch ? m.layout_batch : m.batch);
-  const int width = m.col_stride;
+  const uint32_t width = (uint32_t)m.col_stride;
   int64_t passes = 0, ideal = 0;
-  std::vector<std::vector<uint32_t>> seen(pm.classes);
+  PassCycles pass;
   for (int wg = 0; wg < m.grid; ++wg)
     for (int wave = 0; wave < m.waves; ++wave) {
       const int trip = P.wave_words[(size_t)wg * m.waves + wave];
-      for (int k = 0; k < trip; ++k)
+      for (int k = 0; k < trip; ++k) {
+        const uint32_t* const words = &P.words[((size_t)wg * m.template_words + k) * m.block + (size_t)wave * kWave];
         for (int p = 0; p < pm.npass; ++p) {
-          for (auto& v : seen) v.clear();
+          pass.clear();
           for (int l : pm.lanes[p]) {
-            const uint32_t w = P.words[((size_t)wg * m.template_words + k) * m.block + (size_t)wave * kWave + l];
-            const uint32_t byte = (w >> 16) << m.index_shift;
-            auto& v = seen[(byte / width) % pm.classes];
-            if (std::find(v.begin(), v.end(), byte) == v.end()) v.push_back(byte);
+            const uint32_t byte = (words[l] >> 16) << m.index_shift;
+            pass.add(byte, (int)(byte / width) % pm.classes);
           }
-          size_t worst = 1;
-          for (auto& v : seen) worst = std::max(worst, v.size());
-          passes += (int64_t)worst;
+          passes += pass.cycles();
           ideal += 1;
         }
+      }
     }
   return ideal ? (double)passes / (double)ideal : 1.0;
 }
