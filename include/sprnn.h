@@ -94,9 +94,11 @@ typedef struct sprnn_options_s {
                         (another process gets SPRNN_ERR_HIP from sprnn_create)                         */
   int jitter;        /* test aid: non-zero seeds pseudo-random pauses (0..15 x 64 clocks) of every
                         wavefront before it publishes, before it polls and after it has copied h,
-                        different in every step, to widen the windows of any race in the hand-off.  Bit 30 is
-                        no part of the seed: with it, one-XCD launches act as if the dispatcher had put too
-                        few workgroups on every XCD (see xcd).  Results must not change                */
+                        different in every step, to widen the windows of any race in the hand-off.  Bits 29 and
+                        30 are no part of the seed: with the latter, one-XCD launches act as if the dispatcher
+                        had put too few workgroups on every XCD (see xcd); with the former, a handle whose parts
+                        were asked for runs calls of fewer than 20 steps undivided, as one that was divided by
+                        measurement does up to a length of its own.  Results must not change           */
   int compact;       /* column compaction: a workgroup copies only the 16-byte pieces of h that its rows
                         read, into consecutive LDS positions.  0 auto (when all of h does not fit in
                         LDS, or every workgroup needs less than half of it; with several parts only

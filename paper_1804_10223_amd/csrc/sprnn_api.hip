@@ -656,6 +656,7 @@ int sprnn_create(sprnn_handle_t* out, int hidden, int batch, int activation, con
 // few microseconds longer, which a short call does not win back (LSTM 837 x batch 2, 22 steps: 36.4 us in two parts, 33.6 in
 // one).  Both handles give the same bits; a straight line through the two measured lengths decides.
 static sprnn_handle_s* handle_for_length(sprnn_handle_s* h, int T) {
+  if (h->whole && (h->map.jitter & kShortUndivided)) return T < kAidSteps ? h->whole : h;
   if (!h->by_length) return h;
   auto estimate = [&](const sprnn_handle_s* c) {
     const double step = ((double)c->calibrated_us * kLongSteps - c->calibrated_short_us) / (kLongSteps - kShortSteps);

@@ -31,7 +31,7 @@ struct Mapping {
   int grid = 0, waves = 0, row_waves = 0, block = 0, lanes_per_row = 0;   // grid = workgroups of a part; waves = all, row_waves = those owning rows
   int sync = SPRNN_SYNC_TAGGED, bank_aware = 1, balance = 2, poll_delay = 0, spin_limit = 0, timeline = 0;
   int cooperative = 0;       // 1: cooperative launch instead of an ordinary one
-  int jitter = 0;            // test aid: seed of pseudo-random pauses in the hand-off (0 = none), and kNoPlacement
+  int jitter = 0;            // test aid: seed of pseudo-random pauses in the hand-off (0 = none), kNoPlacement, kShortUndivided
   int half = 0;              // 1: h is exchanged and kept in LDS as binary16 (options.activations = 2)
   int layout_batch = 0;      // samples' worth of 4-byte elements per column of the LDS copy: batch, or batch / 2 with binary16 activations
   int narrow = 0;            // 1: one 4-byte LDS read per sample instead of one wide read per column (ablation)
@@ -83,9 +83,10 @@ int pack(int hidden, int batch, int cell, const int32_t* row_ptr, const int32_t*
 
 double lds_pass_factor(const Packed& P);
 
-// Bit of `jitter` that has one-XCD launches find too few workgroups on every XCD; the other bits are the seed of the pauses.
-constexpr int kNoPlacement = 1 << 30;
-inline int pause_seed(const Mapping& m) { return m.jitter & ~kNoPlacement; }
+// Bits of `jitter` that are no part of the pauses' seed: one-XCD launches find too few workgroups on every XCD; a handle whose
+// parts were asked for runs calls of fewer than kAidSteps steps undivided.
+constexpr int kNoPlacement = 1 << 30, kShortUndivided = 1 << 29, kAidSteps = 20;
+inline int pause_seed(const Mapping& m) { return m.jitter & ~(kNoPlacement | kShortUndivided); }
 
 // Parts asked for in sprnn_options_t.xcd (1: none, or nothing that could be meant), and the options with that replaced.
 inline int parts_asked(const sprnn_options_t* opt) {

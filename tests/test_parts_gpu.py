@@ -176,6 +176,54 @@ def test_one_xcd_launches_with_too_few_workgroups_on_every_xcd(cell, H, B, P, de
             assert torch.equal(got[k], want[k]), (jitter, k)
 
 
+SHORT_UNDIVIDED = 1 << 29   # options.jitter: calls of fewer than 20 steps run on the handle with all samples
+
+
+@pytest.mark.parametrize("cell,H,B,P,dens,opts", [
+    ("relu", 1152, 4, 4, 0.1, {"lanes_per_row": 16, "waves": 9, "xcd": "one"}),
+    ("tanh", 1000, 8, 2, 0.1, {"lanes_per_row": 16}),
+    ("lstm", 512, 8, 4, 0.2, {"lanes_per_row": 8, "waves": 8}),
+    ("gru", 771, 4, 2, 0.15, {"lanes_per_row": 16, "waves": 7}),
+    ("relu", 1000, 8, 2, 0.1, {"lanes_per_row": 16, "waves": 8, "activations": "binary16"}),
+])
+@pytest.mark.parametrize("pauses", [0, 5])
+def test_calls_that_change_between_the_parts_and_the_undivided_handle(cell, H, B, P, dens, opts, pauses):
+    """Calls on both sides of the change, in turn, every one on from where its own ring was left: the same bits."""
+    T = 48
+    w = wl.make_workload("turns", cell, H, B, T, dens, seed=H, h0_std=0.5)
+    rng = np.random.Generator(np.random.PCG64(4))
+    x, h0, e = _dev(w.x), _dev(w.h0), _dev(rng.standard_normal((T, B, H)).astype(np.float32))
+    c0, b_hn = _dev(rng.standard_normal((B, H)).astype(np.float32)), _dev(getattr(w, "b_hn", None))
+    csr = (w.row_ptr, w.col_idx, w.val_bits)
+    vanilla = cell not in GATES and "activations" not in opts
+    extra = dict(opts, parts=P, jitter=SHORT_UNDIVIDED + pauses)
+    print("case", cell, H, B, P, opts, pauses, flush=True)
+
+    def forward(rnn, steps):
+        xs = x[:steps].contiguous()
+        if cell == "lstm":
+            return rnn.forward_lstm_train(xs, h0, c0)
+        return rnn.forward_gru_train(xs, b_hn, h0) if cell == "gru" else (rnn.forward(xs, h0),)
+
+    with binding.SparseRNN(H, B, cell, *csr, **extra) as rnn:
+        want = forward(rnn, T)
+        for steps in (1, 19, 20, 2, 21, 5, 40, 18, 3, T):
+            for k, (a, b) in enumerate(zip(forward(rnn, steps), want)):
+                assert torch.equal(a, b[:steps]), (steps, k)
+            if vanilla:
+                out = torch.empty_like(want[0][:steps])
+                rnn.forward_noalloc(x[:steps].contiguous(), h0, out)
+                assert torch.equal(out, want[0][:steps]), steps
+        assert rnn.check() == binding.SPRNN_OK
+    if vanilla:
+        with binding.SparseRNN(H, B, cell, *binding.transpose_csr(H, H, *csr)[:3], **extra) as bwd:
+            grads = bwd.backward(e, want[0])[0]
+            for steps in (1, 19, 20, 2, 40, 18, T):   # the last steps of the long call: nothing flows in from beyond its end
+                tail = lambda a: a[T - steps:].contiguous()
+                assert torch.equal(bwd.backward(tail(e), tail(want[0]))[0], grads[T - steps:]), steps
+            assert bwd.check() == binding.SPRNN_OK
+
+
 @pytest.mark.parametrize("H,B,P,lanes,dens", [(2000, 8, 4, 8, 0.005), (4096, 4, 2, 8, 0.01)])
 def test_sparse_parts_copy_h_whole_unless_told_otherwise(H, B, P, lanes, dens):
     """Layers whose workgroups would copy only some columns if all samples were in one part: with parts they copy h whole, so that
